@@ -1,4 +1,4 @@
-// Flash-style causal attention on the CDNA4 matrix cores (bf16 in, fp32 accumulate), head size 128.
+// Flash-style causal attention on the CDNA4 matrix cores (bf16 in, fp32 accumulate), head sizes up to 128.
 //
 // The s x s score matrix is never stored: a block walks tiles of 64 rows, keeps running row maxima
 // and sums in registers (online softmax) and accumulates its outputs in MFMA accumulators.
@@ -11,7 +11,7 @@
 // that axis (slot (half h, e) <-> offset 8*(e/4) + 4*h + e%4).  Row statistics need one cross-half
 // exchange per tile and no row-wise shuffles.
 //
-// One tile format.  Every staged tile is [64 rows][128] bf16, row-major as in global memory, fetched
+// One tile format.  Every staged tile is [64 rows][128 or 64] bf16, row-major as in global memory, fetched
 // straight into LDS (buffer_load ... lds), double buffered.  An operand that is needed with the tile's
 // rows as MFMA rows is read with plain 16-byte LDS reads; an operand that is needed TRANSPOSED (V in
 // O^T = V^T P^T, K in dQ^T = K^T dS^T, Q and dO in the dK/dV kernel) is read from the same tile with
@@ -40,22 +40,39 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
 
-constexpr int D = 128;               // head size
 constexpr int TILE = 64;             // rows of a staged tile
-constexpr int ROWB = D * 2;          // bytes per tile row
-constexpr int TILE_BYTES = TILE * ROWB;
 constexpr float kLog2e = 1.4426950408889634f;
 
-// Position of 16-byte chunk c (of 16) in tile row `row`.  row_key takes 16 distinct values over 16
-// consecutive rows (plain reads of one chunk column by 16 lanes hit 16 different bank groups); its bits
-// 2:1 are the row's low bits (the 4 rows of a transposing read land in 4 different 32-byte windows);
-// and chunk bit 1 is folded into bit 3 (the two 16-lane groups of a half-wave use different 128-byte halves).
-__device__ __forceinline__ int row_key(int row) { return ((row & 3) << 1) | ((row >> 2) & 1) | (((row >> 3) & 1) << 3); }
-__device__ __forceinline__ int place(int c, int row) { return c ^ row_key(row) ^ (((c >> 1) & 1) << 3); }
-__device__ __forceinline__ int unplace(int pc, int row) {
-  const int t = pc ^ row_key(row);
-  return t ^ (((t >> 1) & 1) << 3);
-}
+// Head sizes.  DP: the head size rounded up to a multiple of 32, the width the products run at (32, 64, 96 or 128).
+// EX = false: head size 128, probabilities and dS go to the second product as bf16.  EX = true: every other head size
+// up to 128; columns from the head size to DP are staged as zeros, and probabilities and dS keep 16 significand bits
+// (a bf16 value plus the bf16 of what it leaves, two MFMAs), because these head sizes have always had them in fp32:
+// the error against 64 bits is the plain-ALU kernels' (1.6e-3 forward, 1.7e-3 backward, the rounding of the results).
+// What these kernels replaced ran one wave per row out of L2: 43.6 ms for a forward and backward pass over 2 sequences
+// of 1500, 16 query and 4 kv heads of 64, where this form takes 0.131 ms (39 us forward, 39 dQ, 49 dK/dV); bound by the
+// latency of a tile step (S product, softmax, PV product, barrier), as the short sequences of head size 128 are.
+//
+// A staged tile: [64][128] bf16 for DP 96 and 128, [64][64] for DP 32 and 64 (half the LDS: three blocks a unit).
+template <int DP> struct TileFmt {
+  static constexpr int ROWB = DP > 64 ? 256 : 128;  // bytes per tile row
+  static constexpr int CPR = ROWB / 16;             // 16-byte chunks per row
+  static constexpr int BYTES = TILE * ROWB;
+  // Position of chunk c in tile row `row` is c ^ key(row) (256-byte rows: chunk bit 1 is also folded into bit 3, so
+  // that the two 16-lane groups of a half-wave use different 128-byte halves).  The key takes as many distinct values
+  // over 16 consecutive rows as there are chunk positions (plain reads of one chunk column by 16 lanes hit 16 different
+  // bank groups), and the 4 rows of a transposing read land in different windows: 32-byte windows of a 256-byte row
+  // (key bits 2:1 = the row's low bits), 64-byte halves of 128-byte rows (key bit 2 = row bit 1; row bit 0 already
+  // picks the half of the 256 bytes of banks).
+  static __device__ __forceinline__ int key(int row) {
+    if constexpr (DP > 64) return ((row & 3) << 1) | ((row >> 2) & 1) | (((row >> 3) & 1) << 3);
+    else return (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
+  }
+  static __device__ __forceinline__ int unplace(int pc, int row) {
+    const int t = pc ^ key(row);
+    if constexpr (DP > 64) return t ^ (((t >> 1) & 1) << 3);
+    else return t;
+  }
+};
 
 struct FlashParams {
   const bf16 *qkv;
@@ -65,23 +82,27 @@ struct FlashParams {
   float *lse;
   const float *lse_in;
   const float *dvec;
-  float *part;                   // grouped-query dK/dV partials [batch][nq][seq][2][D] fp32, or NULL
-  int seq, batch, nq, nkv, row;  // row = (nq + 2 nkv) * D
-  float scale;                   // 1 / sqrt(D)
+  float *part;                   // grouped-query dK/dV partials [batch][nq][seq][2][d] fp32, or NULL
+  int seq, batch, nq, nkv, row;  // row = (nq + 2 nkv) * d
+  int d;                         // head size
+  float scale;                   // 1 / sqrt(d)
   uint32_t qkv_bytes, ctx_bytes;
 };
 
-// ---- global -> LDS: one [64][128] tile, 4 wave-wide loads per wave -------------------------------
-template <int NW = 4> struct TileLoaderN {
-  static constexpr int NL = 16 / NW;  // wave-wide loads per wave and tile
+// ---- global -> LDS: one tile, 16 (DP > 64) or 8 wave-wide loads a block ------------------------------
+template <int DP, bool EX, int NW> struct TileLoaderN {
+  using F = TileFmt<DP>;
+  static constexpr int NL = F::BYTES / 1024 / NW;  // wave-wide loads per wave and tile
   uint32_t voff[NL];
-  // row_stride: elements between consecutive tile rows in global memory
-  __device__ __forceinline__ void init(int64_t row_stride, int wave, int lane) {
+  // row_stride: elements between consecutive tile rows in global memory; d: head size
+  __device__ __forceinline__ void init(int64_t row_stride, int d, int wave, int lane) {
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
       const int idx = (i * NW + wave) * 64 + lane;  // chunk position in the LDS tile
-      const int row = idx >> 4, c = unplace(idx & 15, row);
+      const int row = idx / F::CPR, c = F::unplace(idx % F::CPR, row);
       voff[i] = (uint32_t)(((int64_t)row * row_stride + c * 8) * 2);
+      // columns past the head size: an offset that stays outside every tensor (below 2 GiB) whatever row is added
+      if (EX && c * 8 >= d) voff[i] = 0x80000000u;
     }
   }
   // rows0: element offset of tile row 0 (a multiple of the row stride), base: element offset of column 0
@@ -95,67 +116,52 @@ template <int NW = 4> struct TileLoaderN {
                                                0);
   }
 };
-typedef TileLoaderN<4> TileLoader;
 
+// Fragment reads.  Every lane-dependent part of an address fits one per-lane base (relative to the tile, which must
+// start on a 256-byte boundary); what changes with the reduction slice, the 32-column block and the row group is an XOR
+// of the 16-byte chunk index with a compile-time constant plus a multiple of the row pitch, so that one register per
+// kind of read serves all of them (written through the placement function the compiler keeps one address register per
+// read, about forty of them).
+//
 // A-operand fragment, tile rows as MFMA rows: row r32 + lane%32, reduction slots 16ks + 8hh + 0..7
-__device__ __forceinline__ bf16x8 frag_rows(const char *tile, int r32, int ks, int lane) {
-  const int r = r32 + (lane & 31), hh = lane >> 5;
-  return *reinterpret_cast<const bf16x8 *>(tile + r * ROWB + (place(2 * ks + hh, r) << 4));
+template <int DP> __device__ __forceinline__ uint32_t rows_base(int lane) {
+  const int l32 = lane & 31, hh = lane >> 5;
+  return (uint32_t)(l32 * TileFmt<DP>::ROWB + ((hh ^ TileFmt<DP>::key(l32)) << 4));
+}
+template <int DP> __device__ __forceinline__ bf16x8 frag_rows_at(const char *tile, uint32_t base, int r32, int ks) {
+  const uint32_t x = (uint32_t)(((2 * ks) ^ (DP > 64 ? (ks & 1) << 3 : 0)) << 4);  // chunk 2ks + hh sits at hh ^ key ^ this
+  return *reinterpret_cast<const bf16x8 *>(tile + ((base ^ x) + (uint32_t)(r32 * TileFmt<DP>::ROWB)));
 }
 // A-operand fragment of the TRANSPOSED tile: MFMA row = tile column c32 + lane%32, reduction axis =
 // tile rows 16kk .. 16kk+15 in the permuted order (slot (hh, e) <-> row 16kk + 8*(e/4) + 4hh + e%4).
 // ds_read_b64_tr_b16: within 16 lanes, lane i receives element i%4 of the 8-byte pieces addressed by
 // lanes i/4, i/4+4, i/4+8, i/4+12; lane s addresses tile[row0 + s/4][col0 + 4*(s%4) ..+3].
-__device__ __forceinline__ bf16x8 frag_cols(const char *tile, int c32, int kk, int lane) {
-  const int g = lane >> 4, s = lane & 15;
-  const int col = c32 + 16 * (g & 1) + 4 * (s & 3);
-  const int c = col >> 3, half = (col >> 2) & 1;
-  union { s16x4 h[2]; bf16x8 v; } x;
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int row = 16 * kk + 8 * t + 4 * (g >> 1) + (s >> 2);
-    const char *a = tile + row * ROWB + (place(c, row) << 4) + (half << 3);
-    x.h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(a));
-  }
-  return x.v;
-}
-// The same two fragment reads with the address arithmetic written out.  Every lane-dependent part of an address
-// fits one per-lane base (relative to the tile, which must start on a 256-byte boundary); what changes with the
-// reduction slice, the 32-column block and the row group is an XOR of the 16-byte chunk index with a compile-time
-// constant plus a multiple of the row pitch, so that one register per kind of read serves all of them (written
-// through place() the compiler keeps one address register per read, about forty of them).
-__device__ __forceinline__ uint32_t rows_base(int lane) {  // for frag_rows: row lane%32 of a 32-row block
-  const int l32 = lane & 31, hh = lane >> 5;
-  return (uint32_t)(l32 * ROWB + ((hh ^ row_key(l32)) << 4));
-}
-__device__ __forceinline__ bf16x8 frag_rows_at(const char *tile, uint32_t base, int r32, int ks) {
-  const uint32_t x = (uint32_t)(((2 * ks) ^ ((ks & 1) << 3)) << 4);  // place(2ks + hh, row) = hh ^ row_key ^ this
-  return *reinterpret_cast<const bf16x8 *>(tile + ((base ^ x) + (uint32_t)(r32 * ROWB)));
-}
-__device__ __forceinline__ uint32_t cols_base(int lane) {  // for frag_cols: the lane's column piece and row inside a group of 8
+template <int DP> __device__ __forceinline__ uint32_t cols_base(int lane) {  // the lane's column piece and row inside a group of 8
   const int g = lane >> 4, s = lane & 15;
   const int col = 16 * (g & 1) + 4 * (s & 3), c = col >> 3, half = (col >> 2) & 1;
   const int r = 4 * (g >> 1) + (s >> 2);
-  const int pl = c ^ row_key(r) ^ (((c >> 1) & 1) << 3);
-  return (uint32_t)(r * ROWB + (pl << 4) + (half << 3));
+  const int pl = c ^ TileFmt<DP>::key(r) ^ (DP > 64 ? ((c >> 1) & 1) << 3 : 0);
+  return (uint32_t)(r * TileFmt<DP>::ROWB + (pl << 4) + (half << 3));
 }
-__device__ __forceinline__ bf16x8 frag_cols_at(const char *tile, uint32_t base, int c32, int kk) {
+template <int DP> __device__ __forceinline__ bf16x8 frag_cols_at(const char *tile, uint32_t base, int c32, int kk) {
   union { s16x4 h[2]; bf16x8 v; } x;
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
-    const uint32_t xr = (uint32_t)((((c32 >> 3)) ^ (t << 3)) << 4);  // chunk index: + 4 per 32 columns, row_key bit 3 = t
-    const char *a = tile + ((base ^ xr) + (uint32_t)((16 * kk + 8 * t) * ROWB));
+    // chunk index: + 4 per 32 columns; row 8t + r: bit 3 of the key of a 256-byte row is t, bit 1 of a 128-byte row's
+    const uint32_t xr = (uint32_t)(((c32 >> 3) ^ (t << (DP > 64 ? 3 : 1))) << 4);
+    const char *a = tile + ((base ^ xr) + (uint32_t)((16 * kk + 8 * t) * TileFmt<DP>::ROWB));
     x.h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(a));
   }
   return x.v;
 }
 // B-operand fragments straight from global memory: 8 consecutive elements of row (lane%32) per step
-__device__ __forceinline__ void load_row_frags(const bf16 *rowptr, bool valid, int hh, bf16x8 (&f)[D / 16]) {
+template <int DP, bool EX>
+__device__ __forceinline__ void load_row_frags(const bf16 *rowptr, bool valid, int d, int hh, bf16x8 (&f)[DP / 16]) {
 #pragma unroll
-  for (int ks = 0; ks < D / 16; ++ks) {
+  for (int ks = 0; ks < DP / 16; ++ks) {
     union { u32x4 u; bf16x8 v; } x;
     x.u = u32x4{0u, 0u, 0u, 0u};
-    if (valid) x.u = *reinterpret_cast<const u32x4 *>(rowptr + ks * 16 + hh * 8);
+    if (valid && (!EX || ks * 16 + hh * 8 < d)) x.u = *reinterpret_cast<const u32x4 *>(rowptr + ks * 16 + hh * 8);
     f[ks] = x.v;
   }
 }
@@ -166,27 +172,38 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16 &a, int v0) {
   for (int e = 0; e < 8; ++e) r[e] = (bf16)a[v0 + e];
   return r;
 }
+// what pack8 left behind: the next 8 significand bits
+__device__ __forceinline__ bf16x8 pack8_rest(const f32x16 &a, const bf16x8 &hi, int v0) {
+  bf16x8 r;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) r[e] = (bf16)(a[v0 + e] - (float)hi[e]);
+  return r;
+}
 // offset along the accumulator-row axis of register v in a 32x32 tile
 __device__ __forceinline__ int acc_row(int v, int hh) { return 8 * (v >> 2) + 4 * hh + (v & 3); }
 
 // writes O^T-style accumulators (rows = head-dim slots, lane = token row) to out[token][col0 + d]
-__device__ __forceinline__ void store_transposed(const f32x16 (&acc)[D / 32], float mul, bf16 *dst_row, int hh) {
+template <int DP, bool EX>
+__device__ __forceinline__ void store_transposed(const f32x16 (&acc)[DP / 32], float mul, bf16 *dst_row, int d, int hh) {
 #pragma unroll
-  for (int dt = 0; dt < D / 32; ++dt)
+  for (int dt = 0; dt < DP / 32; ++dt)
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
+      if (EX && dt * 32 + 8 * q4 >= d) continue;  // d is a multiple of 8
       bf16x4 o;
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[e] = (bf16)(acc[dt][q4 * 4 + e] * mul);
       *reinterpret_cast<bf16x4 *>(dst_row + dt * 32 + 8 * q4 + 4 * hh) = o;
     }
 }
-// the same accumulators as fp32: part_row points at [D] floats of this lane's token
-__device__ __forceinline__ void store_transposed_f32(const f32x16 (&acc)[D / 32], float mul, float *part_row, int hh) {
+// the same accumulators as fp32: part_row points at [d] floats of this lane's token
+template <int DP, bool EX>
+__device__ __forceinline__ void store_transposed_f32(const f32x16 (&acc)[DP / 32], float mul, float *part_row, int d, int hh) {
 #pragma unroll
-  for (int dt = 0; dt < D / 32; ++dt)
+  for (int dt = 0; dt < DP / 32; ++dt)
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
+      if (EX && dt * 32 + 8 * q4 >= d) continue;
       f32x4 o;
 #pragma unroll
       for (int e = 0; e < 4; ++e) o[e] = acc[dt][q4 * 4 + e] * mul;
@@ -203,11 +220,12 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(0)"
 // index of the wave: only those pay for the mask.  The running maximum is kept in exponent units
 // (m = max * scale * log2 e); the accumulators and the row sum are rescaled only when some row of the wave saw its
 // maximum rise (the factor is exactly 1 otherwise).
-struct FwdRow {
-  f32x16 o[D / 32];
+template <int DP> struct FwdRow {
+  f32x16 o[DP / 32];
   float m, l;
 };
-__device__ __forceinline__ void fwd_tile(const char *kt, const char *vt, const bf16x8 (&qf)[D / 16], FwdRow &r, int j0,
+template <int DP, bool EX>
+__device__ __forceinline__ void fwd_tile(const char *kt, const char *vt, const bf16x8 (&qf)[DP / 16], FwdRow<DP> &r, int j0,
                                          int q0w, int q, int hh, float sc2, uint32_t rb, uint32_t cb) {
   f32x16 s[2];
 #pragma unroll
@@ -215,8 +233,8 @@ __device__ __forceinline__ void fwd_tile(const char *kt, const char *vt, const b
 #pragma unroll
     for (int v = 0; v < 16; ++v) s[t][v] = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks)
-      s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows_at(kt, rb, t * 32, ks), qf[ks], s[t], 0, 0, 0);
+    for (int ks = 0; ks < DP / 16; ++ks)
+      s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows_at<DP>(kt, rb, t * 32, ks), qf[ks], s[t], 0, 0, 0);
   }
   if (j0 + TILE - 1 > q0w) {  // wave-uniform
 #pragma unroll
@@ -237,7 +255,7 @@ __device__ __forceinline__ void fwd_tile(const char *kt, const char *vt, const b
     r.m = mx;
     r.l *= alpha;
 #pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt)
+    for (int dt = 0; dt < DP / 32; ++dt)
 #pragma unroll
       for (int v = 0; v < 16; ++v) r.o[dt][v] *= alpha;
   }
@@ -254,16 +272,23 @@ __device__ __forceinline__ void fwd_tile(const char *kt, const char *vt, const b
 #pragma unroll
   for (int kk = 0; kk < TILE / 16; ++kk) {
     const bf16x8 pf = pack8(s[kk >> 1], 8 * (kk & 1));
+    bf16x8 pr;
+    if (EX) pr = pack8_rest(s[kk >> 1], pf, 8 * (kk & 1));
 #pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt)
-      r.o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_at(vt, cb, dt * 32, kk), pf, r.o[dt], 0, 0, 0);
+    for (int dt = 0; dt < DP / 32; ++dt) {
+      const bf16x8 vf = frag_cols_at<DP>(vt, cb, dt * 32, kk);
+      r.o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf, r.o[dt], 0, 0, 0);
+      if (EX) r.o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pr, r.o[dt], 0, 0, 0);
+    }
   }
 }
-__device__ __forceinline__ void fwd_finish(const FlashParams &p, FwdRow &r, int q, int n, int g, int hh) {
+template <int DP, bool EX>
+__device__ __forceinline__ void fwd_finish(const FlashParams &p, FwdRow<DP> &r, int q, int n, int g, int hh) {
+  const int hd = EX ? p.d : DP;
   r.l += __shfl_xor(r.l, 32, 64);
   if (q < p.seq) {
     const int64_t trow = (int64_t)q * p.batch + n;
-    store_transposed(r.o, 1.f / r.l, p.ctx + trow * (p.nq * D) + g * D, hh);
+    store_transposed<DP, EX>(r.o, 1.f / r.l, p.ctx + trow * (p.nq * hd) + g * hd, hd, hh);
     if (hh == 0) p.lse[((int64_t)n * p.nq + g) * p.seq + q] = (r.m + log2f(r.l)) * 0.6931471805599453f;
   }
 }
@@ -271,34 +296,34 @@ __device__ __forceinline__ void fwd_finish(const FlashParams &p, FwdRow &r, int 
 // block = 32 NW query rows of one (batch entry, query head); wave = 32 query rows.  Four waves, two blocks per
 // compute unit; or eight waves, one block: the same waves per unit, but every staged K / V tile serves twice the query
 // rows, which halves the bytes a unit pulls from L2 into LDS per MFMA (what bounds the walk of a long sequence).
-template <int NW>
-__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void flash_fwd_kernel(const FlashParams p) {
-  __shared__ __align__(1024) char lds[2][2][TILE_BYTES];  // [stage][K, V]
+template <int DP, bool EX, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 4 ? (DP > 64 ? 2 : 3) : 1) void flash_fwd_kernel(const FlashParams p) {
+  __shared__ __align__(1024) char lds[2][2][TileFmt<DP>::BYTES];  // [stage][K, V]
   constexpr int QB = 32 * NW;
   const int qt = gridDim.z - 1 - blockIdx.z, g = blockIdx.x, n = blockIdx.y;  // heads fastest, longest walks first
-  const int kap = g / (p.nq / p.nkv);
+  const int kap = g / (p.nq / p.nkv), hd = EX ? p.d : DP;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
   const int q0w = qt * QB + wave * 32;
   const int q = q0w + l32;
   const int64_t tstride = (int64_t)p.batch * p.row;  // elements between consecutive positions
-  const int koff = p.nq * D + kap * D, voff = (p.nq + p.nkv) * D + kap * D;
+  const int koff = p.nq * hd + kap * hd, voff = (p.nq + p.nkv) * hd + kap * hd;
   const rsrc_t rs = make_rsrc(p.qkv, p.qkv_bytes);
-  TileLoaderN<NW> ld;
-  ld.init(tstride, wave, lane);
+  TileLoaderN<DP, EX, NW> ld;
+  ld.init(tstride, hd, wave, lane);
 
-  bf16x8 qf[D / 16];
-  load_row_frags(p.qkv + (int64_t)n * p.row + (int64_t)q * tstride + g * D, q < p.seq, hh, qf);
+  bf16x8 qf[DP / 16];
+  load_row_frags<DP, EX>(p.qkv + (int64_t)n * p.row + (int64_t)q * tstride + g * hd, q < p.seq, hd, hh, qf);
 
-  FwdRow r;
+  FwdRow<DP> r;
 #pragma unroll
-  for (int dt = 0; dt < D / 32; ++dt)
+  for (int dt = 0; dt < DP / 32; ++dt)
 #pragma unroll
     for (int v = 0; v < 16; ++v) r.o[dt][v] = 0.f;
   r.m = -INFINITY;
   r.l = 0.f;
   const float sc2 = p.scale * kLog2e;
-  const uint32_t rb = rows_base(lane), cb = cols_base(lane);
+  const uint32_t rb = rows_base<DP>(lane), cb = cols_base<DP>(lane);
 
   const int kv_end = (qt * QB + QB < p.seq) ? qt * QB + QB : p.seq;
   const int ntile = (kv_end + TILE - 1) / TILE;
@@ -314,47 +339,46 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void flash_fwd_kernel(con
       ld.issue(rs, lds[cur ^ 1][1], r0, (int64_t)n * p.row + voff, wave);
     }
     if (j0 > q0w + 31) continue;  // every key of this tile lies after every query row of the wave
-    fwd_tile(lds[cur][0], lds[cur][1], qf, r, j0, q0w, q, hh, sc2, rb, cb);
+    fwd_tile<DP, EX>(lds[cur][0], lds[cur][1], qf, r, j0, q0w, q, hh, sc2, rb, cb);
   }
   wait_loads();
-  fwd_finish(p, r, q, n, g, hh);
+  fwd_finish<DP, EX>(p, r, q, n, g, hh);
 }
-template __global__ void flash_fwd_kernel<4>(const FlashParams);
-template __global__ void flash_fwd_kernel<8>(const FlashParams);
 
 // The same for grids of at most one block per compute unit (short sequences, few heads), where the chain of tile
 // steps of the last query rows bounds the kernel: eight waves; waves w and w + 4 share a SIMD and 32 query rows
 // and take the even and the odd key tiles, each with its own maximum, row sum and accumulators; at the end the odd
 // side's state goes through LDS and the even side merges it (o = o1 2^(m1-m) + o2 2^(m2-m), the row sum alike).
 // Half as many steps, and the two waves of a SIMD overlap each other's softmax and MFMA phases.
+template <int DP, bool EX>
 __global__ __launch_bounds__(512, 1) void flash_fwd_split_kernel(const FlashParams p) {
   extern __shared__ __align__(1024) char smem[];  // [stage][parity][K, V] tiles
   const int qt = gridDim.z - 1 - blockIdx.z, g = blockIdx.x, n = blockIdx.y;  // heads fastest, longest walks first
-  const int kap = g / (p.nq / p.nkv);
+  const int kap = g / (p.nq / p.nkv), hd = EX ? p.d : DP;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int qg = wave & 3, par = wave >> 2;
   const int l32 = lane & 31, hh = lane >> 5;
   const int q0w = qt * 128 + qg * 32;
   const int q = q0w + l32;
   const int64_t tstride = (int64_t)p.batch * p.row;
-  const int koff = p.nq * D + kap * D, voff = (p.nq + p.nkv) * D + kap * D;
+  const int koff = p.nq * hd + kap * hd, voff = (p.nq + p.nkv) * hd + kap * hd;
   const rsrc_t rs = make_rsrc(p.qkv, p.qkv_bytes);
-  TileLoaderN<8> ld;
-  ld.init(tstride, wave, lane);
-  auto tile = [&](int stage, int parity, int which) { return smem + ((stage * 2 + parity) * 2 + which) * TILE_BYTES; };
+  TileLoaderN<DP, EX, 8> ld;
+  ld.init(tstride, hd, wave, lane);
+  auto tile = [&](int stage, int parity, int which) { return smem + ((stage * 2 + parity) * 2 + which) * TileFmt<DP>::BYTES; };
 
-  bf16x8 qf[D / 16];
-  load_row_frags(p.qkv + (int64_t)n * p.row + (int64_t)q * tstride + g * D, q < p.seq, hh, qf);
+  bf16x8 qf[DP / 16];
+  load_row_frags<DP, EX>(p.qkv + (int64_t)n * p.row + (int64_t)q * tstride + g * hd, q < p.seq, hd, hh, qf);
 
-  FwdRow r;
+  FwdRow<DP> r;
 #pragma unroll
-  for (int dt = 0; dt < D / 32; ++dt)
+  for (int dt = 0; dt < DP / 32; ++dt)
 #pragma unroll
     for (int v = 0; v < 16; ++v) r.o[dt][v] = 0.f;
   r.m = -INFINITY;
   r.l = 0.f;
   const float sc2 = p.scale * kLog2e;
-  const uint32_t rb = rows_base(lane), cb = cols_base(lane);
+  const uint32_t rb = rows_base<DP>(lane), cb = cols_base<DP>(lane);
 
   const int kv_end = (qt * 128 + 128 < p.seq) ? qt * 128 + 128 : p.seq;
   const int ntile = (kv_end + TILE - 1) / TILE, nstep = (ntile + 1) / 2;
@@ -377,31 +401,31 @@ __global__ __launch_bounds__(512, 1) void flash_fwd_split_kernel(const FlashPara
     if (step + 1 < nstep) issue_step(step + 1, cur ^ 1);
     const int jt = 2 * step + par, j0 = jt * TILE;
     if (jt >= ntile || j0 > q0w + 31) continue;
-    fwd_tile(tile(cur, par, 0), tile(cur, par, 1), qf, r, j0, q0w, q, hh, sc2, rb, cb);
+    fwd_tile<DP, EX>(tile(cur, par, 0), tile(cur, par, 1), qf, r, j0, q0w, q, hh, sc2, rb, cb);
   }
   wait_loads();
   __syncthreads();  // the tiles are no longer needed: the odd side's state goes where they were
-  float *xch = reinterpret_cast<float *>(smem) + (size_t)qg * ((D / 32) * 16 + 2) * 64;  // [qg][o..., m, l][lane]
+  float *xch = reinterpret_cast<float *>(smem) + (size_t)qg * ((DP / 32) * 16 + 2) * 64;  // [qg][o..., m, l][lane]
   if (par == 1) {
 #pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt)
+    for (int dt = 0; dt < DP / 32; ++dt)
 #pragma unroll
       for (int v = 0; v < 16; ++v) xch[(dt * 16 + v) * 64 + lane] = r.o[dt][v];
-    xch[(D / 32) * 16 * 64 + lane] = r.m;
-    xch[((D / 32) * 16 + 1) * 64 + lane] = r.l;
+    xch[(DP / 32) * 16 * 64 + lane] = r.m;
+    xch[((DP / 32) * 16 + 1) * 64 + lane] = r.l;
   }
   __syncthreads();
   if (par == 0) {
-    const float m2 = xch[(D / 32) * 16 * 64 + lane], l2 = xch[((D / 32) * 16 + 1) * 64 + lane];
+    const float m2 = xch[(DP / 32) * 16 * 64 + lane], l2 = xch[((DP / 32) * 16 + 1) * 64 + lane];
     const float mm = fmaxf(r.m, m2);  // r.m is finite: the even side always has key tile 0
     const float a1 = __builtin_amdgcn_exp2f(r.m - mm), a2 = __builtin_amdgcn_exp2f(m2 - mm);
     r.m = mm;
     r.l = r.l * a1 + l2 * a2;
 #pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt)
+    for (int dt = 0; dt < DP / 32; ++dt)
 #pragma unroll
       for (int v = 0; v < 16; ++v) r.o[dt][v] = r.o[dt][v] * a1 + xch[(dt * 16 + v) * 64 + lane] * a2;
-    fwd_finish(p, r, q, n, g, hh);
+    fwd_finish<DP, EX>(p, r, q, n, g, hh);
   }
 }
 
@@ -409,8 +433,9 @@ __global__ __launch_bounds__(512, 1) void flash_fwd_split_kernel(const FlashPara
 // dQ: same walk as the forward pass; dQ^T += K^T dS^T
 // =================================================================================================
 // one wave, one staged K / V tile: probabilities from the stored log-sum-exp, dS = P (dP - D), dQ^T += K^T dS^T
-__device__ __forceinline__ void dq_tile(const char *kt, const char *vt, const bf16x8 (&qf)[D / 16],
-                                        const bf16x8 (&dof)[D / 16], f32x16 (&acc)[D / 32], float lse2, float dq_d, int j0,
+template <int DP, bool EX>
+__device__ __forceinline__ void dq_tile(const char *kt, const char *vt, const bf16x8 (&qf)[DP / 16],
+                                        const bf16x8 (&dof)[DP / 16], f32x16 (&acc)[DP / 32], float lse2, float dq_d, int j0,
                                         int q0w, int q, int hh, float sc2, uint32_t rb, uint32_t cb) {
   f32x16 ds[2];
 #pragma unroll
@@ -419,9 +444,9 @@ __device__ __forceinline__ void dq_tile(const char *kt, const char *vt, const bf
 #pragma unroll
     for (int v = 0; v < 16; ++v) s[v] = dp[v] = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) {
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows_at(kt, rb, t * 32, ks), qf[ks], s, 0, 0, 0);
-      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows_at(vt, rb, t * 32, ks), dof[ks], dp, 0, 0, 0);
+    for (int ks = 0; ks < DP / 16; ++ks) {
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows_at<DP>(kt, rb, t * 32, ks), qf[ks], s, 0, 0, 0);
+      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows_at<DP>(vt, rb, t * 32, ks), dof[ks], dp, 0, 0, 0);
     }
 #pragma unroll
     for (int v = 0; v < 16; ++v)
@@ -437,19 +462,24 @@ __device__ __forceinline__ void dq_tile(const char *kt, const char *vt, const bf
 #pragma unroll
   for (int kk = 0; kk < TILE / 16; ++kk) {
     const bf16x8 df = pack8(ds[kk >> 1], 8 * (kk & 1));
+    bf16x8 dr;
+    if (EX) dr = pack8_rest(ds[kk >> 1], df, 8 * (kk & 1));
 #pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt)
-      acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_at(kt, cb, dt * 32, kk), df, acc[dt], 0, 0, 0);
+    for (int dt = 0; dt < DP / 32; ++dt) {
+      const bf16x8 kf = frag_cols_at<DP>(kt, cb, dt * 32, kk);
+      acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, df, acc[dt], 0, 0, 0);
+      if (EX) acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, dr, acc[dt], 0, 0, 0);
+    }
   }
 }
 
 // block = 128 query rows (tile qt) of one (batch entry, query head), four waves; lds: [stage][K, V] tiles, 64 KB.
 // In a block of eight waves the other four only keep the barrier count (one barrier per key tile).
-template <int NW = 4>
+template <int DP, bool EX, int NW>
 __device__ __forceinline__ void dq_block(const FlashParams &p, char *lds_base, int qt, int g, int n) {
-  char (*lds)[2][TILE_BYTES] = reinterpret_cast<char (*)[2][TILE_BYTES]>(lds_base);
+  char (*lds)[2][TileFmt<DP>::BYTES] = reinterpret_cast<char (*)[2][TileFmt<DP>::BYTES]>(lds_base);
   constexpr int QB = 32 * NW;  // query rows of the block (NW = 8: see the forward kernel)
-  const int kap = g / (p.nq / p.nkv);
+  const int kap = g / (p.nq / p.nkv), hd = EX ? p.d : DP;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (wave >= NW) {
     const int kv_end_x = (qt * QB + QB < p.seq) ? qt * QB + QB : p.seq;
@@ -462,26 +492,26 @@ __device__ __forceinline__ void dq_block(const FlashParams &p, char *lds_base, i
   const int q = q0w + l32;
   const bool qvalid = q < p.seq;
   const int64_t tstride = (int64_t)p.batch * p.row;
-  const int koff = p.nq * D + kap * D, voff = (p.nq + p.nkv) * D + kap * D;
-  const int64_t cstride = (int64_t)p.batch * p.nq * D;
+  const int koff = p.nq * hd + kap * hd, voff = (p.nq + p.nkv) * hd + kap * hd;
+  const int64_t cstride = (int64_t)p.batch * p.nq * hd;
   const rsrc_t rs = make_rsrc(p.qkv, p.qkv_bytes);
-  TileLoaderN<NW> ld;
-  ld.init(tstride, wave, lane);
+  TileLoaderN<DP, EX, NW> ld;
+  ld.init(tstride, hd, wave, lane);
 
-  bf16x8 qf[D / 16], dof[D / 16];
-  load_row_frags(p.qkv + (int64_t)n * p.row + (int64_t)q * tstride + g * D, qvalid, hh, qf);
-  load_row_frags(p.dctx + (int64_t)n * p.nq * D + (int64_t)q * cstride + g * D, qvalid, hh, dof);
+  bf16x8 qf[DP / 16], dof[DP / 16];
+  load_row_frags<DP, EX>(p.qkv + (int64_t)n * p.row + (int64_t)q * tstride + g * hd, qvalid, hd, hh, qf);
+  load_row_frags<DP, EX>(p.dctx + (int64_t)n * p.nq * hd + (int64_t)q * cstride + g * hd, qvalid, hd, hh, dof);
   const int64_t si = ((int64_t)n * p.nq + g) * p.seq + q;
   const float lse2 = qvalid ? p.lse_in[si] * kLog2e : 0.f;
   const float dq_d = qvalid ? p.dvec[si] : 0.f;
 
-  f32x16 acc[D / 32];
+  f32x16 acc[DP / 32];
 #pragma unroll
-  for (int dt = 0; dt < D / 32; ++dt)
+  for (int dt = 0; dt < DP / 32; ++dt)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[dt][v] = 0.f;
   const float sc2 = p.scale * kLog2e;
-  const uint32_t rb = rows_base(lane), cb = cols_base(lane);
+  const uint32_t rb = rows_base<DP>(lane), cb = cols_base<DP>(lane);
 
   const int kv_end = (qt * QB + QB < p.seq) ? qt * QB + QB : p.seq;
   const int ntile = (kv_end + TILE - 1) / TILE;
@@ -497,18 +527,17 @@ __device__ __forceinline__ void dq_block(const FlashParams &p, char *lds_base, i
       ld.issue(rs, lds[cur ^ 1][1], r0, (int64_t)n * p.row + voff, wave);
     }
     if (j0 > q0w + 31) continue;
-    dq_tile(lds[cur][0], lds[cur][1], qf, dof, acc, lse2, dq_d, j0, q0w, q, hh, sc2, rb, cb);
+    dq_tile<DP, EX>(lds[cur][0], lds[cur][1], qf, dof, acc, lse2, dq_d, j0, q0w, q, hh, sc2, rb, cb);
   }
   wait_loads();
-  if (qvalid) store_transposed(acc, p.scale, p.dqkv + ((int64_t)q * p.batch + n) * p.row + g * D, hh);
+  if (qvalid) store_transposed<DP, EX>(acc, p.scale, p.dqkv + ((int64_t)q * p.batch + n) * p.row + g * hd, hd, hh);
 }
-template <int NW>
-__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void flash_bwd_dq_kernel(const FlashParams p) {
-  __shared__ __align__(1024) char lds[4 * TILE_BYTES];
-  dq_block<NW>(p, lds, gridDim.z - 1 - blockIdx.z, blockIdx.x, blockIdx.y);  // heads fastest, longest walks first
+template <int DP, bool EX, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 4 ? (DP > 64 ? 2 : 3) : 1) void flash_bwd_dq_kernel(const FlashParams p) {
+  __shared__ __align__(1024) char lds[4 * TileFmt<DP>::BYTES];
+  const int qt = gridDim.z - 1 - blockIdx.z, g = blockIdx.x, n = blockIdx.y;  // heads fastest, longest walks first
+  dq_block<DP, EX, NW>(p, lds, qt, g, n);
 }
-template __global__ void flash_bwd_dq_kernel<4>(const FlashParams);
-template __global__ void flash_bwd_dq_kernel<8>(const FlashParams);
 
 // =================================================================================================
 // dK, dV: block = 128 key rows of one (batch entry, query head), eight waves: wave = 32 key rows x one 32-query
@@ -518,9 +547,10 @@ template __global__ void flash_bwd_dq_kernel<8>(const FlashParams);
 // result is the gradient.  Grouped heads: it is that head's fp32 partial.
 // =================================================================================================
 // smem: [stage][Q, dO] tiles, then [stage][lse, D] rows of floats, then the V fragments (kDkvLds bytes)
-constexpr int kDkvLds = 4 * TILE_BYTES + 2 * 2 * TILE * (int)sizeof(float) + 128 * D * 2;
+template <int DP> constexpr int kDkvLds = 4 * TileFmt<DP>::BYTES + 2 * 2 * TILE * (int)sizeof(float) + 128 * DP * 2;
+template <int DP, bool EX>
 __device__ __forceinline__ void dkv_block(const FlashParams &p, char *smem, int kt, int g, int n) {
-  const int group = p.nq / p.nkv, kap = g / group;
+  const int group = p.nq / p.nkv, kap = g / group, hd = EX ? p.d : DP;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int kr = wave & 3, t = wave >> 2;  // key-row group, query half
   const int l32 = lane & 31, hh = lane >> 5;
@@ -528,35 +558,35 @@ __device__ __forceinline__ void dkv_block(const FlashParams &p, char *smem, int 
   const int j = j0w + l32;
   const bool jvalid = j < p.seq;
   const int64_t tstride = (int64_t)p.batch * p.row;
-  const int koff = p.nq * D + kap * D, voff = (p.nq + p.nkv) * D + kap * D;
-  const int64_t cstride = (int64_t)p.batch * p.nq * D;
+  const int koff = p.nq * hd + kap * hd, voff = (p.nq + p.nkv) * hd + kap * hd;
+  const int64_t cstride = (int64_t)p.batch * p.nq * hd;
   const rsrc_t rq = make_rsrc(p.qkv, p.qkv_bytes), rdo = make_rsrc(p.dctx, p.ctx_bytes);
-  TileLoaderN<8> lq, ldo;
-  lq.init(tstride, wave, lane);
-  ldo.init(cstride, wave, lane);
-  auto tile = [&](int stage, int which) { return smem + (stage * 2 + which) * TILE_BYTES; };
-  float *stats = reinterpret_cast<float *>(smem + 4 * TILE_BYTES);  // [stage][2][TILE]
+  TileLoaderN<DP, EX, 8> lq, ldo;
+  lq.init(tstride, hd, wave, lane);
+  ldo.init(cstride, hd, wave, lane);
+  auto tile = [&](int stage, int which) { return smem + (stage * 2 + which) * TileFmt<DP>::BYTES; };
+  float *stats = reinterpret_cast<float *>(smem + 4 * TileFmt<DP>::BYTES);  // [stage][2][TILE]
 
   // The wave's K fragments stay in registers; its V fragments live in LDS ([key-row group][slice][lane], 16 bytes
   // each: 32 KB a block, written once by the first query half) and are read again at every use, which keeps the
   // kernel inside 256 registers without spills.
-  bf16x8 kf[D / 16];
-  load_row_frags(p.qkv + (int64_t)n * p.row + (int64_t)j * tstride + koff, jvalid, hh, kf);
-  char *vl = smem + 4 * TILE_BYTES + 2 * 2 * TILE * (int)sizeof(float) + (kr * (D / 16) * 64 + lane) * 16;
+  bf16x8 kf[DP / 16];
+  load_row_frags<DP, EX>(p.qkv + (int64_t)n * p.row + (int64_t)j * tstride + koff, jvalid, hd, hh, kf);
+  char *vl = smem + 4 * TileFmt<DP>::BYTES + 2 * 2 * TILE * (int)sizeof(float) + (kr * (DP / 16) * 64 + lane) * 16;
   if (t == 0) {
-    bf16x8 vf[D / 16];
-    load_row_frags(p.qkv + (int64_t)n * p.row + (int64_t)j * tstride + voff, jvalid, hh, vf);
+    bf16x8 vf[DP / 16];
+    load_row_frags<DP, EX>(p.qkv + (int64_t)n * p.row + (int64_t)j * tstride + voff, jvalid, hd, hh, vf);
 #pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) *reinterpret_cast<bf16x8 *>(vl + ks * 64 * 16) = vf[ks];
+    for (int ks = 0; ks < DP / 16; ++ks) *reinterpret_cast<bf16x8 *>(vl + ks * 64 * 16) = vf[ks];
   }
 
-  f32x16 dk[D / 32], dv[D / 32];
+  f32x16 dk[DP / 32], dv[DP / 32];
 #pragma unroll
-  for (int dt = 0; dt < D / 32; ++dt)
+  for (int dt = 0; dt < DP / 32; ++dt)
 #pragma unroll
     for (int v = 0; v < 16; ++v) dk[dt][v] = dv[dt][v] = 0.f;
   const float sc2 = p.scale * kLog2e;
-  const uint32_t rb = rows_base(lane), cb = cols_base(lane);
+  const uint32_t rb = rows_base<DP>(lane), cb = cols_base<DP>(lane);
 
   const int it_begin = (kt * 128) / TILE;
   const int it_end = (p.seq + TILE - 1) / TILE;
@@ -566,8 +596,8 @@ __device__ __forceinline__ void dkv_block(const FlashParams &p, char *smem, int 
   float st_lse = 0.f, st_d = 0.f;
   auto issue_step = [&](int step, int stage) {
     const int i0 = (it_begin + step) * TILE;
-    lq.issue(rq, tile(stage, 0), (int64_t)i0 * tstride, (int64_t)n * p.row + g * D, wave);
-    ldo.issue(rdo, tile(stage, 1), (int64_t)i0 * cstride, (int64_t)n * p.nq * D + g * D, wave);
+    lq.issue(rq, tile(stage, 0), (int64_t)i0 * tstride, (int64_t)n * p.row + g * hd, wave);
+    ldo.issue(rdo, tile(stage, 1), (int64_t)i0 * cstride, (int64_t)n * p.nq * hd + g * hd, wave);
     if (threadIdx.x < TILE) {
       const int i = i0 + threadIdx.x;
       const int64_t sidx = ((int64_t)n * p.nq + g) * p.seq + i;
@@ -596,9 +626,9 @@ __device__ __forceinline__ void dkv_block(const FlashParams &p, char *smem, int 
 #pragma unroll
     for (int v = 0; v < 16; ++v) s[v] = dp[v] = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) {
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows_at(qt, rb, t * 32, ks), kf[ks], s, 0, 0, 0);
-      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows_at(dot, rb, t * 32, ks), *reinterpret_cast<const bf16x8 *>(vl + ks * 64 * 16), dp, 0, 0, 0);
+    for (int ks = 0; ks < DP / 16; ++ks) {
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows_at<DP>(qt, rb, t * 32, ks), kf[ks], s, 0, 0, 0);
+      dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows_at<DP>(dot, rb, t * 32, ks), *reinterpret_cast<const bf16x8 *>(vl + ks * 64 * 16), dp, 0, 0, 0);
     }
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
@@ -623,29 +653,35 @@ __device__ __forceinline__ void dkv_block(const FlashParams &p, char *smem, int 
       const int kk = 2 * t + k2;
       const bf16x8 pf = pack8(s, 8 * k2);
       const bf16x8 df = pack8(dp, 8 * k2);
+      bf16x8 pr, dr;
+      if (EX) pr = pack8_rest(s, pf, 8 * k2), dr = pack8_rest(dp, df, 8 * k2);
 #pragma unroll
-      for (int dt = 0; dt < D / 32; ++dt) {
-        dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_at(dot, cb, dt * 32, kk), pf, dv[dt], 0, 0, 0);
-        dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols_at(qt, cb, dt * 32, kk), df, dk[dt], 0, 0, 0);
+      for (int dt = 0; dt < DP / 32; ++dt) {
+        const bf16x8 dof = frag_cols_at<DP>(dot, cb, dt * 32, kk);
+        dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dof, pf, dv[dt], 0, 0, 0);
+        if (EX) dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dof, pr, dv[dt], 0, 0, 0);
+        const bf16x8 qf = frag_cols_at<DP>(qt, cb, dt * 32, kk);
+        dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf, df, dk[dt], 0, 0, 0);
+        if (EX) dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf, dr, dk[dt], 0, 0, 0);
       }
     }
   }
   wait_loads();
   // the second query half hands its sums to the first through LDS (the tiles are no longer needed): dK, then dV
-  float *xch = reinterpret_cast<float *>(smem) + (size_t)kr * (D / 32) * 16 * 64;  // [kr][dt][v][lane]
+  float *xch = reinterpret_cast<float *>(smem) + (size_t)kr * (DP / 32) * 16 * 64;  // [kr][dt][v][lane]
 #pragma unroll
   for (int which = 0; which < 2; ++which) {
     __syncthreads();
     if (t == 1) {
 #pragma unroll
-      for (int dt = 0; dt < D / 32; ++dt)
+      for (int dt = 0; dt < DP / 32; ++dt)
 #pragma unroll
         for (int v = 0; v < 16; ++v) xch[(dt * 16 + v) * 64 + lane] = which == 0 ? dk[dt][v] : dv[dt][v];
     }
     __syncthreads();
     if (t == 0) {
 #pragma unroll
-      for (int dt = 0; dt < D / 32; ++dt)
+      for (int dt = 0; dt < DP / 32; ++dt)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const float other = xch[(dt * 16 + v) * 64 + lane];
@@ -656,20 +692,22 @@ __device__ __forceinline__ void dkv_block(const FlashParams &p, char *smem, int 
   }
   if (jvalid && t == 0) {
     if (p.part) {
-      float *out = p.part + (((int64_t)n * p.nq + g) * p.seq + j) * (2 * D);
-      store_transposed_f32(dk, p.scale, out, hh);
-      store_transposed_f32(dv, 1.f, out + D, hh);
+      float *out = p.part + (((int64_t)n * p.nq + g) * p.seq + j) * (2 * hd);
+      store_transposed_f32<DP, EX>(dk, p.scale, out, hd, hh);
+      store_transposed_f32<DP, EX>(dv, 1.f, out + hd, hd, hh);
     } else {
       bf16 *out = p.dqkv + ((int64_t)j * p.batch + n) * p.row;
-      store_transposed(dk, p.scale, out + koff, hh);
-      store_transposed(dv, 1.f, out + voff, hh);
+      store_transposed<DP, EX>(dk, p.scale, out + koff, hd, hh);
+      store_transposed<DP, EX>(dv, 1.f, out + voff, hd, hh);
     }
   }
 }
 
+template <int DP, bool EX>
 __global__ __launch_bounds__(512, 1) void flash_bwd_dkv_kernel(const FlashParams p) {
   extern __shared__ __align__(1024) char smem[];
-  dkv_block(p, smem, blockIdx.z, blockIdx.x, blockIdx.y);  // heads fastest, longest walks first
+  const int kt = blockIdx.z, g = blockIdx.x, n = blockIdx.y;  // heads fastest, longest walks first
+  dkv_block<DP, EX>(p, smem, kt, g, n);
 }
 
 // Both backward kernels in one launch, for grids that leave compute units idle (at most one block of each kind per
@@ -677,16 +715,33 @@ __global__ __launch_bounds__(512, 1) void flash_bwd_dkv_kernel(const FlashParams
 // kinds longest first, so that the chip works on the two independent halves of the backward pass at once instead of
 // waiting twice for a longest walk (2048 tokens, 12 heads: 192 + 192 blocks on 256 units).  Blocks of eight waves;
 // in a dQ block four of them only keep the barrier count.
+template <int DP, bool EX>
 __global__ __launch_bounds__(512, 1) void flash_bwd_both_kernel(const FlashParams p) {
   extern __shared__ __align__(1024) char smem[];
-  const int rank = blockIdx.z >> 1, tiles = gridDim.z >> 1;
-  if (blockIdx.z & 1) dq_block<4>(p, smem, tiles - 1 - rank, blockIdx.x, blockIdx.y);
-  else dkv_block(p, smem, rank, blockIdx.x, blockIdx.y);
+  const int rank = blockIdx.z >> 1, tiles = gridDim.z >> 1, g = blockIdx.x, n = blockIdx.y;
+  if (blockIdx.z & 1) dq_block<DP, EX, 4>(p, smem, tiles - 1 - rank, g, n);
+  else dkv_block<DP, EX>(p, smem, rank, g, n);
 }
+
+// Every kernel of a family by name, ahead of the host code that takes its address.
+#define TM_FLASH_FAMILY(DP, EX)                                                \
+  template __global__ void flash_fwd_kernel<DP, EX, 4>(const FlashParams);     \
+  template __global__ void flash_fwd_split_kernel<DP, EX>(const FlashParams);  \
+  template __global__ void flash_bwd_dq_kernel<DP, EX, 4>(const FlashParams);  \
+  template __global__ void flash_bwd_dkv_kernel<DP, EX>(const FlashParams);    \
+  template __global__ void flash_bwd_both_kernel<DP, EX>(const FlashParams);
+TM_FLASH_FAMILY(128, false)
+template __global__ void flash_fwd_kernel<128, false, 8>(const FlashParams);
+template __global__ void flash_bwd_dq_kernel<128, false, 8>(const FlashParams);
+TM_FLASH_FAMILY(32, true)
+TM_FLASH_FAMILY(64, true)
+TM_FLASH_FAMILY(96, true)
+TM_FLASH_FAMILY(128, true)
 
 // dK, dV of a kv head = sum of its query heads' partials, added in head order; thread = 4 columns
 __global__ __launch_bounds__(256) void flash_dkv_reduce_kernel(const FlashParams p) {
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;  // over [batch][nkv][seq][2 * D / 4]
+  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;  // over [batch][nkv][seq][2 * d / 4]
+  const int D = p.d;
   const int64_t total = (int64_t)p.batch * p.nkv * p.seq * (2 * D / 4);
   if (idx >= total) return;
   const int c4 = (int)(idx % (2 * D / 4));
@@ -709,18 +764,24 @@ __global__ __launch_bounds__(256) void flash_dkv_reduce_kernel(const FlashParams
   *reinterpret_cast<bf16x4 *>(out) = o;
 }
 
-bool attn_mfma_supported(int dtype, int64_t d) { return dtype == TM_DTYPE_BF16 && d == D; }
+// Every bf16 head size up to 128, as long as 32-bit offsets reach the tensors and the grid holds the sequence (head size
+// 128 reports what it cannot take itself; the other head sizes have the plain-ALU kernels behind them).
+bool attn_mfma_supported(int dtype, int64_t seq, int64_t batch, int64_t nq, int64_t nkv, int64_t d) {
+  if (dtype != TM_DTYPE_BF16 || d > 128) return false;
+  return d == 128 || seq * batch * (nq + 2 * nkv) * d * 2 < (1LL << 31);
+}
 
-static FlashParams make_params(int64_t seq, int64_t batch, int64_t nq, int64_t nkv) {
+static FlashParams make_params(int64_t seq, int64_t batch, int64_t nq, int64_t nkv, int64_t d) {
   FlashParams p = {};
   p.seq = (int)seq;
   p.batch = (int)batch;
   p.nq = (int)nq;
   p.nkv = (int)nkv;
-  p.row = (int)((nq + 2 * nkv) * D);
-  p.scale = (float)(1.0 / sqrt((double)D));
+  p.d = (int)d;
+  p.row = (int)((nq + 2 * nkv) * d);
+  p.scale = (float)(1.0 / sqrt((double)d));
   p.qkv_bytes = (uint32_t)(seq * batch * p.row * 2);
-  p.ctx_bytes = (uint32_t)(seq * batch * nq * D * 2);
+  p.ctx_bytes = (uint32_t)(seq * batch * nq * d * 2);
   return p;
 }
 
@@ -764,11 +825,36 @@ static bool use_both(dim3 grid) {
   return (int64_t)grid.x * grid.y * grid.z <= units;
 }
 
+static bool reserve_lds(const void *kernel, int bytes) {
+  return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
+}
+
+template <int DP, bool EX> static int launch_fwd(const FlashParams &p, dim3 grid, hipStream_t s) {
+  if (use_split(grid)) {
+    constexpr int lds = 8 * TileFmt<DP>::BYTES;
+    static bool attr_set = false;  // one flag per kernel family
+    if (!attr_set && !reserve_lds(reinterpret_cast<const void *>(&flash_fwd_split_kernel<DP, EX>), lds))
+      return fail(TM_ELAUNCH, "flash_fwd: cannot reserve LDS");
+    attr_set = true;
+    g_last_kernel = "flash_fwd_split_kernel";
+    flash_fwd_split_kernel<DP, EX><<<grid, 512, lds, s>>>(p);
+  } else {
+    g_last_kernel = "flash_fwd_kernel";
+    bool wide = false;
+    if constexpr (!EX) {
+      wide = use_wide(p.seq, p.batch, p.nq);
+      if (wide)
+        flash_fwd_kernel<DP, EX, 8><<<dim3(grid.x, grid.y, (unsigned)ceil_div(p.seq, 256)), 512, 0, s>>>(p);
+    }
+    if (!wide) flash_fwd_kernel<DP, EX, 4><<<grid, 256, 0, s>>>(p);
+  }
+  return check_launch("flash_fwd");
+}
+
 int attn_fwd_mfma_launch(int64_t seq, int64_t batch, int64_t nq, int64_t nkv, int64_t d, const void *qkv, void *ctx,
                          float *lse, hipStream_t s) {
-  (void)d;
-  if (seq * batch * (nq + 2 * nkv) * D * 2 >= (1LL << 31)) return fail(TM_ESIZE, "flash_fwd: qkv tensor above 2 GiB");
-  FlashParams p = make_params(seq, batch, nq, nkv);
+  if (seq * batch * (nq + 2 * nkv) * d * 2 >= (1LL << 31)) return fail(TM_ESIZE, "flash_fwd: qkv tensor above 2 GiB");
+  FlashParams p = make_params(seq, batch, nq, nkv, d);
   p.qkv = (const bf16 *)qkv;
   p.ctx = (bf16 *)ctx;
   p.lse = lse;
@@ -777,37 +863,52 @@ int attn_fwd_mfma_launch(int64_t seq, int64_t batch, int64_t nq, int64_t nkv, in
   // With the heads outermost instead, a long sequence's late heads start their longest walks when the chip is
   // already draining (16384 tokens, 8 heads, 512 block slots: 408 tile steps end to end against 258 balanced).
   dim3 grid((unsigned)nq, (unsigned)batch, (unsigned)ceil_div(seq, 128));
-  if (use_split(grid)) {
-    const int lds = 8 * TILE_BYTES;
-    static bool attr_set = false;
-    if (!attr_set) {
-      if (hipFuncSetAttribute(reinterpret_cast<const void *>(&flash_fwd_split_kernel),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
-        return fail(TM_ELAUNCH, "flash_fwd: cannot reserve LDS");
-      attr_set = true;
-    }
-    g_last_kernel = "flash_fwd_split_kernel";
-    flash_fwd_split_kernel<<<grid, 512, lds, s>>>(p);
-  } else {
-    g_last_kernel = "flash_fwd_kernel";
-    if (use_wide(seq, batch, nq))
-      flash_fwd_kernel<8><<<dim3((unsigned)nq, (unsigned)batch, (unsigned)ceil_div(seq, 256)), 512, 0, s>>>(p);
-    else
-      flash_fwd_kernel<4><<<grid, 256, 0, s>>>(p);
-  }
-  return check_launch("flash_fwd");
+  if (d == 128) return launch_fwd<128, false>(p, grid, s);
+  if (d <= 32) return launch_fwd<32, true>(p, grid, s);
+  if (d <= 64) return launch_fwd<64, true>(p, grid, s);
+  if (d <= 96) return launch_fwd<96, true>(p, grid, s);
+  return launch_fwd<128, true>(p, grid, s);
 }
 
-int64_t attn_bwd_mfma_partial_floats(int64_t seq, int64_t batch, int64_t nq, int64_t nkv) {
-  return nq == nkv ? 0 : batch * nq * seq * 2 * D;
+template <int DP, bool EX> static int launch_bwd(const FlashParams &p, dim3 gq, hipStream_t s) {
+  constexpr int lds = kDkvLds<DP>;
+  static_assert(lds >= 4 * TileFmt<DP>::BYTES, "the dQ block's tiles fit the dK/dV block's LDS");
+  static_assert(lds >= 4 * (DP / 32) * 16 * 64 * 4, "the second query half's sums fit");
+  static bool attr_set = false;
+  if (!attr_set && (!reserve_lds(reinterpret_cast<const void *>(&flash_bwd_dkv_kernel<DP, EX>), lds) ||
+                    !reserve_lds(reinterpret_cast<const void *>(&flash_bwd_both_kernel<DP, EX>), lds)))
+    return fail(TM_ELAUNCH, "flash_bwd: cannot reserve LDS");
+  attr_set = true;
+  g_last_kernel = "flash_bwd_dq_kernel+flash_bwd_dkv_kernel";
+  if (use_both(gq) && 2 * gq.z <= 65535) {
+    g_last_kernel = "flash_bwd_both_kernel";
+    flash_bwd_both_kernel<DP, EX><<<dim3(gq.x, gq.y, 2 * gq.z), 512, lds, s>>>(p);
+  } else {
+    bool wide = false;
+    if constexpr (!EX) {
+      wide = use_wide(p.seq, p.batch, p.nq);
+      if (wide)
+        flash_bwd_dq_kernel<DP, EX, 8><<<dim3(gq.x, gq.y, (unsigned)ceil_div(p.seq, 256)), 512, 0, s>>>(p);
+    }
+    if (!wide) flash_bwd_dq_kernel<DP, EX, 4><<<gq, 256, 0, s>>>(p);
+    flash_bwd_dkv_kernel<DP, EX><<<gq, 512, lds, s>>>(p);
+  }
+  if (p.part) {
+    const int64_t total = (int64_t)p.batch * p.nkv * p.seq * (2 * p.d / 4);
+    flash_dkv_reduce_kernel<<<(unsigned)ceil_div(total, (int64_t)256), 256, 0, s>>>(p);
+  }
+  return check_launch("flash_bwd");
+}
+
+int64_t attn_bwd_mfma_partial_floats(int64_t seq, int64_t batch, int64_t nq, int64_t nkv, int64_t d) {
+  return nq == nkv ? 0 : batch * nq * seq * 2 * d;
 }
 
 int attn_bwd_mfma_launch(int64_t seq, int64_t batch, int64_t nq, int64_t nkv, int64_t d, const void *qkv,
                          const void *dctx, const float *lse, const float *dvec, float *part, void *dqkv,
                          hipStream_t s) {
-  (void)d;
-  if (seq * batch * (nq + 2 * nkv) * D * 2 >= (1LL << 31)) return fail(TM_ESIZE, "flash_bwd: qkv tensor above 2 GiB");
-  FlashParams p = make_params(seq, batch, nq, nkv);
+  if (seq * batch * (nq + 2 * nkv) * d * 2 >= (1LL << 31)) return fail(TM_ESIZE, "flash_bwd: qkv tensor above 2 GiB");
+  FlashParams p = make_params(seq, batch, nq, nkv, d);
   p.qkv = (const bf16 *)qkv;
   p.dctx = (const bf16 *)dctx;
   p.lse_in = lse;
@@ -816,35 +917,12 @@ int attn_bwd_mfma_launch(int64_t seq, int64_t batch, int64_t nq, int64_t nkv, in
   p.part = nq == nkv ? nullptr : part;
   if (nq != nkv && !part) return fail(TM_EINVAL, "flash_bwd: grouped heads need the partial buffer");
   if (ceil_div(seq, 128) > 65535 || batch > 65535) return fail(TM_ESIZE, "flash_bwd: sequence or batch too long for the grid");
-  const unsigned tiles = (unsigned)ceil_div(seq, 128);
-  dim3 gq((unsigned)nq, (unsigned)batch, tiles);  // heads fastest: see the forward launch
-  const int lds = kDkvLds;
-  static_assert(kDkvLds >= 4 * TILE_BYTES, "the dQ block's tiles fit the dK/dV block's LDS");
-  static bool attr_set = false;
-  if (!attr_set) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void *>(&flash_bwd_dkv_kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void *>(&flash_bwd_both_kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
-      return fail(TM_ELAUNCH, "flash_bwd: cannot reserve LDS");
-    attr_set = true;
-  }
-  g_last_kernel = "flash_bwd_dq_kernel+flash_bwd_dkv_kernel";
-  if (use_both(gq) && 2 * tiles <= 65535) {
-    g_last_kernel = "flash_bwd_both_kernel";
-    flash_bwd_both_kernel<<<dim3((unsigned)nq, (unsigned)batch, 2 * tiles), 512, lds, s>>>(p);
-  } else {
-    if (use_wide(seq, batch, nq))
-      flash_bwd_dq_kernel<8><<<dim3((unsigned)nq, (unsigned)batch, (unsigned)ceil_div(seq, 256)), 512, 0, s>>>(p);
-    else
-      flash_bwd_dq_kernel<4><<<gq, 256, 0, s>>>(p);
-    flash_bwd_dkv_kernel<<<gq, 512, lds, s>>>(p);
-  }
-  if (p.part) {
-    const int64_t total = batch * nkv * seq * (2 * D / 4);
-    flash_dkv_reduce_kernel<<<(unsigned)ceil_div(total, (int64_t)256), 256, 0, s>>>(p);
-  }
-  return check_launch("flash_bwd");
+  dim3 gq((unsigned)nq, (unsigned)batch, (unsigned)ceil_div(seq, 128));  // heads fastest: see the forward launch
+  if (d == 128) return launch_bwd<128, false>(p, gq, s);
+  if (d <= 32) return launch_bwd<32, true>(p, gq, s);
+  if (d <= 64) return launch_bwd<64, true>(p, gq, s);
+  if (d <= 96) return launch_bwd<96, true>(p, gq, s);
+  return launch_bwd<128, true>(p, gq, s);
 }
 
 }  // namespace tmk

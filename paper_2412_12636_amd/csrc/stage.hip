@@ -70,7 +70,7 @@ static int validate(const tm_stage_config_t *c) {
   if (T > 0x7fffffffLL / 8) return fail(TM_ESIZE, "config: too many tokens");
   // the same condition as the attention entry points: what the matrix-core kernels do not take goes to the
   // plain-ALU kernels, which hold a row of scores in LDS
-  if (!attn_mfma_supported(c->dtype, c->head_dim) && c->seq > attn_generic_max_seq())
+  if (!(c->dtype == TM_DTYPE_BF16 && c->head_dim == 128) && c->seq > attn_generic_max_seq())
     return fail(TM_ESIZE, "config: seq above %d needs bf16 with head_dim 128", attn_generic_max_seq());
   return TM_OK;
 }

@@ -418,6 +418,40 @@ def test_attention_block_forms(env, monkeypatch, split, seq, batch, nq, nkv):
     assert rel_err(got[..., A + nkv * d:], dv.reshape(seq, batch, -1)) <= tol
 
 
+@pytest.mark.parametrize("form", ["0", "1"], ids=["separate_blocks", "split_and_single_launch"])
+@pytest.mark.parametrize("seq,batch,nq,nkv,d", [(65, 1, 2, 2, 8), (300, 2, 4, 2, 32), (129, 1, 2, 1, 40), (1, 2, 2, 1, 64),
+                                                 (193, 1, 2, 2, 64), (64, 1, 4, 1, 72), (200, 2, 2, 2, 80), (130, 1, 2, 1, 96),
+                                                 (127, 1, 1, 1, 104), (257, 1, 2, 1, 120)])
+def test_attention_head_sizes_below_128(env, monkeypatch, form, seq, batch, nq, nkv, d):
+    """bf16 head sizes other than 128 on the matrix cores: every padded width (32, 64, 96, 128), head sizes with and
+    without padding columns, one position, ends of tiles, grouped heads, in every block form.  Probabilities keep 16
+    significand bits there, so a result is off by its own rounding to bf16 (2^-9 of a value) and, behind ctx, by
+    ctx's rounding in the row statistics of the backward pass: 2^-8 for ctx, 2^-7 for the gradients."""
+    torch, tm = env
+    for name in ("TM_ATTN_SPLIT", "TM_ATTN_BWD_BOTH"):
+        monkeypatch.setenv(name, form)
+    print(f"attention form={form} seq={seq} batch={batch} nq={nq} nkv={nkv} d={d}", flush=True)
+    rng = np.random.default_rng(seq * 5 + d)
+    A, B, W = nq * d, nkv * d, (nq + 2 * nkv) * d
+    qkv, dctx = rand(rng, (seq, batch, W), 1.0, BF16), rand(rng, (seq, batch, A), 0.1, BF16)
+    s = stream_ptr(torch)
+    qd = to_dev(torch, qkv, BF16)
+    ctx = torch.full((seq + 1, batch, A), 7.0, dtype=torch.bfloat16, device="cuda")        # one row more: stays as it is
+    dqkv = torch.full((seq + 1, batch, W), 7.0, dtype=torch.bfloat16, device="cuda")
+    lse = torch.zeros((batch, nq, seq), dtype=torch.float32, device="cuda")
+    scratch = torch.empty(tm.tm_op_attn_bwd_scratch_bytes(BF16, seq, batch, nq, nkv, d), dtype=torch.uint8, device="cuda")
+    tm.tm_op_attn_fwd(BF16, seq, batch, nq, nkv, d, qd, ctx, lse, s)
+    tm.tm_op_attn_bwd(BF16, seq, batch, nq, nkv, d, qd, ctx, to_dev(torch, dctx, BF16), lse, scratch, dqkv, s)
+    q64 = qkv.astype(np.float64)
+    q, k, v = (a.reshape(seq, batch, -1, d) for a in (q64[..., :A], q64[..., A:A + B], q64[..., A + B:]))
+    assert rel_err(to_host(ctx[:seq]), so.attention_fwd(q, k, v).reshape(seq, batch, A)) <= 2.0 ** -8
+    refs = so.attention_bwd(dctx.astype(np.float64).reshape(seq, batch, nq, d), q, k, v)
+    got = to_host(dqkv[:seq])
+    for part, ref in zip((got[..., :A], got[..., A:A + B], got[..., A + B:]), refs):
+        assert rel_err(part, ref.reshape(seq, batch, -1)) <= 2.0 ** -7
+    assert bool((ctx[seq:] == 7.0).all()) and bool((dqkv[seq:] == 7.0).all())
+
+
 @pytest.mark.parametrize("both", ["0", "1"], ids=["two_launches", "one_launch"])
 @pytest.mark.parametrize("seq,batch,nq,nkv", [(700, 1, 3, 3), (300, 2, 4, 2), (64, 1, 1, 1), (1, 1, 2, 1), (129, 1, 2, 2),
                                                (193, 1, 2, 1)],
