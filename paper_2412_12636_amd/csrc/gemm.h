@@ -47,10 +47,13 @@ int64_t gemm_mfma_splitk_bytes(const GemmArgs &g);
 int gemm_mfma_tune(const GemmArgs *variants, int n, hipStream_t s);
 // Number of tile configurations, and a process-wide override (index, or -1 for the automatic choice).
 // dw[N,K] = dy[T,N]^T x[T,K] (bf16 operands) with the Adam update of those N*K parameters in the product's
-// epilogue.  `supported` says whether the shapes and pointers allow it (matrix-core path, T a multiple of 64).
+// epilogue.  `supported` says whether the shapes and pointers allow it (matrix-core path).
 bool linear_wgrad_adam_supported(int64_t T, int64_t N, int64_t K, const void *dy, const void *x, const float *dw);
 int linear_wgrad_adam(int64_t T, int64_t N, int64_t K, const void *dy, const void *x, float *dw, const AdamTarget &target,
                       hipStream_t s);
+// Configurations whose kernels take a reduction length that is not a multiple of 64 of an operand with contiguous
+// reduction axis; the other pipelined ones run such products as 128x128 (configuration 1).
+inline bool gemm_config_takes_ragged_k(int config) { return config == 9 || config == 10 || config >= 13; }
 int gemm_mfma_config_count();
 int gemm_mfma_force_config(int index);
 

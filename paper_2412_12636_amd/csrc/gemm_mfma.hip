@@ -67,6 +67,7 @@ static int heuristic_config(const GemmArgs &g) {
   int pick = 0;
   const int layout = layout_of(g);
   for (int c = 0; c < kNumConfigs; ++c) {
+    if (g.K % 64 != 0 && layout != 2 && c != 1 && !gemm_config_takes_ragged_k(c)) continue;
     const TileConfig &t = kConfigs[c];
     const int64_t nb = ceil_div(g.M, t.bm) * ceil_div(g.N, t.bn);
     const double passes = (double)ceil_div(nb, 256 * t.occ);
@@ -137,7 +138,7 @@ static bool fused_on_large_tiles(const GemmArgs &g) {
     if (const char *t = getenv("TM_GEMM_FUSED_LARGE_MAXT")) max_t = atoll(t);
   }
   const TileConfig &t = kConfigs[kLdwLargeConfig];
-  return on && g.K <= max_t && g.K % 64 == 0 && ceil_div(g.M, t.bm) * ceil_div(g.N, t.bn) >= 512;
+  return on && g.K <= max_t && ceil_div(g.M, t.bm) * ceil_div(g.N, t.bn) >= 512;
 }
 
 static int pick_config(const GemmArgs &g) {
@@ -242,7 +243,7 @@ int gemm_mfma_tune(const GemmArgs *variants, int n, hipStream_t s) {
   if (n <= 0 || forced_config() >= 0) return TM_OK;
   std::vector<GemmArgs> v(variants, variants + n);
   for (GemmArgs &g : v) {
-    if (!gemm_mfma_supported(g) || g.K % 64 != 0) return TM_OK;
+    if (!gemm_mfma_supported(g)) return TM_OK;
     if (g.M != v[0].M || g.N != v[0].N || g.K != v[0].K || layout_of(g) != layout_of(v[0]))
       return fail(TM_EINVAL, "gemm_mfma_tune: variants differ in shape or layout");
     g.bias = nullptr;

@@ -22,11 +22,9 @@
 // What bounds the kernel is the path from L2 into LDS (about 50 bytes per clock and compute unit, and
 // only whole 128-byte lines count: hence 64-element steps) together with the LDS reads, so the tile
 // shapes trade traffic per flop against how evenly the tiles fill the 256 compute units.
-// A reduction length that is not a multiple of 64 cannot be masked on this path; such shapes take the
-// staged kernel below.
-//
-// Staged kernel (gemm_staged_kernel): 128x128 tile, global -> registers -> LDS with the reduction
-// tail masked on the way; strided operands are transposed in registers.  Any K that is a multiple of 8.
+// A reduction length that is not a multiple of 64: a strided operand's rows past the end are past the tensor and read
+// as zero; of an operand with contiguous reduction axis the lanes whose 16-byte chunk lies behind the end get an offset
+// outside the tensor, which does the same.
 //
 // Global accesses use buffer descriptors: reads past the end of a tensor return zero and writes
 // past the end are dropped, so ragged M / N edges need no branches.  Only the per-lane offset is
@@ -35,8 +33,7 @@
 // Epilogue.  bf16 results: the MFMA operands are passed swapped, so an accumulator tile is C^T and every
 // lane owns four consecutive output columns of one row; the block's tile is assembled in LDS and leaves
 // as whole rows (16 bytes per lane), a residual operand arrives the same way.  fp32 results: natural
-// orientation, a store instruction writes two whole 128-byte lines, streamed past the caches.  (The staged
-// kernel stores its bf16 results straight from the accumulators.)
+// orientation, a store instruction writes two whole 128-byte lines, streamed past the caches.
 //
 // Block index -> tile mapping: consecutive hardware block ids land on different XCDs (8 per chip,
 // each with its own L2); ids are re-numbered so that every XCD works on a contiguous range of
@@ -318,19 +315,32 @@ template <int R, int BK, int NW = 4> struct DirectKC {
     return BK == 64 ? ((row ^ (row >> 3)) & 7) : ((row >> 1) & 3);
   }
   uint32_t voff[NLOAD];
-  __device__ __forceinline__ void init(int64_t ld, int row0, int wave, int lane) {
+  int k_end, k_lane;  // the reduction length, and the k of this lane's chunk of load 0 inside a step
+  __device__ __forceinline__ void init(int64_t ld, int row0, int wave, int lane, int K) {
+    static_assert(BK == 64 && (NW == 2 || NW == 4 || NW == 8), "chunk of load i = chunk of load 0 ^ (i * NW) % 8");
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i) {
       const int row = (i * NW + wave) * RPL + lane / CPR;
       const int c = (lane % CPR) ^ swz(row);  // logical chunk that belongs at this lane's LDS position
       voff[i] = (uint32_t)(((int64_t)(row0 + row) * ld + c * 8) * 2);
+      if (i == 0) k_lane = c * 8;
+    }
+    k_end = K;
+  }
+  // The last step of a length that is not a multiple of 64: chunks past the end of the reduction hold the next row's
+  // elements.  Their lanes get an offset outside every tensor (below 2 GiB), which reads as zero.
+  __device__ __forceinline__ void issue(rsrc_t rs, char *tile, int k0, int64_t /*ld*/, int wave, bool tail) const {
+#pragma unroll
+    for (int i = 0; i < NLOAD; ++i) {
+      uint32_t off = voff[i];
+      if (tail && k0 + (k_lane ^ (((i * NW) & 7) * 8)) >= k_end) off = 0x80000000u;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(tile + (i * NW + wave) * 1024), 16, off, (uint32_t)k0 * 2u, 0, 0);
     }
   }
-  __device__ __forceinline__ void issue(rsrc_t rs, char *tile, int k0, int64_t /*ld*/, int wave) const {
-#pragma unroll
-    for (int i = 0; i < NLOAD; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(tile + (i * NW + wave) * 1024), 16, voff[i],
-                                               (uint32_t)k0 * 2u, 0, 0);
+  // picks the form by a scalar branch: for waves whose loads are not interleaved with MFMAs
+  __device__ __forceinline__ void issue_any(rsrc_t rs, char *tile, int k0, int64_t ld, int wave) const {
+    if (k0 + BK > k_end) issue(rs, tile, k0, ld, wave, true);
+    else issue(rs, tile, k0, ld, wave, false);
   }
   // fragment of the 32-row block starting at r32: lane's row r32 + lane%32, reduction slots 16ks + 8hh + 0..7
   static __device__ __forceinline__ bf16x8 frag(const char *tile, int r32, int ks, int lane) {
@@ -360,7 +370,7 @@ template <int R, int BK, int NW = 4> struct DirectKS {
     return CPR % 16 == 0 ? low ^ (((low >> 1) & 1) << 3) : low;
   }
   uint32_t voff[NLOAD];
-  __device__ __forceinline__ void init(int64_t ld, int row0, int wave, int lane) {
+  __device__ __forceinline__ void init(int64_t ld, int row0, int wave, int lane, int /*K*/) {
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i) {
       const int idx = (i * NW + wave) * 64 + lane;
@@ -368,12 +378,16 @@ template <int R, int BK, int NW = 4> struct DirectKS {
       voff[i] = (uint32_t)(((int64_t)kk * ld + row0 + c * 8) * 2);
     }
   }
-  __device__ __forceinline__ void issue(rsrc_t rs, char *tile, int k0, int64_t ld, int wave) const {
+  __device__ __forceinline__ void issue(rsrc_t rs, char *tile, int k0, int64_t ld, int wave, bool /*tail*/) const {
     // the step offset travels in the per-lane offset: that one is checked against the buffer size
     const uint32_t koff = (uint32_t)((int64_t)k0 * ld * 2);
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(tile + (i * NW + wave) * 1024), 16, voff[i] + koff, 0, 0, 0);
+  }
+  // rows past the end of the reduction are past the tensor and read as zero: one form for every length
+  __device__ __forceinline__ void issue_any(rsrc_t rs, char *tile, int k0, int64_t ld, int wave) const {
+    issue(rs, tile, k0, ld, wave, false);
   }
   // ds_read_b64_tr_b16: within 16 lanes, lane i receives element (i%4) of the 8-byte pieces addressed
   // by lanes i/4, i/4+4, i/4+8, i/4+12.  With lane s addressing T[k0 + s/4][r0 + 4*(s%4) ..+3], lane i
@@ -577,7 +591,8 @@ template <int MF, int DSN, int LOADS, int i> __device__ __forceinline__ void sch
 // can have in flight between L2 and LDS (free LDS space) against the latency of that path (a 64 KB burst of a
 // block takes about 2500 clocks to arrive even from L2), not LDS or MFMA throughput.  A third stage for B alone
 // measured nothing (the A tiles of the same batch are as late); three of both need tiles of at most 53 KB a stage.
-template <int BM, int BN, int BK, int WGM, int WGN, bool A_KC, bool B_KC, int EPI, int NSA = 2, int NSB = 2>
+// TAIL: the last step may be ragged (K not a multiple of BK) and an operand has a contiguous reduction axis.
+template <int BM, int BN, int BK, int WGM, int WGN, bool A_KC, bool B_KC, int EPI, int NSA = 2, int NSB = 2, bool TAIL = false>
 __global__ __launch_bounds__(64 * WGM * WGN, (WGM * WGN == 4 && BM * BN <= 256 * 128 && NSB == 2) ? 2 : 1) void gemm_pipe_kernel(
     const MfmaGemmParams p_in) {
   static_assert(NSA >= 2 && NSA <= 3 && NSB >= NSA && NSB <= 3, "two or three LDS stages, B at least as many as A");
@@ -617,8 +632,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, (WGM * WGN == 4 && BM * BN <= 256 *
   LA la;
   LB lb;
   const rsrc_t ra = make_rsrc(p.A, p.a_bytes), rb = make_rsrc(p.B, p.b_bytes);
-  la.init(p.lda, m0, wave, lane);
-  lb.init(p.ldb, n0, wave, lane);
+  la.init(p.lda, m0, wave, lane, p.K);
+  lb.init(p.ldb, n0, wave, lane, p.K);
 
   f32x16 acc[TM][TN];
 #pragma unroll
@@ -631,8 +646,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, (WGM * WGN == 4 && BM * BN <= 256 *
   const int nk = (p.K + BK - 1) / BK;
   bf16x8 a[2][TM], b[2][TN];
   // prologue: stage 0 in LDS, its slice 0 in registers, stage 1 in flight
-  la.issue(ra, lds, 0, p.lda, wave);
-  lb.issue(rb, lds + B_BASE, 0, p.ldb, wave);
+  la.issue(ra, lds, 0, p.lda, wave, TAIL);
+  lb.issue(rb, lds + B_BASE, 0, p.ldb, wave, TAIL);
   wait_vmcnt<0>();
   __builtin_amdgcn_s_barrier();
 #pragma unroll
@@ -642,8 +657,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, (WGM * WGN == 4 && BM * BN <= 256 *
 #pragma unroll
   for (int ahead = 1; ahead < NSB; ++ahead) {
     const int k1 = (ahead < nk ? ahead : nk - 1) * BK;  // never past K: a surplus fetch repeats the last step
-    if (ahead < NSA) la.issue(ra, lds + ahead * LA::BYTES, k1, p.lda, wave);
-    lb.issue(rb, lds + B_BASE + ahead * LB::BYTES, k1, p.ldb, wave);
+    if (ahead < NSA) la.issue(ra, lds + ahead * LA::BYTES, k1, p.lda, wave, TAIL);
+    lb.issue(rb, lds + B_BASE + ahead * LB::BYTES, k1, p.ldb, wave, TAIL);
   }
 
   int ca = 0, na = 1, cb = 0, nb = 1;  // LDS stages of steps kt and kt+1, per operand
@@ -673,8 +688,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, (WGM * WGN == 4 && BM * BN <= 256 *
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     // the current stages are free: fetch steps kt+NSA / kt+NSB into them (at the end the last step again, never consumed)
-    la.issue(ra, As, (kt + NSA < nk ? kt + NSA : nk - 1) * BK, p.lda, wave);
-    lb.issue(rb, Bs, (kt + NSB < nk ? kt + NSB : nk - 1) * BK, p.ldb, wave);
+    la.issue(ra, As, (kt + NSA < nk ? kt + NSA : nk - 1) * BK, p.lda, wave, TAIL);
+    lb.issue(rb, Bs, (kt + NSB < nk ? kt + NSB : nk - 1) * BK, p.ldb, wave, TAIL);
 #pragma unroll
     for (int i = 0; i < TM; ++i) a[0][i] = LA::frag(An, wm * WM + i * 32, 0, lane);
 #pragma unroll
@@ -756,23 +771,23 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP), 3) void gemm_ldw_kernel(cons
     LA la;
     LB lb;
     const rsrc_t ra = make_rsrc(p.A, p.a_bytes), rb = make_rsrc(p.B, p.b_bytes);
-    la.init(p.lda, m0, lw, lane);
-    lb.init(p.ldb, n0, lw, lane);
-    la.issue(ra, lds, 0, p.lda, lw);
-    lb.issue(rb, lds + B_BASE, 0, p.ldb, lw);
+    la.init(p.lda, m0, lw, lane, p.K);
+    lb.init(p.ldb, n0, lw, lane, p.K);
+    la.issue_any(ra, lds, 0, p.lda, lw);
+    lb.issue_any(rb, lds + B_BASE, 0, p.ldb, lw);
     wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
     {
       const int k1 = (1 < nk ? 1 : nk - 1) * BK;  // never past K: a surplus fetch repeats the last step
-      la.issue(ra, lds + LA::BYTES, k1, p.lda, lw);
-      lb.issue(rb, lds + B_BASE + LB::BYTES, k1, p.ldb, lw);
+      la.issue_any(ra, lds + LA::BYTES, k1, p.lda, lw);
+      lb.issue_any(rb, lds + B_BASE + LB::BYTES, k1, p.ldb, lw);
     }
     for (int kt = 0; kt < nk; ++kt) {
       wait_vmcnt<0>();  // this wave's part of step kt+1 has landed
       __builtin_amdgcn_s_barrier();
       const int k2 = (kt + 2 < nk ? kt + 2 : nk - 1) * BK;
-      la.issue(ra, lds + (kt & 1) * LA::BYTES, k2, p.lda, lw);
-      lb.issue(rb, lds + B_BASE + (kt & 1) * LB::BYTES, k2, p.ldb, lw);
+      la.issue_any(ra, lds + (kt & 1) * LA::BYTES, k2, p.lda, lw);
+      lb.issue_any(rb, lds + B_BASE + (kt & 1) * LB::BYTES, k2, p.ldb, lw);
     }
     wait_vmcnt<0>();  // drain the look-ahead loads before the stages are reused or the block exits
     if constexpr (EPI == 0) {
@@ -918,8 +933,8 @@ __global__ __launch_bounds__(512, 1) void gemm_alt_kernel(const MfmaGemmParams p
   LA la;
   LB lb;
   const rsrc_t ra = make_rsrc(p.A, p.a_bytes), rb = make_rsrc(p.B, p.b_bytes);
-  la.init(p.lda, m0, wave, lane);
-  lb.init(p.ldb, n0, wave, lane);
+  la.init(p.lda, m0, wave, lane, p.K);
+  lb.init(p.ldb, n0, wave, lane, p.K);
 
   f32x16 acc[TM][TN];
 #pragma unroll
@@ -935,8 +950,8 @@ __global__ __launch_bounds__(512, 1) void gemm_alt_kernel(const MfmaGemmParams p
   auto issue = [&](int step) {
     const int k0 = (step < nk ? step : nk - 1) * BK;
     char *st = lds + (step & 1) * STAGE;
-    la.issue(ra, st, k0, p.lda, wave);
-    lb.issue(rb, st + LA::BYTES, k0, p.ldb, wave);
+    la.issue_any(ra, st, k0, p.lda, wave);
+    lb.issue_any(rb, st + LA::BYTES, k0, p.ldb, wave);
   };
   // Fragment addresses of an operand with contiguous reduction axis: row r of the tile, 16-byte chunk
   // (2 ks + lane/32) ^ swz(r).  swz looks at row bits 0..5 only and 32 rows further on it flips bit 2, so
@@ -1026,145 +1041,6 @@ __global__ __launch_bounds__(512, 1) void gemm_alt_kernel(const MfmaGemmParams p
 }
 
 // =================================================================================================
-// staged kernel (any K that is a multiple of 8): 128x128x64, registers in between
-// =================================================================================================
-constexpr int SBK = 64, SROWB = SBK * 2;
-__device__ __forceinline__ int sswz(int row) { return (row ^ (row >> 3)) & 7; }
-
-template <int R> struct StagedKC {
-  static constexpr int NCH = R / 32;
-  u32x4 reg[NCH];
-  uint32_t voff[NCH];
-  __device__ __forceinline__ void init(int64_t ld, int row0) {
-    const int c = threadIdx.x & 7, r0 = threadIdx.x >> 3;
-#pragma unroll
-    for (int i = 0; i < NCH; ++i) voff[i] = (uint32_t)(((int64_t)(row0 + r0 + 32 * i) * ld + c * 8) * 2);
-  }
-  __device__ __forceinline__ void g2r(rsrc_t rs, int k0) {
-#pragma unroll
-    for (int i = 0; i < NCH; ++i) reg[i] = buf_load16(rs, voff[i], (uint32_t)k0 * 2);
-  }
-  // the mask is applied here, after the MFMAs that overlap the loads, so that it forces no early wait
-  __device__ __forceinline__ void r2s(char *lds, int k_left) const {
-    const int c = threadIdx.x & 7, r0 = threadIdx.x >> 3;
-    const bool drop = c * 8 >= k_left;
-#pragma unroll
-    for (int i = 0; i < NCH; ++i) {
-      const int r = r0 + 32 * i;
-      u32x4 v = reg[i];
-      if (drop) v = u32x4{0u, 0u, 0u, 0u};
-      *reinterpret_cast<u32x4 *>(lds + r * SROWB + ((c ^ sswz(r)) << 4)) = v;
-    }
-  }
-};
-
-template <int R> struct StagedKS {
-  static constexpr int RB = R / 8, KG_STEP = 256 / RB, NB = 16 / KG_STEP;
-  u32x4 reg[NB][4];
-  uint32_t voff[NB];
-  int64_t ldb2;
-  __device__ __forceinline__ void init(int64_t ld, int row0) {
-    const int rb = threadIdx.x % RB, kg0 = threadIdx.x / RB;
-    ldb2 = ld * 2;
-#pragma unroll
-    for (int i = 0; i < NB; ++i) voff[i] = (uint32_t)(((int64_t)(kg0 + i * KG_STEP) * 4 * ld + row0 + rb * 8) * 2);
-  }
-  __device__ __forceinline__ void g2r(rsrc_t rs, int k0) {
-    const uint32_t base = (uint32_t)((int64_t)k0 * ldb2);
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) reg[i][j] = buf_load16(rs, voff[i] + (uint32_t)(j * ldb2), base);
-  }
-  // 4 k-rows x 8 columns per thread are transposed in registers into 8 pieces of 4 k-values
-  __device__ __forceinline__ void r2s(char *lds, int /*k_left*/) const {
-    const int rb = threadIdx.x % RB, kg0 = threadIdx.x / RB;
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const int kg = kg0 + i * KG_STEP;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int w = e >> 1;
-        u32x2 o;
-        if (e & 1) {
-          o[0] = (reg[i][0][w] >> 16) | (reg[i][1][w] & 0xffff0000u);
-          o[1] = (reg[i][2][w] >> 16) | (reg[i][3][w] & 0xffff0000u);
-        } else {
-          o[0] = (reg[i][0][w] & 0xffffu) | (reg[i][1][w] << 16);
-          o[1] = (reg[i][2][w] & 0xffffu) | (reg[i][3][w] << 16);
-        }
-        const int r = rb * 8 + e;
-        *reinterpret_cast<u32x2 *>(lds + r * SROWB + (((kg >> 1) ^ sswz(r)) << 4) + ((kg & 1) << 3)) = o;
-      }
-    }
-  }
-};
-template <int R, bool KC> struct StagedSel { typedef StagedKC<R> type; };
-template <int R> struct StagedSel<R, false> { typedef StagedKS<R> type; };
-
-template <bool A_KC, bool B_KC, int EPI>
-__global__ __launch_bounds__(256) void gemm_staged_kernel(const MfmaGemmParams p) {
-  constexpr int BM = 128, BN = 128, WM = 64, WN = 64, TM = 2, TN = 2;
-  constexpr int A_BYTES = BM * SROWB, STAGE = (BM + BN) * SROWB;
-  __shared__ __align__(16) char lds[2 * STAGE];
-  int m0, n0;
-  tile_of_block(p, BM, BN, m0, n0);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, hh = lane >> 5;
-  typename StagedSel<BM, A_KC>::type la;
-  typename StagedSel<BN, B_KC>::type lb;
-  const rsrc_t ra = make_rsrc(p.A, p.a_bytes), rb = make_rsrc(p.B, p.b_bytes);
-  la.init(p.lda, m0);
-  lb.init(p.ldb, n0);
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  const int nk = (p.K + SBK - 1) / SBK;
-  la.g2r(ra, 0);
-  lb.g2r(rb, 0);
-  la.r2s(lds, p.K);
-  lb.r2s(lds + A_BYTES, p.K);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < nk) {
-      la.g2r(ra, (kt + 1) * SBK);
-      lb.g2r(rb, (kt + 1) * SBK);
-    }
-    const char *As = lds + cur * STAGE, *Bs = As + A_BYTES;
-#pragma unroll
-    for (int ks = 0; ks < SBK / 16; ++ks) {
-      bf16x8 a[TM], b[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int r = wm * WM + i * 32 + l32;
-        a[i] = *reinterpret_cast<const bf16x8 *>(As + r * SROWB + (((2 * ks + hh) ^ sswz(r)) << 4));
-      }
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int r = wn * WN + j * 32 + l32;
-        b[j] = *reinterpret_cast<const bf16x8 *>(Bs + r * SROWB + (((2 * ks + hh) ^ sswz(r)) << 4));
-      }
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = mfma_for<EPI>(a[i], b[j], acc[i][j]);
-    }
-    if (kt + 1 < nk) {
-      char *nx = lds + (cur ^ 1) * STAGE;
-      la.r2s(nx, p.K - (kt + 1) * SBK);
-      lb.r2s(nx + A_BYTES, p.K - (kt + 1) * SBK);
-    }
-    __syncthreads();
-  }
-  epilogue<TM, TN, EPI>(p, acc, m0 + wm * WM, n0 + wn * WN, l32, hh);
-}
-
-// =================================================================================================
 // host side: one layout (A_KC, B_KC, EPI) per translation unit, so that the variants compile in parallel
 // =================================================================================================
 template <bool A_KC, bool B_KC, int EPI> static MfmaGemmParams make_params(const GemmArgs &g, int BM, int BN) {
@@ -1217,7 +1093,7 @@ static std::string kernel_tag(const char *base, int bm, int bn, int wgm, int wgn
          std::to_string(wgn) + "," + (akc ? "kc" : "ks") + "," + (bkc ? "kc" : "ks") + ",epi" + std::to_string(epi) + ">";
 }
 
-template <int BM, int BN, int WGM, int WGN, bool A_KC, bool B_KC, int EPI, int NSA = 2, int NSB = 2>
+template <int BM, int BN, int WGM, int WGN, bool A_KC, bool B_KC, int EPI, int NSA = 2, int NSB = 2, bool TAIL = false>
 static int launch_pipe(const GemmArgs &g, hipStream_t s) {
   constexpr int BK = GEMM_BK;
   const MfmaGemmParams p = make_params<A_KC, B_KC, EPI>(g, BM, BN);
@@ -1225,7 +1101,7 @@ static int launch_pipe(const GemmArgs &g, hipStream_t s) {
   static_assert(lds_bytes <= 160 * 1024, "LDS");
   static bool attr_set = false;  // per instantiation
   if (!attr_set) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_pipe_kernel<BM, BN, BK, WGM, WGN, A_KC, B_KC, EPI, NSA, NSB>),
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_pipe_kernel<BM, BN, BK, WGM, WGN, A_KC, B_KC, EPI, NSA, NSB, TAIL>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes) != hipSuccess)
       return fail(TM_ELAUNCH, "gemm_mfma: cannot reserve %d bytes of LDS", lds_bytes);
     attr_set = true;
@@ -1237,7 +1113,7 @@ static int launch_pipe(const GemmArgs &g, hipStream_t s) {
   if (EPI == 3 && !g.adam) return fail(TM_EINVAL, "gemm_mfma: the fused update needs its target");
   if (g.k_splits > 1 && (EPI != 2 || g.K % ((int64_t)BK * g.k_splits) != 0))
     return fail(TM_EINVAL, "gemm_mfma: split reduction needs whole steps per part and fp32 results");
-  gemm_pipe_kernel<BM, BN, BK, WGM, WGN, A_KC, B_KC, EPI, NSA, NSB>
+  gemm_pipe_kernel<BM, BN, BK, WGM, WGN, A_KC, B_KC, EPI, NSA, NSB, TAIL>
       <<<dim3((unsigned)nblk, (unsigned)(g.k_splits > 1 ? g.k_splits : 1)), 64 * WGM * WGN, lds_bytes, s>>>(p);
   return check_launch("gemm_pipe");
 }
@@ -1290,14 +1166,6 @@ static int launch_ldw(const GemmArgs &g, hipStream_t s) {
   return check_launch("gemm_ldw");
 }
 
-template <bool A_KC, bool B_KC, int EPI> static int launch_staged(const GemmArgs &g, hipStream_t s) {
-  const MfmaGemmParams p = make_params<A_KC, B_KC, EPI>(g, 128, 128);
-  static const std::string name = kernel_tag("gemm_staged_kernel", 128, 128, 2, 2, A_KC, B_KC, EPI);
-  g_last_kernel = name.c_str();
-  gemm_staged_kernel<A_KC, B_KC, EPI><<<dim3((unsigned)(p.tiles_m * p.tiles_n)), 256, 0, s>>>(p);
-  return check_launch("gemm_staged");
-}
-
 // The tile configurations (BM, BN, wave grid).  gemm_mfma.hip holds the same list with each entry's
 // occupancy and measured relative speed, in the same order.
 // configurations of the alternating kernel follow those of the pipelined one in the numbering
@@ -1334,8 +1202,13 @@ template <bool A_KC, bool B_KC, int EPI> static int launch_staged(const GemmArgs
 
 // config: index into the list above, as chosen by gemm_mfma_config()
 template <bool A_KC, bool B_KC, int EPI> static int launch_layout(const GemmArgs &g, int config, hipStream_t s) {
-  if (g.K % GEMM_BK != 0) return launch_staged<A_KC, B_KC, EPI>(g, s);  // the pipelined kernel takes whole steps only
   int idx = 0;
+  // a ragged last step of an operand with contiguous reduction axis: the kernels with loader waves and the alternating
+  // kernel take it as they are, the pipelined kernel in one form (the extra vector instructions between its MFMAs cost
+  // the other forms 1 %)
+  if constexpr (A_KC || B_KC) {
+    if (g.K % GEMM_BK != 0 && !gemm_config_takes_ragged_k(config)) return launch_pipe<128, 128, 2, 2, A_KC, B_KC, EPI, 2, 2, true>(g, s);
+  }
 #define X(BM_, BN_, WGM_, WGN_) \
   if (config == idx++) return launch_pipe<BM_, BN_, WGM_, WGN_, A_KC, B_KC, EPI>(g, s);
   TM_GEMM_CONFIGS(X)

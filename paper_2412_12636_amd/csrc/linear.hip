@@ -64,7 +64,7 @@ extern "C" int tm_op_linear_wgrad(int dtype, int64_t T, int64_t N, int64_t K, co
 
 namespace tmk {
 bool linear_wgrad_adam_supported(int64_t T, int64_t N, int64_t K, const void *dy, const void *x, const float *dw) {
-  if (T <= 0 || N <= 0 || K <= 0 || T % 64 != 0) return false;
+  if (T <= 0 || N <= 0 || K <= 0) return false;
   GemmArgs g{N, K, T, dy, 1, N, x, 1, K, const_cast<float *>(dw), K, nullptr, nullptr, 3};
   return gemm_mfma_supported(g);
 }

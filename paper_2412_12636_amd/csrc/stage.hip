@@ -637,7 +637,9 @@ static int stage_bwd(tm_stage_t *st, const void *dy_in, void *dx_out, void *stre
   // bytes per parameter a weight-gradient product moves besides its operands when the update rides in its epilogue:
   // three fp32 states read and written, the bf16 copy, and the gradient where it is stored
   // (plus the product's two operands, read once)
-  const double fused_bytes_per_param = fuse ? 26.0 + (st->grad_mode != TM_GRAD_TRANSIENT ? 4.0 : 0.0) : 0.0;
+  // (a token count that is not a multiple of 64 keeps its gradients in TM_GRAD_TRANSIENT mode too, as documented)
+  const bool store_grad = st->grad_mode != TM_GRAD_TRANSIENT || d.T % 64 != 0;
+  const double fused_bytes_per_param = fuse ? 26.0 + (store_grad ? 4.0 : 0.0) : 0.0;
   auto wgrad_bytes = [&](int64_t N, int64_t K, const void *dyp, const void *xp, int64_t pb, int64_t w_off) -> double {
     return fuse && linear_wgrad_adam_supported(d.T, N, K, dyp, xp, grads + pb + w_off)
                ? fused_bytes_per_param * (double)N * (double)K + es * (double)d.T * (double)(N + K)
@@ -652,7 +654,7 @@ static int stage_bwd(tm_stage_t *st, const void *dy_in, void *dx_out, void *stre
       t.exp_avg_sq = st->buf.exp_avg_sq + pb + w_off;
       t.lowp = (bf16 *)st->buf.params + pb + w_off;
       t.a = ascal;
-      t.store_grad = st->grad_mode != TM_GRAD_TRANSIENT;
+      t.store_grad = store_grad;
       fused.push_back({w_off, N * K});
       return linear_wgrad_adam(d.T, N, K, dyp, xp, dw, t, sw);
     }
