@@ -23,4 +23,11 @@ int attn_bwd_mfma_launch(int64_t seq, int64_t batch, int64_t nq, int64_t nkv, in
                          const void *dctx, const float *lse, const float *dvec, float *part, void *dqkv,
                          hipStream_t s);
 
+// fp32, head sizes up to 128; part as in the bf16 kernels (attn_bwd_mfma_partial_floats)
+bool attn_f32_supported(int dtype, int64_t seq, int64_t batch, int64_t nq, int64_t nkv, int64_t d);
+int attn_fwd_f32_launch(int64_t seq, int64_t batch, int64_t nq, int64_t nkv, int64_t d, const void *qkv, void *ctx, float *lse,
+                        hipStream_t s);
+int attn_bwd_f32_launch(int64_t seq, int64_t batch, int64_t nq, int64_t nkv, int64_t d, const void *qkv, const void *dctx,
+                        const float *lse, const float *dvec, float *part, void *dqkv, hipStream_t s);
+
 }  // namespace tmk

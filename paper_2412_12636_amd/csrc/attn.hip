@@ -1,5 +1,5 @@
 // Causal attention entry points: argument checks and dispatch between the MFMA flash-style
-// kernels (bf16, head sizes up to 128) and the plain-ALU kernels (everything else).
+// kernels (bf16 and fp32, head sizes up to 128) and the plain-ALU kernels (everything else).
 #include "attn.h"
 #include "../../include/tm_ops.h"
 
@@ -23,6 +23,7 @@ extern "C" int tm_op_attn_fwd(int dtype, int64_t seq, int64_t batch, int64_t nq,
   if (!qkv || !ctx || !lse) return fail(TM_EINVAL, "attn_fwd: NULL pointer");
   hipStream_t s = (hipStream_t)stream;
   if (attn_mfma_supported(dtype, seq, batch, nq, nkv, d)) return attn_fwd_mfma_launch(seq, batch, nq, nkv, d, qkv, ctx, lse, s);
+  if (attn_f32_supported(dtype, seq, batch, nq, nkv, d)) return attn_fwd_f32_launch(seq, batch, nq, nkv, d, qkv, ctx, lse, s);
   return attn_fwd_generic_launch(dtype, seq, batch, nq, nkv, d, qkv, ctx, lse, s);
 }
 
@@ -30,7 +31,8 @@ extern "C" int64_t tm_op_attn_bwd_scratch_bytes(int dtype, int64_t seq, int64_t 
                                                 int64_t d) {
   if (int e = check_attn("attn_bwd_scratch_bytes", dtype, seq, batch, nq, nkv, d)) return e;
   const int64_t dvec = (batch * nq * seq + 63) / 64 * 64;  // the row statistics D, padded to 256 bytes
-  const int64_t part = attn_mfma_supported(dtype, seq, batch, nq, nkv, d) ? attn_bwd_mfma_partial_floats(seq, batch, nq, nkv, d) : 0;
+  const bool tiled = attn_mfma_supported(dtype, seq, batch, nq, nkv, d) || attn_f32_supported(dtype, seq, batch, nq, nkv, d);
+  const int64_t part = tiled ? attn_bwd_mfma_partial_floats(seq, batch, nq, nkv, d) : 0;
   return (dvec + part) * (int64_t)sizeof(float);
 }
 
@@ -46,5 +48,7 @@ extern "C" int tm_op_attn_bwd(int dtype, int64_t seq, int64_t batch, int64_t nq,
   if (int e = attn_dvec_launch(dtype, seq, batch, nq, nkv, d, ctx, dctx, dvec, s)) return e;
   if (attn_mfma_supported(dtype, seq, batch, nq, nkv, d))
     return attn_bwd_mfma_launch(seq, batch, nq, nkv, d, qkv, dctx, lse, dvec, part, dqkv, s);
+  if (attn_f32_supported(dtype, seq, batch, nq, nkv, d))
+    return attn_bwd_f32_launch(seq, batch, nq, nkv, d, qkv, dctx, lse, dvec, part, dqkv, s);
   return attn_bwd_generic_launch(dtype, seq, batch, nq, nkv, d, qkv, dctx, lse, dvec, dqkv, s);
 }

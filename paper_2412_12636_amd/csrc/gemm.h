@@ -34,6 +34,10 @@ struct GemmArgs {
 
 int gemm_generic(int dtype, const GemmArgs &g, hipStream_t s);
 
+// fp32 operands through the matrix cores.
+bool gemm_f32_supported(const GemmArgs &g);
+int gemm_f32(const GemmArgs &g, hipStream_t s);
+
 // bf16 operands through the matrix cores.  Needs: one of each operand's strides equal to 1, the
 // other a multiple of 8; the extent along each operand's contiguous axis a multiple of 8;
 // 16-byte aligned base pointers.

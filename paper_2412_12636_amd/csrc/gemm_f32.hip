@@ -1,0 +1,277 @@
+// fp32 GEMM on the matrix cores (v_mfma_f32_32x32x2_f32: fp32 operands, fp32 accumulation), the products of the fp32
+// stage dtype.
+//
+// A step is 32 elements of the reduction axis.  Operand tiles go straight into LDS (buffer_load ... lds, 16 bytes per
+// lane), several steps ahead:
+//   * contiguous reduction axis: LDS tile [row][32], 16-byte chunks XOR-swizzled by row; a lane reads four reduction
+//     elements of its row at once, 8j + 4hh .. +3 (hh: half of the wave), and they feed four MFMAs one by one;
+//   * strided reduction axis: LDS tile [k][rows], the global layout; a lane reads element (8j + 4hh + i, row).
+// Both kinds pair the reduction elements the same way, so any two layouts combine.
+//
+// Bound by the MFMA rate: 64 clocks for 32x32x2, a quarter of a wave's 64x64 tile per pair of reduction elements, for
+// which LDS delivers 16 bytes per clock and unit and L2 eight.  What decides the time of a small product is therefore how
+// evenly its tiles cover the SIMDs: blocks of 128x128, of 64x64, and of 32x32 whose four waves split every step's
+// reduction elements (their sums meet in LDS in wave order).
+// (The twelve products of a layer of hidden 1024, SwiGLU width 4096, 1024 tokens: 4.9 ms = 21 TFLOP/s on the 64x64
+// plain-ALU tile kernel that this one replaces, 1.03 ms = 100 TFLOP/s here; its largest run at 113, the vendor BLAS reaches
+// 150 on 8192^3.)
+#include "gemm.h"
+
+namespace tmk {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) void *lds_ptr_t;
+
+constexpr int FK = 32;  // reduction elements of a step
+
+struct F32GemmParams {
+  int M, N, K;
+  const float *A, *B;
+  int64_t lda, ldb;  // the non-unit strides
+  float *C;
+  int64_t ldc;
+  const float *bias, *residual;
+  int tiles_m;
+  uint32_t a_bytes, b_bytes, c_bytes;
+};
+
+// element (r, k) at base[r*ld + k]; LDS [R][32]
+template <int R, int NW> struct F32KC {
+  static constexpr int NLOAD = R * FK * 4 / 1024 / NW, BYTES = R * FK * 4;
+  static __device__ __forceinline__ int swz(int row) { return (row ^ (row >> 3)) & 7; }
+  uint32_t voff[NLOAD];
+  int chunk[NLOAD], k_end;
+  __device__ __forceinline__ void init(int64_t ld, int row0, int K, int wave, int lane) {
+#pragma unroll
+    for (int i = 0; i < NLOAD; ++i) {
+      const int row = (i * NW + wave) * 8 + lane / 8;
+      chunk[i] = ((lane % 8) ^ swz(row)) * 4;
+      voff[i] = (uint32_t)(((int64_t)(row0 + row) * ld + chunk[i]) * 4);
+    }
+    k_end = K;
+  }
+  // chunks past the end of the reduction hold the next row's elements: their lanes read outside the tensor (zero)
+  __device__ __forceinline__ void issue(rsrc_t rs, char *tile, int k0, int64_t, int wave) const {
+#pragma unroll
+    for (int i = 0; i < NLOAD; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(tile + (i * NW + wave) * 1024), 16,
+                                               k0 + chunk[i] < k_end ? voff[i] : 0x80000000u, (uint32_t)k0 * 4u, 0, 0);
+  }
+  static __device__ __forceinline__ f32x4 frag(const char *tile, int r32, int j, int lane) {
+    const int r = r32 + (lane & 31), hh = lane >> 5;
+    return *reinterpret_cast<const f32x4 *>(tile + r * FK * 4 + (((2 * j + hh) ^ swz(r)) << 4));
+  }
+};
+
+// element (r, k) at base[k*ld + r]; LDS [32][R].  The two halves of a wave read k-rows that are four apart: XOR of one
+// chunk bit with k bit 2 sends them to different 128-byte halves (R = 32 has only one).
+template <int R, int NW> struct F32KS {
+  static constexpr int CPR = R / 4, NLOAD = R * FK * 4 / 1024 / NW, BYTES = R * FK * 4;
+  static __device__ __forceinline__ int swz(int kk) { return CPR >= 16 ? ((kk >> 2) & 1) << 3 : 0; }
+  uint32_t voff[NLOAD];
+  __device__ __forceinline__ void init(int64_t ld, int row0, int, int wave, int lane) {
+#pragma unroll
+    for (int i = 0; i < NLOAD; ++i) {
+      const int idx = (i * NW + wave) * 64 + lane, kk = idx / CPR, c = (idx % CPR) ^ swz(kk);
+      voff[i] = (uint32_t)(((int64_t)kk * ld + row0 + c * 4) * 4);
+    }
+  }
+  __device__ __forceinline__ void issue(rsrc_t rs, char *tile, int k0, int64_t ld, int wave) const {
+    const uint32_t koff = (uint32_t)((int64_t)k0 * ld * 4);  // in the checked offset: rows past the end read as zero
+#pragma unroll
+    for (int i = 0; i < NLOAD; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(tile + (i * NW + wave) * 1024), 16, voff[i] + koff, 0, 0, 0);
+  }
+  static __device__ __forceinline__ f32x4 frag(const char *tile, int r32, int j, int lane) {
+    const int r = r32 + (lane & 31), hh = lane >> 5;
+    f32x4 x;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int kk = 8 * j + 4 * hh + i;
+      x[i] = *reinterpret_cast<const float *>(tile + kk * R * 4 + (((r >> 2) ^ swz(4 * hh)) << 4) + ((r & 3) << 2));
+    }
+    return x;
+  }
+};
+template <int R, int NW, bool KC> struct F32Sel { typedef F32KC<R, NW> type; };
+template <int R, int NW> struct F32Sel<R, NW, false> { typedef F32KS<R, NW> type; };
+
+// WM, WN: wave tile; KSPL: waves that split a step's reduction elements; NS: LDS stages
+template <int BM, int BN, int WM, int WN, int KSPL, int NS, bool A_KC, bool B_KC, int EPI>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const F32GemmParams p) {
+  constexpr int NW = (BM / WM) * (BN / WN) * KSPL, TM = WM / 32, TN = WN / 32;
+  static_assert(NW == 4, "four waves");
+  static_assert(KSPL == 1 || (KSPL == 4 && TM == 1 && TN == 1), "split waves hold one tile each");
+  typedef typename F32Sel<BM, NW, A_KC>::type LA;
+  typedef typename F32Sel<BN, NW, B_KC>::type LB;
+  constexpr int STAGE = LA::BYTES + LB::BYTES, LOADS = LA::NLOAD + LB::NLOAD;
+  extern __shared__ __align__(1024) char lds[];
+  const int m0 = (int)(blockIdx.x % p.tiles_m) * BM, n0 = (int)(blockIdx.x / p.tiles_m) * BN;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ks = KSPL > 1 ? wave : 0, wt = KSPL > 1 ? 0 : wave;
+  const int wm = (wt / (BN / WN)) * WM, wn = (wt % (BN / WN)) * WN;
+  LA la;
+  LB lb;
+  const rsrc_t ra = make_rsrc(p.A, p.a_bytes), rb = make_rsrc(p.B, p.b_bytes);
+  la.init(p.lda, m0, p.K, wave, lane);
+  lb.init(p.ldb, n0, p.K, wave, lane);
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  const int nk = (p.K + FK - 1) / FK;
+  auto issue = [&](int step) {  // never past K: a surplus fetch repeats the last step into a stage nobody reads again
+    char *st = lds + (step % NS) * STAGE;
+    const int k0 = (step < nk ? step : nk - 1) * FK;
+    la.issue(ra, st, k0, p.lda, wave);
+    lb.issue(rb, st + LA::BYTES, k0, p.ldb, wave);
+  };
+#pragma unroll
+  for (int s = 0; s < NS - 1; ++s) issue(s);
+  for (int kt = 0; kt < nk; ++kt) {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * LOADS) : "memory");  // own loads of step kt have landed
+    __builtin_amdgcn_s_barrier();  // everyone's have; everyone has read step kt - 1
+    issue(kt + NS - 1);
+    const char *As = lds + (kt % NS) * STAGE, *Bs = As + LA::BYTES;
+#pragma unroll
+    for (int jj = 0; jj < 4 / KSPL; ++jj) {
+      const int j = KSPL > 1 ? ks : jj;
+      f32x4 a[TM], b[TN];
+#pragma unroll
+      for (int t = 0; t < TM; ++t) a[t] = LA::frag(As, wm + t * 32, j, lane);
+#pragma unroll
+      for (int t = 0; t < TN; ++t) b[t] = LB::frag(Bs, wn + t * 32, j, lane);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+          for (int tn = 0; tn < TN; ++tn) acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[tm][i], b[tn][i], acc[tm][tn], 0, 0, 0);
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // the look-ahead loads, before LDS is reused or the block exits
+
+  const int l32 = lane & 31, hh = lane >> 5;
+  int v_first = 0, v_count = 16;
+  if constexpr (KSPL > 1) {  // wave w finishes registers 4w .. 4w+3 of the tile, over all waves in wave order
+    __syncthreads();
+    float *x = reinterpret_cast<float *>(lds);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) x[(wave * 16 + v) * 64 + lane] = acc[0][0][v];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float s = x[(4 * wave + e) * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) s += x[(w * 16 + 4 * wave + e) * 64 + lane];
+      acc[0][0][e] = s;
+    }
+    v_first = 4 * wave;
+    v_count = 4;
+  }
+  const rsrc_t rc = make_rsrc(p.C, p.c_bytes);
+  const rsrc_t rres = make_rsrc(p.residual ? (const void *)p.residual : p.C, p.c_bytes);
+#pragma unroll
+  for (int tn = 0; tn < TN; ++tn) {
+    const int col = n0 + wn + tn * 32 + l32;
+    const float bias = EPI == 0 && p.bias && col < p.N ? p.bias[col] : 0.f;
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm) {
+      uint32_t off[16];
+      float old[16];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int v = v_first + e, row = m0 + wm + tm * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
+        off[e] = e < v_count && col < p.N && row < p.M ? (uint32_t)(((int64_t)row * p.ldc + col) * 4) : 0xfffffff0u;
+        old[e] = 0.f;
+      }
+      if (EPI == 1 || (EPI == 0 && p.residual)) {
+#pragma unroll
+        for (int e = 0; e < (KSPL > 1 ? 4 : 16); ++e)
+          old[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(EPI == 1 ? rc : rres, off[e], 0, 0));
+      }
+#pragma unroll
+      for (int e = 0; e < (KSPL > 1 ? 4 : 16); ++e) {
+        const float o = EPI == 0 ? (acc[tm][tn][e] + bias) + old[e] : old[e] + acc[tm][tn][e];
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, o), rc, off[e], 0, 0);
+      }
+    }
+  }
+}
+
+#define TM_F32_GEMM(AKC, BKC, EPI)                                                             \
+  template __global__ void gemm_f32_kernel<128, 128, 64, 64, 1, 2, AKC, BKC, EPI>(const F32GemmParams); \
+  template __global__ void gemm_f32_kernel<64, 64, 32, 32, 1, 3, AKC, BKC, EPI>(const F32GemmParams);   \
+  template __global__ void gemm_f32_kernel<32, 32, 32, 32, 4, 4, AKC, BKC, EPI>(const F32GemmParams);
+TM_F32_GEMM(true, true, 0)
+TM_F32_GEMM(true, false, 0)
+TM_F32_GEMM(false, false, 1)
+TM_F32_GEMM(false, false, 2)
+
+// One of each operand's strides is 1, 16-byte chunks along it are aligned and whole, 32-bit offsets reach everything.
+bool gemm_f32_supported(const GemmArgs &g) {
+  auto operand_ok = [&](const void *ptr, int64_t rs, int64_t cs, int64_t rows) {
+    if (((uintptr_t)ptr) & 15) return false;
+    if (cs == 1) return rs % 4 == 0 && g.K % 4 == 0 && rows * rs * 4 < (1LL << 31);
+    if (rs == 1) return cs % 4 == 0 && rows % 4 == 0 && g.K * cs * 4 < (1LL << 31) && (g.K + FK) * cs * 4 < (1LL << 32);
+    return false;
+  };
+  if (g.M <= 0 || g.N <= 0 || g.K <= 0 || g.M > 0x3fffffff || g.N > 0x3fffffff || g.K > 0x3fffffff || g.c_mode > 2) return false;
+  if (!operand_ok(g.A, g.a_rs, g.a_cs, g.M) || !operand_ok(g.B, g.b_rs, g.b_cs, g.N)) return false;
+  if (g.M * g.ldc * 4 >= (1LL << 31)) return false;
+  return g.c_mode ? (g.a_cs != 1 && g.b_cs != 1) : g.a_cs == 1;
+}
+
+template <int BM, int BN, int WM, int WN, int KSPL, int NS, bool A_KC, bool B_KC, int EPI>
+static int launch(const GemmArgs &g, hipStream_t s) {
+  F32GemmParams p;
+  p.M = (int)g.M;
+  p.N = (int)g.N;
+  p.K = (int)g.K;
+  p.A = (const float *)g.A;
+  p.lda = A_KC ? g.a_rs : g.a_cs;
+  p.B = (const float *)g.B;
+  p.ldb = B_KC ? g.b_rs : g.b_cs;
+  p.C = (float *)g.C;
+  p.ldc = g.ldc;
+  p.bias = (const float *)g.bias;
+  p.residual = (const float *)g.residual;
+  p.tiles_m = (int)ceil_div(g.M, BM);
+  p.a_bytes = (uint32_t)((A_KC ? g.M * g.a_rs : g.K * g.a_cs) * 4);
+  p.b_bytes = (uint32_t)((B_KC ? g.N * g.b_rs : g.K * g.b_cs) * 4);
+  p.c_bytes = (uint32_t)(g.M * g.ldc * 4);
+  constexpr int stages = NS * (BM + BN) * FK * 4, sums = KSPL > 1 ? 4 * 16 * 64 * 4 : 0;
+  constexpr int lds = stages > sums ? stages : sums;
+  static bool attr_set = false;  // per instantiation
+  if (!attr_set && hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_f32_kernel<BM, BN, WM, WN, KSPL, NS, A_KC, B_KC, EPI>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
+    return fail(TM_ELAUNCH, "gemm_f32: cannot reserve %d bytes of LDS", lds);
+  attr_set = true;
+  const int64_t blocks = (int64_t)p.tiles_m * ceil_div(g.N, BN);
+  if (blocks > 0x7fffffff) return fail(TM_ESIZE, "gemm_f32: too many tiles");
+  g_last_kernel = "gemm_f32_kernel";
+  gemm_f32_kernel<BM, BN, WM, WN, KSPL, NS, A_KC, B_KC, EPI><<<(unsigned)blocks, 256, lds, s>>>(p);
+  return check_launch("gemm_f32");
+}
+
+// A block's time is its share of the MFMA rate, BM * BN per step, and a unit works through ceil(blocks / 256) of them;
+// the smaller tiles read LDS and synchronise more per MFMA (factors measured on products that fill the chip).
+template <bool A_KC, bool B_KC, int EPI> static int pick(const GemmArgs &g, hipStream_t s) {
+  auto cost = [&](int64_t b, double factor) { return (double)ceil_div(ceil_div(g.M, b) * ceil_div(g.N, b), (int64_t)256) * b * b * factor; };
+  const double c128 = cost(128, 1.0), c64 = cost(64, 1.1), c32 = cost(32, 1.5);
+  if (c128 <= c64 && c128 <= c32) return launch<128, 128, 64, 64, 1, 2, A_KC, B_KC, EPI>(g, s);
+  if (c64 <= c32) return launch<64, 64, 32, 32, 1, 3, A_KC, B_KC, EPI>(g, s);
+  return launch<32, 32, 32, 32, 4, 4, A_KC, B_KC, EPI>(g, s);
+}
+
+int gemm_f32(const GemmArgs &g, hipStream_t s) {
+  if (g.c_mode == 1) return pick<false, false, 1>(g, s);
+  if (g.c_mode == 2) return pick<false, false, 2>(g, s);
+  return g.b_cs == 1 ? pick<true, true, 0>(g, s) : pick<true, false, 0>(g, s);
+}
+
+}  // namespace tmk

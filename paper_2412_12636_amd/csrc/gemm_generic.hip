@@ -1,5 +1,5 @@
-// Plain-ALU tiled GEMM with arbitrary strides: the fp32 stage dtype and bf16 shapes the MFMA
-// kernels do not take.  64x64 output tile per 256-thread block, 4x4 outputs per thread,
+// Plain-ALU tiled GEMM with arbitrary strides: shapes the MFMA kernels do not take (2 GiB and more,
+// misaligned rows).  64x64 output tile per 256-thread block, 4x4 outputs per thread,
 // fp32 fused multiply-adds, operands staged through LDS 16 reduction steps at a time.
 #include "gemm.h"
 

@@ -1,5 +1,5 @@
-// The three products of a linear map y = x W^T + b, dispatched to the MFMA kernels (bf16) or the
-// plain-ALU kernel (fp32, and bf16 shapes the MFMA path does not take).
+// The three products of a linear map y = x W^T + b, dispatched to the MFMA kernels of their dtype or the
+// plain-ALU kernel (tensors that 32-bit offsets do not reach or whose rows are not 16-byte aligned).
 #include "gemm.h"
 #include "../../include/tm_ops.h"
 
@@ -16,6 +16,7 @@ static int check_linear(const char *what, int dtype, int64_t T, int64_t N, int64
 
 static int run(int dtype, const GemmArgs &g, hipStream_t s) {
   if (dtype == TM_DTYPE_BF16 && gemm_mfma_supported(g)) return gemm_mfma(g, s);
+  if (dtype == TM_DTYPE_FP32 && gemm_f32_supported(g)) return gemm_f32(g, s);
   return gemm_generic(dtype, g, s);
 }
 

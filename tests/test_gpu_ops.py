@@ -155,6 +155,38 @@ def test_reduction_lengths_off_the_step_in_every_configuration(env, T, N, K):
         tm.tm_gemm_force_config(-1)
 
 
+@pytest.mark.parametrize("T,N,K", [(1, 8, 8), (33, 40, 72), (257, 136, 200), (300, 1096, 520), (2050, 2056, 40), (2048, 2040, 72)],
+                         ids=["one_row", "split_waves", "split_waves_ragged", "tiles_of_64", "tiles_of_64_ragged", "tiles_of_128"])
+def test_linear_fp32_tiles(env, T, N, K):
+    """The fp32 products in each of their tile forms, ragged in every dimension, against the definition (fp32 sums of
+    at most 2056 terms: 1e-5), with one infinite row of x: its neighbours stay as they are."""
+    torch, tm = env
+    print(f"linear fp32 T={T} N={N} K={K}", flush=True)
+    rng = np.random.default_rng(T + N + K)
+    x, w, dy = rand(rng, (T, K), 1.0, FP32), rand(rng, (N, K), 0.05, FP32), rand(rng, (T, N), 0.1, FP32)
+    bias, res, g0 = rand(rng, (N,), 0.5, FP32), rand(rng, (T, N), 1.0, FP32), rand(rng, (N, K), 1.0, FP32)
+    xd, wd, dyd, bd, rd = (to_dev(torch, a, FP32) for a in (x, w, dy, bias, res))
+    s = stream_ptr(torch)
+    y, yb, dx = (torch.full((T + 1, n), 7.0, device="cuda") for n in (N, N, K))
+    dw0, dw1 = torch.full((N + 1, K), 7.0, device="cuda"), torch.full((N + 1, K), 7.0, device="cuda")
+    dw1[:N].copy_(to_dev(torch, g0, FP32))
+    tm.tm_op_linear_fwd(FP32, T, N, K, xd, wd, bd, rd, y, s)
+    tm.tm_op_linear_dgrad(FP32, T, N, K, dyd, wd, dx, s)
+    tm.tm_op_linear_wgrad(FP32, T, N, K, dyd, xd, dw0, 0, s)
+    tm.tm_op_linear_wgrad(FP32, T, N, K, dyd, xd, dw1, 1, s)
+    x64, w64, dy64 = (a.astype(np.float64) for a in (x, w, dy))
+    assert rel_err(to_host(y[:T]), x64 @ w64.T + bias + res) <= 1e-5
+    assert rel_err(to_host(dx[:T]), dy64 @ w64) <= 1e-5
+    assert rel_err(to_host(dw0[:N]), dy64.T @ x64) <= 1e-5
+    assert rel_err(to_host(dw1[:N]), g0 + dy64.T @ x64) <= 1e-5
+    for t, n in ((y, T), (dx, T), (dw0, N), (dw1, N)):
+        assert bool((t[n:] == 7.0).all())
+    xd[T // 2] = float("inf")
+    tm.tm_op_linear_fwd(FP32, T, N, K, xd, wd, bd, rd, yb, s)
+    rows = np.arange(T) != T // 2
+    assert np.array_equal(yb[:T].cpu().numpy()[rows], y[:T].cpu().numpy()[rows])
+
+
 def test_input_gradient_with_split_reduction(env):
     """dx = dy W with few output tiles and a long reduction: with scratch the reduction is split (the size
     query says so), the result meets the same tolerance against the definition and is reproducible; without
@@ -492,6 +524,35 @@ def test_attention_head_sizes_below_128(env, monkeypatch, form, seq, batch, nq, 
     got = to_host(dqkv[:seq])
     for part, ref in zip((got[..., :A], got[..., A:A + B], got[..., A + B:]), refs):
         assert rel_err(part, ref.reshape(seq, batch, -1)) <= 2.0 ** -7
+    assert bool((ctx[seq:] == 7.0).all()) and bool((dqkv[seq:] == 7.0).all())
+
+
+@pytest.mark.parametrize("seq,batch,nq,nkv,d", [(1, 2, 2, 1, 8), (32, 1, 2, 2, 32), (33, 2, 4, 2, 40), (64, 1, 1, 1, 64), (65, 1, 4, 1, 64),
+                                                 (200, 2, 2, 2, 80), (130, 1, 2, 1, 96), (127, 1, 2, 2, 104), (257, 1, 2, 1, 128)])
+def test_attention_fp32_tiles(env, seq, batch, nq, nkv, d):
+    """fp32 attention on the matrix cores: every padded width (32, 64, 96, 128), with and without padding columns, one
+    position, ends of the 32-row tiles and 64-row blocks, grouped heads.  fp32 throughout: an exponent of magnitude up to
+    30 is off by 30 * 2^-23 = 4e-6, which bounds a probability's relative error; 1e-5 with the sums."""
+    torch, tm = env
+    print(f"attention fp32 seq={seq} batch={batch} nq={nq} nkv={nkv} d={d}", flush=True)
+    rng = np.random.default_rng(seq * 11 + d)
+    A, B, W = nq * d, nkv * d, (nq + 2 * nkv) * d
+    qkv, dctx = rand(rng, (seq, batch, W), 1.0, FP32), rand(rng, (seq, batch, A), 0.1, FP32)
+    s = stream_ptr(torch)
+    qd = to_dev(torch, qkv, FP32)
+    ctx = torch.full((seq + 1, batch, A), 7.0, device="cuda")        # one row more: stays as it is
+    dqkv = torch.full((seq + 1, batch, W), 7.0, device="cuda")
+    lse = torch.zeros((batch, nq, seq), dtype=torch.float32, device="cuda")
+    scratch = torch.empty(tm.tm_op_attn_bwd_scratch_bytes(FP32, seq, batch, nq, nkv, d), dtype=torch.uint8, device="cuda")
+    tm.tm_op_attn_fwd(FP32, seq, batch, nq, nkv, d, qd, ctx, lse, s)
+    tm.tm_op_attn_bwd(FP32, seq, batch, nq, nkv, d, qd, ctx, to_dev(torch, dctx, FP32), lse, scratch, dqkv, s)
+    q64 = qkv.astype(np.float64)
+    q, k, v = (a.reshape(seq, batch, -1, d) for a in (q64[..., :A], q64[..., A:A + B], q64[..., A + B:]))
+    assert rel_err(to_host(ctx[:seq]), so.attention_fwd(q, k, v).reshape(seq, batch, A)) <= 1e-5
+    refs = so.attention_bwd(dctx.astype(np.float64).reshape(seq, batch, nq, d), q, k, v)
+    got = to_host(dqkv[:seq])
+    for part, ref in zip((got[..., :A], got[..., A:A + B], got[..., A + B:]), refs):
+        assert rel_err(part, ref.reshape(seq, batch, -1)) <= 1e-5
     assert bool((ctx[seq:] == 7.0).all()) and bool((dqkv[seq:] == 7.0).all())
 
 
