@@ -55,9 +55,9 @@ int gemm_mfma_tune(const GemmArgs *variants, int n, hipStream_t s);
 bool linear_wgrad_adam_supported(int64_t T, int64_t N, int64_t K, const void *dy, const void *x, const float *dw);
 int linear_wgrad_adam(int64_t T, int64_t N, int64_t K, const void *dy, const void *x, float *dw, const AdamTarget &target,
                       hipStream_t s);
-// Configurations whose kernels take a reduction length that is not a multiple of 64 of an operand with contiguous
-// reduction axis; the other pipelined ones run such products as 128x128 (configuration 1).
-inline bool gemm_config_takes_ragged_k(int config) { return config == 9 || config == 10 || config >= 13; }
+// Configurations with a form for a reduction length that is not a multiple of 64 of an operand with contiguous
+// reduction axis; the others run such products as 128x128 (configuration 1).
+inline bool gemm_config_takes_ragged_k(int config) { return config >= 13 && config != 15; }
 int gemm_mfma_config_count();
 int gemm_mfma_force_config(int index);
 

@@ -21,7 +21,8 @@ bool gemm_mfma_supported(const GemmArgs &g) {
   auto operand_ok = [&](const void *ptr, int64_t rs, int64_t cs, int64_t rows) {
     if (((uintptr_t)ptr) & 15) return false;
     if (cs == 1) return rs % 8 == 0 && g.K % 8 == 0;
-    if (rs == 1) return cs % 8 == 0 && rows % 8 == 0;
+    // (a ragged last step's rows past the end must not wrap around the 32-bit offset)
+    if (rs == 1) return cs % 8 == 0 && rows % 8 == 0 && (g.K + 64) * cs * 2 < (1LL << 32);
     return false;
   };
   if (g.M <= 0 || g.N <= 0 || g.K <= 0) return false;
@@ -36,43 +37,98 @@ bool gemm_mfma_supported(const GemmArgs &g) {
 }
 
 // ---- tile configurations -------------------------------------------------------------------------
-// Same order as TM_GEMM_CONFIGS in gemm_mfma_impl.h.  occ: blocks a compute unit holds at once (LDS: two
-// stages of (BM+BN) x 128 bytes out of 160 KB; four-wave blocks of up to 256x128 outputs leave room for
-// two).  speed[layout]: measured rate per busy compute unit relative to 128x192, per operand layout (0: both
-// reduction axes contiguous, 1: B strided, 2: both strided; the transposing LDS reads of the strided layouts
-// favour the small four-wave tiles, the plain reads the large ones), from products of 2048 to 4096 rows.
+// Same order as TM_GEMM_CONFIGS in gemm_mfma_impl.h.  occ: blocks a compute unit holds at once (LDS: the stages of
+// (BM+BN) x 128 bytes out of 160 KB).  Per operand layout (0: both reduction axes contiguous, 1: B strided, 2: both
+// strided) what a product costs in microseconds: start, and per pass of blocks over the chip epi + steps of 64
+// reduction elements at
+//   one block on each unit:  alone + fill * (share of the units that have one: the others' power and bandwidth are free)
+//   two blocks on a unit:    pair
+// Fitted (relative least squares, 5 to 15 % rms) to every configuration's time on 146 products of 64 to 16384 rows,
+// widths and reduction lengths from 128 to 20480, with weights that rotate through 400 MB.  The pick is 1 to 2.5 % slower
+// than the fastest configuration on them (geometric mean); a model of relative speeds that took two blocks a unit for
+// granted and knew no fixed cost was 50 to 61 % slower, most of it on products whose large tiles leave units idle.
+struct LayoutCost {
+  double start, alone, fill, pair, epi;
+};
 struct TileConfig {
   int bm, bn, wgm, wgn, occ;
-  double speed[3];
+  LayoutCost cost[3];
 };
 static const TileConfig kConfigs[] = {
-    {128, 192, 2, 2, 2, {1.00, 1.00, 1.00}}, {128, 128, 2, 2, 2, {0.95, 0.86, 0.91}}, {192, 128, 2, 2, 2, {0.98, 0.98, 1.00}},
-    {256, 192, 4, 2, 1, {1.08, 0.90, 0.88}}, {192, 256, 2, 4, 1, {1.00, 0.90, 0.90}}, {256, 256, 2, 4, 1, {1.22, 1.00, 1.00}},
-    {256, 256, 4, 2, 1, {1.20, 0.98, 1.00}}, {256, 128, 4, 2, 1, {0.88, 0.78, 0.80}}, {256, 192, 2, 2, 1, {1.09, 0.80, 0.83}},
+    // the pipelined kernel
+    {128, 192, 2, 2, 2,
+     {{1.65, 0.608, 0.236, 1.334, 4.00}, {0.00, 0.835, 0.387, 1.320, 5.17}, {0.00, 0.714, 0.542, 1.364, 4.47}}},
+    {128, 128, 2, 2, 2,
+     {{0.00, 0.514, 0.216, 0.936, 4.08}, {0.01, 0.729, 0.273, 1.075, 3.85}, {0.00, 0.626, 0.346, 1.059, 3.87}}},
+    {192, 128, 2, 2, 2,
+     {{0.99, 0.572, 0.303, 1.325, 4.03}, {0.00, 0.817, 0.399, 1.295, 4.42}, {0.00, 0.752, 0.478, 1.378, 4.44}}},
+    {256, 192, 4, 2, 1,
+     {{0.00, 0.833, 0.519, 0.000, 6.06}, {0.00, 1.053, 0.499, 0.000, 5.39}, {0.00, 0.945, 0.645, 0.000, 5.16}}},
+    {192, 256, 2, 4, 1,
+     {{0.23, 0.831, 0.521, 0.000, 5.55}, {0.00, 1.049, 0.463, 0.000, 5.01}, {0.00, 1.033, 0.617, 0.000, 5.11}}},
+    {256, 256, 2, 4, 1,
+     {{0.00, 1.006, 0.647, 0.000, 6.50}, {0.00, 1.326, 0.551, 0.000, 5.54}, {0.00, 1.302, 0.727, 0.000, 5.69}}},
+    {256, 256, 4, 2, 1,
+     {{0.00, 1.015, 0.643, 0.000, 6.61}, {0.00, 1.288, 0.581, 0.000, 5.85}, {0.00, 1.183, 0.759, 0.000, 5.52}}},
+    {256, 128, 4, 2, 1,
+     {{1.35, 0.640, 0.387, 0.000, 3.55}, {0.67, 0.880, 0.372, 0.000, 3.61}, {0.00, 0.827, 0.410, 0.000, 4.29}}},
+    {256, 192, 2, 2, 1,
+     {{0.80, 0.928, 0.381, 0.000, 7.42}, {0.18, 1.330, 0.374, 0.000, 7.03}, {0.00, 1.159, 0.544, 0.000, 5.79}}},
     // the alternating kernel (gemm_alt_kernel)
-    {256, 256, 2, 4, 1, {1.00, 1.10, 1.06}}, {256, 256, 4, 2, 1, {1.00, 1.10, 1.06}},
+    {256, 256, 2, 4, 1,
+     {{0.00, 1.267, 0.542, 0.000, 6.75}, {0.00, 1.277, 0.420, 0.000, 6.34}, {0.00, 1.240, 0.540, 0.000, 6.74}}},
+    {256, 256, 4, 2, 1,
+     {{0.00, 1.269, 0.530, 0.000, 6.90}, {0.00, 1.276, 0.467, 0.000, 6.65}, {0.00, 1.196, 0.601, 0.000, 6.88}}},
     // the pipelined kernel with three LDS stages
-    {256, 128, 4, 2, 1, {1.05, 0.78, 0.80}}, {128, 256, 2, 4, 1, {1.05, 0.78, 0.80}},
+    {256, 128, 4, 2, 1,
+     {{0.49, 0.598, 0.301, 0.000, 4.77}, {0.67, 0.897, 0.350, 0.000, 3.78}, {0.00, 0.846, 0.379, 0.000, 4.59}}},
+    {128, 256, 2, 4, 1,
+     {{0.57, 0.576, 0.327, 0.000, 4.77}, {0.82, 0.930, 0.337, 0.000, 3.73}, {0.00, 0.830, 0.396, 0.000, 4.56}}},
     // the kernel with loader waves (gemm_ldw_kernel)
-    {256, 192, 4, 2, 1, {1.12, 1.17, 1.10}}, {128, 192, 2, 2, 2, {0.70, 0.80, 0.85}}, {256, 192, 4, 2, 1, {1.10, 1.10, 1.05}},
+    {256, 192, 4, 2, 1,
+     {{0.00, 0.740, 0.521, 0.000, 6.15}, {0.00, 0.769, 0.423, 0.000, 6.03}, {0.00, 0.683, 0.511, 0.000, 6.07}}},
+    {128, 192, 2, 2, 2,
+     {{0.00, 0.578, 0.292, 1.860, 5.20}, {0.00, 0.592, 0.264, 1.706, 5.04}, {0.00, 0.422, 0.447, 1.575, 4.81}}},
+    {256, 192, 4, 2, 1,
+     {{0.00, 0.752, 0.494, 0.000, 6.39}, {0.00, 0.769, 0.416, 0.000, 6.32}, {0.00, 0.686, 0.513, 0.000, 6.41}}},
+    // ... on small tiles with more stages
+    {64, 64, 2, 2, 2,
+     {{2.49, 0.168, 0.030, 0.419, 1.91}, {2.67, 0.183, 0.036, 0.427, 1.41}, {2.38, 0.139, 0.076, 0.381, 1.51}}},
+    {128, 64, 2, 2, 2,
+     {{2.15, 0.246, 0.119, 0.680, 2.39}, {2.61, 0.283, 0.075, 0.708, 1.75}, {1.90, 0.280, 0.099, 0.654, 2.40}}},
+    {64, 128, 2, 2, 2,
+     {{1.91, 0.259, 0.106, 0.654, 2.71}, {2.41, 0.273, 0.080, 0.681, 2.17}, {1.90, 0.260, 0.090, 0.644, 2.38}}},
+    {128, 128, 2, 2, 1,
+     {{1.62, 0.299, 0.209, 0.000, 3.64}, {1.52, 0.320, 0.192, 0.000, 3.62}, {1.27, 0.286, 0.192, 0.000, 3.46}}},
 };
 constexpr int kNumConfigs = sizeof(kConfigs) / sizeof(kConfigs[0]);
 
 static int layout_of(const GemmArgs &g) { return g.c_mode ? 2 : (g.b_cs == 1 ? 0 : 1); }
 
-// Estimated time: the chip works through the tiles in passes of 256*occ blocks, each pass taking
-// occ * BM * BN / speed.
+static double config_us(const GemmArgs &g, int c, int layout) {
+  const TileConfig &t = kConfigs[c];
+  const LayoutCost &k = t.cost[layout];
+  const int64_t nb = ceil_div(g.M, t.bm) * ceil_div(g.N, t.bn);
+  const double steps = (double)ceil_div(g.K, (int64_t)64);
+  if (t.occ == 1) {
+    const double passes = (double)ceil_div(nb, (int64_t)256);
+    return k.start + passes * (k.epi + steps * (k.alone + k.fill * (double)nb / (256.0 * passes)));
+  }
+  const int64_t rest = nb % 512;
+  const double pairs = (double)(nb / 512 + (rest > 256)), alone = rest > 0 && rest <= 256 ? 1.0 : 0.0;
+  return k.start + (pairs + alone) * k.epi + steps * (pairs * k.pair + alone * (k.alone + k.fill * (double)rest / 256.0));
+}
+static bool config_takes(const GemmArgs &g, int c, int layout) {
+  return g.K % 64 == 0 || layout == 2 || c == 1 || gemm_config_takes_ragged_k(c);
+}
 static int heuristic_config(const GemmArgs &g) {
   double best = 1e300;
   int pick = 0;
   const int layout = layout_of(g);
   for (int c = 0; c < kNumConfigs; ++c) {
-    if (g.K % 64 != 0 && layout != 2 && c != 1 && !gemm_config_takes_ragged_k(c)) continue;
-    const TileConfig &t = kConfigs[c];
-    const int64_t nb = ceil_div(g.M, t.bm) * ceil_div(g.N, t.bn);
-    const double passes = (double)ceil_div(nb, 256 * t.occ);
-    const double cost = passes * t.occ * t.bm * t.bn / t.speed[layout];
-    if (cost < best) best = cost, pick = c;
+    if (!config_takes(g, c, layout)) continue;
+    const double us = config_us(g, c, layout);
+    if (us < 0.99 * best) best = us, pick = c;  // near ties (the forms with four and with two loaders) go to the first
   }
   return pick;
 }
@@ -102,24 +158,30 @@ int gemm_mfma_force_config(int index) {
 }
 
 // Configurations found by gemm_mfma_tune(), keyed by (layout, M, N, K).  A weight-gradient product that also applies
-// the update (c_mode 3) spends most of its time in the epilogue, streaming the optimizer state.  Where the large
-// staggered form does not apply (fused_on_large_tiles below) it is faster with two small blocks per compute unit than
-// with one large block whose units all stream at once, so it keeps the best of the configurations that allow two
-// blocks: layout key 3.
+// the update (c_mode 3) has layout key 3: its choice weighs the stream of optimizer state against the main loop.
 typedef std::tuple<int, int64_t, int64_t, int64_t> TuneKey;
 static std::map<TuneKey, int> g_tuned;
 static std::mutex g_tuned_mutex;
 constexpr int kFusedLayoutKey = 3;
 
-static int heuristic_config_fused(const GemmArgs &g) {
+// Time of a fused-update product from the main loop's: many small blocks overlap one another's main loops and state
+// streams (26 bytes per parameter, priced at 5 TB/s), large ones pull fewer operand bytes.  Fitted to 32 matrices of
+// 768 x 768 to 12288 x 6144 parameters and 300 to 8192 tokens, on which it picks within 1 % of the fastest of nine
+// configurations on average; two 128x192 or 128x128 blocks a unit for all of them were 30 % slower (1024 x 1024, 4000
+// tokens: 69 -> 22 us on 64x64 tiles; 2048 x 4096, 2048 tokens: 83 -> 73).
+struct FusedCost {
+  int config;
+  double main, stream, start;
+};
+static const FusedCost kFused[] = {{13, 0.70, 0.68, 24.8}, {14, 0.90, 0.49, 19.8}, {16, 0.99, 0.37, 3.0}, {19, 0.98, 0.69, 9.3}};
+// main_us[c]: the plain product's measured time per configuration, or NULL for the model's
+static int fused_config(const GemmArgs &g, const float *main_us) {
   double best = 1e300;
-  int pick = 0;
-  for (int c = 0; c < kNumConfigs; ++c) {
-    const TileConfig &t = kConfigs[c];
-    if (t.occ < 2) continue;
-    const int64_t nb = ceil_div(g.M, t.bm) * ceil_div(g.N, t.bn);
-    const double cost = (double)ceil_div(nb, 256 * t.occ) * t.occ * t.bm * t.bn / t.speed[2];
-    if (cost < best) best = cost, pick = c;
+  int pick = kFused[0].config;
+  const double stream_us = (double)g.M * g.N * 26 / 5e6;
+  for (const FusedCost &f : kFused) {
+    const double us = f.main * (main_us ? main_us[f.config] : config_us(g, f.config, 2)) + f.stream * stream_us + f.start;
+    if (us < best) best = us, pick = f.config;
   }
   return pick;
 }
@@ -151,7 +213,7 @@ static int pick_config(const GemmArgs &g) {
     auto it = g_tuned.find(TuneKey(fused ? kFusedLayoutKey : layout_of(g), g.M, g.N, g.K));
     if (it != g_tuned.end()) return it->second;
   }
-  return fused ? heuristic_config_fused(g) : heuristic_config(g);
+  return fused ? fused_config(g, nullptr) : heuristic_config(g);
 }
 
 static int launch_config(const GemmArgs &g, int config, hipStream_t s) {
@@ -215,10 +277,24 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
   *reinterpret_cast<bf16x8 *>(out + m * ldc + n) = o;
 }
 
+// Whether the split pays: its parts' product (the fp32 results leave uncached: two and a half epilogues) and the pass
+// that adds them, against the unsplit product on the best tiles.  (2048 x 2048 over 4096: 58 us split, 30 unsplit on
+// 128x128 tiles; 2048 x 512 over 4096: 29 against 17; 2048 x 1536 over 12288, the 175B shard's: 88 against 95.)
+static bool split_pays(const GemmArgs &g, int parts, bool large) {
+  GemmArgs p = g;
+  p.K = g.K / parts;
+  const int c = large ? kLdwLargeConfig : 0;
+  const int64_t nb = ceil_div(g.M, (int64_t)kConfigs[c].bm) * ceil_div(g.N, (int64_t)kConfigs[c].bn) * parts;
+  const LayoutCost &k = kConfigs[c].cost[1];
+  const double step_us = !large && nb > 256 ? k.pair : k.alone + k.fill * (nb < 256 ? (double)nb / 256.0 : 1.0);
+  const double split_us = 2.5 * k.epi + (double)(p.K / 64) * step_us + 5.0 + (double)parts * g.M * g.N * 4 / 3e6;
+  return 0.92 * split_us < config_us(g, heuristic_config(g), 1);  // the estimate of the split is up to 8 % high
+}
+
 int gemm_mfma(const GemmArgs &g, hipStream_t s) {
   bool large = false;
   const int parts = splitk_parts(g, &large);
-  if (parts > 1 && g.splitk_scratch && g.splitk_bytes >= (int64_t)parts * g.M * g.N * 4 &&
+  if (parts > 1 && split_pays(g, parts, large) && g.splitk_scratch && g.splitk_bytes >= (int64_t)parts * g.M * g.N * 4 &&
       (((uintptr_t)g.splitk_scratch) & 15) == 0 && g.M * g.N * 4 < (1LL << 31) && forced_config() < 0) {
     GemmArgs p = g;
     p.C = g.splitk_scratch;
@@ -272,14 +348,12 @@ int gemm_mfma_tune(const GemmArgs *variants, int n, hipStream_t s) {
       if (rc == TM_OK && hipEventElapsedTime(&ms, e0, e1) == hipSuccess && ms < ms_of[c]) ms_of[c] = ms;
     }
   }
-  int best = 0, best_two = -1;  // best_two: among the configurations with two blocks per compute unit
-  for (int c = 0; c < kNumConfigs; ++c) {
+  int best = 0;
+  for (int c = 0; c < kNumConfigs; ++c)
     if (ms_of[c] < ms_of[best]) best = c;
-    if (kConfigs[c].occ >= 2 && (best_two < 0 || ms_of[c] < ms_of[best_two])) best_two = c;
-  }
-  // the cost model's pick stays unless it loses by more than 2 %: keeps the choice stable against timer noise
+  // the cost model's pick stays unless it loses by more than 1 %: keeps the choice stable against timer noise
   const int first = heuristic_config(v[0]);
-  if (ms_of[first] <= 1.02f * ms_of[best]) best = first;
+  if (ms_of[first] <= 1.01f * ms_of[best]) best = first;
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (rc != TM_OK) return rc;
@@ -291,8 +365,11 @@ int gemm_mfma_tune(const GemmArgs *variants, int n, hipStream_t s) {
   }
   std::lock_guard<std::mutex> lock(g_tuned_mutex);
   g_tuned[key] = best;
-  if (layout_of(v[0]) == 2 && best_two >= 0)
-    g_tuned[TuneKey(kFusedLayoutKey, v[0].M, v[0].N, v[0].K)] = getenv("TM_GEMM_FUSED_ANY") ? best : best_two;
+  if (layout_of(v[0]) == 2) {
+    float us[kNumConfigs];
+    for (int c = 0; c < kNumConfigs; ++c) us[c] = ms_of[c] * 1e3f;
+    g_tuned[TuneKey(kFusedLayoutKey, v[0].M, v[0].N, v[0].K)] = getenv("TM_GEMM_FUSED_ANY") ? best : fused_config(v[0], us);
+  }
   return TM_OK;
 }
 

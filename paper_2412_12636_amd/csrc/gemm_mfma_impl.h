@@ -303,7 +303,8 @@ __device__ __forceinline__ void epilogue(const MfmaGemmParams &p, const f32x16 (
 // =================================================================================================
 
 // ---- operand with contiguous reduction axis: element (r, k) at base[r*ld + k]; LDS [R][BK] --------
-template <int R, int BK, int NW = 4> struct DirectKC {
+// TAIL: the last step may be ragged (a reduction length that is not a multiple of BK).
+template <int R, int BK, int NW = 4, bool TAIL = false> struct DirectKC {
   static constexpr int ROWB = BK * 2;               // bytes per LDS row
   static constexpr int CPR = BK / 8;                // 16-byte chunks per row
   static constexpr int RPL = 64 / CPR;              // rows covered by one wave-wide load
@@ -315,32 +316,27 @@ template <int R, int BK, int NW = 4> struct DirectKC {
     return BK == 64 ? ((row ^ (row >> 3)) & 7) : ((row >> 1) & 3);
   }
   uint32_t voff[NLOAD];
-  int k_end, k_lane;  // the reduction length, and the k of this lane's chunk of load 0 inside a step
+  int k_end, k_lane;  // TAIL: the reduction length, and the k of this lane's chunk of load 0 inside a step
   __device__ __forceinline__ void init(int64_t ld, int row0, int wave, int lane, int K) {
-    static_assert(BK == 64 && (NW == 2 || NW == 4 || NW == 8), "chunk of load i = chunk of load 0 ^ (i * NW) % 8");
+    static_assert(!TAIL || (BK == 64 && (NW == 2 || NW == 4 || NW == 8)), "chunk of load i = chunk of load 0 ^ (i * NW) % 8");
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i) {
       const int row = (i * NW + wave) * RPL + lane / CPR;
       const int c = (lane % CPR) ^ swz(row);  // logical chunk that belongs at this lane's LDS position
       voff[i] = (uint32_t)(((int64_t)(row0 + row) * ld + c * 8) * 2);
-      if (i == 0) k_lane = c * 8;
+      if (TAIL && i == 0) k_lane = c * 8;
     }
-    k_end = K;
+    if (TAIL) k_end = K;
   }
-  // The last step of a length that is not a multiple of 64: chunks past the end of the reduction hold the next row's
-  // elements.  Their lanes get an offset outside every tensor (below 2 GiB), which reads as zero.
-  __device__ __forceinline__ void issue(rsrc_t rs, char *tile, int k0, int64_t /*ld*/, int wave, bool tail) const {
+  __device__ __forceinline__ void issue(rsrc_t rs, char *tile, int k0, int64_t /*ld*/, int wave) const {
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i) {
       uint32_t off = voff[i];
-      if (tail && k0 + (k_lane ^ (((i * NW) & 7) * 8)) >= k_end) off = 0x80000000u;
+      // chunks past the end of the reduction hold the next row's elements: their lanes get an offset outside every
+      // tensor (below 2 GiB), which reads as zero
+      if (TAIL && k0 + (k_lane ^ (((i * NW) & 7) * 8)) >= k_end) off = 0x80000000u;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(tile + (i * NW + wave) * 1024), 16, off, (uint32_t)k0 * 2u, 0, 0);
     }
-  }
-  // picks the form by a scalar branch: for waves whose loads are not interleaved with MFMAs
-  __device__ __forceinline__ void issue_any(rsrc_t rs, char *tile, int k0, int64_t ld, int wave) const {
-    if (k0 + BK > k_end) issue(rs, tile, k0, ld, wave, true);
-    else issue(rs, tile, k0, ld, wave, false);
   }
   // fragment of the 32-row block starting at r32: lane's row r32 + lane%32, reduction slots 16ks + 8hh + 0..7
   static __device__ __forceinline__ bf16x8 frag(const char *tile, int r32, int ks, int lane) {
@@ -378,16 +374,13 @@ template <int R, int BK, int NW = 4> struct DirectKS {
       voff[i] = (uint32_t)(((int64_t)kk * ld + row0 + c * 8) * 2);
     }
   }
-  __device__ __forceinline__ void issue(rsrc_t rs, char *tile, int k0, int64_t ld, int wave, bool /*tail*/) const {
-    // the step offset travels in the per-lane offset: that one is checked against the buffer size
+  __device__ __forceinline__ void issue(rsrc_t rs, char *tile, int k0, int64_t ld, int wave) const {
+    // the step offset travels in the per-lane offset: that one is checked against the buffer size (rows past the end of
+    // the reduction read as zero)
     const uint32_t koff = (uint32_t)((int64_t)k0 * ld * 2);
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(tile + (i * NW + wave) * 1024), 16, voff[i] + koff, 0, 0, 0);
-  }
-  // rows past the end of the reduction are past the tensor and read as zero: one form for every length
-  __device__ __forceinline__ void issue_any(rsrc_t rs, char *tile, int k0, int64_t ld, int wave) const {
-    issue(rs, tile, k0, ld, wave, false);
   }
   // ds_read_b64_tr_b16: within 16 lanes, lane i receives element (i%4) of the 8-byte pieces addressed
   // by lanes i/4, i/4+4, i/4+8, i/4+12.  With lane s addressing T[k0 + s/4][r0 + 4*(s%4) ..+3], lane i
@@ -407,8 +400,8 @@ template <int R, int BK, int NW = 4> struct DirectKS {
   }
 };
 
-template <int R, int BK, bool KC, int NW = 4> struct DirectSel { typedef DirectKC<R, BK, NW> type; };
-template <int R, int BK, int NW> struct DirectSel<R, BK, false, NW> { typedef DirectKS<R, BK, NW> type; };
+template <int R, int BK, bool KC, int NW = 4, bool TAIL = false> struct DirectSel { typedef DirectKC<R, BK, NW, TAIL> type; };
+template <int R, int BK, int NW, bool TAIL> struct DirectSel<R, BK, false, NW, TAIL> { typedef DirectKS<R, BK, NW> type; };
 
 template <int N> __device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
@@ -591,7 +584,8 @@ template <int MF, int DSN, int LOADS, int i> __device__ __forceinline__ void sch
 // can have in flight between L2 and LDS (free LDS space) against the latency of that path (a 64 KB burst of a
 // block takes about 2500 clocks to arrive even from L2), not LDS or MFMA throughput.  A third stage for B alone
 // measured nothing (the A tiles of the same batch are as late); three of both need tiles of at most 53 KB a stage.
-// TAIL: the last step may be ragged (K not a multiple of BK) and an operand has a contiguous reduction axis.
+// TAIL: the last step may be ragged (K not a multiple of BK) and an operand has a contiguous reduction axis.  A form of
+// its own: the extra vector instructions beside the loads cost the products of whole steps 1 %.
 template <int BM, int BN, int BK, int WGM, int WGN, bool A_KC, bool B_KC, int EPI, int NSA = 2, int NSB = 2, bool TAIL = false>
 __global__ __launch_bounds__(64 * WGM * WGN, (WGM * WGN == 4 && BM * BN <= 256 * 128 && NSB == 2) ? 2 : 1) void gemm_pipe_kernel(
     const MfmaGemmParams p_in) {
@@ -612,8 +606,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, (WGM * WGN == 4 && BM * BN <= 256 *
   constexpr int NW = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;
   static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile");
-  typedef typename DirectSel<BM, BK, A_KC, NW>::type LA;
-  typedef typename DirectSel<BN, BK, B_KC, NW>::type LB;
+  typedef typename DirectSel<BM, BK, A_KC, NW, TAIL>::type LA;
+  typedef typename DirectSel<BN, BK, B_KC, NW, TAIL>::type LB;
   constexpr int B_BASE = NSA * LA::BYTES;  // LDS: the A stages, then the B stages
   constexpr int LOADS = LA::NLOAD + LB::NLOAD;
   // loads that may still be in flight when step kt+1's tiles must have landed: the batches issued later
@@ -646,8 +640,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, (WGM * WGN == 4 && BM * BN <= 256 *
   const int nk = (p.K + BK - 1) / BK;
   bf16x8 a[2][TM], b[2][TN];
   // prologue: stage 0 in LDS, its slice 0 in registers, stage 1 in flight
-  la.issue(ra, lds, 0, p.lda, wave, TAIL);
-  lb.issue(rb, lds + B_BASE, 0, p.ldb, wave, TAIL);
+  la.issue(ra, lds, 0, p.lda, wave);
+  lb.issue(rb, lds + B_BASE, 0, p.ldb, wave);
   wait_vmcnt<0>();
   __builtin_amdgcn_s_barrier();
 #pragma unroll
@@ -657,8 +651,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, (WGM * WGN == 4 && BM * BN <= 256 *
 #pragma unroll
   for (int ahead = 1; ahead < NSB; ++ahead) {
     const int k1 = (ahead < nk ? ahead : nk - 1) * BK;  // never past K: a surplus fetch repeats the last step
-    if (ahead < NSA) la.issue(ra, lds + ahead * LA::BYTES, k1, p.lda, wave, TAIL);
-    lb.issue(rb, lds + B_BASE + ahead * LB::BYTES, k1, p.ldb, wave, TAIL);
+    if (ahead < NSA) la.issue(ra, lds + ahead * LA::BYTES, k1, p.lda, wave);
+    lb.issue(rb, lds + B_BASE + ahead * LB::BYTES, k1, p.ldb, wave);
   }
 
   int ca = 0, na = 1, cb = 0, nb = 1;  // LDS stages of steps kt and kt+1, per operand
@@ -688,8 +682,8 @@ __global__ __launch_bounds__(64 * WGM * WGN, (WGM * WGN == 4 && BM * BN <= 256 *
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     // the current stages are free: fetch steps kt+NSA / kt+NSB into them (at the end the last step again, never consumed)
-    la.issue(ra, As, (kt + NSA < nk ? kt + NSA : nk - 1) * BK, p.lda, wave, TAIL);
-    lb.issue(rb, Bs, (kt + NSB < nk ? kt + NSB : nk - 1) * BK, p.ldb, wave, TAIL);
+    la.issue(ra, As, (kt + NSA < nk ? kt + NSA : nk - 1) * BK, p.lda, wave);
+    lb.issue(rb, Bs, (kt + NSB < nk ? kt + NSB : nk - 1) * BK, p.ldb, wave);
 #pragma unroll
     for (int i = 0; i < TM; ++i) a[0][i] = LA::frag(An, wm * WM + i * 32, 0, lane);
 #pragma unroll
@@ -727,7 +721,9 @@ __global__ __launch_bounds__(64 * WGM * WGN, (WGM * WGN == 4 && BM * BN <= 256 *
 // for them, and the SIMD's issue logic serves the multiplying waves while a loader wave is held up.  Two LDS stages
 // and the same barrier placement as the pipelined kernel (before the last reduction slice of a step), so an output
 // element is accumulated in the same order as in every other configuration.
-template <int BM, int BN, int BK, int WGM, int WGN, int NP, bool A_KC, bool B_KC, int EPI>
+// NS: LDS stages.  Two for the large tiles, whose step lasts as long as a load takes; small tiles (few output tiles, a
+// long reduction) have short steps, and their loaders run NS - 1 steps ahead.
+template <int BM, int BN, int BK, int WGM, int WGN, int NP, bool A_KC, bool B_KC, int EPI, int NS = 2, bool TAIL = false>
 __global__ __launch_bounds__(64 * (WGM * WGN + NP), 3) void gemm_ldw_kernel(const MfmaGemmParams p_in) {
   extern __shared__ __align__(16) char lds[];
   MfmaGemmParams p = p_in;
@@ -748,9 +744,9 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP), 3) void gemm_ldw_kernel(cons
   constexpr int NC = WGM * WGN;  // multiplying waves
   constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;
   static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile");
-  typedef typename DirectSel<BM, BK, A_KC, NP>::type LA;  // the tiles are fetched by the NP loader waves
-  typedef typename DirectSel<BN, BK, B_KC, NP>::type LB;
-  constexpr int B_BASE = 2 * LA::BYTES;
+  typedef typename DirectSel<BM, BK, A_KC, NP, TAIL>::type LA;  // the tiles are fetched by the NP loader waves
+  typedef typename DirectSel<BN, BK, B_KC, NP, TAIL>::type LB;
+  constexpr int B_BASE = NS * LA::BYTES;
   constexpr int KS = BK / 16;
   static_assert(KS % 2 == 0, "fragment buffers alternate");
   constexpr int MF = TM * TN;
@@ -766,28 +762,35 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP), 3) void gemm_ldw_kernel(cons
   const int nk = (p.K + BK - 1) / BK;
 
   if (wave >= NC) {
-    // ---- loader wave: stage 0, barrier, stage 1; then per step: wait for step kt+1, barrier, fetch step kt+2 ----
+    // ---- loader wave: the first steps, barrier; then per step: wait for step kt+1, barrier, fetch step kt+NS ----
     const int lw = wave - NC;
     LA la;
     LB lb;
     const rsrc_t ra = make_rsrc(p.A, p.a_bytes), rb = make_rsrc(p.B, p.b_bytes);
     la.init(p.lda, m0, lw, lane, p.K);
     lb.init(p.ldb, n0, lw, lane, p.K);
-    la.issue_any(ra, lds, 0, p.lda, lw);
-    lb.issue_any(rb, lds + B_BASE, 0, p.ldb, lw);
-    wait_vmcnt<0>();
-    __builtin_amdgcn_s_barrier();
-    {
-      const int k1 = (1 < nk ? 1 : nk - 1) * BK;  // never past K: a surplus fetch repeats the last step
-      la.issue_any(ra, lds + LA::BYTES, k1, p.lda, lw);
-      lb.issue_any(rb, lds + B_BASE + LB::BYTES, k1, p.ldb, lw);
+    auto issue = [&](int step) {  // never past K: a surplus fetch repeats the last step into a stage nobody reads again
+      const int k0 = (step < nk ? step : nk - 1) * BK, st = NS == 2 ? step & 1 : step % NS;
+      la.issue(ra, lds + st * LA::BYTES, k0, p.lda, lw);
+      lb.issue(rb, lds + B_BASE + st * LB::BYTES, k0, p.ldb, lw);
+    };
+    constexpr int LOADS = LA::NLOAD + LB::NLOAD;
+    static_assert((NS - 1) * LOADS <= 63, "the wait counter holds 63");
+    if constexpr (NS == 2) {
+      issue(0);
+      wait_vmcnt<0>();
+      __builtin_amdgcn_s_barrier();
+      issue(1);
+    } else {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) issue(s);
+      wait_vmcnt<(NS - 1) * LOADS>();
+      __builtin_amdgcn_s_barrier();
     }
     for (int kt = 0; kt < nk; ++kt) {
-      wait_vmcnt<0>();  // this wave's part of step kt+1 has landed
+      wait_vmcnt<(NS - 2) * LOADS>();  // this wave's part of step kt+1 has landed (loads complete in order)
       __builtin_amdgcn_s_barrier();
-      const int k2 = (kt + 2 < nk ? kt + 2 : nk - 1) * BK;
-      la.issue_any(ra, lds + (kt & 1) * LA::BYTES, k2, p.lda, lw);
-      lb.issue_any(rb, lds + B_BASE + (kt & 1) * LB::BYTES, k2, p.ldb, lw);
+      issue(kt + NS);
     }
     wait_vmcnt<0>();  // drain the look-ahead loads before the stages are reused or the block exits
     if constexpr (EPI == 0) {
@@ -834,10 +837,11 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP), 3) void gemm_ldw_kernel(cons
   for (int j = 0; j < TN; ++j) b[0][j] = LB::frag(lds + B_BASE, wn * WN + j * 32, 0, lane);
   __builtin_amdgcn_s_setprio(1);
   for (int kt = 0; kt < nk; ++kt) {
-    const char *As = lds + (kt & 1) * LA::BYTES;
-    const char *Bs = lds + B_BASE + (kt & 1) * LB::BYTES;
-    const char *An = lds + ((kt + 1) & 1) * LA::BYTES;
-    const char *Bn = lds + B_BASE + ((kt + 1) & 1) * LB::BYTES;
+    const int cur = NS == 2 ? kt & 1 : kt % NS, next = NS == 2 ? cur ^ 1 : (kt + 1) % NS;
+    const char *As = lds + cur * LA::BYTES;
+    const char *Bs = lds + B_BASE + cur * LB::BYTES;
+    const char *An = lds + next * LA::BYTES;
+    const char *Bn = lds + B_BASE + next * LB::BYTES;
 #pragma unroll
     for (int ks = 0; ks + 1 < KS; ++ks) {
 #pragma unroll
@@ -892,7 +896,7 @@ __global__ __launch_bounds__(64 * (WGM * WGN + NP), 3) void gemm_ldw_kernel(cons
     for (int f = 0; f < MF - HAND; ++f)
       adam_tile(p, r, acc[f / TN][f % TN], m0 + wm * WM + (f / TN) * 32, n0 + wn * WN + (f % TN) * 32 + (lane & 31), lane >> 5);
   } else {
-    epilogue<TM, TN, EPI, TM_LDW_VB>(p, acc, m0 + wm * WM, n0 + wn * WN, lane & 31, lane >> 5);
+    epilogue<TM, TN, EPI, MF == 6 ? TM_LDW_VB : 16>(p, acc, m0 + wm * WM, n0 + wn * WN, lane & 31, lane >> 5);
   }
 }
 
@@ -950,8 +954,8 @@ __global__ __launch_bounds__(512, 1) void gemm_alt_kernel(const MfmaGemmParams p
   auto issue = [&](int step) {
     const int k0 = (step < nk ? step : nk - 1) * BK;
     char *st = lds + (step & 1) * STAGE;
-    la.issue_any(ra, st, k0, p.lda, wave);
-    lb.issue_any(rb, st + LA::BYTES, k0, p.ldb, wave);
+    la.issue(ra, st, k0, p.lda, wave);
+    lb.issue(rb, st + LA::BYTES, k0, p.ldb, wave);
   };
   // Fragment addresses of an operand with contiguous reduction axis: row r of the tile, 16-byte chunk
   // (2 ks + lane/32) ^ swz(r).  swz looks at row bits 0..5 only and 32 rows further on it flips bit 2, so
@@ -1140,16 +1144,16 @@ static int launch_alt(const GemmArgs &g, hipStream_t s) {
   return check_launch("gemm_alt");
 }
 
-template <int BM, int BN, int WGM, int WGN, int NP, bool A_KC, bool B_KC, int EPI>
+template <int BM, int BN, int WGM, int WGN, int NP, bool A_KC, bool B_KC, int EPI, int NS = 2, bool TAIL = false>
 static int launch_ldw(const GemmArgs &g, hipStream_t s) {
   constexpr int BK = GEMM_BK;
   MfmaGemmParams p = make_params<A_KC, B_KC, EPI>(g, BM, BN);
-  if (EPI == 3 && NP == 4) stagger_of(p, BM, BN, (int64_t)p.tiles_m * p.tiles_n);
-  constexpr int lds_bytes = 2 * (BM + BN) * BK * 2 > BM * BN * 2 ? 2 * (BM + BN) * BK * 2 : BM * BN * 2;
+  if (EPI == 3 && NP == 4 && NS == 2) stagger_of(p, BM, BN, (int64_t)p.tiles_m * p.tiles_n);
+  constexpr int lds_bytes = NS * (BM + BN) * BK * 2 > BM * BN * 2 ? NS * (BM + BN) * BK * 2 : BM * BN * 2;
   static_assert(lds_bytes <= 160 * 1024, "LDS");
   static bool attr_set = false;  // per instantiation
   if (!attr_set) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_ldw_kernel<BM, BN, BK, WGM, WGN, NP, A_KC, B_KC, EPI>),
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_ldw_kernel<BM, BN, BK, WGM, WGN, NP, A_KC, B_KC, EPI, NS, TAIL>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes) != hipSuccess)
       return fail(TM_ELAUNCH, "gemm_mfma: cannot reserve %d bytes of LDS", lds_bytes);
     attr_set = true;
@@ -1159,9 +1163,9 @@ static int launch_ldw(const GemmArgs &g, hipStream_t s) {
   if (g.k_splits > 1 && (EPI != 2 || g.K % ((int64_t)BK * g.k_splits) != 0))
     return fail(TM_EINVAL, "gemm_mfma: split reduction needs whole steps per part and fp32 results");
   if (EPI == 3 && !g.adam) return fail(TM_EINVAL, "gemm_mfma: the fused update needs its target");
-  static const std::string name = kernel_tag(NP == 4 ? "gemm_ldw4_kernel" : "gemm_ldw2_kernel", BM, BN, WGM, WGN, A_KC, B_KC, EPI);
+  static const std::string name = kernel_tag(NS > 2 ? "gemm_ldw_deep_kernel" : NP == 4 ? "gemm_ldw4_kernel" : "gemm_ldw2_kernel", BM, BN, WGM, WGN, A_KC, B_KC, EPI);
   g_last_kernel = name.c_str();
-  gemm_ldw_kernel<BM, BN, BK, WGM, WGN, NP, A_KC, B_KC, EPI>
+  gemm_ldw_kernel<BM, BN, BK, WGM, WGN, NP, A_KC, B_KC, EPI, NS, TAIL>
       <<<dim3((unsigned)nblk, (unsigned)(g.k_splits > 1 ? g.k_splits : 1)), 64 * (WGM * WGN + NP), lds_bytes, s>>>(p);
   return check_launch("gemm_ldw");
 }
@@ -1174,6 +1178,12 @@ static int launch_ldw(const GemmArgs &g, hipStream_t s) {
 #define TM_GEMM_PIPE33_CONFIGS(X) X(256, 128, 4, 2) X(128, 256, 2, 4)
 // ... then the kernel with loader waves (eight multiplying waves and four loaders)
 #define TM_GEMM_LDW_CONFIGS(X) X(256, 192, 4, 2, 4) X(128, 192, 2, 2, 2) X(256, 192, 4, 2, 2)
+// ... then the same kernel on small tiles with more stages: X(BM, BN, wave grid, loaders, stages)
+#define TM_GEMM_DEEP_CONFIGS(X) X(64, 64, 2, 2, 2, 4) X(128, 64, 2, 2, 2, 3) X(64, 128, 2, 2, 2, 3) X(128, 128, 2, 2, 4, 4)
+// ... and those of the last two lists that have a form for a ragged last step: X(number, BM, BN, wave grid, loaders, stages)
+#define TM_GEMM_RAGGED_CONFIGS(X) \
+  X(13, 256, 192, 4, 2, 4, 2) X(14, 128, 192, 2, 2, 2, 2) X(16, 64, 64, 2, 2, 2, 4) X(17, 128, 64, 2, 2, 2, 3) \
+  X(18, 64, 128, 2, 2, 2, 3) X(19, 128, 128, 2, 2, 4, 4)
 #define TM_GEMM_CONFIGS(X) \
   X(128, 192, 2, 2) X(128, 128, 2, 2) X(192, 128, 2, 2) X(256, 192, 4, 2) X(192, 256, 2, 4) X(256, 256, 2, 4) \
   X(256, 256, 4, 2) X(256, 128, 4, 2) X(256, 192, 2, 2)
@@ -1198,16 +1208,34 @@ static int launch_ldw(const GemmArgs &g, hipStream_t s) {
   template __global__ void gemm_pipe_kernel<128, 256, GEMM_BK, 2, 4, AKC, BKC, EPI, 3, 3>(const MfmaGemmParams); \
   template __global__ void gemm_ldw_kernel<256, 192, GEMM_BK, 4, 2, 4, AKC, BKC, EPI>(const MfmaGemmParams); \
   template __global__ void gemm_ldw_kernel<128, 192, GEMM_BK, 2, 2, 2, AKC, BKC, EPI>(const MfmaGemmParams); \
-  template __global__ void gemm_ldw_kernel<256, 192, GEMM_BK, 4, 2, 2, AKC, BKC, EPI>(const MfmaGemmParams);
+  template __global__ void gemm_ldw_kernel<256, 192, GEMM_BK, 4, 2, 2, AKC, BKC, EPI>(const MfmaGemmParams); \
+  template __global__ void gemm_ldw_kernel<64, 64, GEMM_BK, 2, 2, 2, AKC, BKC, EPI, 4>(const MfmaGemmParams); \
+  template __global__ void gemm_ldw_kernel<128, 64, GEMM_BK, 2, 2, 2, AKC, BKC, EPI, 3>(const MfmaGemmParams); \
+  template __global__ void gemm_ldw_kernel<64, 128, GEMM_BK, 2, 2, 2, AKC, BKC, EPI, 3>(const MfmaGemmParams); \
+  template __global__ void gemm_ldw_kernel<128, 128, GEMM_BK, 2, 2, 4, AKC, BKC, EPI, 4>(const MfmaGemmParams);
+
+#define TM_GEMM_INSTANTIATE_RAGGED(AKC, BKC, EPI) \
+  template __global__ void gemm_pipe_kernel<128, 128, GEMM_BK, 2, 2, AKC, BKC, EPI, 2, 2, true>(const MfmaGemmParams); \
+  template __global__ void gemm_ldw_kernel<256, 192, GEMM_BK, 4, 2, 4, AKC, BKC, EPI, 2, true>(const MfmaGemmParams); \
+  template __global__ void gemm_ldw_kernel<128, 192, GEMM_BK, 2, 2, 2, AKC, BKC, EPI, 2, true>(const MfmaGemmParams); \
+  template __global__ void gemm_ldw_kernel<64, 64, GEMM_BK, 2, 2, 2, AKC, BKC, EPI, 4, true>(const MfmaGemmParams); \
+  template __global__ void gemm_ldw_kernel<128, 64, GEMM_BK, 2, 2, 2, AKC, BKC, EPI, 3, true>(const MfmaGemmParams); \
+  template __global__ void gemm_ldw_kernel<64, 128, GEMM_BK, 2, 2, 2, AKC, BKC, EPI, 3, true>(const MfmaGemmParams); \
+  template __global__ void gemm_ldw_kernel<128, 128, GEMM_BK, 2, 2, 4, AKC, BKC, EPI, 4, true>(const MfmaGemmParams);
 
 // config: index into the list above, as chosen by gemm_mfma_config()
 template <bool A_KC, bool B_KC, int EPI> static int launch_layout(const GemmArgs &g, int config, hipStream_t s) {
   int idx = 0;
-  // a ragged last step of an operand with contiguous reduction axis: the kernels with loader waves and the alternating
-  // kernel take it as they are, the pipelined kernel in one form (the extra vector instructions between its MFMAs cost
-  // the other forms 1 %)
-  if constexpr (A_KC || B_KC) {
-    if (g.K % GEMM_BK != 0 && !gemm_config_takes_ragged_k(config)) return launch_pipe<128, 128, 2, 2, A_KC, B_KC, EPI, 2, 2, true>(g, s);
+  if constexpr (A_KC || B_KC) {  // a ragged last step: see gemm_config_takes_ragged_k
+    if (g.K % GEMM_BK != 0) {
+      switch (config) {
+#define X(C_, BM_, BN_, WGM_, WGN_, NP_, NS_) \
+  case C_: return launch_ldw<BM_, BN_, WGM_, WGN_, NP_, A_KC, B_KC, EPI, NS_, true>(g, s);
+        TM_GEMM_RAGGED_CONFIGS(X)
+#undef X
+        default: return launch_pipe<128, 128, 2, 2, A_KC, B_KC, EPI, 2, 2, true>(g, s);
+      }
+    }
   }
 #define X(BM_, BN_, WGM_, WGN_) \
   if (config == idx++) return launch_pipe<BM_, BN_, WGM_, WGN_, A_KC, B_KC, EPI>(g, s);
@@ -1224,6 +1252,10 @@ template <bool A_KC, bool B_KC, int EPI> static int launch_layout(const GemmArgs
 #define X(BM_, BN_, WGM_, WGN_, NP_) \
   if (config == idx++) return launch_ldw<BM_, BN_, WGM_, WGN_, NP_, A_KC, B_KC, EPI>(g, s);
   TM_GEMM_LDW_CONFIGS(X)
+#undef X
+#define X(BM_, BN_, WGM_, WGN_, NP_, NS_) \
+  if (config == idx++) return launch_ldw<BM_, BN_, WGM_, WGN_, NP_, A_KC, B_KC, EPI, NS_>(g, s);
+  TM_GEMM_DEEP_CONFIGS(X)
 #undef X
   return fail(TM_EINVAL, "gemm_mfma: no tile configuration %d", config);
 }

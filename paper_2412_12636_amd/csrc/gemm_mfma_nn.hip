@@ -3,7 +3,7 @@
 
 namespace tmk {
 TM_GEMM_INSTANTIATE(true, false, 0)
-template __global__ void gemm_pipe_kernel<128, 128, GEMM_BK, 2, 2, true, false, 0, 2, 2, true>(const MfmaGemmParams);
+TM_GEMM_INSTANTIATE_RAGGED(true, false, 0)
 TM_GEMM_INSTANTIATE_ONE(128, 192, 2, 2, true, false, 2)  // fp32 partial results of a split reduction
 template __global__ void gemm_ldw_kernel<256, 192, GEMM_BK, 4, 2, 4, true, false, 2>(const MfmaGemmParams);
 int gemm_mfma_nn(const GemmArgs &g, int config, hipStream_t s) { return launch_layout<true, false, 0>(g, config, s); }
