@@ -48,16 +48,55 @@ __global__ __launch_bounds__(64) void attn_fwd_generic(const T *__restrict__ qkv
   if (lane == 0) lse[((int64_t)n * a.nq + g) * a.seq + i] = mx + logf(sum);
 }
 
-// dvec[n,g,i] = sum_e dctx[i,g,e] * ctx[i,g,e]
-template <typename T>
-__global__ __launch_bounds__(64) void attn_dvec_kernel(const T *__restrict__ ctx, const T *__restrict__ dctx,
-                                                      float *__restrict__ dvec, AttnShape a) {
-  const int i = blockIdx.x, g = blockIdx.y, n = blockIdx.z, lane = threadIdx.x;
-  const int64_t off = ((int64_t)i * a.batch + n) * (a.nq * a.d) + g * a.d;
-  float s = 0.f;
-  for (int e = lane; e < a.d; e += 64) s = fmaf(to_f32(ctx[off + e]), to_f32(dctx[off + e]), s);
-  s = wave_sum(s);
-  if (lane == 0) dvec[((int64_t)n * a.nq + g) * a.seq + i] = s;
+// dvec[n,g,i] = sum_e dctx[i,g,e] * ctx[i,g,e].  HBM-bound: a group of G lanes (d / VN rounded up to a power of two)
+// holds one row of one head, 16 bytes a lane, in memory order (heads, entries, positions), four of them in flight.  (One
+// wave per row and head left all but d / 2 bytes' worth of lanes idle and launched a block for each: 16384 positions, 8
+// heads of 128: 34 -> 16 us.)
+template <typename T, int G>
+__global__ __launch_bounds__(256) void attn_dvec_kernel(const T *__restrict__ ctx, const T *__restrict__ dctx,
+                                                       float *__restrict__ dvec, AttnShape a, int64_t total) {
+  constexpr int VN = Vec<T>::N, PER = 256 / G, ITEMS = 4;
+  const int l = threadIdx.x % G;
+  const bool live = l * VN < a.d;
+  const int64_t first = (int64_t)blockIdx.x * (PER * ITEMS) + threadIdx.x / G;
+  float c[ITEMS][VN], dc[ITEMS][VN];
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const int64_t item = first + k * PER;
+#pragma unroll
+    for (int e = 0; e < VN; ++e) c[k][e] = dc[k][e] = 0.f;
+    if (live && item < total) {
+      load_vec<T>(ctx + item * a.d + l * VN, c[k]);
+      load_vec<T>(dctx + item * a.d + l * VN, dc[k]);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    float s = 0.f;
+#pragma unroll
+    for (int e = 0; e < VN; ++e) s = fmaf(c[k][e], dc[k][e], s);
+#pragma unroll
+    for (int off = G / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    const int64_t item = first + k * PER;
+    if (l == 0 && item < total) {
+      const int64_t t = item / a.nq;
+      const int g = (int)(item - t * a.nq), i = (int)(t / a.batch), n = (int)(t - (int64_t)i * a.batch);
+      dvec[((int64_t)n * a.nq + g) * a.seq + i] = s;
+    }
+  }
+}
+template <typename T, int G>
+static void dvec_launch(const AttnShape &a, const void *ctx, const void *dctx, float *dvec, hipStream_t s) {
+  const int64_t total = (int64_t)a.seq * a.batch * a.nq;
+  attn_dvec_kernel<T, G><<<(unsigned)ceil_div(total, (int64_t)(256 / G * 4)), 256, 0, s>>>((const T *)ctx, (const T *)dctx, dvec, a, total);
+}
+template <typename T> static void dvec_t(const AttnShape &a, const void *ctx, const void *dctx, float *dvec, hipStream_t s) {
+  const int chunks = a.d / Vec<T>::N;
+  if (chunks <= 4) dvec_launch<T, 4>(a, ctx, dctx, dvec, s);
+  else if (chunks <= 8) dvec_launch<T, 8>(a, ctx, dctx, dvec, s);
+  else if (chunks <= 16) dvec_launch<T, 16>(a, ctx, dctx, dvec, s);
+  else if (chunks <= 32) dvec_launch<T, 32>(a, ctx, dctx, dvec, s);
+  else dvec_launch<T, 64>(a, ctx, dctx, dvec, s);
 }
 
 template <typename T>
@@ -190,11 +229,8 @@ int attn_fwd_generic_launch(int dtype, int64_t seq, int64_t batch, int64_t nq, i
 int attn_dvec_launch(int dtype, int64_t seq, int64_t batch, int64_t nq, int64_t nkv, int64_t d, const void *ctx,
                      const void *dctx, float *dvec, hipStream_t s) {
   const AttnShape a = make_shape(seq, batch, nq, nkv, d);
-  dim3 grid(a.seq, a.nq, a.batch);
-  if (dtype == TM_DTYPE_BF16)
-    attn_dvec_kernel<bf16><<<grid, 64, 0, s>>>((const bf16 *)ctx, (const bf16 *)dctx, dvec, a);
-  else
-    attn_dvec_kernel<float><<<grid, 64, 0, s>>>((const float *)ctx, (const float *)dctx, dvec, a);
+  if (dtype == TM_DTYPE_BF16) dvec_t<bf16>(a, ctx, dctx, dvec, s);
+  else dvec_t<float>(a, ctx, dctx, dvec, s);
   return check_launch("attn_dvec");
 }
 
