@@ -49,7 +49,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 // (a bf16 value plus the bf16 of what it leaves, two MFMAs), because these head sizes have always had them in fp32:
 // the error against 64 bits is the plain-ALU kernels' (1.6e-3 forward, 1.7e-3 backward, the rounding of the results).
 // What these kernels replaced ran one wave per row out of L2: 43.6 ms for a forward and backward pass over 2 sequences
-// of 1500, 16 query and 4 kv heads of 64, where this form takes 0.131 ms (39 us forward, 39 dQ, 49 dK/dV); bound by the
+// of 1500, 16 query and 4 kv heads of 64, where this form takes 0.103 ms (33 us forward, 65 backward); bound by the
 // latency of a tile step (S product, softmax, PV product, barrier), as the short sequences of head size 128 are.
 //
 // A staged tile: [64][128] bf16 for DP 96 and 128, [64][64] for DP 32 and 64 (half the LDS: three blocks a unit).
@@ -297,7 +297,7 @@ __device__ __forceinline__ void fwd_finish(const FlashParams &p, FwdRow<DP> &r, 
 // compute unit; or eight waves, one block: the same waves per unit, but every staged K / V tile serves twice the query
 // rows, which halves the bytes a unit pulls from L2 into LDS per MFMA (what bounds the walk of a long sequence).
 template <int DP, bool EX, int NW>
-__global__ __launch_bounds__(64 * NW, NW == 4 ? (DP > 64 ? 2 : 3) : 1) void flash_fwd_kernel(const FlashParams p) {
+__global__ __launch_bounds__(64 * NW, NW == 4 ? (DP > 64 ? 2 : 4) : 1) void flash_fwd_kernel(const FlashParams p) {
   __shared__ __align__(1024) char lds[2][2][TileFmt<DP>::BYTES];  // [stage][K, V]
   constexpr int QB = 32 * NW;
   const int qt = gridDim.z - 1 - blockIdx.z, g = blockIdx.x, n = blockIdx.y;  // heads fastest, longest walks first
@@ -351,7 +351,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (DP > 64 ? 2 : 3) : 1) void flas
 // side's state goes through LDS and the even side merges it (o = o1 2^(m1-m) + o2 2^(m2-m), the row sum alike).
 // Half as many steps, and the two waves of a SIMD overlap each other's softmax and MFMA phases.
 template <int DP, bool EX>
-__global__ __launch_bounds__(512, 1) void flash_fwd_split_kernel(const FlashParams p) {
+__global__ __launch_bounds__(512, DP > 64 ? 1 : 4) void flash_fwd_split_kernel(const FlashParams p) {
   extern __shared__ __align__(1024) char smem[];  // [stage][parity][K, V] tiles
   const int qt = gridDim.z - 1 - blockIdx.z, g = blockIdx.x, n = blockIdx.y;  // heads fastest, longest walks first
   const int kap = g / (p.nq / p.nkv), hd = EX ? p.d : DP;
@@ -547,21 +547,22 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (DP > 64 ? 2 : 3) : 1) void flas
 // result is the gradient.  Grouped heads: it is that head's fp32 partial.
 // =================================================================================================
 // smem: [stage][Q, dO] tiles, then [stage][lse, D] rows of floats, then the V fragments (kDkvLds bytes)
-template <int DP> constexpr int kDkvLds = 4 * TileFmt<DP>::BYTES + 2 * 2 * TILE * (int)sizeof(float) + 128 * DP * 2;
-template <int DP, bool EX>
+template <int DP, int NKR = 4> constexpr int kDkvLds = 4 * TileFmt<DP>::BYTES + 2 * 2 * TILE * (int)sizeof(float) + 32 * NKR * DP * 2;
+// NKR: 32-key-row groups of the block, two waves each
+template <int DP, bool EX, int NKR = 4>
 __device__ __forceinline__ void dkv_block(const FlashParams &p, char *smem, int kt, int g, int n) {
   const int group = p.nq / p.nkv, kap = g / group, hd = EX ? p.d : DP;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int kr = wave & 3, t = wave >> 2;  // key-row group, query half
+  const int kr = wave % NKR, t = wave / NKR;  // key-row group, query half
   const int l32 = lane & 31, hh = lane >> 5;
-  const int j0w = kt * 128 + kr * 32;
+  const int j0w = kt * (32 * NKR) + kr * 32;
   const int j = j0w + l32;
   const bool jvalid = j < p.seq;
   const int64_t tstride = (int64_t)p.batch * p.row;
   const int koff = p.nq * hd + kap * hd, voff = (p.nq + p.nkv) * hd + kap * hd;
   const int64_t cstride = (int64_t)p.batch * p.nq * hd;
   const rsrc_t rq = make_rsrc(p.qkv, p.qkv_bytes), rdo = make_rsrc(p.dctx, p.ctx_bytes);
-  TileLoaderN<DP, EX, 8> lq, ldo;
+  TileLoaderN<DP, EX, 2 * NKR> lq, ldo;
   lq.init(tstride, hd, wave, lane);
   ldo.init(cstride, hd, wave, lane);
   auto tile = [&](int stage, int which) { return smem + (stage * 2 + which) * TileFmt<DP>::BYTES; };
@@ -588,7 +589,7 @@ __device__ __forceinline__ void dkv_block(const FlashParams &p, char *smem, int 
   const float sc2 = p.scale * kLog2e;
   const uint32_t rb = rows_base<DP>(lane), cb = cols_base<DP>(lane);
 
-  const int it_begin = (kt * 128) / TILE;
+  const int it_begin = (kt * (32 * NKR)) / TILE;
   const int it_end = (p.seq + TILE - 1) / TILE;
   const int total = it_end - it_begin;
   // the query tiles of this head, double buffered; the row statistics of a step are fetched into registers one
@@ -723,6 +724,21 @@ __global__ __launch_bounds__(512, 1) void flash_bwd_both_kernel(const FlashParam
   else dkv_block<DP, EX>(p, smem, rank, g, n);
 }
 
+// The backward pass of head sizes up to 64 in one launch: blocks of four waves, a dK/dV block of 64 key rows or a dQ block
+// of 128 query rows, three of them on a unit (168 registers, 41 KB), two dK/dV blocks to every dQ block in dispatch order
+// and both kinds longest walk first.  (With the wide head sizes' blocks, eight waves of 169 registers and one block a
+// unit, two launches took 39 + 49 us on 2 sequences of 1500 positions, 16 heads of 64; this one takes 65.)
+template <int DP, bool EX>
+__global__ __launch_bounds__(256, 3) void flash_bwd_narrow_kernel(const FlashParams p) {
+  extern __shared__ __align__(1024) char smem[];
+  const int rank = blockIdx.z / 3, kind = blockIdx.z % 3, tiles = gridDim.z / 3, g = blockIdx.x, n = blockIdx.y;
+  if (kind == 2) {
+    dq_block<DP, EX, 4>(p, smem, tiles - 1 - rank, g, n);
+  } else if ((2 * rank + kind) * 64 < p.seq) {
+    dkv_block<DP, EX, 2>(p, smem, 2 * rank + kind, g, n);
+  }
+}
+
 // Every kernel of a family by name, ahead of the host code that takes its address.
 #define TM_FLASH_FAMILY(DP, EX)                                                \
   template __global__ void flash_fwd_kernel<DP, EX, 4>(const FlashParams);     \
@@ -733,8 +749,12 @@ __global__ __launch_bounds__(512, 1) void flash_bwd_both_kernel(const FlashParam
 TM_FLASH_FAMILY(128, false)
 template __global__ void flash_fwd_kernel<128, false, 8>(const FlashParams);
 template __global__ void flash_bwd_dq_kernel<128, false, 8>(const FlashParams);
-TM_FLASH_FAMILY(32, true)
-TM_FLASH_FAMILY(64, true)
+#define TM_FLASH_NARROW(DP)                                                    \
+  template __global__ void flash_fwd_kernel<DP, true, 4>(const FlashParams);     \
+  template __global__ void flash_fwd_split_kernel<DP, true>(const FlashParams);  \
+  template __global__ void flash_bwd_narrow_kernel<DP, true>(const FlashParams);
+TM_FLASH_NARROW(32)
+TM_FLASH_NARROW(64)
 TM_FLASH_FAMILY(96, true)
 TM_FLASH_FAMILY(128, true)
 
@@ -786,10 +806,11 @@ static FlashParams make_params(int64_t seq, int64_t batch, int64_t nq, int64_t n
 }
 
 // The eight-wave forward kernel that splits a query block's key tiles between two waves serves grids that leave
-// compute units without a second block (at most one block per unit).  TM_ATTN_SPLIT=0 / 1 in the environment forces
-// the choice (tuning and test aid).  (The same form of the dQ kernel was faster alone and slower inside the backward
-// pass, where its 128 KB blocks wait for LDS beside the weight-gradient products of the other stream: not kept.)
-static bool use_split(dim3 grid) {
+// compute units without a second block (at most one block per unit; two for head sizes up to 64, of which two blocks of
+// eight waves fit a unit).  TM_ATTN_SPLIT=0 / 1 in the environment forces the choice (tuning and test aid).  (The same
+// form of the dQ kernel was faster alone and slower inside the backward pass, where its 128 KB blocks wait for LDS beside
+// the weight-gradient products of the other stream: not kept.)
+static bool use_split(dim3 grid, int blocks_per_unit) {
   if (const char *e = getenv("TM_ATTN_SPLIT")) return e[0] == '1';
   static int units = 0;
   if (!units) {
@@ -798,7 +819,7 @@ static bool use_split(dim3 grid) {
         units <= 0)
       units = 256;
   }
-  return (int64_t)grid.x * grid.y * grid.z <= units;
+  return (int64_t)grid.x * grid.y * grid.z <= (int64_t)units * blocks_per_unit;
 }
 
 // Blocks of 256 query rows (eight waves) for the forward and dQ walks of grids that still give every compute unit two
@@ -830,7 +851,7 @@ static bool reserve_lds(const void *kernel, int bytes) {
 }
 
 template <int DP, bool EX> static int launch_fwd(const FlashParams &p, dim3 grid, hipStream_t s) {
-  if (use_split(grid)) {
+  if (use_split(grid, DP > 64 ? 1 : 2)) {
     constexpr int lds = 8 * TileFmt<DP>::BYTES;
     static bool attr_set = false;  // one flag per kernel family
     if (!attr_set && !reserve_lds(reinterpret_cast<const void *>(&flash_fwd_split_kernel<DP, EX>), lds))
@@ -870,6 +891,24 @@ int attn_fwd_mfma_launch(int64_t seq, int64_t batch, int64_t nq, int64_t nkv, in
   return launch_fwd<128, true>(p, grid, s);
 }
 
+static int reduce_heads(const FlashParams &p, hipStream_t s) {  // grouped heads: the heads' partials of dK and dV
+  if (p.part) {
+    const int64_t total = (int64_t)p.batch * p.nkv * p.seq * (2 * p.d / 4);
+    flash_dkv_reduce_kernel<<<(unsigned)ceil_div(total, (int64_t)256), 256, 0, s>>>(p);
+  }
+  return check_launch("flash_bwd");
+}
+
+template <int DP> static int launch_bwd_narrow(const FlashParams &p, dim3 gq, hipStream_t s) {
+  constexpr int lds = kDkvLds<DP, 2>;
+  static_assert(lds >= 4 * TileFmt<DP>::BYTES && lds >= 2 * (DP / 32) * 16 * 64 * 4, "the dQ block's tiles and the second half's sums fit");
+  static_assert(lds <= 64 * 1024, "no LDS attribute needed");
+  if (3 * (int64_t)gq.z > 65535) return fail(TM_ESIZE, "flash_bwd: sequence too long for the grid");
+  g_last_kernel = "flash_bwd_narrow_kernel";
+  flash_bwd_narrow_kernel<DP, true><<<dim3(gq.x, gq.y, 3 * gq.z), 256, lds, s>>>(p);
+  return reduce_heads(p, s);
+}
+
 template <int DP, bool EX> static int launch_bwd(const FlashParams &p, dim3 gq, hipStream_t s) {
   constexpr int lds = kDkvLds<DP>;
   static_assert(lds >= 4 * TileFmt<DP>::BYTES, "the dQ block's tiles fit the dK/dV block's LDS");
@@ -893,11 +932,7 @@ template <int DP, bool EX> static int launch_bwd(const FlashParams &p, dim3 gq, 
     if (!wide) flash_bwd_dq_kernel<DP, EX, 4><<<gq, 256, 0, s>>>(p);
     flash_bwd_dkv_kernel<DP, EX><<<gq, 512, lds, s>>>(p);
   }
-  if (p.part) {
-    const int64_t total = (int64_t)p.batch * p.nkv * p.seq * (2 * p.d / 4);
-    flash_dkv_reduce_kernel<<<(unsigned)ceil_div(total, (int64_t)256), 256, 0, s>>>(p);
-  }
-  return check_launch("flash_bwd");
+  return reduce_heads(p, s);
 }
 
 int64_t attn_bwd_mfma_partial_floats(int64_t seq, int64_t batch, int64_t nq, int64_t nkv, int64_t d) {
@@ -919,8 +954,8 @@ int attn_bwd_mfma_launch(int64_t seq, int64_t batch, int64_t nq, int64_t nkv, in
   if (ceil_div(seq, 128) > 65535 || batch > 65535) return fail(TM_ESIZE, "flash_bwd: sequence or batch too long for the grid");
   dim3 gq((unsigned)nq, (unsigned)batch, (unsigned)ceil_div(seq, 128));  // heads fastest: see the forward launch
   if (d == 128) return launch_bwd<128, false>(p, gq, s);
-  if (d <= 32) return launch_bwd<32, true>(p, gq, s);
-  if (d <= 64) return launch_bwd<64, true>(p, gq, s);
+  if (d <= 32) return launch_bwd_narrow<32>(p, gq, s);
+  if (d <= 64) return launch_bwd_narrow<64>(p, gq, s);
   if (d <= 96) return launch_bwd<96, true>(p, gq, s);
   return launch_bwd<128, true>(p, gq, s);
 }
