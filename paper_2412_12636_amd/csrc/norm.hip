@@ -8,26 +8,55 @@ namespace tmk {
 constexpr int kNormThreads = 512;
 constexpr int kNormMaxChunks = 4;  // 16-byte chunks per thread: hidden <= 512 * 4 * Vec::N
 
+// Threads of a row.  TPR = 512: a block per row, for rows of more than 4 KB.  Shorter rows leave most of such a block
+// idle and one small row in flight per block (4000 rows of 2 KB: 13.3 us forward, 21 backward; a wave per row: 6.4 and
+// 11), so they take one wave (no barrier in the row sums) or two, and a block holds 512 / TPR rows.
+//
+// Sum of two values over the TPR threads of this thread's row; red: 2 * 512 / 64 floats.
+template <int TPR> __device__ __forceinline__ void row_sum2(float &a, float &b, float *red) {
+  if constexpr (TPR == kNormThreads) {
+    block_sum2<kNormThreads>(a, b, red);
+  } else {
+    a = wave_sum(a);
+    b = wave_sum(b);
+    if constexpr (TPR == 128) {
+      constexpr int NW = kNormThreads / kWave;
+      const int w = threadIdx.x / kWave;
+      __syncthreads();  // protects `red` against the previous use
+      if (threadIdx.x % kWave == 0) {
+        red[w] = a;
+        red[NW + w] = b;
+      }
+      __syncthreads();
+      a = red[w & ~1] + red[w | 1];
+      b = red[NW + (w & ~1)] + red[NW + (w | 1)];
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------------------
 // forward: one block per token row; the row stays in registers between the passes.
 // Every access goes through a per-row buffer descriptor (chunks past the row read as zero).
 // ---------------------------------------------------------------------------------------
-template <typename T, int KIND, int NCH>
+template <typename T, int KIND, int NCH, int TPR = kNormThreads>
 __global__ __launch_bounds__(kNormThreads) void norm_fwd_kernel(
     const T *__restrict__ x, const T *__restrict__ gain, const T *__restrict__ offset, T *__restrict__ out,
-    float *__restrict__ mean_out, float *__restrict__ rstd_out, int h, float eps) {
+    float *__restrict__ mean_out, float *__restrict__ rstd_out, int64_t rows, int h, float eps) {
   constexpr int VN = Vec<T>::N;
   __shared__ float red[2 * kNormThreads / kWave];
-  const int64_t row = blockIdx.x;
-  const uint32_t row_bytes = (uint32_t)h * sizeof(T);
+  const int tid = threadIdx.x % TPR;
+  const int sub = TPR == kNormThreads ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / TPR);  // uniform over a wave
+  const int64_t row = (int64_t)blockIdx.x * (kNormThreads / TPR) + sub;
+  // a row past the end (several rows a block): reads as zero, nothing is written
+  const uint32_t row_bytes = row < rows ? (uint32_t)h * sizeof(T) : 0u, width_bytes = (uint32_t)h * sizeof(T);
   const rsrc_t rx = make_rsrc(x + row * h, row_bytes), ro = make_rsrc(out + row * h, row_bytes);
-  const rsrc_t rg = make_rsrc(gain, row_bytes), rf = make_rsrc(KIND == TM_NORM_LAYERNORM ? offset : gain, row_bytes);
+  const rsrc_t rg = make_rsrc(gain, width_bytes), rf = make_rsrc(KIND == TM_NORM_LAYERNORM ? offset : gain, width_bytes);
   const int nchunk = h / VN;
 
   float vals[NCH][VN];
   float s1 = 0.f, s2 = 0.f;
 #pragma unroll
-  for (int c = 0; c < NCH; ++c) buf_load_vec<T>(rx, (threadIdx.x + c * kNormThreads) * 16u, vals[c]);
+  for (int c = 0; c < NCH; ++c) buf_load_vec<T>(rx, (tid + c * TPR) * 16u, vals[c]);
 #pragma unroll
   for (int c = 0; c < NCH; ++c)
 #pragma unroll
@@ -35,32 +64,32 @@ __global__ __launch_bounds__(kNormThreads) void norm_fwd_kernel(
       s1 += vals[c][i];
       s2 += vals[c][i] * vals[c][i];
     }
-  block_sum2<kNormThreads>(s1, s2, red);
+  row_sum2<TPR>(s1, s2, red);
   float mu = 0.f, rstd;
   if (KIND == TM_NORM_LAYERNORM) {
     mu = s1 / h;
     float q = 0.f, dummy = 0.f;  // second pass over registers: sum of squared deviations
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-      const bool live = threadIdx.x + c * kNormThreads < nchunk;
+      const bool live = tid + c * TPR < nchunk;
 #pragma unroll
       for (int i = 0; i < VN; ++i) {
         const float dlt = vals[c][i] - mu;
         q += live ? dlt * dlt : 0.f;
       }
     }
-    block_sum2<kNormThreads>(q, dummy, red);
+    row_sum2<TPR>(q, dummy, red);
     rstd = 1.0f / sqrtf(q / h + eps);
   } else {
     rstd = 1.0f / sqrtf(s2 / h + eps);
   }
-  if (threadIdx.x == 0) {
+  if (tid == 0 && row < rows) {
     if (mean_out) mean_out[row] = mu;
     rstd_out[row] = rstd;
   }
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
-    const uint32_t off = (threadIdx.x + c * kNormThreads) * 16u;
+    const uint32_t off = (tid + c * TPR) * 16u;
     float g[VN], o[VN], r[VN];
     buf_load_vec<T>(rg, off, g);
     if (KIND == TM_NORM_LAYERNORM) buf_load_vec<T>(rf, off, o);
@@ -80,19 +109,21 @@ __global__ __launch_bounds__(kNormThreads) void norm_fwd_kernel(
 // stored dx: the gradient of the bias of the linear map that produced x's residual input, which would
 // otherwise cost one more pass over dx)
 // ---------------------------------------------------------------------------------------
-template <typename T, int KIND, int NCH, bool XSUM>
+template <typename T, int KIND, int NCH, bool XSUM, int TPR = kNormThreads>
 __global__ __launch_bounds__(kNormThreads) void norm_bwd_kernel(
     const T *__restrict__ dout, const T *__restrict__ x, const float *__restrict__ mean,
     const float *__restrict__ rstd, const T *__restrict__ gain, const T *dres, T *dx,
     float *__restrict__ partial, int64_t rows, int h) {
   constexpr int VN = Vec<T>::N;
   __shared__ float red[2 * kNormThreads / kWave];
+  constexpr int RPB = kNormThreads / TPR;  // rows of a block at a time
+  const int tid = threadIdx.x % TPR, sub = TPR == kNormThreads ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / TPR);
   const uint32_t row_bytes = (uint32_t)h * sizeof(T);
   const rsrc_t rg = make_rsrc(gain, row_bytes);
   float gacc[NCH][VN], oacc[NCH][VN], gn[NCH][VN], xacc[XSUM ? NCH : 1][VN];
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
-    buf_load_vec<T>(rg, (threadIdx.x + c * kNormThreads) * 16u, gn[c]);
+    buf_load_vec<T>(rg, (tid + c * TPR) * 16u, gn[c]);
 #pragma unroll
     for (int i = 0; i < VN; ++i) {
       gacc[c][i] = oacc[c][i] = 0.f;
@@ -104,11 +135,12 @@ __global__ __launch_bounds__(kNormThreads) void norm_bwd_kernel(
   typedef uint32_t raw4 __attribute__((ext_vector_type(4)));
   raw4 nw[NCH], nx[NCH], nr[NCH];
   auto fetch = [&](int64_t row) {
-    const rsrc_t rd = make_rsrc(dout + row * h, row_bytes), rx = make_rsrc(x + row * h, row_bytes);
-    const rsrc_t rr = make_rsrc(dres ? dres + row * h : dout, dres ? row_bytes : 0u);  // no residual: reads zeros
+    const uint32_t bytes = TPR == kNormThreads || row < rows ? row_bytes : 0u;  // a row past the end reads as zeros
+    const rsrc_t rd = make_rsrc(dout + row * h, bytes), rx = make_rsrc(x + row * h, bytes);
+    const rsrc_t rr = make_rsrc(dres ? dres + row * h : dout, dres ? bytes : 0u);  // no residual: reads zeros
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-      const uint32_t off = (threadIdx.x + c * kNormThreads) * 16u;
+      const uint32_t off = (tid + c * TPR) * 16u;
       nw[c] = __builtin_bit_cast(raw4, __builtin_amdgcn_raw_buffer_load_b128(rd, off, 0, 0));
       nx[c] = __builtin_bit_cast(raw4, __builtin_amdgcn_raw_buffer_load_b128(rx, off, 0, 0));
       nr[c] = __builtin_bit_cast(raw4, __builtin_amdgcn_raw_buffer_load_b128(rr, off, 0, 0));
@@ -120,11 +152,15 @@ __global__ __launch_bounds__(kNormThreads) void norm_bwd_kernel(
 #pragma unroll
     for (int i = 0; i < VN; ++i) out[i] = to_f32(u.v.v[i]);
   };
-  if ((int64_t)blockIdx.x < rows) fetch(blockIdx.x);
-  for (int64_t row = blockIdx.x; row < rows; row += gridDim.x) {
-    const rsrc_t ro = make_rsrc(dx + row * h, row_bytes);
-    const float mu = (KIND == TM_NORM_LAYERNORM) ? mean[row] : 0.f;
-    const float rs = rstd[row];
+  // all rows of a block advance together (barriers in the row sums): the loop runs on the block's first row
+  const int64_t stride = (int64_t)gridDim.x * RPB;
+  if ((int64_t)blockIdx.x * RPB < rows) fetch((int64_t)blockIdx.x * RPB + sub);
+  for (int64_t row0 = (int64_t)blockIdx.x * RPB; row0 < rows; row0 += stride) {
+    const int64_t row = row0 + sub;
+    const bool in = TPR == kNormThreads || row < rows;
+    const rsrc_t ro = make_rsrc(dx + row * h, in ? row_bytes : 0u);
+    const float mu = KIND == TM_NORM_LAYERNORM && in ? mean[row] : 0.f;
+    const float rs = in ? rstd[row] : 0.f;
     float w[NCH][VN], xh[NCH][VN], res[NCH][VN];
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
@@ -132,12 +168,12 @@ __global__ __launch_bounds__(kNormThreads) void norm_bwd_kernel(
       unpack(nx[c], xh[c]);
       unpack(nr[c], res[c]);
     }
-    if (row + gridDim.x < rows) fetch(row + gridDim.x);
+    if (row0 + stride < rows) fetch(row + stride);
     const int nchunk = h / VN;
     float sw = 0.f, swx = 0.f;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-      const bool live = threadIdx.x + c * kNormThreads < nchunk;  // x reads as 0 past the row: xhat would be -mu*rs
+      const bool live = tid + c * TPR < nchunk;  // x reads as 0 past the row: xhat would be -mu*rs
 #pragma unroll
       for (int i = 0; i < VN; ++i) {
         const float d = w[c][i];
@@ -150,7 +186,7 @@ __global__ __launch_bounds__(kNormThreads) void norm_bwd_kernel(
         swx += w[c][i] * xv;
       }
     }
-    block_sum2<kNormThreads>(sw, swx, red);
+    row_sum2<TPR>(sw, swx, red);
     const float mw = (KIND == TM_NORM_LAYERNORM) ? sw / h : 0.f;
     const float mwx = swx / h;
 #pragma unroll
@@ -160,15 +196,36 @@ __global__ __launch_bounds__(kNormThreads) void norm_bwd_kernel(
         res[c][i] += (w[c][i] - mw - xh[c][i] * mwx) * rs;
         if (XSUM) xacc[c][i] += to_f32(from_f32<T>(res[c][i]));  // the value as stored
       }
-      buf_store_vec<T>(ro, (threadIdx.x + c * kNormThreads) * 16u, res[c]);
+      buf_store_vec<T>(ro, (tid + c * TPR) * 16u, res[c]);
     }
+  }
+  if constexpr (RPB > 1) {  // the block's rows: their sums meet in LDS, added in row order, by the first TPR threads
+    __shared__ float sums[kNormThreads * VN];
+    auto join = [&](float (&v)[VN]) {
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < VN; ++i) sums[i * kNormThreads + threadIdx.x] = v[i];
+      __syncthreads();
+      if (sub == 0) {
+#pragma unroll
+        for (int i = 0; i < VN; ++i)
+          for (int r = 1; r < RPB; ++r) v[i] += sums[i * kNormThreads + r * TPR + tid];
+      }
+    };
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      join(gacc[c]);
+      join(oacc[c]);
+      if constexpr (XSUM) join(xacc[c]);
+    }
+    if (sub != 0) return;
   }
   const rsrc_t rp = make_rsrc(partial + (int64_t)blockIdx.x * 3 * h, (uint32_t)h * 4u);
   const rsrc_t rq = make_rsrc(partial + (int64_t)blockIdx.x * 3 * h + h, (uint32_t)h * 4u);
   const rsrc_t rz = make_rsrc(partial + (int64_t)blockIdx.x * 3 * h + 2 * h, (uint32_t)h * 4u);
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
-    const uint32_t col = (threadIdx.x + c * kNormThreads) * VN;
+    const uint32_t col = (tid + c * TPR) * VN;
 #pragma unroll
     for (int v4 = 0; v4 < VN / 4; ++v4) {
       float a[4], b[4];
@@ -191,12 +248,13 @@ __global__ __launch_bounds__(kNormThreads) void norm_bwd_kernel(
 
 // the three column reductions of the norm's backward pass in one launch: slice s of the partial rows goes to outs[s]
 // (NULL: skipped); same summation order as reduce_partials_kernel
+constexpr int kRowLanes = 16;  // row lanes of a block: 256 partial rows are four loads deep (four lanes: 7 us a launch, now 4.8)
 struct ReduceOuts {
   float *out[3];
 };
-__global__ __launch_bounds__(256) void reduce_partials3_kernel(const float *__restrict__ partial, int R, int h, ReduceOuts outs,
+__global__ __launch_bounds__(64 * kRowLanes) void reduce_partials3_kernel(const float *__restrict__ partial, int R, int h, ReduceOuts outs,
                                                                int accumulate) {
-  __shared__ float sm[4][64];
+  __shared__ float sm[kRowLanes][64];
   const int lane = threadIdx.x & 63, ry = threadIdx.x >> 6;
   const int per_slice = (h + 63) / 64;
   const int slice = blockIdx.x / per_slice, c = (blockIdx.x % per_slice) * 64 + lane;
@@ -207,48 +265,52 @@ __global__ __launch_bounds__(256) void reduce_partials3_kernel(const float *__re
   float s = 0.f;
   if (c < h) {
     int r = ry;
-    for (; r + 12 < R; r += 16) {
-      const float a0 = src[(int64_t)r * ld + c], a1 = src[(int64_t)(r + 4) * ld + c];
-      const float a2 = src[(int64_t)(r + 8) * ld + c], a3 = src[(int64_t)(r + 12) * ld + c];
+    for (; r + 3 * kRowLanes < R; r += 4 * kRowLanes) {
+      const float a0 = src[(int64_t)r * ld + c], a1 = src[(int64_t)(r + kRowLanes) * ld + c];
+      const float a2 = src[(int64_t)(r + 2 * kRowLanes) * ld + c], a3 = src[(int64_t)(r + 3 * kRowLanes) * ld + c];
       s += a0;
       s += a1;
       s += a2;
       s += a3;
     }
-    for (; r < R; r += 4) s += src[(int64_t)r * ld + c];
+    for (; r < R; r += kRowLanes) s += src[(int64_t)r * ld + c];
   }
   sm[ry][lane] = s;
   __syncthreads();
   if (ry == 0 && c < h) {
-    const float t = ((sm[0][lane] + sm[1][lane]) + sm[2][lane]) + sm[3][lane];
+    float t = sm[0][lane];
+#pragma unroll
+    for (int k = 1; k < kRowLanes; ++k) t += sm[k][lane];
     out[c] = accumulate ? out[c] + t : t;
   }
 }
 
-// out[c] (+)= sum_{r<R} partial[r*ld + c].  Block = 64 columns x 4 row lanes; lane y adds rows
-// y, y+4, ... in ascending order, then the four lane sums are added in lane order: a fixed order.
-__global__ __launch_bounds__(256) void reduce_partials_kernel(const float *__restrict__ partial, int R, int64_t ld,
+// out[c] (+)= sum_{r<R} partial[r*ld + c].  Block = 64 columns x 16 row lanes; lane y adds rows
+// y, y+16, ... in ascending order, then the lane sums are added in lane order: a fixed order.
+__global__ __launch_bounds__(64 * kRowLanes) void reduce_partials_kernel(const float *__restrict__ partial, int R, int64_t ld,
                                                               int n, float *__restrict__ out, int accumulate) {
-  __shared__ float sm[4][64];
+  __shared__ float sm[kRowLanes][64];
   const int lane = threadIdx.x & 63, ry = threadIdx.x >> 6;
   const int c = blockIdx.x * 64 + lane;
   float s = 0.f;
   if (c < n) {
     int r = ry;
-    for (; r + 12 < R; r += 16) {  // four independent loads in flight per trip
-      const float a0 = partial[(int64_t)r * ld + c], a1 = partial[(int64_t)(r + 4) * ld + c];
-      const float a2 = partial[(int64_t)(r + 8) * ld + c], a3 = partial[(int64_t)(r + 12) * ld + c];
+    for (; r + 3 * kRowLanes < R; r += 4 * kRowLanes) {  // four independent loads in flight per trip
+      const float a0 = partial[(int64_t)r * ld + c], a1 = partial[(int64_t)(r + kRowLanes) * ld + c];
+      const float a2 = partial[(int64_t)(r + 2 * kRowLanes) * ld + c], a3 = partial[(int64_t)(r + 3 * kRowLanes) * ld + c];
       s += a0;
       s += a1;
       s += a2;
       s += a3;
     }
-    for (; r < R; r += 4) s += partial[(int64_t)r * ld + c];
+    for (; r < R; r += kRowLanes) s += partial[(int64_t)r * ld + c];
   }
   sm[ry][lane] = s;
   __syncthreads();
   if (ry == 0 && c < n) {
-    const float t = ((sm[0][lane] + sm[1][lane]) + sm[2][lane]) + sm[3][lane];
+    float t = sm[0][lane];
+#pragma unroll
+    for (int k = 1; k < kRowLanes; ++k) t += sm[k][lane];
     out[c] = accumulate ? out[c] + t : t;
   }
 }
@@ -271,7 +333,17 @@ __global__ __launch_bounds__(kColLanes *kColRowsPerBlock) void colsum_partial_ke
 #pragma unroll
   for (int i = 0; i < VN; ++i) acc[i] = 0.f;
   if (col < n) {
-    for (int64_t r = r0 + ry; r < r1; r += kColRowsPerBlock) {
+    int64_t r = r0 + ry;
+    for (; r + 3 * kColRowsPerBlock < r1; r += 4 * kColRowsPerBlock) {  // four rows in flight
+      float v[4][VN];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) load_vec<T>(dy + (r + k * kColRowsPerBlock) * n + col, v[k]);
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int i = 0; i < VN; ++i) acc[i] += v[k][i];
+    }
+    for (; r < r1; r += kColRowsPerBlock) {
       float v[VN];
       load_vec<T>(dy + r * n + col, v);
 #pragma unroll
@@ -293,7 +365,20 @@ __global__ __launch_bounds__(kColLanes *kColRowsPerBlock) void colsum_partial_ke
 }
 
 static int norm_bwd_blocks(int64_t T) { return (int)(T < 256 ? T : 256); }
-static int colsum_groups(int64_t T) { return (int)(T < 32 * kColRowsPerBlock ? ceil_div(T, kColRowsPerBlock) : 32); }
+// threads of a row for width h (see the top of this file)
+static int norm_tpr(int64_t h, int vn) { return h <= 2 * 64 * vn ? 64 : h <= 2 * 128 * vn ? 128 : kNormThreads; }
+// blocks of the backward pass = partial rows: never more than norm_bwd_blocks, which sizes the scratch
+static int norm_bwd_grid(int64_t T, int64_t h, int vn) {
+  const int64_t groups = ceil_div(T, (int64_t)(kNormThreads / norm_tpr(h, vn)));
+  return (int)(groups < 256 ? groups : 256);
+}
+// Row groups of a column sum, at most as many as a norm has partial rows (min(T, 256), which sizes the scratch): about 64
+// rows each, and 32 groups where that would leave too few blocks (fewer for up to 512 rows).
+static int colsum_groups(int64_t T) {
+  if (T <= 512) return (int)ceil_div(T, (int64_t)16);
+  return (int)(T <= 2048 ? 32 : T < 256 * 64 ? ceil_div(T, (int64_t)64) : 256);
+}
+
 
 // chunks per thread, rounded up to an instantiated count
 static int pick_nch(int h, int vn) {
@@ -318,12 +403,27 @@ static int norm_fwd_t(int kind, int64_t rows, int h, float eps, const void *x, c
                       void *out, float *mean, float *rstd, hipStream_t s) {
   const int nch = pick_nch(h, Vec<T>::N);
   g_last_kernel = "norm_fwd_kernel";
+#define TM_NORM_FWD_NARROW(NCH, TPR)                                                                              \
+  do {                                                                                                            \
+    const unsigned grid = (unsigned)ceil_div(rows, (int64_t)(kNormThreads / TPR));                                \
+    if (kind == TM_NORM_LAYERNORM)                                                                                \
+      norm_fwd_kernel<T, TM_NORM_LAYERNORM, NCH, TPR><<<grid, kNormThreads, 0, s>>>(                              \
+          (const T *)x, (const T *)gain, (const T *)offset, (T *)out, mean, rstd, rows, h, eps);                  \
+    else                                                                                                          \
+      norm_fwd_kernel<T, TM_NORM_RMSNORM, NCH, TPR><<<grid, kNormThreads, 0, s>>>(                                \
+          (const T *)x, (const T *)gain, nullptr, (T *)out, mean, rstd, rows, h, eps);                            \
+    return check_launch("norm_fwd");                                                                              \
+  } while (0)
+  if (h <= 64 * Vec<T>::N) TM_NORM_FWD_NARROW(1, 64);
+  if (h <= 2 * 64 * Vec<T>::N) TM_NORM_FWD_NARROW(2, 64);
+  if (h <= 2 * 128 * Vec<T>::N) TM_NORM_FWD_NARROW(2, 128);
+#undef TM_NORM_FWD_NARROW
   if (kind == TM_NORM_LAYERNORM) {
     TM_NCH_SWITCH(nch, (norm_fwd_kernel<T, TM_NORM_LAYERNORM, NCH><<<dim3((unsigned)rows), kNormThreads, 0, s>>>(
-                           (const T *)x, (const T *)gain, (const T *)offset, (T *)out, mean, rstd, h, eps)))
+                           (const T *)x, (const T *)gain, (const T *)offset, (T *)out, mean, rstd, rows, h, eps)))
   } else {
     TM_NCH_SWITCH(nch, (norm_fwd_kernel<T, TM_NORM_RMSNORM, NCH><<<dim3((unsigned)rows), kNormThreads, 0, s>>>(
-                           (const T *)x, (const T *)gain, nullptr, (T *)out, mean, rstd, h, eps)))
+                           (const T *)x, (const T *)gain, nullptr, (T *)out, mean, rstd, rows, h, eps)))
   }
   return check_launch("norm_fwd");
 }
@@ -331,9 +431,23 @@ static int norm_fwd_t(int kind, int64_t rows, int h, float eps, const void *x, c
 template <typename T, bool XSUM>
 static int norm_bwd_t(int kind, int64_t rows, int h, const void *dout, const void *x, const float *mean,
                       const float *rstd, const void *gain, const void *dres, void *dx, float *partial, hipStream_t s) {
-  const int G = norm_bwd_blocks(rows);
+  const int G = norm_bwd_grid(rows, h, Vec<T>::N);
   const int nch = pick_nch(h, Vec<T>::N);
   g_last_kernel = "norm_bwd_kernel";
+#define TM_NORM_BWD_NARROW(NCH, TPR)                                                                                   \
+  do {                                                                                                                 \
+    if (kind == TM_NORM_LAYERNORM)                                                                                     \
+      norm_bwd_kernel<T, TM_NORM_LAYERNORM, NCH, XSUM, TPR><<<G, kNormThreads, 0, s>>>(                                \
+          (const T *)dout, (const T *)x, mean, rstd, (const T *)gain, (const T *)dres, (T *)dx, partial, rows, h);     \
+    else                                                                                                               \
+      norm_bwd_kernel<T, TM_NORM_RMSNORM, NCH, XSUM, TPR><<<G, kNormThreads, 0, s>>>(                                  \
+          (const T *)dout, (const T *)x, mean, rstd, (const T *)gain, (const T *)dres, (T *)dx, partial, rows, h);     \
+    return check_launch("norm_bwd");                                                                                   \
+  } while (0)
+  if (h <= 64 * Vec<T>::N) TM_NORM_BWD_NARROW(1, 64);
+  if (h <= 2 * 64 * Vec<T>::N) TM_NORM_BWD_NARROW(2, 64);
+  if (h <= 2 * 128 * Vec<T>::N) TM_NORM_BWD_NARROW(2, 128);
+#undef TM_NORM_BWD_NARROW
   if (kind == TM_NORM_LAYERNORM) {
     TM_NCH_SWITCH(nch, (norm_bwd_kernel<T, TM_NORM_LAYERNORM, NCH, XSUM><<<G, kNormThreads, 0, s>>>(
                            (const T *)dout, (const T *)x, mean, rstd, (const T *)gain, (const T *)dres, (T *)dx,
@@ -397,9 +511,9 @@ static int norm_bwd_any(int dtype, int kind, int64_t T, int64_t h, const void *d
     e = dtype == TM_DTYPE_BF16 ? norm_bwd_t<bf16, false>(kind, T, (int)h, dout, x, mean, rstd, gain, dres, dx, partial, s)
                                : norm_bwd_t<float, false>(kind, T, (int)h, dout, x, mean, rstd, gain, dres, dx, partial, s);
   if (e) return e;
-  const int G = norm_bwd_blocks(T);
+  const int G = norm_bwd_grid(T, h, dtype == TM_DTYPE_BF16 ? Vec<bf16>::N : Vec<float>::N);
   ReduceOuts outs{{dgain, kind == TM_NORM_LAYERNORM ? doffset : nullptr, dx_colsum}};
-  reduce_partials3_kernel<<<3 * (int)ceil_div(h, 64), 256, 0, s>>>(partial, G, (int)h, outs, accumulate);
+  reduce_partials3_kernel<<<3 * (int)ceil_div(h, 64), 64 * kRowLanes, 0, s>>>(partial, G, (int)h, outs, accumulate);
   return check_launch("norm_bwd reduce");
 }
 
@@ -434,6 +548,6 @@ extern "C" int tm_op_bias_grad(int dtype, int64_t T, int64_t N, const void *dy, 
   else
     colsum_partial_kernel<float><<<grid, kColLanes * kColRowsPerBlock, 0, s>>>((const float *)dy, partial, T, (int)N,
                                                                                rows_per_group);
-  reduce_partials_kernel<<<(int)ceil_div(N, 64), 256, 0, s>>>(partial, R, N, (int)N, db, accumulate);
+  reduce_partials_kernel<<<(int)ceil_div(N, 64), 64 * kRowLanes, 0, s>>>(partial, R, N, (int)N, db, accumulate);
   return check_launch("bias_grad");
 }

@@ -350,6 +350,22 @@ def test_norm_fwd_bwd(env, dtype, kind, T, h):
     assert rel_err(to_host(csum), 2.0 * (rdx + dres).sum(axis=0)) <= tol_of(dtype)
 
 
+@pytest.mark.parametrize("dtype,kind,T,h", [
+    (BF16, so.NORM_LAYERNORM, 1, 8), (BF16, so.NORM_RMSNORM, 9, 512), (BF16, so.NORM_LAYERNORM, 300, 520), (BF16, so.NORM_RMSNORM, 2500, 1024),
+    (BF16, so.NORM_LAYERNORM, 7, 1032), (BF16, so.NORM_LAYERNORM, 1500, 2048), (BF16, so.NORM_RMSNORM, 5, 2056),
+    (FP32, so.NORM_LAYERNORM, 17, 264), (FP32, so.NORM_RMSNORM, 2100, 512), (FP32, so.NORM_LAYERNORM, 3, 1024), (FP32, so.NORM_LAYERNORM, 4, 1032)])
+def test_norm_rows_of_a_wave_or_two(env, dtype, kind, T, h):
+    """The widths at which a row goes to one wave, two waves or a whole block, and row counts that leave part of a block's
+    rows empty (one row; one more than a block holds; more rows than the blocks take at once): as test_norm_fwd_bwd."""
+    test_norm_fwd_bwd(env, dtype, kind, T, h)
+
+
+@pytest.mark.parametrize("dtype,T,N", [(BF16, 1, 8), (BF16, 513, 520), (FP32, 2049, 264), (BF16, 17000, 24)])
+def test_bias_grad_row_groups(env, dtype, T, N):
+    """One group of one row, and the row counts at which the number of row groups changes, as test_bias_grad."""
+    test_bias_grad(env, dtype, T, N)
+
+
 # ------------------------------------------------------------------ activations
 @pytest.mark.parametrize("dtype", [BF16, FP32])
 @pytest.mark.parametrize("act", [so.ACT_GELU_TANH, so.ACT_GELU_ERF, so.ACT_SWIGLU])
