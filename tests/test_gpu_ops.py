@@ -414,6 +414,24 @@ def test_rotary_forward_and_inverse(env, dtype, seq, batch, heads, d):
     assert rel_err(to_host(buf), z64) <= (TOL_BF16 if dtype == BF16 else 1e-5)
 
 
+@pytest.mark.parametrize("dtype,seq,batch,heads,d", [(BF16, 1, 1, 1, 16), (BF16, 37, 2, 5, 80), (FP32, 9, 3, 2, 8), (FP32, 130, 1, 33, 64),
+                                                     (BF16, 5, 1, 2, 512)])
+def test_rotary_rows_and_elements_agree(env, dtype, seq, batch, heads, d):
+    """The form for whole 16-byte chunks (several rows a block, one row, a ragged last block, more heads than a pass of the
+    block holds, the widest half) against the element-wise form, which a buffer off the 16-byte alignment takes."""
+    torch, tm = env
+    width = (heads + 1) * d
+    z = to_dev(torch, rand(np.random.default_rng(d), (seq, batch, width), 1.0, dtype), dtype)
+    buf = z.clone()
+    store = torch.empty(z.numel() + 16, dtype=z.dtype, device="cuda")
+    off = store[1:1 + z.numel()].view_as(z)
+    off.copy_(z)
+    for inverse in (0, 1, 1):
+        tm.tm_op_rotary(dtype, seq, batch, heads, d, width, 10000.0, inverse, buf, stream_ptr(torch))
+        tm.tm_op_rotary(dtype, seq, batch, heads, d, width, 10000.0, inverse, off, stream_ptr(torch))
+        assert torch.equal(buf, off)
+
+
 # ------------------------------------------------------------------ attention
 ATTN_SHAPES = [
     # dtype, seq, batch, nq, nkv, d
