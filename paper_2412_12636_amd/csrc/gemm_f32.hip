@@ -97,15 +97,16 @@ template <int R, int NW> struct F32KS {
 template <int R, int NW, bool KC> struct F32Sel { typedef F32KC<R, NW> type; };
 template <int R, int NW> struct F32Sel<R, NW, false> { typedef F32KS<R, NW> type; };
 
-// WM, WN: wave tile; KSPL: waves that split a step's reduction elements; NS: LDS stages
-template <int BM, int BN, int WM, int WN, int KSPL, int NS, bool A_KC, bool B_KC, int EPI>
+// WM, WN: wave tile; KSPL: waves that split a step's reduction elements; NS: LDS stages; SUB: steps of a stage, for tiles
+// whose single step is shorter than the barrier and the LDS latency around it
+template <int BM, int BN, int WM, int WN, int KSPL, int NS, int SUB, bool A_KC, bool B_KC, int EPI>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const F32GemmParams p) {
   constexpr int NW = (BM / WM) * (BN / WN) * KSPL, TM = WM / 32, TN = WN / 32;
   static_assert(NW == 4, "four waves");
   static_assert(KSPL == 1 || (KSPL == 4 && TM == 1 && TN == 1), "split waves hold one tile each");
   typedef typename F32Sel<BM, NW, A_KC>::type LA;
   typedef typename F32Sel<BN, NW, B_KC>::type LB;
-  constexpr int STAGE = LA::BYTES + LB::BYTES, LOADS = LA::NLOAD + LB::NLOAD;
+  constexpr int STEP = LA::BYTES + LB::BYTES, STAGE = SUB * STEP, LOADS = SUB * (LA::NLOAD + LB::NLOAD);
   extern __shared__ __align__(1024) char lds[];
   const int m0 = (int)(blockIdx.x % p.tiles_m) * BM, n0 = (int)(blockIdx.x / p.tiles_m) * BN;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -123,23 +124,26 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const F32GemmParams p) {
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  const int nk = (p.K + FK - 1) / FK;
-  auto issue = [&](int step) {  // never past K: a surplus fetch repeats the last step into a stage nobody reads again
-    char *st = lds + (step % NS) * STAGE;
-    const int k0 = (step < nk ? step : nk - 1) * FK;
-    la.issue(ra, st, k0, p.lda, wave);
-    lb.issue(rb, st + LA::BYTES, k0, p.ldb, wave);
+  const int nk = (p.K + SUB * FK - 1) / (SUB * FK);
+  auto issue = [&](int stage) {  // steps past the end of the reduction read as zero
+    char *st = lds + (stage % NS) * STAGE;
+#pragma unroll
+    for (int u = 0; u < SUB; ++u) {
+      const int k0 = (stage * SUB + u) * FK;
+      la.issue(ra, st + u * STEP, k0, p.lda, wave);
+      lb.issue(rb, st + u * STEP + LA::BYTES, k0, p.ldb, wave);
+    }
   };
 #pragma unroll
   for (int s = 0; s < NS - 1; ++s) issue(s);
   for (int kt = 0; kt < nk; ++kt) {
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * LOADS) : "memory");  // own loads of step kt have landed
-    __builtin_amdgcn_s_barrier();  // everyone's have; everyone has read step kt - 1
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * LOADS) : "memory");  // own loads of stage kt have landed
+    __builtin_amdgcn_s_barrier();  // everyone's have; everyone has read stage kt - 1
     issue(kt + NS - 1);
-    const char *As = lds + (kt % NS) * STAGE, *Bs = As + LA::BYTES;
 #pragma unroll
-    for (int jj = 0; jj < 4 / KSPL; ++jj) {
-      const int j = KSPL > 1 ? ks : jj;
+    for (int jj = 0; jj < SUB * (4 / KSPL); ++jj) {
+      const char *As = lds + (kt % NS) * STAGE + (jj / (4 / KSPL)) * STEP, *Bs = As + LA::BYTES;
+      const int j = KSPL > 1 ? ks : jj % 4;
       f32x4 a[TM], b[TN];
 #pragma unroll
       for (int t = 0; t < TM; ++t) a[t] = LA::frag(As, wm + t * 32, j, lane);
@@ -204,9 +208,9 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const F32GemmParams p) {
 }
 
 #define TM_F32_GEMM(AKC, BKC, EPI)                                                             \
-  template __global__ void gemm_f32_kernel<128, 128, 64, 64, 1, 2, AKC, BKC, EPI>(const F32GemmParams); \
-  template __global__ void gemm_f32_kernel<64, 64, 32, 32, 1, 3, AKC, BKC, EPI>(const F32GemmParams);   \
-  template __global__ void gemm_f32_kernel<32, 32, 32, 32, 4, 4, AKC, BKC, EPI>(const F32GemmParams);
+  template __global__ void gemm_f32_kernel<128, 128, 64, 64, 1, 2, 1, AKC, BKC, EPI>(const F32GemmParams); \
+  template __global__ void gemm_f32_kernel<64, 64, 32, 32, 1, 3, 1, AKC, BKC, EPI>(const F32GemmParams);   \
+  template __global__ void gemm_f32_kernel<32, 32, 32, 32, 4, 4, 2, AKC, BKC, EPI>(const F32GemmParams);
 TM_F32_GEMM(true, true, 0)
 TM_F32_GEMM(true, false, 0)
 TM_F32_GEMM(false, false, 1)
@@ -217,7 +221,7 @@ bool gemm_f32_supported(const GemmArgs &g) {
   auto operand_ok = [&](const void *ptr, int64_t rs, int64_t cs, int64_t rows) {
     if (((uintptr_t)ptr) & 15) return false;
     if (cs == 1) return rs % 4 == 0 && g.K % 4 == 0 && rows * rs * 4 < (1LL << 31);
-    if (rs == 1) return cs % 4 == 0 && rows % 4 == 0 && g.K * cs * 4 < (1LL << 31) && (g.K + FK) * cs * 4 < (1LL << 32);
+    if (rs == 1) return cs % 4 == 0 && rows % 4 == 0 && g.K * cs * 4 < (1LL << 31) && (g.K + 2 * FK) * cs * 4 < (1LL << 32);
     return false;
   };
   if (g.M <= 0 || g.N <= 0 || g.K <= 0 || g.M > 0x3fffffff || g.N > 0x3fffffff || g.K > 0x3fffffff || g.c_mode > 2) return false;
@@ -226,7 +230,7 @@ bool gemm_f32_supported(const GemmArgs &g) {
   return g.c_mode ? (g.a_cs != 1 && g.b_cs != 1) : g.a_cs == 1;
 }
 
-template <int BM, int BN, int WM, int WN, int KSPL, int NS, bool A_KC, bool B_KC, int EPI>
+template <int BM, int BN, int WM, int WN, int KSPL, int NS, int SUB, bool A_KC, bool B_KC, int EPI>
 static int launch(const GemmArgs &g, hipStream_t s) {
   F32GemmParams p;
   p.M = (int)g.M;
@@ -244,17 +248,17 @@ static int launch(const GemmArgs &g, hipStream_t s) {
   p.a_bytes = (uint32_t)((A_KC ? g.M * g.a_rs : g.K * g.a_cs) * 4);
   p.b_bytes = (uint32_t)((B_KC ? g.N * g.b_rs : g.K * g.b_cs) * 4);
   p.c_bytes = (uint32_t)(g.M * g.ldc * 4);
-  constexpr int stages = NS * (BM + BN) * FK * 4, sums = KSPL > 1 ? 4 * 16 * 64 * 4 : 0;
+  constexpr int stages = NS * SUB * (BM + BN) * FK * 4, sums = KSPL > 1 ? 4 * 16 * 64 * 4 : 0;
   constexpr int lds = stages > sums ? stages : sums;
   static bool attr_set = false;  // per instantiation
-  if (!attr_set && hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_f32_kernel<BM, BN, WM, WN, KSPL, NS, A_KC, B_KC, EPI>),
+  if (!attr_set && hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_f32_kernel<BM, BN, WM, WN, KSPL, NS, SUB, A_KC, B_KC, EPI>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
     return fail(TM_ELAUNCH, "gemm_f32: cannot reserve %d bytes of LDS", lds);
   attr_set = true;
   const int64_t blocks = (int64_t)p.tiles_m * ceil_div(g.N, BN);
   if (blocks > 0x7fffffff) return fail(TM_ESIZE, "gemm_f32: too many tiles");
   g_last_kernel = "gemm_f32_kernel";
-  gemm_f32_kernel<BM, BN, WM, WN, KSPL, NS, A_KC, B_KC, EPI><<<(unsigned)blocks, 256, lds, s>>>(p);
+  gemm_f32_kernel<BM, BN, WM, WN, KSPL, NS, SUB, A_KC, B_KC, EPI><<<(unsigned)blocks, 256, lds, s>>>(p);
   return check_launch("gemm_f32");
 }
 
@@ -263,9 +267,9 @@ static int launch(const GemmArgs &g, hipStream_t s) {
 template <bool A_KC, bool B_KC, int EPI> static int pick(const GemmArgs &g, hipStream_t s) {
   auto cost = [&](int64_t b, double factor) { return (double)ceil_div(ceil_div(g.M, b) * ceil_div(g.N, b), (int64_t)256) * b * b * factor; };
   const double c128 = cost(128, 1.0), c64 = cost(64, 1.1), c32 = cost(32, 1.5);
-  if (c128 <= c64 && c128 <= c32) return launch<128, 128, 64, 64, 1, 2, A_KC, B_KC, EPI>(g, s);
-  if (c64 <= c32) return launch<64, 64, 32, 32, 1, 3, A_KC, B_KC, EPI>(g, s);
-  return launch<32, 32, 32, 32, 4, 4, A_KC, B_KC, EPI>(g, s);
+  if (c128 <= c64 && c128 <= c32) return launch<128, 128, 64, 64, 1, 2, 1, A_KC, B_KC, EPI>(g, s);
+  if (c64 <= c32) return launch<64, 64, 32, 32, 1, 3, 1, A_KC, B_KC, EPI>(g, s);
+  return launch<32, 32, 32, 32, 4, 4, 2, A_KC, B_KC, EPI>(g, s);
 }
 
 int gemm_f32(const GemmArgs &g, hipStream_t s) {
