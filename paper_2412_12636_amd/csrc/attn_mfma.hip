@@ -90,9 +90,9 @@ struct FlashParams {
 };
 
 // ---- global -> LDS: one tile, 16 (DP > 64) or 8 wave-wide loads a block ------------------------------
-template <int DP, bool EX, int NW> struct TileLoaderN {
+template <int DP, bool EX, int NW, int KT = TILE> struct TileLoaderN {  // KT: rows of the tile
   using F = TileFmt<DP>;
-  static constexpr int NL = F::BYTES / 1024 / NW;  // wave-wide loads per wave and tile
+  static constexpr int NL = KT * F::ROWB / 1024 / NW;  // wave-wide loads per wave and tile
   uint32_t voff[NL];
   // row_stride: elements between consecutive tile rows in global memory; d: head size
   __device__ __forceinline__ void init(int64_t row_stride, int d, int wave, int lane) {
@@ -224,28 +224,28 @@ template <int DP> struct FwdRow {
   f32x16 o[DP / 32];
   float m, l;
 };
-template <int DP, bool EX>
+template <int DP, bool EX, int KT = TILE>
 __device__ __forceinline__ void fwd_tile(const char *kt, const char *vt, const bf16x8 (&qf)[DP / 16], FwdRow<DP> &r, int j0,
                                          int q0w, int q, int hh, float sc2, uint32_t rb, uint32_t cb) {
-  f32x16 s[2];
+  f32x16 s[KT / 32];
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
+  for (int t = 0; t < KT / 32; ++t) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) s[t][v] = 0.f;
 #pragma unroll
     for (int ks = 0; ks < DP / 16; ++ks)
       s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows_at<DP>(kt, rb, t * 32, ks), qf[ks], s[t], 0, 0, 0);
   }
-  if (j0 + TILE - 1 > q0w) {  // wave-uniform
+  if (j0 + KT - 1 > q0w) {  // wave-uniform
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < KT / 32; ++t)
 #pragma unroll
       for (int v = 0; v < 16; ++v)
         if (j0 + t * 32 + acc_row(v, hh) > q) s[t][v] = -INFINITY;
   }
   float mraw = -INFINITY;
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
+  for (int t = 0; t < KT / 32; ++t)
 #pragma unroll
     for (int v = 0; v < 16; ++v) mraw = fmaxf(mraw, s[t][v]);
   float mx = fmaxf(r.m, mraw * sc2);
@@ -261,7 +261,7 @@ __device__ __forceinline__ void fwd_tile(const char *kt, const char *vt, const b
   }
   float ps = 0.f;
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
+  for (int t = 0; t < KT / 32; ++t)
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][v], sc2, -r.m));
@@ -270,7 +270,7 @@ __device__ __forceinline__ void fwd_tile(const char *kt, const char *vt, const b
     }
   r.l += ps;
 #pragma unroll
-  for (int kk = 0; kk < TILE / 16; ++kk) {
+  for (int kk = 0; kk < KT / 16; ++kk) {
     const bf16x8 pf = pack8(s[kk >> 1], 8 * (kk & 1));
     bf16x8 pr;
     if (EX) pr = pack8_rest(s[kk >> 1], pf, 8 * (kk & 1));
@@ -350,22 +350,33 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (DP > 64 ? 2 : 4) : 1) void flas
 // and take the even and the odd key tiles, each with its own maximum, row sum and accumulators; at the end the odd
 // side's state goes through LDS and the even side merges it (o = o1 2^(m1-m) + o2 2^(m2-m), the row sum alike).
 // Half as many steps, and the two waves of a SIMD overlap each other's softmax and MFMA phases.
-template <int DP, bool EX>
-__global__ __launch_bounds__(512, DP > 64 ? 1 : 4) void flash_fwd_split_kernel(const FlashParams p) {
+// NPAR = 4: blocks of 64 query rows, each group of 32 walked by four waves that take every fourth tile (of 32 keys for the
+// wide head sizes, so that two stages of four tiles fit the LDS): a quarter of the steps, twice the blocks, for grids whose
+// blocks of 128 leave units idle (2048 positions, 4 heads of 128: 38.7 -> 31.4 us; where the line lies: fwd_ways).
+template <int DP, bool EX, int NPAR> struct SplitFmt {
+  static constexpr int NG = 8 / NPAR, QB = 32 * NG, KT = NPAR == 4 && DP > 64 ? 32 : TILE;
+  static constexpr int TB = KT * TileFmt<DP>::ROWB, STATE = ((DP / 32) * 16 + 2) * 64;  // floats of a wave's state
+  static constexpr int TILES = 2 * NPAR * 2 * TB, LDS = TILES;
+  static_assert(NG * (NPAR - 1) * STATE * 4 <= TILES, "the states fit where the tiles were");
+};
+template <int DP, bool EX, int NPAR>
+__global__ __launch_bounds__(512, DP > 64 ? 1 : NPAR == 2 ? 4 : 2) void flash_fwd_split_kernel(const FlashParams p) {
   extern __shared__ __align__(1024) char smem[];  // [stage][parity][K, V] tiles
+  using S = SplitFmt<DP, EX, NPAR>;
+  constexpr int KT = S::KT, QB = S::QB, NG = S::NG;
   const int qt = gridDim.z - 1 - blockIdx.z, g = blockIdx.x, n = blockIdx.y;  // heads fastest, longest walks first
   const int kap = g / (p.nq / p.nkv), hd = EX ? p.d : DP;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int qg = wave & 3, par = wave >> 2;
+  const int qg = wave % NG, par = wave / NG;
   const int l32 = lane & 31, hh = lane >> 5;
-  const int q0w = qt * 128 + qg * 32;
+  const int q0w = qt * QB + qg * 32;
   const int q = q0w + l32;
   const int64_t tstride = (int64_t)p.batch * p.row;
   const int koff = p.nq * hd + kap * hd, voff = (p.nq + p.nkv) * hd + kap * hd;
   const rsrc_t rs = make_rsrc(p.qkv, p.qkv_bytes);
-  TileLoaderN<DP, EX, 8> ld;
+  TileLoaderN<DP, EX, 8, KT> ld;
   ld.init(tstride, hd, wave, lane);
-  auto tile = [&](int stage, int parity, int which) { return smem + ((stage * 2 + parity) * 2 + which) * TileFmt<DP>::BYTES; };
+  auto tile = [&](int stage, int parity, int which) { return smem + ((stage * NPAR + parity) * 2 + which) * S::TB; };
 
   bf16x8 qf[DP / 16];
   load_row_frags<DP, EX>(p.qkv + (int64_t)n * p.row + (int64_t)q * tstride + g * hd, q < p.seq, hd, hh, qf);
@@ -380,14 +391,14 @@ __global__ __launch_bounds__(512, DP > 64 ? 1 : 4) void flash_fwd_split_kernel(c
   const float sc2 = p.scale * kLog2e;
   const uint32_t rb = rows_base<DP>(lane), cb = cols_base<DP>(lane);
 
-  const int kv_end = (qt * 128 + 128 < p.seq) ? qt * 128 + 128 : p.seq;
-  const int ntile = (kv_end + TILE - 1) / TILE, nstep = (ntile + 1) / 2;
-  auto issue_step = [&](int step, int stage) {  // both parities' tiles; a tile past the walk's end is not fetched
+  const int kv_end = (qt * QB + QB < p.seq) ? qt * QB + QB : p.seq;
+  const int ntile = (kv_end + KT - 1) / KT, nstep = (ntile + NPAR - 1) / NPAR;
+  auto issue_step = [&](int step, int stage) {  // all parities' tiles; a tile past the walk's end is not fetched
 #pragma unroll
-    for (int parity = 0; parity < 2; ++parity) {
-      const int jt = 2 * step + parity;
+    for (int parity = 0; parity < NPAR; ++parity) {
+      const int jt = NPAR * step + parity;
       if (jt < ntile) {
-        const int64_t r0 = (int64_t)jt * TILE * tstride;
+        const int64_t r0 = (int64_t)jt * KT * tstride;
         ld.issue(rs, tile(stage, parity, 0), r0, (int64_t)n * p.row + koff, wave);
         ld.issue(rs, tile(stage, parity, 1), r0, (int64_t)n * p.row + voff, wave);
       }
@@ -399,32 +410,37 @@ __global__ __launch_bounds__(512, DP > 64 ? 1 : 4) void flash_fwd_split_kernel(c
     wait_loads();
     __builtin_amdgcn_s_barrier();  // this step's tiles are in LDS; everyone is done with the other stage
     if (step + 1 < nstep) issue_step(step + 1, cur ^ 1);
-    const int jt = 2 * step + par, j0 = jt * TILE;
+    const int jt = NPAR * step + par, j0 = jt * KT;
     if (jt >= ntile || j0 > q0w + 31) continue;
-    fwd_tile<DP, EX>(tile(cur, par, 0), tile(cur, par, 1), qf, r, j0, q0w, q, hh, sc2, rb, cb);
+    fwd_tile<DP, EX, KT>(tile(cur, par, 0), tile(cur, par, 1), qf, r, j0, q0w, q, hh, sc2, rb, cb);
   }
   wait_loads();
-  __syncthreads();  // the tiles are no longer needed: the odd side's state goes where they were
-  float *xch = reinterpret_cast<float *>(smem) + (size_t)qg * ((DP / 32) * 16 + 2) * 64;  // [qg][o..., m, l][lane]
-  if (par == 1) {
+  __syncthreads();  // the tiles are no longer needed: the other sides' states go where they were
+  float *xch = reinterpret_cast<float *>(smem);  // [qg][parity - 1][o..., m, l][lane]
+  if (par > 0) {
+    float *x = xch + (size_t)(qg * (NPAR - 1) + par - 1) * S::STATE;
 #pragma unroll
     for (int dt = 0; dt < DP / 32; ++dt)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) xch[(dt * 16 + v) * 64 + lane] = r.o[dt][v];
-    xch[(DP / 32) * 16 * 64 + lane] = r.m;
-    xch[((DP / 32) * 16 + 1) * 64 + lane] = r.l;
+      for (int v = 0; v < 16; ++v) x[(dt * 16 + v) * 64 + lane] = r.o[dt][v];
+    x[(DP / 32) * 16 * 64 + lane] = r.m;
+    x[((DP / 32) * 16 + 1) * 64 + lane] = r.l;
   }
   __syncthreads();
   if (par == 0) {
-    const float m2 = xch[(DP / 32) * 16 * 64 + lane], l2 = xch[((DP / 32) * 16 + 1) * 64 + lane];
-    const float mm = fmaxf(r.m, m2);  // r.m is finite: the even side always has key tile 0
-    const float a1 = __builtin_amdgcn_exp2f(r.m - mm), a2 = __builtin_amdgcn_exp2f(m2 - mm);
-    r.m = mm;
-    r.l = r.l * a1 + l2 * a2;
 #pragma unroll
-    for (int dt = 0; dt < DP / 32; ++dt)
+    for (int o = 0; o < NPAR - 1; ++o) {
+      const float *x = xch + (size_t)(qg * (NPAR - 1) + o) * S::STATE;
+      const float m2 = x[(DP / 32) * 16 * 64 + lane], l2 = x[((DP / 32) * 16 + 1) * 64 + lane];
+      const float mm = fmaxf(r.m, m2);  // r.m is finite: this side always has key tile 0
+      const float a1 = __builtin_amdgcn_exp2f(r.m - mm), a2 = __builtin_amdgcn_exp2f(m2 - mm);
+      r.m = mm;
+      r.l = r.l * a1 + l2 * a2;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) r.o[dt][v] = r.o[dt][v] * a1 + xch[(dt * 16 + v) * 64 + lane] * a2;
+      for (int dt = 0; dt < DP / 32; ++dt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) r.o[dt][v] = r.o[dt][v] * a1 + x[(dt * 16 + v) * 64 + lane] * a2;
+    }
     fwd_finish<DP, EX>(p, r, q, n, g, hh);
   }
 }
@@ -475,13 +491,16 @@ __device__ __forceinline__ void dq_tile(const char *kt, const char *vt, const bf
 
 // block = 128 query rows (tile qt) of one (batch entry, query head), four waves; lds: [stage][K, V] tiles, 64 KB.
 // In a block of eight waves the other four only keep the barrier count (one barrier per key tile).
-template <int DP, bool EX, int NW>
+// NPAR = 2: eight waves, waves w and w + 4 share query rows and take the even and the odd key tiles ([stage][parity]
+// tiles, twice the LDS); their sums meet through LDS, first side + second side.
+template <int DP, bool EX, int NW, int NPAR = 1>
 __device__ __forceinline__ void dq_block(const FlashParams &p, char *lds_base, int qt, int g, int n) {
-  char (*lds)[2][TileFmt<DP>::BYTES] = reinterpret_cast<char (*)[2][TileFmt<DP>::BYTES]>(lds_base);
+  auto tile = [&](int stage, int parity, int which) { return lds_base + ((stage * NPAR + parity) * 2 + which) * TileFmt<DP>::BYTES; };
   constexpr int QB = 32 * NW;  // query rows of the block (NW = 8: see the forward kernel)
   const int kap = g / (p.nq / p.nkv), hd = EX ? p.d : DP;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (wave >= NW) {
+  const int lane = threadIdx.x & 63, wave_id = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = NPAR == 1 ? wave_id : wave_id % NW, par = NPAR == 1 ? 0 : wave_id / NW;
+  if (NPAR == 1 && wave >= NW) {
     const int kv_end_x = (qt * QB + QB < p.seq) ? qt * QB + QB : p.seq;
     const int ntile_x = (kv_end_x + TILE - 1) / TILE;
     for (int jt = 0; jt < ntile_x; ++jt) __builtin_amdgcn_s_barrier();
@@ -495,8 +514,8 @@ __device__ __forceinline__ void dq_block(const FlashParams &p, char *lds_base, i
   const int koff = p.nq * hd + kap * hd, voff = (p.nq + p.nkv) * hd + kap * hd;
   const int64_t cstride = (int64_t)p.batch * p.nq * hd;
   const rsrc_t rs = make_rsrc(p.qkv, p.qkv_bytes);
-  TileLoaderN<DP, EX, NW> ld;
-  ld.init(tstride, hd, wave, lane);
+  TileLoaderN<DP, EX, NW * NPAR> ld;
+  ld.init(tstride, hd, wave_id, lane);
 
   bf16x8 qf[DP / 16], dof[DP / 16];
   load_row_frags<DP, EX>(p.qkv + (int64_t)n * p.row + (int64_t)q * tstride + g * hd, qvalid, hd, hh, qf);
@@ -515,21 +534,44 @@ __device__ __forceinline__ void dq_block(const FlashParams &p, char *lds_base, i
 
   const int kv_end = (qt * QB + QB < p.seq) ? qt * QB + QB : p.seq;
   const int ntile = (kv_end + TILE - 1) / TILE;
-  ld.issue(rs, lds[0][0], 0, (int64_t)n * p.row + koff, wave);
-  ld.issue(rs, lds[0][1], 0, (int64_t)n * p.row + voff, wave);
-  for (int jt = 0; jt < ntile; ++jt) {
-    const int j0 = jt * TILE, cur = jt & 1;
+  auto issue_step = [&](int step, int stage) {
+#pragma unroll
+    for (int parity = 0; parity < NPAR; ++parity) {
+      const int jt = NPAR * step + parity;
+      if (NPAR == 1 || jt < ntile) {
+        const int64_t r0 = (int64_t)jt * TILE * tstride;
+        ld.issue(rs, tile(stage, parity, 0), r0, (int64_t)n * p.row + koff, wave_id);
+        ld.issue(rs, tile(stage, parity, 1), r0, (int64_t)n * p.row + voff, wave_id);
+      }
+    }
+  };
+  const int nstep = (ntile + NPAR - 1) / NPAR;
+  issue_step(0, 0);
+  for (int step = 0; step < nstep; ++step) {
+    const int jt = NPAR * step + par, j0 = jt * TILE, cur = step & 1;
     wait_loads();
     __builtin_amdgcn_s_barrier();
-    if (jt + 1 < ntile) {
-      const int64_t r0 = (int64_t)(j0 + TILE) * tstride;
-      ld.issue(rs, lds[cur ^ 1][0], r0, (int64_t)n * p.row + koff, wave);
-      ld.issue(rs, lds[cur ^ 1][1], r0, (int64_t)n * p.row + voff, wave);
-    }
-    if (j0 > q0w + 31) continue;
-    dq_tile<DP, EX>(lds[cur][0], lds[cur][1], qf, dof, acc, lse2, dq_d, j0, q0w, q, hh, sc2, rb, cb);
+    if (step + 1 < nstep) issue_step(step + 1, cur ^ 1);
+    if ((NPAR > 1 && jt >= ntile) || j0 > q0w + 31) continue;
+    dq_tile<DP, EX>(tile(cur, par, 0), tile(cur, par, 1), qf, dof, acc, lse2, dq_d, j0, q0w, q, hh, sc2, rb, cb);
   }
   wait_loads();
+  if constexpr (NPAR == 2) {
+    float *xch = reinterpret_cast<float *>(lds_base) + (size_t)wave * (DP / 32) * 16 * 64;  // [wave][dt][v][lane]
+    __syncthreads();
+    if (par == 1) {
+#pragma unroll
+      for (int dt = 0; dt < DP / 32; ++dt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) xch[(dt * 16 + v) * 64 + lane] = acc[dt][v];
+    }
+    __syncthreads();
+    if (par == 1) return;
+#pragma unroll
+    for (int dt = 0; dt < DP / 32; ++dt)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[dt][v] += xch[(dt * 16 + v) * 64 + lane];
+  }
   if (qvalid) store_transposed<DP, EX>(acc, p.scale, p.dqkv + ((int64_t)q * p.batch + n) * p.row + g * hd, hd, hh);
 }
 template <int DP, bool EX, int NW>
@@ -547,13 +589,16 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (DP > 64 ? 2 : 3) : 1) void flas
 // result is the gradient.  Grouped heads: it is that head's fp32 partial.
 // =================================================================================================
 // smem: [stage][Q, dO] tiles, then [stage][lse, D] rows of floats, then the V fragments (kDkvLds bytes)
-template <int DP, int NKR = 4> constexpr int kDkvLds = 4 * TileFmt<DP>::BYTES + 2 * 2 * TILE * (int)sizeof(float) + 32 * NKR * DP * 2;
-// NKR: 32-key-row groups of the block, two waves each
-template <int DP, bool EX, int NKR = 4>
+template <int DP, int NKR = 4, int NPAR = 1>
+constexpr int kDkvLds = NPAR * (4 * TileFmt<DP>::BYTES + 2 * 2 * TILE * (int)sizeof(float)) + 32 * NKR * DP * 2;
+// NKR: 32-key-row groups of the block, two waves each; NPAR = 2: four waves each, which share the walk as even and odd
+// query tiles ([stage][parity] tiles and statistics, twice the LDS)
+template <int DP, bool EX, int NKR = 4, int NPAR = 1>
 __device__ __forceinline__ void dkv_block(const FlashParams &p, char *smem, int kt, int g, int n) {
   const int group = p.nq / p.nkv, kap = g / group, hd = EX ? p.d : DP;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int kr = wave % NKR, t = wave / NKR;  // key-row group, query half
+  const int kr = wave % NKR, t = NPAR == 1 ? wave / NKR : (wave / NKR) & 1;  // key-row group, query half
+  const int par = NPAR == 1 ? 0 : wave / (2 * NKR);                          // even or odd query tiles
   const int l32 = lane & 31, hh = lane >> 5;
   const int j0w = kt * (32 * NKR) + kr * 32;
   const int j = j0w + l32;
@@ -562,19 +607,19 @@ __device__ __forceinline__ void dkv_block(const FlashParams &p, char *smem, int 
   const int koff = p.nq * hd + kap * hd, voff = (p.nq + p.nkv) * hd + kap * hd;
   const int64_t cstride = (int64_t)p.batch * p.nq * hd;
   const rsrc_t rq = make_rsrc(p.qkv, p.qkv_bytes), rdo = make_rsrc(p.dctx, p.ctx_bytes);
-  TileLoaderN<DP, EX, 2 * NKR> lq, ldo;
+  TileLoaderN<DP, EX, 2 * NKR * NPAR> lq, ldo;
   lq.init(tstride, hd, wave, lane);
   ldo.init(cstride, hd, wave, lane);
-  auto tile = [&](int stage, int which) { return smem + (stage * 2 + which) * TileFmt<DP>::BYTES; };
-  float *stats = reinterpret_cast<float *>(smem + 4 * TileFmt<DP>::BYTES);  // [stage][2][TILE]
+  auto tile = [&](int stage, int parity, int which) { return smem + ((stage * NPAR + parity) * 2 + which) * TileFmt<DP>::BYTES; };
+  float *stats = reinterpret_cast<float *>(smem + NPAR * 4 * TileFmt<DP>::BYTES);  // [stage][parity][2][TILE]
 
   // The wave's K fragments stay in registers; its V fragments live in LDS ([key-row group][slice][lane], 16 bytes
   // each: 32 KB a block, written once by the first query half) and are read again at every use, which keeps the
   // kernel inside 256 registers without spills.
   bf16x8 kf[DP / 16];
   load_row_frags<DP, EX>(p.qkv + (int64_t)n * p.row + (int64_t)j * tstride + koff, jvalid, hd, hh, kf);
-  char *vl = smem + 4 * TileFmt<DP>::BYTES + 2 * 2 * TILE * (int)sizeof(float) + (kr * (DP / 16) * 64 + lane) * 16;
-  if (t == 0) {
+  char *vl = smem + NPAR * (4 * TileFmt<DP>::BYTES + 2 * 2 * TILE * (int)sizeof(float)) + (kr * (DP / 16) * 64 + lane) * 16;
+  if (t == 0 && par == 0) {
     bf16x8 vf[DP / 16];
     load_row_frags<DP, EX>(p.qkv + (int64_t)n * p.row + (int64_t)j * tstride + voff, jvalid, hd, hh, vf);
 #pragma unroll
@@ -595,32 +640,40 @@ __device__ __forceinline__ void dkv_block(const FlashParams &p, char *smem, int 
   // the query tiles of this head, double buffered; the row statistics of a step are fetched into registers one
   // step ahead by the first wave and put into LDS just before the barrier that publishes the step's tiles
   float st_lse = 0.f, st_d = 0.f;
+  const int st_par = NPAR == 1 ? 0 : threadIdx.x / TILE, st_row = NPAR == 1 ? threadIdx.x : threadIdx.x % TILE;
   auto issue_step = [&](int step, int stage) {
-    const int i0 = (it_begin + step) * TILE;
-    lq.issue(rq, tile(stage, 0), (int64_t)i0 * tstride, (int64_t)n * p.row + g * hd, wave);
-    ldo.issue(rdo, tile(stage, 1), (int64_t)i0 * cstride, (int64_t)n * p.nq * hd + g * hd, wave);
-    if (threadIdx.x < TILE) {
-      const int i = i0 + threadIdx.x;
+#pragma unroll
+    for (int parity = 0; parity < NPAR; ++parity) {
+      const int it = NPAR * step + parity, i0 = (it_begin + it) * TILE;
+      if (NPAR == 1 || it < total) {
+        lq.issue(rq, tile(stage, parity, 0), (int64_t)i0 * tstride, (int64_t)n * p.row + g * hd, wave);
+        ldo.issue(rdo, tile(stage, parity, 1), (int64_t)i0 * cstride, (int64_t)n * p.nq * hd + g * hd, wave);
+      }
+    }
+    if (threadIdx.x < NPAR * TILE) {
+      const int i = (it_begin + NPAR * step + st_par) * TILE + st_row;
       const int64_t sidx = ((int64_t)n * p.nq + g) * p.seq + i;
       st_lse = i < p.seq ? p.lse_in[sidx] * kLog2e : 0.f;
       st_d = i < p.seq ? p.dvec[sidx] : 0.f;
     }
   };
+  const int nstep = (total + NPAR - 1) / NPAR;
   issue_step(0, 0);
-  for (int step = 0; step < total; ++step) {
-    const int cur = step & 1;
-    const int i0 = (it_begin + step) * TILE;
+  for (int step = 0; step < nstep; ++step) {
+    const int cur = step & 1, it = NPAR * step + par;
+    const int i0 = (it_begin + it) * TILE;
     wait_loads();
-    if (threadIdx.x < TILE) {
-      float *st = stats + cur * 2 * TILE;
-      st[threadIdx.x] = st_lse;
-      st[TILE + threadIdx.x] = st_d;
+    if (threadIdx.x < NPAR * TILE) {
+      float *st = stats + (cur * NPAR + st_par) * 2 * TILE;
+      st[st_row] = st_lse;
+      st[TILE + st_row] = st_d;
     }
     __syncthreads();  // tiles and statistics of this step are visible; the other stage is free
-    if (step + 1 < total) issue_step(step + 1, cur ^ 1);
+    if (step + 1 < nstep) issue_step(step + 1, cur ^ 1);
+    if (NPAR > 1 && it >= total) continue;
     if (i0 + t * 32 + 31 < j0w) continue;  // every query of this wave's half lies before every key row of the wave
-    const char *qt = tile(cur, 0), *dot = tile(cur, 1);
-    const float *lse_s = stats + cur * 2 * TILE, *dv_s = lse_s + TILE;
+    const char *qt = tile(cur, par, 0), *dot = tile(cur, par, 1);
+    const float *lse_s = stats + (cur * NPAR + par) * 2 * TILE, *dv_s = lse_s + TILE;
 
     const bool diag = i0 + t * 32 < j0w + 31;  // some query index may be below some key index
     f32x16 s, dp;
@@ -668,30 +721,36 @@ __device__ __forceinline__ void dkv_block(const FlashParams &p, char *smem, int 
     }
   }
   wait_loads();
-  // the second query half hands its sums to the first through LDS (the tiles are no longer needed): dK, then dV
-  float *xch = reinterpret_cast<float *>(smem) + (size_t)kr * (DP / 32) * 16 * 64;  // [kr][dt][v][lane]
+  // the other query halves (and parities) hand their sums to the first through LDS (the tiles are no longer needed), dK,
+  // then dV: added in the order first half, second half, the odd tiles' halves
+  constexpr int NSIDE = 2 * NPAR;
+  const int side = par * 2 + t;
+  float *xch = reinterpret_cast<float *>(smem) + (size_t)kr * (NSIDE - 1) * (DP / 32) * 16 * 64;  // [kr][side - 1][dt][v][lane]
 #pragma unroll
   for (int which = 0; which < 2; ++which) {
     __syncthreads();
-    if (t == 1) {
+    if (side > 0) {
+      float *x = xch + (size_t)(side - 1) * (DP / 32) * 16 * 64;
 #pragma unroll
       for (int dt = 0; dt < DP / 32; ++dt)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) xch[(dt * 16 + v) * 64 + lane] = which == 0 ? dk[dt][v] : dv[dt][v];
+        for (int v = 0; v < 16; ++v) x[(dt * 16 + v) * 64 + lane] = which == 0 ? dk[dt][v] : dv[dt][v];
     }
     __syncthreads();
-    if (t == 0) {
+    if (side == 0) {
 #pragma unroll
-      for (int dt = 0; dt < DP / 32; ++dt)
+      for (int o = 0; o < NSIDE - 1; ++o)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const float other = xch[(dt * 16 + v) * 64 + lane];
-          if (which == 0) dk[dt][v] += other;
-          else dv[dt][v] += other;
-        }
+        for (int dt = 0; dt < DP / 32; ++dt)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            const float other = xch[((size_t)o * (DP / 32) * 16 + dt * 16 + v) * 64 + lane];
+            if (which == 0) dk[dt][v] += other;
+            else dv[dt][v] += other;
+          }
     }
   }
-  if (jvalid && t == 0) {
+  if (jvalid && side == 0) {
     if (p.part) {
       float *out = p.part + (((int64_t)n * p.nq + g) * p.seq + j) * (2 * hd);
       store_transposed_f32<DP, EX>(dk, p.scale, out, hd, hh);
@@ -739,10 +798,27 @@ __global__ __launch_bounds__(256, 3) void flash_bwd_narrow_kernel(const FlashPar
   }
 }
 
+// The backward pass for grids that leave units idle even as a single launch (the line: bwd_form): every walk is shared by two sets of waves that take
+// alternate tiles (dK/dV blocks of 64 key rows, dQ blocks of 128 query rows, eight waves each, one block a unit), which
+// halves the longest chain of tile steps: what bounds the single launch is the chain of key tile 0's walk, about 2 us a step
+// for 1 us of MFMAs.  Dispatch order as above.  (2048 positions, 4 heads of 128: 68 -> 50 us.)
+template <int DP, bool EX>
+__global__ __launch_bounds__(512, 1) void flash_bwd_split_kernel(const FlashParams p) {
+  extern __shared__ __align__(1024) char smem[];
+  const int rank = blockIdx.z / 3, kind = blockIdx.z % 3, tiles = gridDim.z / 3, g = blockIdx.x, n = blockIdx.y;
+  if (kind == 2) {
+    dq_block<DP, EX, 4, 2>(p, smem, tiles - 1 - rank, g, n);
+  } else if ((2 * rank + kind) * 64 < p.seq) {
+    dkv_block<DP, EX, 2, 2>(p, smem, 2 * rank + kind, g, n);
+  }
+}
+
 // Every kernel of a family by name, ahead of the host code that takes its address.
 #define TM_FLASH_FAMILY(DP, EX)                                                \
   template __global__ void flash_fwd_kernel<DP, EX, 4>(const FlashParams);     \
-  template __global__ void flash_fwd_split_kernel<DP, EX>(const FlashParams);  \
+  template __global__ void flash_fwd_split_kernel<DP, EX, 2>(const FlashParams);  \
+  template __global__ void flash_fwd_split_kernel<DP, EX, 4>(const FlashParams);  \
+  template __global__ void flash_bwd_split_kernel<DP, EX>(const FlashParams);  \
   template __global__ void flash_bwd_dq_kernel<DP, EX, 4>(const FlashParams);  \
   template __global__ void flash_bwd_dkv_kernel<DP, EX>(const FlashParams);    \
   template __global__ void flash_bwd_both_kernel<DP, EX>(const FlashParams);
@@ -751,7 +827,9 @@ template __global__ void flash_fwd_kernel<128, false, 8>(const FlashParams);
 template __global__ void flash_bwd_dq_kernel<128, false, 8>(const FlashParams);
 #define TM_FLASH_NARROW(DP)                                                    \
   template __global__ void flash_fwd_kernel<DP, true, 4>(const FlashParams);     \
-  template __global__ void flash_fwd_split_kernel<DP, true>(const FlashParams);  \
+  template __global__ void flash_fwd_split_kernel<DP, true, 2>(const FlashParams);  \
+  template __global__ void flash_fwd_split_kernel<DP, true, 4>(const FlashParams);  \
+  template __global__ void flash_bwd_split_kernel<DP, true>(const FlashParams);  \
   template __global__ void flash_bwd_narrow_kernel<DP, true>(const FlashParams);
 TM_FLASH_NARROW(32)
 TM_FLASH_NARROW(64)
@@ -805,13 +883,7 @@ static FlashParams make_params(int64_t seq, int64_t batch, int64_t nq, int64_t n
   return p;
 }
 
-// The eight-wave forward kernel that splits a query block's key tiles between two waves serves grids that leave
-// compute units without a second block (at most one block per unit; two for head sizes up to 64, of which two blocks of
-// eight waves fit a unit).  TM_ATTN_SPLIT=0 / 1 in the environment forces the choice (tuning and test aid).  (The same
-// form of the dQ kernel was faster alone and slower inside the backward pass, where its 128 KB blocks wait for LDS beside
-// the weight-gradient products of the other stream: not kept.)
-static bool use_split(dim3 grid, int blocks_per_unit) {
-  if (const char *e = getenv("TM_ATTN_SPLIT")) return e[0] == '1';
+static int unit_count() {
   static int units = 0;
   if (!units) {
     int dev = 0;
@@ -819,31 +891,43 @@ static bool use_split(dim3 grid, int blocks_per_unit) {
         units <= 0)
       units = 256;
   }
-  return (int64_t)grid.x * grid.y * grid.z <= (int64_t)units * blocks_per_unit;
+  return units;
+}
+
+// Sets of waves among which the forward kernel shares a walk: four, in blocks of 64 query rows, where every such block has
+// a unit to itself, or, with walks of 1024 positions and more, half of the units a second one after the first; two, in
+// blocks of 128, where the grid leaves compute units without a second block (at most one block per unit; two for head sizes
+// up to 64, of which two blocks of eight waves fit a unit); else one.  A sequence of one block has nothing to share four
+// ways.  Measured, one / two / four sets: 2048 positions, 8 heads of 128 (256 blocks) 46.8 / 39.3 / 32.4 us, 12 heads (384)
+// 51.0 / 42.4 / 34.8, 4096 and 8 (512) 87.5 / 71.4 / 63.0; heads of 64: 1024 x 2 and 16 heads (512) 26.6 / 20.9 / 18.8, but
+// 512 x 4 and 16 (512) 16.8 / 14.4 / 15.0, 1500 x 2 and 16 (768) 38.5 / 31.1 / 32.8.
+// TM_ATTN_SPLIT=0 / 1 / 2 in the environment forces 1 / 2 / 4 (tuning and test aid).
+static int fwd_ways(const FlashParams &p, dim3 grid, int blocks_per_unit) {
+  if (const char *e = getenv("TM_ATTN_SPLIT")) return e[0] == '2' ? 4 : e[0] == '1' ? 2 : 1;
+  const int64_t deep = (int64_t)p.nq * p.batch * ceil_div(p.seq, 64);
+  if (p.seq > 128 && deep <= (p.seq >= 1024 ? 2 : 1) * (int64_t)unit_count()) return 4;
+  return (int64_t)grid.x * grid.y * grid.z <= (int64_t)unit_count() * blocks_per_unit ? 2 : 1;
 }
 
 // Blocks of 256 query rows (eight waves) for the forward and dQ walks of grids that still give every compute unit two
 // such blocks.  TM_ATTN_WIDE=0 / 1 forces the choice.
 static bool use_wide(int64_t seq, int64_t batch, int64_t nq) {
   if (const char *e = getenv("TM_ATTN_WIDE")) return e[0] == '1';
-  int dev = 0, units = 0;
-  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      units <= 0)
-    units = 256;
-  return ceil_div(seq, 256) * batch * nq >= 2 * (int64_t)units;
+  return ceil_div(seq, 256) * batch * nq >= 2 * (int64_t)unit_count();
 }
 
-// One launch for both backward kernels where neither fills the chip by itself.  TM_ATTN_BWD_BOTH=0 / 1 forces the choice.
-static bool use_both(dim3 grid) {
-  if (const char *e = getenv("TM_ATTN_BWD_BOTH")) return e[0] == '1';
-  static int units = 0;
-  if (!units) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        units <= 0)
-      units = 256;
-  }
-  return (int64_t)grid.x * grid.y * grid.z <= units;
+// The backward pass as two launches (0), as one that holds both kinds of blocks where neither fills the chip by itself (1),
+// or as one of shared walks (2) where even those blocks, three per 128 positions, have a unit each, or, with walks of 1024
+// (2048) positions and more, up to 3/2 (15/8) blocks a unit.  Short walks of the narrow head sizes stay with their own kernel.
+// Measured, form 1 / 2: 2048 positions, 4 heads of 128 (192 blocks) 68.0 / 50.2 us, 8 heads (384) 69.5 / 53.6, 10 (480)
+// 72.2 / 66.2, 12 (576) 74.4 / 79.4; 1024 and 16 heads (384) 44.2 / 40.4, 20 (480) 47.2 / 47.9; 512 x 2 and 8 heads (192) 36.2 / 31.6, 16 heads (384) 32.2 / 34.0; heads of 64: 2048
+// and 8 (384) 50.6 / 41.6, 384 x 2 and 8 (144) 18.0 / 17.5, 192 x 4 and 8 (192) 15.1 / 15.7.
+// TM_ATTN_BWD_BOTH=0 / 1 / 2 forces the choice.
+static int bwd_form(const FlashParams &p, dim3 grid) {
+  if (const char *e = getenv("TM_ATTN_BWD_BOTH")) return e[0] == '2' ? 2 : e[0] == '1' ? 1 : 0;
+  const int64_t blocks = (int64_t)grid.x * grid.y * grid.z, units = unit_count();
+  if (p.seq > (p.d > 64 ? 128 : 320) && 3 * blocks <= (p.seq >= 2048 ? units * 15 / 8 : p.seq >= 1024 ? units * 3 / 2 : units)) return 2;
+  return blocks <= units ? 1 : 0;
 }
 
 static bool reserve_lds(const void *kernel, int bytes) {
@@ -851,14 +935,24 @@ static bool reserve_lds(const void *kernel, int bytes) {
 }
 
 template <int DP, bool EX> static int launch_fwd(const FlashParams &p, dim3 grid, hipStream_t s) {
-  if (use_split(grid, DP > 64 ? 1 : 2)) {
-    constexpr int lds = 8 * TileFmt<DP>::BYTES;
+  const int ways = fwd_ways(p, grid, DP > 64 ? 1 : 2);
+  if (ways == 4) {
+    using S = SplitFmt<DP, EX, 4>;
+    static_assert(S::QB == 64, "blocks of 64 query rows");
     static bool attr_set = false;  // one flag per kernel family
-    if (!attr_set && !reserve_lds(reinterpret_cast<const void *>(&flash_fwd_split_kernel<DP, EX>), lds))
+    if (!attr_set && !reserve_lds(reinterpret_cast<const void *>(&flash_fwd_split_kernel<DP, EX, 4>), S::LDS))
       return fail(TM_ELAUNCH, "flash_fwd: cannot reserve LDS");
     attr_set = true;
     g_last_kernel = "flash_fwd_split_kernel";
-    flash_fwd_split_kernel<DP, EX><<<grid, 512, lds, s>>>(p);
+    flash_fwd_split_kernel<DP, EX, 4><<<dim3(grid.x, grid.y, (unsigned)ceil_div(p.seq, 64)), 512, S::LDS, s>>>(p);
+  } else if (ways == 2) {
+    constexpr int lds = SplitFmt<DP, EX, 2>::LDS;
+    static bool attr_set = false;
+    if (!attr_set && !reserve_lds(reinterpret_cast<const void *>(&flash_fwd_split_kernel<DP, EX, 2>), lds))
+      return fail(TM_ELAUNCH, "flash_fwd: cannot reserve LDS");
+    attr_set = true;
+    g_last_kernel = "flash_fwd_split_kernel";
+    flash_fwd_split_kernel<DP, EX, 2><<<grid, 512, lds, s>>>(p);
   } else {
     g_last_kernel = "flash_fwd_kernel";
     bool wide = false;
@@ -899,17 +993,38 @@ static int reduce_heads(const FlashParams &p, hipStream_t s) {  // grouped heads
   return check_launch("flash_bwd");
 }
 
+// the split form where it applies: launched (true) or not
+template <int DP, bool EX> static bool launch_bwd_split(const FlashParams &p, dim3 gq, hipStream_t s, int *status) {
+  constexpr int dkv = kDkvLds<DP, 2, 2>, dq = 8 * TileFmt<DP>::BYTES, lds = dkv > dq ? dkv : dq;
+  static_assert(lds <= 160 * 1024 && lds >= 2 * 3 * (DP / 32) * 16 * 64 * 4, "fits, and the other sides' sums do");
+  if (3 * (int64_t)gq.z > 65535 || bwd_form(p, gq) != 2) return false;
+  static bool attr_set = false;
+  if (!attr_set && !reserve_lds(reinterpret_cast<const void *>(&flash_bwd_split_kernel<DP, EX>), lds)) {
+    *status = fail(TM_ELAUNCH, "flash_bwd: cannot reserve LDS");
+    return true;
+  }
+  attr_set = true;
+  g_last_kernel = "flash_bwd_split_kernel";
+  flash_bwd_split_kernel<DP, EX><<<dim3(gq.x, gq.y, 3 * gq.z), 512, lds, s>>>(p);
+  *status = reduce_heads(p, s);
+  return true;
+}
+
 template <int DP> static int launch_bwd_narrow(const FlashParams &p, dim3 gq, hipStream_t s) {
   constexpr int lds = kDkvLds<DP, 2>;
   static_assert(lds >= 4 * TileFmt<DP>::BYTES && lds >= 2 * (DP / 32) * 16 * 64 * 4, "the dQ block's tiles and the second half's sums fit");
   static_assert(lds <= 64 * 1024, "no LDS attribute needed");
   if (3 * (int64_t)gq.z > 65535) return fail(TM_ESIZE, "flash_bwd: sequence too long for the grid");
+  int status = TM_OK;
+  if (launch_bwd_split<DP, true>(p, gq, s, &status)) return status;
   g_last_kernel = "flash_bwd_narrow_kernel";
   flash_bwd_narrow_kernel<DP, true><<<dim3(gq.x, gq.y, 3 * gq.z), 256, lds, s>>>(p);
   return reduce_heads(p, s);
 }
 
 template <int DP, bool EX> static int launch_bwd(const FlashParams &p, dim3 gq, hipStream_t s) {
+  int status = TM_OK;
+  if (launch_bwd_split<DP, EX>(p, gq, s, &status)) return status;
   constexpr int lds = kDkvLds<DP>;
   static_assert(lds >= 4 * TileFmt<DP>::BYTES, "the dQ block's tiles fit the dK/dV block's LDS");
   static_assert(lds >= 4 * (DP / 32) * 16 * 64 * 4, "the second query half's sums fit");
@@ -919,7 +1034,7 @@ template <int DP, bool EX> static int launch_bwd(const FlashParams &p, dim3 gq, 
     return fail(TM_ELAUNCH, "flash_bwd: cannot reserve LDS");
   attr_set = true;
   g_last_kernel = "flash_bwd_dq_kernel+flash_bwd_dkv_kernel";
-  if (use_both(gq) && 2 * gq.z <= 65535) {
+  if (bwd_form(p, gq) != 0 && 2 * gq.z <= 65535) {
     g_last_kernel = "flash_bwd_both_kernel";
     flash_bwd_both_kernel<DP, EX><<<dim3(gq.x, gq.y, 2 * gq.z), 512, lds, s>>>(p);
   } else {

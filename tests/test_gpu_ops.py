@@ -527,14 +527,16 @@ def test_attention_block_forms(env, monkeypatch, split, seq, batch, nq, nkv):
     assert rel_err(got[..., A + nkv * d:], dv.reshape(seq, batch, -1)) <= tol
 
 
-@pytest.mark.parametrize("form", ["0", "1"], ids=["separate_blocks", "split_and_single_launch"])
+@pytest.mark.parametrize("form", ["0", "1", "2"], ids=["separate_blocks", "split_and_single_launch", "shared_walks"])
 @pytest.mark.parametrize("seq,batch,nq,nkv,d", [(65, 1, 2, 2, 8), (300, 2, 4, 2, 32), (129, 1, 2, 1, 40), (1, 2, 2, 1, 64),
                                                  (193, 1, 2, 2, 64), (64, 1, 4, 1, 72), (200, 2, 2, 2, 80), (130, 1, 2, 1, 96),
-                                                 (127, 1, 1, 1, 104), (257, 1, 2, 1, 120)])
+                                                 (127, 1, 1, 1, 104), (257, 1, 2, 1, 120), (1, 1, 2, 1, 128), (65, 2, 2, 2, 128),
+                                                 (300, 1, 2, 1, 128)])
 def test_attention_head_sizes_below_128(env, monkeypatch, form, seq, batch, nq, nkv, d):
-    """bf16 head sizes other than 128 on the matrix cores: every padded width (32, 64, 96, 128), head sizes with and
-    without padding columns, one position, ends of tiles, grouped heads, in every block form.  Probabilities keep 16
-    significand bits there, so a result is off by its own rounding to bf16 (2^-9 of a value) and, behind ctx, by
+    """bf16 head sizes on the matrix cores: every padded width (32, 64, 96, 128), head sizes with and without padding
+    columns, one position, ends of tiles, grouped heads, in every block form (0: a walk per block; 1: two sets of waves
+    share a forward walk, one backward launch; 2: four share a forward walk, two a backward one).  Below 128
+    probabilities keep 16 significand bits, so a result is off by its own rounding to bf16 (2^-9 of a value) and, behind ctx, by
     ctx's rounding in the row statistics of the backward pass: 2^-8 for ctx, 2^-7 for the gradients."""
     torch, tm = env
     for name in ("TM_ATTN_SPLIT", "TM_ATTN_BWD_BOTH"):
@@ -553,11 +555,12 @@ def test_attention_head_sizes_below_128(env, monkeypatch, form, seq, batch, nq, 
     tm.tm_op_attn_bwd(BF16, seq, batch, nq, nkv, d, qd, ctx, to_dev(torch, dctx, BF16), lse, scratch, dqkv, s)
     q64 = qkv.astype(np.float64)
     q, k, v = (a.reshape(seq, batch, -1, d) for a in (q64[..., :A], q64[..., A:A + B], q64[..., A + B:]))
-    assert rel_err(to_host(ctx[:seq]), so.attention_fwd(q, k, v).reshape(seq, batch, A)) <= 2.0 ** -8
+    bounds = (tol_of(BF16), tol_of(BF16)) if d == 128 else (2.0 ** -8, 2.0 ** -7)
+    assert rel_err(to_host(ctx[:seq]), so.attention_fwd(q, k, v).reshape(seq, batch, A)) <= bounds[0]
     refs = so.attention_bwd(dctx.astype(np.float64).reshape(seq, batch, nq, d), q, k, v)
     got = to_host(dqkv[:seq])
     for part, ref in zip((got[..., :A], got[..., A:A + B], got[..., A + B:]), refs):
-        assert rel_err(part, ref.reshape(seq, batch, -1)) <= 2.0 ** -7
+        assert rel_err(part, ref.reshape(seq, batch, -1)) <= bounds[1]
     assert bool((ctx[seq:] == 7.0).all()) and bool((dqkv[seq:] == 7.0).all())
 
 
