@@ -57,8 +57,10 @@ template <int DP> struct F32Loader {
 #pragma unroll
     for (int i = 0; i < F::NL; ++i) {
       const int idx = i * 64 + lane, r = idx / F::CPR, c = (idx % F::CPR) ^ F::key(r);
-      // columns past the head size: an offset that stays outside every tensor (below 2 GiB) whatever row is added
-      voff[i] = c * 4 < d ? (uint32_t)((r * row_stride + c * 4) * 4) : 0x80000000u;
+      // columns past the head size, and rows so far behind the tile's first that no tensor (below 2 GiB) holds both: an
+      // offset that stays outside, and below 2^32, whatever tile start inside the tensor is added
+      const int64_t off = (r * row_stride + c * 4) * 4;
+      voff[i] = c * 4 < d && off < 0x80000000LL ? (uint32_t)off : 0x80000000u;
     }
   }
   __device__ __forceinline__ void issue(rsrc_t rs, char *tile, int64_t row0, int64_t base) const {

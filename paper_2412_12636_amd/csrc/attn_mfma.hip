@@ -100,14 +100,16 @@ template <int DP, bool EX, int NW, int KT = TILE> struct TileLoaderN {  // KT: r
     for (int i = 0; i < NL; ++i) {
       const int idx = (i * NW + wave) * 64 + lane;  // chunk position in the LDS tile
       const int row = idx / F::CPR, c = F::unplace(idx % F::CPR, row);
-      voff[i] = (uint32_t)(((int64_t)row * row_stride + c * 8) * 2);
-      // columns past the head size: an offset that stays outside every tensor (below 2 GiB) whatever row is added
-      if (EX && c * 8 >= d) voff[i] = 0x80000000u;
+      // Columns past the head size, and rows so far behind the tile's first that no tensor (below 2 GiB) holds both: an
+      // offset that stays outside whatever tile start is added.  (Cut off at 32 bits instead, such a row's offset would come
+      // round to the tensor's front: one position of 50000 batch entries of 16 heads of 64 is 307 MB, 64 rows are 19 GB.)
+      const int64_t off = ((int64_t)row * row_stride + c * 8) * 2;
+      voff[i] = off >= 0x80000000LL || (EX && c * 8 >= d) ? 0x80000000u : (uint32_t)off;
     }
   }
-  // rows0: element offset of tile row 0 (a multiple of the row stride), base: element offset of column 0
+  // rows0: element offset of tile row 0 (a multiple of the row stride, inside the tensor), base: element offset of column 0
   // inside a row (below the row stride).  The row part travels in the per-lane offset, which the
-  // hardware checks against the buffer size, so rows past the tensor read as zero.
+  // hardware checks against the buffer size, so rows past the tensor read as zero.  The sum stays below 2^32.
   __device__ __forceinline__ void issue(rsrc_t rs, char *tile, int64_t rows0, int64_t base, int wave) const {
     const uint32_t roff = (uint32_t)(rows0 * 2), soff = (uint32_t)(base * 2);
 #pragma unroll

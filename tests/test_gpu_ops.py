@@ -593,6 +593,34 @@ def test_attention_fp32_tiles(env, seq, batch, nq, nkv, d):
     assert bool((ctx[seq:] == 7.0).all()) and bool((dqkv[seq:] == 7.0).all())
 
 
+@pytest.mark.parametrize("dtype,batch,d", [(BF16, 50000, 64), (BF16, 25000, 128), (FP32, 50000, 64)])
+def test_attention_rows_behind_a_short_sequence_read_as_zero(env, dtype, batch, d):
+    """One position of a very large batch: the other rows of the staged query tiles lie behind the tensor, some of them a
+    whole multiple of 2^32 bytes and a little more (bf16: row 42 of both tensors, 42 x 102.4 MB; fp32: row 21), and add
+    nothing to dK and dV.  With one position P = 1 and ctx = V, so dV = dO to the bit (in fp32 to the error of an
+    exponent of about 10: 1e-6 each) and dQ = dK = 0 but for the cancellation dP - D, sums of d products of 0.1: 1e-5."""
+    torch, tm = env
+    print(f"attention of one position dtype={dtype} batch={batch} d={d}", flush=True)
+    heads = 16
+    A, W = heads * d, 3 * heads * d
+    g = torch.Generator(device="cuda").manual_seed(batch + d)
+    td = torch_dtype(torch, dtype)
+    qkv = torch.randn((1, batch, W), generator=g, device="cuda").to(td)
+    dctx = (torch.randn((1, batch, A), generator=g, device="cuda") * 0.1).to(td)
+    ctx, dqkv = torch.zeros_like(dctx), torch.zeros_like(qkv)
+    lse = torch.zeros((batch, heads, 1), dtype=torch.float32, device="cuda")
+    scratch = torch.empty(tm.tm_op_attn_bwd_scratch_bytes(dtype, 1, batch, heads, heads, d), dtype=torch.uint8, device="cuda")
+    s = stream_ptr(torch)
+    tm.tm_op_attn_fwd(dtype, 1, batch, heads, heads, d, qkv, ctx, lse, s)
+    tm.tm_op_attn_bwd(dtype, 1, batch, heads, heads, d, qkv, ctx, dctx, lse, scratch, dqkv, s)
+    dq, dk, dv = dqkv[..., :A], dqkv[..., A:2 * A], dqkv[..., 2 * A:]
+    if dtype == BF16:
+        assert torch.equal(ctx, qkv[..., 2 * A:]) and torch.equal(dv, dctx)
+    else:
+        assert torch.allclose(ctx, qkv[..., 2 * A:], rtol=4e-6, atol=0) and torch.allclose(dv, dctx, rtol=4e-6, atol=0)
+    assert float(dq.abs().max()) <= 1e-5 and float(dk.abs().max()) <= 1e-5
+
+
 @pytest.mark.parametrize("both", ["0", "1"], ids=["two_launches", "one_launch"])
 @pytest.mark.parametrize("seq,batch,nq,nkv", [(700, 1, 3, 3), (300, 2, 4, 2), (64, 1, 1, 1), (1, 1, 2, 1), (129, 1, 2, 2),
                                                (193, 1, 2, 1)],
