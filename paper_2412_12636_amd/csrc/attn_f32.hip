@@ -18,6 +18,7 @@
 #include <math.h>
 
 #include "attn.h"
+#include "attn_rows.h"
 
 namespace tmk {
 
@@ -237,10 +238,12 @@ template <int DP> __global__ __launch_bounds__(256, 1) void f32_fwd_kernel(const
 #pragma unroll
       for (int v = 0; v < 16; ++v) o[dt][v] = o[dt][v] * a1 + x[(dt * 16 + v) * 64 + lane] * a2;
     l += __shfl_xor(l, 32, 64);
-    if (q < p.seq) {
+    const uint32_t redo = nonfinite_rows(nonfinite_trace(o, l * 0.f), q < p.seq);  // see attn_rows.h
+    if (q < p.seq && !((redo >> l32) & 1)) {
       f32_store<DP>(o, 1.f / l, p.ctx + ((int64_t)q * p.batch + n) * (p.nq * d) + g * d, d, hh);
       if (hh == 0) p.lse[((int64_t)n * p.nq + g) * p.seq + q] = (mm + log2f(l)) * 0.6931471805599453f;
     }
+    for (uint32_t r = redo; r; r &= r - 1) attn_row_fwd<float>(p, q0w + __builtin_ctz(r), g, n, lane);
   }
 }
 
@@ -294,7 +297,10 @@ template <int DP> __device__ __forceinline__ void f32_dq_block(const F32Params &
   }
   f32_wait_loads();
   f32_join<DP>(acc, reinterpret_cast<float *>(smem) + (size_t)grp * (DP / 2) * 64, side, lane);
-  if (side == 0 && valid) f32_store<DP>(acc, p.scale, p.dqkv + ((int64_t)q * p.batch + n) * p.row + g * d, d, hh);
+  if (side > 0) return;
+  const uint32_t redo = nonfinite_rows(nonfinite_trace(acc, 0.f), valid);  // see attn_rows.h
+  if (valid && !((redo >> l32) & 1)) f32_store<DP>(acc, p.scale, p.dqkv + ((int64_t)q * p.batch + n) * p.row + g * d, d, hh);
+  for (uint32_t r = redo; r; r &= r - 1) attn_row_dq<float>(p, q0w + __builtin_ctz(r), g, n, lane);
 }
 
 // ---- dK, dV: block = 64 key rows of one (batch entry, query head); the sides take alternate query tiles -----------
@@ -368,7 +374,9 @@ template <int DP> __device__ __forceinline__ void f32_dkv_block(const F32Params 
   float *x = reinterpret_cast<float *>(smem) + (size_t)grp * (DP / 2) * 64;
   f32_join<DP>(dk, x, side, lane);
   f32_join<DP>(dv, x, side, lane);
-  if (side == 0 && valid) {
+  if (side > 0) return;
+  const uint32_t redo = nonfinite_rows(nonfinite_trace(dk, nonfinite_trace(dv, 0.f)), valid);  // see attn_rows.h
+  if (valid && !((redo >> l32) & 1)) {
     if (p.part) {
       float *out = p.part + (((int64_t)n * p.nq + g) * p.seq + j) * (2 * d);
       f32_store<DP>(dk, p.scale, out, d, hh);
@@ -379,6 +387,7 @@ template <int DP> __device__ __forceinline__ void f32_dkv_block(const F32Params 
       f32_store<DP>(dv, 1.f, out + voff, d, hh);
     }
   }
+  for (uint32_t r = redo; r; r &= r - 1) attn_row_dkv<float>(p, j0w + __builtin_ctz(r), g, n, lane);
 }
 
 // Both halves of the backward pass in one launch: the dK/dV block of key tile r and the dQ block of query tile last - r

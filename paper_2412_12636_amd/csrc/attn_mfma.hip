@@ -29,6 +29,7 @@
 #include <stdlib.h>
 
 #include "attn.h"
+#include "attn_rows.h"
 
 namespace tmk {
 
@@ -285,14 +286,17 @@ __device__ __forceinline__ void fwd_tile(const char *kt, const char *vt, const b
   }
 }
 template <int DP, bool EX>
-__device__ __forceinline__ void fwd_finish(const FlashParams &p, FwdRow<DP> &r, int q, int n, int g, int hh) {
-  const int hd = EX ? p.d : DP;
+__device__ __forceinline__ void fwd_finish(const FlashParams &p, FwdRow<DP> &r, int q, int n, int g, int lane) {
+  const int hd = EX ? p.d : DP, hh = lane >> 5;
   r.l += __shfl_xor(r.l, 32, 64);
-  if (q < p.seq) {
+  const uint32_t redo = EX ? nonfinite_rows(nonfinite_trace(r.o, r.l * 0.f), q < p.seq) : 0u;  // see attn_rows.h
+  if (q < p.seq && !((redo >> (q & 31)) & 1)) {
     const int64_t trow = (int64_t)q * p.batch + n;
     store_transposed<DP, EX>(r.o, 1.f / r.l, p.ctx + trow * (p.nq * hd) + g * hd, hd, hh);
     if (hh == 0) p.lse[((int64_t)n * p.nq + g) * p.seq + q] = (r.m + log2f(r.l)) * 0.6931471805599453f;
   }
+  if constexpr (EX)
+    for (uint32_t m = redo; m; m &= m - 1) attn_row_fwd<bf16>(p, q - (lane & 31) + __builtin_ctz(m), g, n, lane);
 }
 
 // block = 32 NW query rows of one (batch entry, query head); wave = 32 query rows.  Four waves, two blocks per
@@ -344,7 +348,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? (DP > 64 ? 2 : 4) : 1) void flas
     fwd_tile<DP, EX>(lds[cur][0], lds[cur][1], qf, r, j0, q0w, q, hh, sc2, rb, cb);
   }
   wait_loads();
-  fwd_finish<DP, EX>(p, r, q, n, g, hh);
+  fwd_finish<DP, EX>(p, r, q, n, g, lane);
 }
 
 // The same for grids of at most one block per compute unit (short sequences, few heads), where the chain of tile
@@ -443,7 +447,7 @@ __global__ __launch_bounds__(512, DP > 64 ? 1 : NPAR == 2 ? 4 : 2) void flash_fw
 #pragma unroll
         for (int v = 0; v < 16; ++v) r.o[dt][v] = r.o[dt][v] * a1 + x[(dt * 16 + v) * 64 + lane] * a2;
     }
-    fwd_finish<DP, EX>(p, r, q, n, g, hh);
+    fwd_finish<DP, EX>(p, r, q, n, g, lane);
   }
 }
 
@@ -574,7 +578,11 @@ __device__ __forceinline__ void dq_block(const FlashParams &p, char *lds_base, i
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[dt][v] += xch[(dt * 16 + v) * 64 + lane];
   }
-  if (qvalid) store_transposed<DP, EX>(acc, p.scale, p.dqkv + ((int64_t)q * p.batch + n) * p.row + g * hd, hd, hh);
+  const uint32_t redo = EX ? nonfinite_rows(nonfinite_trace(acc, 0.f), qvalid) : 0u;  // see attn_rows.h
+  if (qvalid && !((redo >> l32) & 1))
+    store_transposed<DP, EX>(acc, p.scale, p.dqkv + ((int64_t)q * p.batch + n) * p.row + g * hd, hd, hh);
+  if constexpr (EX)
+    for (uint32_t m = redo; m; m &= m - 1) attn_row_dq<bf16>(p, q0w + __builtin_ctz(m), g, n, lane);
 }
 template <int DP, bool EX, int NW>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? (DP > 64 ? 2 : 3) : 1) void flash_bwd_dq_kernel(const FlashParams p) {
@@ -723,6 +731,8 @@ __device__ __forceinline__ void dkv_block(const FlashParams &p, char *smem, int 
     }
   }
   wait_loads();
+  // (from here on with the lane and what follows from it formed anew, which keeps them out of the loop's registers)
+  const int tl = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), tj = j0w + (tl & 31);
   // the other query halves (and parities) hand their sums to the first through LDS (the tiles are no longer needed), dK,
   // then dV: added in the order first half, second half, the odd tiles' halves
   constexpr int NSIDE = 2 * NPAR;
@@ -736,7 +746,7 @@ __device__ __forceinline__ void dkv_block(const FlashParams &p, char *smem, int 
 #pragma unroll
       for (int dt = 0; dt < DP / 32; ++dt)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) x[(dt * 16 + v) * 64 + lane] = which == 0 ? dk[dt][v] : dv[dt][v];
+        for (int v = 0; v < 16; ++v) x[(dt * 16 + v) * 64 + tl] = which == 0 ? dk[dt][v] : dv[dt][v];
     }
     __syncthreads();
     if (side == 0) {
@@ -746,23 +756,27 @@ __device__ __forceinline__ void dkv_block(const FlashParams &p, char *smem, int 
         for (int dt = 0; dt < DP / 32; ++dt)
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
-            const float other = xch[((size_t)o * (DP / 32) * 16 + dt * 16 + v) * 64 + lane];
+            const float other = xch[((size_t)o * (DP / 32) * 16 + dt * 16 + v) * 64 + tl];
             if (which == 0) dk[dt][v] += other;
             else dv[dt][v] += other;
           }
     }
   }
-  if (jvalid && side == 0) {
+  if (side > 0) return;
+  const uint32_t redo = EX ? nonfinite_rows(nonfinite_trace(dk, nonfinite_trace(dv, 0.f)), tj < p.seq) : 0u;  // see attn_rows.h
+  if (tj < p.seq && !((redo >> (tl & 31)) & 1)) {
     if (p.part) {
-      float *out = p.part + (((int64_t)n * p.nq + g) * p.seq + j) * (2 * hd);
-      store_transposed_f32<DP, EX>(dk, p.scale, out, hd, hh);
-      store_transposed_f32<DP, EX>(dv, 1.f, out + hd, hd, hh);
+      float *out = p.part + (((int64_t)n * p.nq + g) * p.seq + tj) * (2 * hd);
+      store_transposed_f32<DP, EX>(dk, p.scale, out, hd, tl >> 5);
+      store_transposed_f32<DP, EX>(dv, 1.f, out + hd, hd, tl >> 5);
     } else {
-      bf16 *out = p.dqkv + ((int64_t)j * p.batch + n) * p.row;
-      store_transposed<DP, EX>(dk, p.scale, out + koff, hd, hh);
-      store_transposed<DP, EX>(dv, 1.f, out + voff, hd, hh);
+      bf16 *out = p.dqkv + ((int64_t)tj * p.batch + n) * p.row;
+      store_transposed<DP, EX>(dk, p.scale, out + koff, hd, tl >> 5);
+      store_transposed<DP, EX>(dv, 1.f, out + voff, hd, tl >> 5);
     }
   }
+  if constexpr (EX)
+    for (uint32_t m = redo; m; m &= m - 1) attn_row_dkv<bf16>(p, j0w + __builtin_ctz(m), g, n, tl);
 }
 
 template <int DP, bool EX>

@@ -621,6 +621,74 @@ def test_attention_rows_behind_a_short_sequence_read_as_zero(env, dtype, batch, 
     assert float(dq.abs().max()) <= 1e-5 and float(dk.abs().max()) <= 1e-5
 
 
+NONFINITE_SHAPES = [(BF16, 70, 2, 2, 40), (BF16, 130, 4, 2, 64), (BF16, 200, 2, 1, 80), (BF16, 129, 2, 2, 120),
+                    (FP32, 70, 4, 2, 24), (FP32, 130, 2, 2, 64), (FP32, 100, 2, 1, 96), (FP32, 65, 1, 1, 128)]
+
+
+@pytest.mark.parametrize("form", ["0", "1", "2"], ids=["separate_blocks", "split_and_single_launch", "shared_walks"])
+@pytest.mark.parametrize("dtype,seq,nq,nkv,d", NONFINITE_SHAPES)
+def test_attention_keeps_infinities_and_nans_to_their_own_rows(env, monkeypatch, form, dtype, seq, nq, nkv, d):
+    """A position that the causal mask excludes from a row leaves the row alone, whatever it holds: an infinite V and a
+    NaN K leave the earlier rows of ctx and dQ what they are without them, an infinite dO and a NaN Q the later rows of dK
+    and dV (position 5 and the one 5 before the end, so tiles hold both kinds of rows).  Rows whose first tile of scores is
+    -Inf have the softmax of the rest.  Head size 128 in bf16 is not meant: it multiplies whole tiles.  Rows as without
+    the value: bf16 results to their rounding, 2^-8 of the largest (2^-7 behind ctx), fp32 to 2e-5."""
+    torch, tm = env
+    for name in ("TM_ATTN_SPLIT", "TM_ATTN_BWD_BOTH"):
+        monkeypatch.setenv(name, form)
+    print(f"attention with infinities form={form} dtype={dtype} seq={seq} heads={nq}/{nkv} d={d}", flush=True)
+    rng = np.random.default_rng(seq + d)
+    A, B, W, batch = nq * d, nkv * d, (nq + 2 * nkv) * d, 2
+    qkv, dctx = rand(rng, (seq, batch, W), 1.0, dtype), rand(rng, (seq, batch, A), 0.1, dtype)
+    s = stream_ptr(torch)
+
+    def run(qd, dd):
+        ctx, dqkv = torch.empty_like(dd), torch.empty_like(qd)
+        lse = torch.zeros((batch, nq, seq), dtype=torch.float32, device="cuda")
+        scratch = torch.empty(tm.tm_op_attn_bwd_scratch_bytes(dtype, seq, batch, nq, nkv, d), dtype=torch.uint8, device="cuda")
+        tm.tm_op_attn_fwd(dtype, seq, batch, nq, nkv, d, qd, ctx, lse, s)
+        tm.tm_op_attn_bwd(dtype, seq, batch, nq, nkv, d, qd, ctx, dd, lse, scratch, dqkv, s)
+        return to_host_raw(ctx), to_host_raw(dqkv)
+
+    to_host_raw = lambda t: t.detach().float().cpu().numpy()
+    clean_ctx, clean_d = run(to_dev(torch, qkv, dtype), to_dev(torch, dctx, dtype))
+    tol = 2.0 ** -7 if dtype == BF16 else 2e-5
+
+    def same(a, b):
+        assert np.isfinite(a).all() and np.abs(a - b).max() <= tol * np.abs(b).max()
+
+    late, early, inf = seq - 5, 5, float("inf")
+    qd, dd = to_dev(torch, qkv, dtype), to_dev(torch, dctx, dtype)
+    qd[late, 1, A + B] = inf                             # V of kv head 0, entry 1
+    qd[late, 1, A] = float("nan")                        # its K
+    ctx, dqkv = run(qd, dd)
+    same(ctx[:late], clean_ctx[:late])
+    same(dqkv[:late, :, :A], clean_d[:late, :, :A])
+    same(ctx[:, 0], clean_ctx[:, 0])
+    assert np.isnan(ctx[late:, 1, :d]).all()             # the rows that attend to it
+
+    qd, dd = to_dev(torch, qkv, dtype), to_dev(torch, dctx, dtype)
+    qd[early, 0, 0] = float("nan")
+    dd[early, 0, 1] = inf
+    ctx, dqkv = run(qd, dd)
+    rows = np.arange(seq) != early
+    same(ctx[rows], clean_ctx[rows])
+    same(dqkv[rows][..., :A], clean_d[rows][..., :A])
+    same(dqkv[early + 1:, :, A:], clean_d[early + 1:, :, A:])
+    same(dqkv[:, 1], clean_d[:, 1])
+    assert np.isnan(dqkv[:early + 1, 0, A:A + d]).all()
+
+    qd = to_dev(torch, qkv, dtype)
+    half = seq // 2
+    qd[:, :, 0:A:d] = 1.0
+    qd[:half, :, A:A + B:d] = -inf                       # the first half's scores are -Inf, and with them whole tiles
+    ctx, _ = run(qd, to_dev(torch, dctx, dtype))
+    q64 = qd.float().cpu().numpy().astype(np.float64)[half:]
+    q, k, v = (a.reshape(seq - half, batch, -1, d) for a in (q64[..., :A], q64[..., A:A + B], q64[..., A + B:]))
+    same(ctx[half:], so.attention_fwd(q, k, v).reshape(seq - half, batch, A))
+    assert np.isnan(ctx[:half]).all()
+
+
 @pytest.mark.parametrize("both", ["0", "1"], ids=["two_launches", "one_launch"])
 @pytest.mark.parametrize("seq,batch,nq,nkv", [(700, 1, 3, 3), (300, 2, 4, 2), (64, 1, 1, 1), (1, 1, 2, 1), (129, 1, 2, 2),
                                                (193, 1, 2, 1)],
