@@ -731,8 +731,10 @@ __device__ __forceinline__ void dkv_block(const FlashParams &p, char *smem, int 
     }
   }
   wait_loads();
-  // (from here on with the lane and what follows from it formed anew, which keeps them out of the loop's registers)
-  const int tl = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), tj = j0w + (tl & 31);
+  // (EX: from here on with the lane and what follows from it formed anew, which keeps them out of the loop's registers; for
+  // head size 128 in bf16 the same costs four spilled ones, 4 % of its backward pass)
+  const int tl = EX ? (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) : lane;
+  const int tj = EX ? j0w + (tl & 31) : j;
   // the other query halves (and parities) hand their sums to the first through LDS (the tiles are no longer needed), dK,
   // then dV: added in the order first half, second half, the odd tiles' halves
   constexpr int NSIDE = 2 * NPAR;
