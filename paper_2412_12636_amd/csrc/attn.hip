@@ -17,11 +17,36 @@ static int check_attn(const char *what, int dtype, int64_t seq, int64_t batch, i
   return TM_OK;
 }
 
+// Very short sequences of many (entry, query head) walks stay with the kernels of one row per wave (but for bf16 with head
+// size 128, which has no other kernel): a tile holds 32 or 64 positions, and what such a walk costs in tiles depends on their
+// number, 1 for any of these lengths.  Up to how many positions that is the faster way, from both kernels' times at 1 to 24
+// positions, 8 to 16384 walks, head sizes 8 to 128 (tiles / rows, us; fwd and bwd):
+//   fp32, 16384 walks of 1 position, heads of 64: 205 / 23, 620 / 68; of 4: 209 / 120, 624 / 339; of 6: 209 / 177, 630 / 518;
+//     of 8: 210 / 268, 634 / 1147; 8192 walks of 8, heads of 96: 219 / 178, 629 / 865; 256 walks of 4: 8.0 / 9.2, 24.0 / 21.9
+//   bf16, 16384 walks of 1 position, heads of 64: 70 / 24, 180 / 79; of 2: 70 / 51, 183 / 199; of 3: 72 / 91, 189 / 277; heads
+//     of 8: of 4: 57 / 35, 147 / 99; of 8: 58 / 78, 148 / 232; 1024 walks, heads of 64: rows are never the faster way
+// Near a limit the two differ by 10 to 20 % either way.
+static int row_kernel_positions(int dtype, bool bwd, int64_t walks, int64_t d) {
+  if (dtype == TM_DTYPE_FP32) {
+    if (d > 64) return walks >= 512 ? (bwd || d == 128 ? 6 : 8) : walks > (bwd ? 128 : 256) ? 4 : 0;
+    if (walks >= 512) return d <= 8 ? 8 : d <= 16 || d > 32 ? 6 : walks >= 2048 ? 5 : 4;
+    return d <= (bwd ? 8 : 16) ? 4 : 0;
+  }
+  if (walks >= 2048)
+    return bwd ? (d <= 8 ? 4 : d <= 24 || d > 64 ? 3 : d <= 48 ? 2 : 1) : (d <= 8 ? 5 : d <= 16 ? 4 : d <= 32 ? 3 : 2);
+  if (walks >= 512) return bwd ? (d <= 8 ? 3 : d <= 16 ? 2 : 0) : (d <= 8 ? 4 : d <= 16 ? 3 : d <= 24 ? 2 : 0);
+  return !bwd && d <= 8 ? 4 : 0;
+}
+static bool rows_pay(int dtype, bool bwd, int64_t seq, int64_t walks, int64_t d) {
+  return !(dtype == TM_DTYPE_BF16 && d == 128) && seq <= row_kernel_positions(dtype, bwd, walks, d);
+}
+
 extern "C" int tm_op_attn_fwd(int dtype, int64_t seq, int64_t batch, int64_t nq, int64_t nkv, int64_t d,
                               const void *qkv, void *ctx, float *lse, void *stream) {
   if (int e = check_attn("attn_fwd", dtype, seq, batch, nq, nkv, d)) return e;
   if (!qkv || !ctx || !lse) return fail(TM_EINVAL, "attn_fwd: NULL pointer");
   hipStream_t s = (hipStream_t)stream;
+  if (rows_pay(dtype, false, seq, batch * nq, d)) return attn_fwd_generic_launch(dtype, seq, batch, nq, nkv, d, qkv, ctx, lse, s);
   if (attn_mfma_supported(dtype, seq, batch, nq, nkv, d)) return attn_fwd_mfma_launch(seq, batch, nq, nkv, d, qkv, ctx, lse, s);
   if (attn_f32_supported(dtype, seq, batch, nq, nkv, d)) return attn_fwd_f32_launch(seq, batch, nq, nkv, d, qkv, ctx, lse, s);
   return attn_fwd_generic_launch(dtype, seq, batch, nq, nkv, d, qkv, ctx, lse, s);
@@ -46,6 +71,8 @@ extern "C" int tm_op_attn_bwd(int dtype, int64_t seq, int64_t batch, int64_t nq,
   float *dvec = (float *)scratch;
   float *part = dvec + (batch * nq * seq + 63) / 64 * 64;
   if (int e = attn_dvec_launch(dtype, seq, batch, nq, nkv, d, ctx, dctx, dvec, s)) return e;
+  if (rows_pay(dtype, true, seq, batch * nq, d))
+    return attn_bwd_generic_launch(dtype, seq, batch, nq, nkv, d, qkv, dctx, lse, dvec, dqkv, s);
   if (attn_mfma_supported(dtype, seq, batch, nq, nkv, d))
     return attn_bwd_mfma_launch(seq, batch, nq, nkv, d, qkv, dctx, lse, dvec, part, dqkv, s);
   if (attn_f32_supported(dtype, seq, batch, nq, nkv, d))

@@ -1,5 +1,5 @@
-// Causal attention without matrix cores: head sizes above 128, and tensors of 2 GiB and more (but for bf16 with
-// head size 128).  One wavefront per query row (forward, dQ) or per key row (dK, dV); scores of
+// Causal attention without matrix cores: head sizes above 128, tensors of 2 GiB and more, and very short sequences of many
+// heads and entries (but for bf16 with head size 128).  One wavefront per query row (forward, dQ) or per key row (dK, dV); scores of
 // the row live in LDS.  Summation orders are fixed, so results are bit-reproducible.
 #include <math.h>
 
