@@ -49,13 +49,14 @@ __global__ __launch_bounds__(64) void attn_fwd_generic(const T *__restrict__ qkv
 }
 
 // dvec[n,g,i] = sum_e dctx[i,g,e] * ctx[i,g,e].  HBM-bound: a group of G lanes (d / VN rounded up to a power of two)
-// holds one row of one head, 16 bytes a lane, in memory order (heads, entries, positions), four of them in flight.  (One
-// wave per row and head left all but d / 2 bytes' worth of lanes idle and launched a block for each: 16384 positions, 8
-// heads of 128: 34 -> 16 us.)
-template <typename T, int G>
+// holds one row of one head, 16 bytes a lane, in memory order (heads, entries, positions), ITEMS of them in flight: four,
+// or one where blocks of four leave units idle.  (One wave per row and head left all but d / 2 bytes' worth of lanes idle
+// and launched a block for each: 16384 positions, 8 heads of 128: 34 -> 16 us.  Small calls are bound by a block's own
+// chain, to which 64-bit divisions added 2 us: 64 to 4096 rows of heads of 128, the whole backward pass 10.7 -> 8.7, 12.4 -> 10.5.)
+template <typename T, int G, int ITEMS>
 __global__ __launch_bounds__(256) void attn_dvec_kernel(const T *__restrict__ ctx, const T *__restrict__ dctx,
                                                        float *__restrict__ dvec, AttnShape a, int64_t total) {
-  constexpr int VN = Vec<T>::N, PER = 256 / G, ITEMS = 4;
+  constexpr int VN = Vec<T>::N, PER = 256 / G;
   const int l = threadIdx.x % G;
   const bool live = l * VN < a.d;
   const int64_t first = (int64_t)blockIdx.x * (PER * ITEMS) + threadIdx.x / G;
@@ -79,8 +80,18 @@ __global__ __launch_bounds__(256) void attn_dvec_kernel(const T *__restrict__ ct
     for (int off = G / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
     const int64_t item = first + k * PER;
     if (l == 0 && item < total) {
-      const int64_t t = item / a.nq;
-      const int g = (int)(item - t * a.nq), i = (int)(t / a.batch), n = (int)(t - (int64_t)i * a.batch);
+      int g, i, n;
+      if (total <= 0x7fffffff) {  // uniform; 64-bit divisions are some hundred instructions each
+        const unsigned t = (unsigned)item / (unsigned)a.nq;
+        g = (int)((unsigned)item - t * (unsigned)a.nq);
+        i = (int)(t / (unsigned)a.batch);
+        n = (int)(t - (unsigned)i * (unsigned)a.batch);
+      } else {
+        const int64_t t = item / a.nq;
+        g = (int)(item - t * a.nq);
+        i = (int)(t / a.batch);
+        n = (int)(t - (int64_t)i * a.batch);
+      }
       dvec[((int64_t)n * a.nq + g) * a.seq + i] = s;
     }
   }
@@ -88,7 +99,11 @@ __global__ __launch_bounds__(256) void attn_dvec_kernel(const T *__restrict__ ct
 template <typename T, int G>
 static void dvec_launch(const AttnShape &a, const void *ctx, const void *dctx, float *dvec, hipStream_t s) {
   const int64_t total = (int64_t)a.seq * a.batch * a.nq;
-  attn_dvec_kernel<T, G><<<(unsigned)ceil_div(total, (int64_t)(256 / G * 4)), 256, 0, s>>>((const T *)ctx, (const T *)dctx, dvec, a, total);
+  const int64_t rows = 256 / G;  // of a block at a time
+  if (total >= 4 * rows * 512)
+    attn_dvec_kernel<T, G, 4><<<(unsigned)ceil_div(total, 4 * rows), 256, 0, s>>>((const T *)ctx, (const T *)dctx, dvec, a, total);
+  else
+    attn_dvec_kernel<T, G, 1><<<(unsigned)ceil_div(total, rows), 256, 0, s>>>((const T *)ctx, (const T *)dctx, dvec, a, total);
 }
 template <typename T> static void dvec_t(const AttnShape &a, const void *ctx, const void *dctx, float *dvec, hipStream_t s) {
   const int chunks = a.d / Vec<T>::N;
