@@ -8,9 +8,10 @@ namespace tmk {
 constexpr int kNormThreads = 512;
 constexpr int kNormMaxChunks = 4;  // 16-byte chunks per thread: hidden <= 512 * 4 * Vec::N
 
-// Threads of a row.  TPR = 512: a block per row, for rows of more than 4 KB.  Shorter rows leave most of such a block
-// idle and one small row in flight per block (4000 rows of 2 KB: 13.3 us forward, 21 backward; a wave per row: 6.4 and
-// 11), so they take one wave (no barrier in the row sums) or two, and a block holds 512 / TPR rows.
+// Threads of a row.  TPR = 512: a block per row, for rows of more than 4 KB and for few rows.  Many shorter rows leave most
+// of such a block idle and one small row in flight per block (4000 rows of 2 KB: 13.3 us forward, 21 backward; a wave per
+// row: 6.4 and 11), so they take one wave (no barrier in the row sums) or two, and a block holds 512 / TPR rows.  Where the
+// line lies: norm_fwd_tpr, norm_bwd_tpr.
 //
 // Sum of two values over the TPR threads of this thread's row; red: 2 * 512 / 64 floats.
 template <int TPR> __device__ __forceinline__ void row_sum2(float &a, float &b, float *red) {
@@ -395,11 +396,21 @@ __global__ __launch_bounds__(64 * kRowLanes) void colsum_direct_kernel(const T *
 }
 
 static int norm_bwd_blocks(int64_t T) { return (int)(T < 256 ? T : 256); }
-// threads of a row for width h (see the top of this file)
-static int norm_tpr(int64_t h, int vn) { return h <= 2 * 64 * vn ? 64 : h <= 2 * 128 * vn ? 128 : kNormThreads; }
+// Threads of a row for width h (see the top of this file).  Few rows keep a block each, which leaves nothing to join: their
+// time is one row's chain, and several rows a block add the join of their column sums to it.  Measured, a block a row
+// against several rows a block, bf16, backward: 1024 wide, 64 rows 5.4 / 6.9 us, 192 rows 6.5 / 7.3, 256 rows 7.2 / 7.4 (with
+// 300 rows some blocks get a second: 12 / 7.6); 512 wide (one chunk a lane, a shorter join) 32 rows 5.4 / 5.5, 96 rows 5.9 / 5.6.
+// Forward (nothing to join): two waves a row 3.1 / 3.3 at up to 256 rows 2048 wide, one wave 3.0 / 2.8.
+static int norm_fwd_tpr(int64_t T, int64_t h, int vn) {
+  return h <= 2 * 64 * vn ? 64 : h <= 2 * 128 * vn && T > 256 ? 128 : kNormThreads;
+}
+static int norm_bwd_tpr(int64_t T, int64_t h, int vn) {
+  if (T <= (h <= 64 * vn ? 64 : 192)) return kNormThreads;
+  return h <= 2 * 64 * vn ? 64 : h <= 2 * 128 * vn ? 128 : kNormThreads;
+}
 // blocks of the backward pass = partial rows: never more than norm_bwd_blocks, which sizes the scratch
 static int norm_bwd_grid(int64_t T, int64_t h, int vn) {
-  const int64_t groups = ceil_div(T, (int64_t)(kNormThreads / norm_tpr(h, vn)));
+  const int64_t groups = ceil_div(T, (int64_t)(kNormThreads / norm_bwd_tpr(T, h, vn)));
   return (int)(groups < 256 ? groups : 256);
 }
 // Row groups of a column sum, at most as many as a norm has partial rows (min(T, 256), which sizes the scratch): about 64
@@ -444,9 +455,10 @@ static int norm_fwd_t(int kind, int64_t rows, int h, float eps, const void *x, c
           (const T *)x, (const T *)gain, nullptr, (T *)out, mean, rstd, rows, h, eps);                            \
     return check_launch("norm_fwd");                                                                              \
   } while (0)
-  if (h <= 64 * Vec<T>::N) TM_NORM_FWD_NARROW(1, 64);
-  if (h <= 2 * 64 * Vec<T>::N) TM_NORM_FWD_NARROW(2, 64);
-  if (h <= 2 * 128 * Vec<T>::N) TM_NORM_FWD_NARROW(2, 128);
+  const int tpr = norm_fwd_tpr(rows, h, Vec<T>::N);
+  if (tpr == 64 && h <= 64 * Vec<T>::N) TM_NORM_FWD_NARROW(1, 64);
+  if (tpr == 64) TM_NORM_FWD_NARROW(2, 64);
+  if (tpr == 128) TM_NORM_FWD_NARROW(2, 128);
 #undef TM_NORM_FWD_NARROW
   if (kind == TM_NORM_LAYERNORM) {
     TM_NCH_SWITCH(nch, (norm_fwd_kernel<T, TM_NORM_LAYERNORM, NCH><<<dim3((unsigned)rows), kNormThreads, 0, s>>>(
@@ -474,9 +486,10 @@ static int norm_bwd_t(int kind, int64_t rows, int h, const void *dout, const voi
           (const T *)dout, (const T *)x, mean, rstd, (const T *)gain, (const T *)dres, (T *)dx, partial, rows, h);     \
     return check_launch("norm_bwd");                                                                                   \
   } while (0)
-  if (h <= 64 * Vec<T>::N) TM_NORM_BWD_NARROW(1, 64);
-  if (h <= 2 * 64 * Vec<T>::N) TM_NORM_BWD_NARROW(2, 64);
-  if (h <= 2 * 128 * Vec<T>::N) TM_NORM_BWD_NARROW(2, 128);
+  const int tpr = norm_bwd_tpr(rows, h, Vec<T>::N);
+  if (tpr == 64 && h <= 64 * Vec<T>::N) TM_NORM_BWD_NARROW(1, 64);
+  if (tpr == 64) TM_NORM_BWD_NARROW(2, 64);
+  if (tpr == 128) TM_NORM_BWD_NARROW(2, 128);
 #undef TM_NORM_BWD_NARROW
   if (kind == TM_NORM_LAYERNORM) {
     TM_NCH_SWITCH(nch, (norm_bwd_kernel<T, TM_NORM_LAYERNORM, NCH, XSUM><<<G, kNormThreads, 0, s>>>(

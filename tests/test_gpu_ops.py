@@ -353,10 +353,14 @@ def test_norm_fwd_bwd(env, dtype, kind, T, h):
 @pytest.mark.parametrize("dtype,kind,T,h", [
     (BF16, so.NORM_LAYERNORM, 1, 8), (BF16, so.NORM_RMSNORM, 9, 512), (BF16, so.NORM_LAYERNORM, 300, 520), (BF16, so.NORM_RMSNORM, 2500, 1024),
     (BF16, so.NORM_LAYERNORM, 7, 1032), (BF16, so.NORM_LAYERNORM, 1500, 2048), (BF16, so.NORM_RMSNORM, 5, 2056),
-    (FP32, so.NORM_LAYERNORM, 17, 264), (FP32, so.NORM_RMSNORM, 2100, 512), (FP32, so.NORM_LAYERNORM, 3, 1024), (FP32, so.NORM_LAYERNORM, 4, 1032)])
+    (FP32, so.NORM_LAYERNORM, 17, 264), (FP32, so.NORM_RMSNORM, 2100, 512), (FP32, so.NORM_LAYERNORM, 3, 1024), (FP32, so.NORM_LAYERNORM, 4, 1032),
+    (BF16, so.NORM_LAYERNORM, 64, 512), (BF16, so.NORM_RMSNORM, 65, 512), (BF16, so.NORM_LAYERNORM, 192, 1024), (BF16, so.NORM_LAYERNORM, 193, 1024),
+    (BF16, so.NORM_LAYERNORM, 193, 2048), (BF16, so.NORM_LAYERNORM, 257, 1536), (FP32, so.NORM_LAYERNORM, 193, 264), (FP32, so.NORM_LAYERNORM, 257, 1024),
+    (FP32, so.NORM_LAYERNORM, 65, 256)])
 def test_norm_rows_of_a_wave_or_two(env, dtype, kind, T, h):
-    """The widths at which a row goes to one wave, two waves or a whole block, and row counts that leave part of a block's
-    rows empty (one row; one more than a block holds; more rows than the blocks take at once): as test_norm_fwd_bwd."""
+    """The widths and row counts at which a row goes to one wave, two waves or a whole block, and row counts that leave part
+    of a block's rows empty (one row; one more than a block holds; more rows than the blocks take at once): as
+    test_norm_fwd_bwd."""
     test_norm_fwd_bwd(env, dtype, kind, T, h)
 
 
