@@ -56,15 +56,17 @@ template <int VN> __device__ __forceinline__ void put_grad(float *__restrict__ p
 }
 
 // ---- embedding backward: one block per vocabulary row, its tokens' rows added in token order (reproducible) -----
-template <typename T>
+// PER * 256 tokens are compared at once, PER per thread; the waves' ballots go to LDS and every thread then walks the set
+// bits in ascending token order, so the sum is taken in the same order as a serial scan, whatever PER is: the fewest that
+// take all tokens at once, up to 2048 tokens (64 tokens, 1000 rows of 512: 6.4 us with 8 per thread, 3.4 with one; 4096 tokens, 32000
+// rows of 512: 93 with 8, 200 with one).
+template <typename T, int PER>
 __global__ __launch_bounds__(kRoleThreads) void embed_bwd_kernel(const int32_t *__restrict__ tokens, const T *__restrict__ dx0,
                                                                 float *__restrict__ dw, int64_t n_tokens, int h, int v0,
                                                                 int accumulate) {
   constexpr int VN = Vec<T>::N;
   constexpr int MAXCH = 8;  // h <= 256 * 8 * VN
-  // 2048 tokens are compared at once (eight per thread); the waves' ballots go to LDS and every thread then walks the
-  // set bits in ascending token order, so the sum is taken in the same order as a serial scan
-  constexpr int PER = 8, NW = kRoleThreads / 64;
+  constexpr int NW = kRoleThreads / 64;
   __shared__ unsigned long long hits[PER * NW];
   const int want = (int)blockIdx.x + v0;
   bool named = false;  // by any token: uniform over the block
@@ -136,6 +138,20 @@ __global__ __launch_bounds__(kRoleThreads) void pos_grad_kernel(const T *__restr
       }
     put_grad<VN>(dpos + (int64_t)p * h + c, s, accumulate);
   }
+}
+
+template <typename T, int PER>
+static void embed_bwd_per(const int32_t *tokens, const void *dx0, float *dw, int64_t n_tokens, int64_t h, int64_t v_local, int64_t v0,
+                          int accumulate, hipStream_t s) {
+  embed_bwd_kernel<T, PER><<<(unsigned)v_local, kRoleThreads, 0, s>>>(tokens, (const T *)dx0, dw, n_tokens, (int)h, (int)v0, accumulate);
+}
+template <typename T>
+static void embed_bwd_launch(const int32_t *tokens, const void *dx0, float *dw, int64_t n_tokens, int64_t h, int64_t v_local, int64_t v0,
+                             int accumulate, hipStream_t s) {
+  if (n_tokens <= kRoleThreads) embed_bwd_per<T, 1>(tokens, dx0, dw, n_tokens, h, v_local, v0, accumulate, s);
+  else if (n_tokens <= 2 * kRoleThreads) embed_bwd_per<T, 2>(tokens, dx0, dw, n_tokens, h, v_local, v0, accumulate, s);
+  else if (n_tokens <= 4 * kRoleThreads) embed_bwd_per<T, 4>(tokens, dx0, dw, n_tokens, h, v_local, v0, accumulate, s);
+  else embed_bwd_per<T, 8>(tokens, dx0, dw, n_tokens, h, v_local, v0, accumulate, s);
 }
 
 // ---- cross-entropy over the rank's vocabulary shard, one block per token row -----------------------
@@ -231,12 +247,8 @@ extern "C" int tm_op_embed_bwd(int dtype, int64_t seq, int64_t batch, int64_t h,
   if (h > hmax) return fail(TM_ESIZE, "embed_bwd: width %lld above the limit %lld", (long long)h, (long long)hmax);
   hipStream_t s = (hipStream_t)stream;
   g_last_kernel = "embed_bwd_kernel";
-  if (dtype == TM_DTYPE_BF16)
-    embed_bwd_kernel<bf16><<<(unsigned)v_local, kRoleThreads, 0, s>>>(tokens, (const bf16 *)dx0, dw, seq * batch, (int)h, (int)v0,
-                                                                      accumulate);
-  else
-    embed_bwd_kernel<float><<<(unsigned)v_local, kRoleThreads, 0, s>>>(tokens, (const float *)dx0, dw, seq * batch, (int)h,
-                                                                       (int)v0, accumulate);
+  if (dtype == TM_DTYPE_BF16) embed_bwd_launch<bf16>(tokens, dx0, dw, seq * batch, h, v_local, v0, accumulate, s);
+  else embed_bwd_launch<float>(tokens, dx0, dw, seq * batch, h, v_local, v0, accumulate, s);
   if (dpos) {
     if (dtype == TM_DTYPE_BF16)
       pos_grad_kernel<bf16><<<(unsigned)n_pos, kRoleThreads, 0, s>>>((const bf16 *)dx0, dpos, (int)seq, (int)batch, (int)h, accumulate);

@@ -26,7 +26,7 @@ def _tokens(rng, lo, hi, shape):
 
 @pytest.mark.parametrize("dtype,seq,batch,h,v_local,with_pos", [
     (BF16, 70, 3, 264, 40, True),       # ragged everything, ids below / inside / above the shard
-    (BF16, 1100, 1, 512, 96, False),    # more tokens than one scan window of the backward kernel
+    (BF16, 2100, 1, 512, 96, False),    # more tokens than one scan window of the backward kernel
     (FP32, 33, 2, 72, 24, True),
 ])
 def test_embedding_forward_and_backward(env, dtype, seq, batch, h, v_local, with_pos):
@@ -63,6 +63,14 @@ def test_embedding_forward_and_backward(env, dtype, seq, batch, h, v_local, with
     tm.tm_op_embed_bwd(dtype, seq, batch, h, v_local, v0, tok_d, to_dev(torch, dx0, dtype), dw2, None, 0, 0, s)
     torch.cuda.synchronize()
     assert torch.equal(dw2, dw)                                  # reproducible
+
+
+@pytest.mark.parametrize("dtype,seq,batch", [(BF16, 1, 1), (BF16, 128, 2), (BF16, 257, 1), (FP32, 512, 1), (FP32, 171, 3), (BF16, 1024, 1),
+                                             (BF16, 205, 5), (FP32, 1024, 2), (BF16, 2049, 1), (BF16, 4100, 1)])
+def test_embedding_gradient_scan_windows(env, dtype, seq, batch):
+    """Token counts at which the backward kernel's scan window changes (256, 512, 1024, 2048 and one more), and counts of
+    one and of several windows: as test_embedding_forward_and_backward."""
+    test_embedding_forward_and_backward(env, dtype, seq, batch, 72, 24, False)
 
 
 @pytest.mark.parametrize("dtype,T,v_local", [(BF16, 37, 264), (BF16, 5, 2056), (FP32, 19, 72)])
