@@ -133,9 +133,9 @@ __global__ __launch_bounds__(kEwThreads) void rotary_kernel(T *buf, int64_t rows
 // The same for rows of whole 16-byte chunks (half a head a multiple of a chunk, everything 16-byte aligned): a block takes
 // rows_per_block rows (about 128 angles), puts the cosines and sines of a row into LDS and rotates all heads from there,
 // a chunk of either half per thread.  The element-wise form above walks the heads one after the other in each thread, two
-// elements at a time: bound by that chain (1024 rows, 32 heads of 64, fp32: 14.3 us, here 6.3; 4096 rows of 9 heads of 128 stay at
-// 10, the double-precision angles).  Same angles, same
-// arithmetic, same bits.
+// elements at a time: bound by that chain (1024 rows, 32 heads of 64, fp32: 14.3 us, here 6.3).  With few heads the chain is
+// short and what counts is the angles, in double precision, which the element-wise form spreads over all threads: it keeps
+// those calls (rotary_heads_for_rows).  Same angles, same arithmetic, same bits.
 constexpr int kRotaryAngles = 256;
 template <typename T>
 __global__ __launch_bounds__(kEwThreads) void rotary_rows_kernel(T *buf, int64_t rows, int batch, int n_heads, int d, int row_width,
@@ -172,10 +172,14 @@ __global__ __launch_bounds__(kEwThreads) void rotary_rows_kernel(T *buf, int64_t
     store_vec<T>(p + half, b);
   }
 }
+// From how many heads on the rows' form is the faster one, from both forms' times, us elements / rows: 1024 rows, heads of 64
+// (32768 angles): 2 heads 2.9 / 3.0, 4 heads 3.3 / 3.1; 1024 and 128: 4 heads 3.3 / 3.8, 9 heads 4.3 / 4.2; 4096 and 128: 9 heads 7.3 / 7.9
+// (fp32 8.0 / 9.2), 16 heads 9.8 / 9.0 (12.4 / 11.3); 16384 and 128: 9 heads 18.9 / 23.4, 16 heads 25.4 / 24.9.
+static int64_t rotary_heads_for_rows(int64_t angles) { return angles >= 262144 ? 13 : angles >= 65536 ? 5 : 3; }
 template <typename T>
 static void rotary_launch(void *buf, int64_t rows, int batch, int n_heads, int d, int64_t row_width, double theta, double sign, hipStream_t s) {
   const int half = d / 2, vn = Vec<T>::N;
-  if (half % vn == 0 && half <= kRotaryAngles && row_width % vn == 0 && row_width <= 0x7fffffff && (((uintptr_t)buf) & 15) == 0) {
+  if (n_heads >= rotary_heads_for_rows(rows * half) && half % vn == 0 && half <= kRotaryAngles && row_width % vn == 0 && row_width <= 0x7fffffff && (((uintptr_t)buf) & 15) == 0) {
     const int rpb = half >= 128 ? 1 : 128 / half;
     rotary_rows_kernel<T><<<(unsigned)ceil_div(rows, (int64_t)rpb), kEwThreads, 0, s>>>((T *)buf, rows, batch, n_heads, d, (int)row_width, theta,
                                                                                       sign, rpb);

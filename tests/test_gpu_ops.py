@@ -418,11 +418,12 @@ def test_rotary_forward_and_inverse(env, dtype, seq, batch, heads, d):
     assert rel_err(to_host(buf), z64) <= (TOL_BF16 if dtype == BF16 else 1e-5)
 
 
-@pytest.mark.parametrize("dtype,seq,batch,heads,d", [(BF16, 1, 1, 1, 16), (BF16, 37, 2, 5, 80), (FP32, 9, 3, 2, 8), (FP32, 130, 1, 33, 64),
-                                                     (BF16, 5, 1, 2, 512)])
+@pytest.mark.parametrize("dtype,seq,batch,heads,d", [(BF16, 1, 1, 3, 16), (BF16, 37, 2, 5, 80), (FP32, 9, 3, 3, 8), (FP32, 130, 1, 33, 64),
+                                                     (BF16, 5, 1, 4, 512), (BF16, 1024, 2, 5, 64), (FP32, 4096, 1, 13, 128), (BF16, 4095, 1, 2, 128)])
 def test_rotary_rows_and_elements_agree(env, dtype, seq, batch, heads, d):
     """The form for whole 16-byte chunks (several rows a block, one row, a ragged last block, more heads than a pass of the
-    block holds, the widest half) against the element-wise form, which a buffer off the 16-byte alignment takes."""
+    block holds, the widest half, the fewest heads it takes at three numbers of angles) against the element-wise form, which a
+    buffer off the 16-byte alignment takes (and calls of few heads: the last)."""
     torch, tm = env
     width = (heads + 1) * d
     z = to_dev(torch, rand(np.random.default_rng(d), (seq, batch, width), 1.0, dtype), dtype)
