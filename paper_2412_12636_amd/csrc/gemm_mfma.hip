@@ -102,6 +102,7 @@ static const TileConfig kConfigs[] = {
      {{1.62, 0.299, 0.209, 0.000, 3.64}, {1.52, 0.320, 0.192, 0.000, 3.62}, {1.27, 0.286, 0.192, 0.000, 3.46}}},
 };
 constexpr int kNumConfigs = sizeof(kConfigs) / sizeof(kConfigs[0]);
+constexpr int kDeep64x128Config = 18;  // index in kConfigs
 
 static int layout_of(const GemmArgs &g) { return g.c_mode ? 2 : (g.b_cs == 1 ? 0 : 1); }
 
@@ -125,6 +126,11 @@ static int heuristic_config(const GemmArgs &g) {
   double best = 1e300;
   int pick = 0;
   const int layout = layout_of(g);
+  // An overwritten weight gradient of one reduction step and 32 M parameters or more is nothing but its fp32 results
+  // leaving for HBM, which the model, fitted to products of two steps and more, does not know.  Small tiles spread the stores
+  // most evenly; 48 tokens, model's tiles / 64 x 128: 16384 x 4096 65 / 54 us, 8192 x 8192 59 / 49, 12288 x 6144 62 / 54, 20480 x
+  // 5120 85 / 75, 8192 x 16384 119 / 99.  (Added to, the same matrices have no best tiles: each loses 5 to 15 % on some.)
+  if (g.c_mode == 2 && g.K <= 64 && g.M * g.N >= (1LL << 25)) return kDeep64x128Config;
   for (int c = 0; c < kNumConfigs; ++c) {
     if (!config_takes(g, c, layout)) continue;
     const double us = config_us(g, c, layout);

@@ -251,10 +251,33 @@ def test_gradient_overwrite_mode_ignores_old_contents(env):
     scratch = torch.empty(tm.tm_op_reduce_scratch_bytes(T, 2 * N), dtype=torch.uint8, device="cuda")
     tm.tm_op_bias_grad(BF16, T, N, dyd, db, scratch, 0, s)
     assert rel_err(to_host(db), dy.astype(np.float64).sum(axis=0)) <= 1e-5
-    # fp32 stage dtype goes through the plain-ALU kernel
+    # the fp32 stage dtype's own kernel
     dwf = torch.full((N, K), float("nan"), dtype=torch.float32, device="cuda")
     tm.tm_op_linear_wgrad(FP32, T, N, K, dyd.float(), xd.float(), dwf, 0, s)
     assert rel_err(to_host(dwf), dy.astype(np.float64).T @ x.astype(np.float64)) <= 1e-5
+
+
+@pytest.mark.parametrize("T,N,K", [(48, 8192, 4096), (64, 8192, 4104), (1, 4096, 8200)])
+def test_weight_gradient_of_one_step_and_many_parameters(env, T, N, K):
+    """One reduction step, whole and ragged, 32 M parameters and more: a rule of its own picks the tiles.  The same bits as
+    those of another configuration, and the definition on a stretch of rows (fp32 sums of exact products: 1e-5)."""
+    torch, tm = env
+    print(f"weight gradient T={T} N={N} K={K}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T)
+    x = torch.randn((T, K), generator=g, device="cuda").bfloat16()
+    dy = (torch.randn((T, N), generator=g, device="cuda") * 0.1).bfloat16()
+    s = stream_ptr(torch)
+    out = [torch.full((N, K), float("nan"), device="cuda") for _ in range(2)]
+    tm.tm_op_linear_wgrad(BF16, T, N, K, dy, x, out[0], 0, s)
+    try:
+        tm.tm_gemm_force_config(1)
+        tm.tm_op_linear_wgrad(BF16, T, N, K, dy, x, out[1], 0, s)
+    finally:
+        tm.tm_gemm_force_config(-1)
+    assert torch.equal(out[0], out[1])
+    rows = slice(N - 50, N)
+    ref = to_host(dy[:, rows]).T @ to_host(x)
+    assert rel_err(to_host(out[0][rows]), ref) <= 1e-5
 
 
 def test_linear_results_are_bit_reproducible(env):
