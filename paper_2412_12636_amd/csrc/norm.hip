@@ -49,7 +49,8 @@ __global__ __launch_bounds__(kNormThreads) void norm_fwd_kernel(
   const int sub = TPR == kNormThreads ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / TPR);  // uniform over a wave
   const int64_t row = (int64_t)blockIdx.x * (kNormThreads / TPR) + sub;
   // a row past the end (several rows a block): reads as zero, nothing is written
-  const uint32_t row_bytes = row < rows ? (uint32_t)h * sizeof(T) : 0u, width_bytes = (uint32_t)h * sizeof(T);
+  const bool in = TPR == kNormThreads || row < rows;
+  const uint32_t row_bytes = in ? (uint32_t)h * sizeof(T) : 0u, width_bytes = (uint32_t)h * sizeof(T);
   const rsrc_t rx = make_rsrc(x + row * h, row_bytes), ro = make_rsrc(out + row * h, row_bytes);
   const rsrc_t rg = make_rsrc(gain, width_bytes), rf = make_rsrc(KIND == TM_NORM_LAYERNORM ? offset : gain, width_bytes);
   const int nchunk = h / VN;
@@ -84,7 +85,7 @@ __global__ __launch_bounds__(kNormThreads) void norm_fwd_kernel(
   } else {
     rstd = 1.0f / sqrtf(s2 / h + eps);
   }
-  if (tid == 0 && row < rows) {
+  if (tid == 0 && in) {
     if (mean_out) mean_out[row] = mu;
     rstd_out[row] = rstd;
   }
