@@ -283,9 +283,11 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
   *reinterpret_cast<bf16x8 *>(out + m * ldc + n) = o;
 }
 
-// Whether the split pays: its parts' product (the fp32 results leave uncached: two and a half epilogues) and the pass
-// that adds them, against the unsplit product on the best tiles.  (2048 x 2048 over 4096: 58 us split, 30 unsplit on
-// 128x128 tiles; 2048 x 512 over 4096: 29 against 17; 2048 x 1536 over 12288, the 175B shard's: 88 against 95.)
+// Whether the split pays: its parts' product and the pass that adds them, against the unsplit product on the best tiles.
+// The constants are fitted to 69 products of 1 to 4096 rows over 4096 to 20480: the choice is 1.2 % slower than the better of
+// the two on them (geometric mean), where always splitting is 3 % slower and never splitting 14 %.  (2048 x 2048 over 4096: 58 us
+// split, 30 unsplit on 128x128 tiles; 2048 x 512 over 4096: 29 against 17; 2048 x 1536 over 12288, the 175B shard's: 84 against 106;
+// 3 x 64 over 8832: 24 against 27.)
 static bool split_pays(const GemmArgs &g, int parts, bool large) {
   GemmArgs p = g;
   p.K = g.K / parts;
@@ -293,8 +295,8 @@ static bool split_pays(const GemmArgs &g, int parts, bool large) {
   const int64_t nb = ceil_div(g.M, (int64_t)kConfigs[c].bm) * ceil_div(g.N, (int64_t)kConfigs[c].bn) * parts;
   const LayoutCost &k = kConfigs[c].cost[1];
   const double step_us = !large && nb > 256 ? k.pair : k.alone + k.fill * (nb < 256 ? (double)nb / 256.0 : 1.0);
-  const double split_us = 2.5 * k.epi + (double)(p.K / 64) * step_us + 5.0 + (double)parts * g.M * g.N * 4 / 3e6;
-  return 0.92 * split_us < config_us(g, heuristic_config(g), 1);  // the estimate of the split is up to 8 % high
+  const double split_us = 1.25 * k.epi + (double)(p.K / 64) * step_us + 6.0 + (double)parts * g.M * g.N * 4 / 5e6;
+  return 0.9 * split_us < config_us(g, heuristic_config(g), 1);
 }
 
 int gemm_mfma(const GemmArgs &g, hipStream_t s) {
