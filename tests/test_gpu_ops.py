@@ -187,23 +187,25 @@ def test_linear_fp32_tiles(env, T, N, K):
     assert np.array_equal(yb[:T].cpu().numpy()[rows], y[:T].cpu().numpy()[rows])
 
 
-def test_input_gradient_with_split_reduction(env):
-    """dx = dy W with few output tiles and a long reduction: with scratch the reduction is split (the size
-    query says so), the result meets the same tolerance against the definition and is reproducible; without
-    scratch the call is the plain product."""
+def split_gradient(env, T, N, K, seed, splits):
+    """dx = dy W with scratch: whether the reduction was split shows in the scratch, which is filled before; the result meets
+    the tolerance against the definition, is reproducible and independent of what the scratch held; without scratch the call
+    is the plain product."""
     torch, tm = env
-    T, N, K = 300, 4096, 264                     # reduction over N = 4096, output 300 x 264: six tiles
-    rng = np.random.default_rng(21)
+    print(f"input gradient T={T} N={N} K={K}", flush=True)
+    rng = np.random.default_rng(seed)
     dy, w = rand(rng, (T, N), 0.1, BF16), rand(rng, (N, K), 0.05, BF16)
     dyd, wd = to_dev(torch, dy, BF16), to_dev(torch, w, BF16)
     s = stream_ptr(torch)
     need = tm.tm_op_linear_dgrad_scratch_bytes(BF16, T, N, K)
-    assert need == 8 * T * K * 4                 # eight parts of 512
-    assert tm.tm_op_linear_dgrad_scratch_bytes(BF16, 2048, 4608, 12288) == 0   # enough tiles: no split
-    scratch = torch.empty(need, dtype=torch.uint8, device="cuda")
-    new = lambda: torch.empty((T, K), dtype=torch.bfloat16, device="cuda")
+    assert need == 8 * T * K * 4                 # eight parts
+    scratch = torch.full((need // 4,), -1.5e30, dtype=torch.float32, device="cuda")
+    new = lambda: torch.full((T, K), float("nan"), dtype=torch.bfloat16, device="cuda")
     a, b, c, d = new(), new(), new(), new()
     tm.tm_op_linear_dgrad_ws(BF16, T, N, K, dyd, wd, a, scratch, need, s)
+    untouched = int((scratch == -1.5e30).sum())
+    assert untouched == (0 if splits else scratch.numel())
+    scratch.fill_(float("nan"))                  # stale partial results must not matter
     tm.tm_op_linear_dgrad_ws(BF16, T, N, K, dyd, wd, b, scratch, need, s)
     tm.tm_op_linear_dgrad_ws(BF16, T, N, K, dyd, wd, c, None, 0, s)
     tm.tm_op_linear_dgrad(BF16, T, N, K, dyd, wd, d, s)
@@ -211,30 +213,23 @@ def test_input_gradient_with_split_reduction(env):
     ref = dy.astype(np.float64) @ w.astype(np.float64)
     assert rel_err(to_host(a), ref) <= TOL_BF16 and rel_err(to_host(d), ref) <= TOL_BF16
     assert torch.equal(a, b) and torch.equal(c, d)
+    if not splits:
+        assert torch.equal(a, d)
 
 
-def test_input_gradient_with_split_reduction_on_large_tiles(env):
-    """Same, at a shape whose parts fill the chip with 256 x 192 tiles (the kernel with loader waves writes the fp32
-    partial results): ragged in both output dimensions, eight parts of 512."""
-    torch, tm = env
-    T, N, K = 1000, 4096, 1096                   # 4 x 6 large tiles, eight parts: 192 blocks
-    rng = np.random.default_rng(22)
-    dy, w = rand(rng, (T, N), 0.1, BF16), rand(rng, (N, K), 0.05, BF16)
-    dyd, wd = to_dev(torch, dy, BF16), to_dev(torch, w, BF16)
-    s = stream_ptr(torch)
-    need = tm.tm_op_linear_dgrad_scratch_bytes(BF16, T, N, K)
-    assert need == 8 * T * K * 4
-    scratch = torch.empty(need, dtype=torch.uint8, device="cuda")
-    new = lambda: torch.full((T, K), float("nan"), dtype=torch.bfloat16, device="cuda")
-    a, b, c = new(), new(), new()
-    tm.tm_op_linear_dgrad_ws(BF16, T, N, K, dyd, wd, a, scratch, need, s)
-    scratch.fill_(255)                           # stale partial results must not matter
-    tm.tm_op_linear_dgrad_ws(BF16, T, N, K, dyd, wd, b, scratch, need, s)
-    tm.tm_op_linear_dgrad(BF16, T, N, K, dyd, wd, c, s)
-    torch.cuda.synchronize()
-    ref = dy.astype(np.float64) @ w.astype(np.float64)
-    assert rel_err(to_host(a), ref) <= TOL_BF16 and rel_err(to_host(c), ref) <= TOL_BF16
-    assert torch.equal(a, b)
+@pytest.mark.parametrize("T,N,K,splits", [(200, 16384, 264, True), (3, 8192, 248, True), (300, 4096, 264, False)])
+def test_input_gradient_with_split_reduction(env, T, N, K, splits):
+    """Few output tiles and a long reduction: eight parts on 128 x 192 tiles, ragged in both output dimensions; and an output
+    that is small enough for it whose reduction is too short for the split to pay."""
+    split_gradient(env, T, N, K, 21, splits)
+    assert env[1].tm_op_linear_dgrad_scratch_bytes(BF16, 2048, 4608, 12288) == 0   # enough tiles: no split
+
+
+@pytest.mark.parametrize("T,N,K,splits", [(1000, 16384, 1496, True), (1000, 4096, 1096, False)])
+def test_input_gradient_with_split_reduction_on_large_tiles(env, T, N, K, splits):
+    """Same, at shapes whose parts fill the chip with 256 x 192 tiles (the kernel with loader waves writes the fp32
+    partial results): ragged in both output dimensions, eight parts."""
+    split_gradient(env, T, N, K, 22, splits)
 
 
 def test_gradient_overwrite_mode_ignores_old_contents(env):
