@@ -32,6 +32,8 @@ bool gemm_mfma_supported(const GemmArgs &g) {
   const int64_t a_bytes = (akc ? g.M * g.a_rs : g.K * g.a_cs) * 2, b_bytes = (bkc ? g.N * g.b_rs : g.K * g.b_cs) * 2;
   const int64_t c_bytes = g.M * g.ldc * (g.c_mode ? 4 : 2);
   if (a_bytes >= (1LL << 31) || b_bytes >= (1LL << 31) || c_bytes >= (1LL << 31)) return false;  // 32-bit offsets
+  // the rows that the last tile has past the result are written outside it, not round 2^32 to its front
+  if ((g.M + 256) * g.ldc * (g.c_mode ? 4 : 2) >= (1LL << 32)) return false;
   if (g.ldc % 8 || (((uintptr_t)g.C) & 15)) return false;
   return g.c_mode ? (!akc && !bkc) : akc;
 }

@@ -252,6 +252,36 @@ def test_gradient_overwrite_mode_ignores_old_contents(env):
     assert rel_err(to_host(dwf), dy.astype(np.float64).T @ x.astype(np.float64)) <= 1e-5
 
 
+@pytest.mark.parametrize("config", [-1, 3], ids=["chosen_tiles", "large_tiles"])
+def test_results_of_very_wide_rows(env, config):
+    """Rows of 2^25 results: a tile's rows past the eighth and last lie 2^32 bytes further on from row 32 (fp32) or 64 (bf16)
+    and must not be written to the front.  All three products, from the definition on columns at the front, in the
+    middle and at the end (eight exact products each: bf16 rounding 2^-8, fp32 1e-6)."""
+    torch, tm = env
+    wide, n = 1 << 25, 8
+    print(f"very wide rows config={config}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(8)
+    small = torch.randn((n, n), generator=g, device="cuda").bfloat16()
+    big = torch.randn((n, wide), generator=g, device="cuda").bfloat16()
+    s = stream_ptr(torch)
+    dw = torch.full((n, wide), float("nan"), device="cuda")
+    dx, y = torch.empty_like(big), torch.empty_like(big)
+    tall = big.t().contiguous()
+    try:
+        tm.tm_gemm_force_config(config)
+        tm.tm_op_linear_wgrad(BF16, n, n, wide, small, big, dw, 0, s)
+        tm.tm_op_linear_dgrad(BF16, n, n, wide, small, big, dx, s)
+        tm.tm_op_linear_fwd(BF16, n, wide, n, small, tall, None, None, y, s)
+    finally:
+        tm.tm_gemm_force_config(-1)
+    for first in (0, wide // 2 - 100, wide - 1000):
+        cols = slice(first, first + 1000)
+        a, b = to_host(small), to_host(big[:, cols])
+        assert rel_err(to_host(dw[:, cols]), a.T @ b) <= 1e-6
+        assert rel_err(to_host(dx[:, cols]), a @ b) <= 2.0 ** -8
+        assert rel_err(to_host(y[:, cols]), a @ b) <= 2.0 ** -8
+
+
 @pytest.mark.parametrize("T,N,K", [(48, 8192, 4096), (64, 8192, 4104), (1, 4096, 8200)])
 def test_weight_gradient_of_one_step_and_many_parameters(env, T, N, K):
     """One reduction step, whole and ragged, 32 M parameters and more: a rule of its own picks the tiles.  The same bits as
