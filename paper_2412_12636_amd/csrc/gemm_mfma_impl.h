@@ -118,21 +118,17 @@ __device__ __forceinline__ void tile_of_block(const MfmaGemmParams &p, int BM, i
   n0 = (in_group / gsz) * BN;
 }
 
-// ---- epilogue shared by both kernels -------------------------------------------------------------
-// EPI 0: bf16 C = acc (+bias) (+residual); acc[i][j] is the transposed 32x32 tile (rows = output columns):
-// register 4q+e of lane l holds C[row = .. + l%32][col = .. + 8q + 4*(l/32) + e].
-// EPI 1: fp32 C += acc;  EPI 2: fp32 C = acc; acc[i][j] is the tile itself: register v of lane l holds
-// C[row = .. + 8*(v/4) + 4*(l/32) + v%4][col = .. + l%32].
-// bf16 results: operands swapped, the accumulator tile is C^T (lane = row, 4 consecutive columns per
-// register quad: 8-byte stores).  fp32 results: natural order, the tile is C (lane%32 = column): a store
+// ---- results straight from the accumulators: fp32 ------------------------------------------------
+// EPI 1: C += acc;  EPI 2: C = acc;  EPI 3: C = acc is the gradient and its parameters are updated.  acc[i][j] is the tile
+// itself, natural order: register v of lane l holds C[row = .. + 8*(v/4) + 4*(l/32) + v%4][col = .. + l%32], so a store
 // instruction writes two whole 128-byte lines.
+// EPI 0, bf16 results: the MFMA operands are swapped and the accumulator tile is C^T (rows = output columns); the block's
+// tile is assembled in LDS (epilogue_lds and its two halves below).
 template <int EPI> __device__ __forceinline__ f32x16 mfma_for(bf16x8 a, bf16x8 b, f32x16 c) {
   if constexpr (EPI == 0) return __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, c, 0, 0, 0);
   else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-// VB: accumulator registers of a 32x32 tile whose state reads are in flight together in the update epilogue (EPI 3):
-// all sixteen where a wave has 256 registers, eight where three waves share a SIMD's register file
 // The update of one 32x32 accumulator tile (EPI 3): register v of lane l holds the gradient of row row0 + 8(v/4) + 4hh + v%4,
 // column col.  All 48 state reads of the tile are in flight together; gradient (if stored), state and the bf16 copy
 // are streamed past the caches.
@@ -176,9 +172,12 @@ __device__ __forceinline__ void adam_tile(const MfmaGemmParams &p, const AdamRsr
 #ifndef TM_LDW_VB
 #define TM_LDW_VB 12
 #endif
+// VB: accumulator registers of a 32x32 tile whose state reads are in flight together in the update epilogue (EPI 3): all
+// sixteen where a wave has 256 registers, TM_LDW_VB where three waves share a SIMD's register file
 template <int TM, int TN, int EPI, int VB = 16>
 __device__ __forceinline__ void epilogue(const MfmaGemmParams &p, const f32x16 (&acc)[TM][TN], int row_base,
                                          int col_base, int l32, int hh) {
+  static_assert(EPI >= 1 && EPI <= 3, "bf16 results leave through LDS");
   if constexpr (EPI == 3) {
     // weight gradient with the Adam update of its parameters: per accumulator register (two whole 128-byte
     // lines per wave) the three state reads are in flight together; gradient, state and the bf16 copy are
@@ -223,79 +222,34 @@ __device__ __forceinline__ void epilogue(const MfmaGemmParams &p, const f32x16 (
     }
     return;
   }
-  if constexpr (EPI != 0) {
-    // fp32 results (weight gradients): whole lines, written once and next read by the optimizer: streamed
-    // past the caches, which keeps the operands of the following products resident
-    constexpr int kStoreNonTemporal = 2;  // cache-policy operand of the buffer store: the nt bit
-    const rsrc_t rc = make_rsrc(p.C, p.c_bytes);
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int col = col_base + j * 32 + l32;
-        const bool col_ok = col < p.N;
-        uint32_t off[16];
-        float old[16];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int row = row_base + i * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
-          off[v] = col_ok ? (uint32_t)(((int64_t)row * p.ldc + col) * 4) : 0xfffffff0u;
-        }
-        if (EPI == 1) {  // all sixteen reads of the tile are in flight before the first add
-#pragma unroll
-          for (int v = 0; v < 16; ++v)
-            old[v] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rc, off[v], 0, kStoreNonTemporal));
-        }
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const float o = EPI == 1 ? old[v] + acc[i][j][v] : acc[i][j][v];
-          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, o), rc, off[v], 0, kStoreNonTemporal);
-        }
-      }
-    return;
-  }
-  const uint32_t c_elem = 2u;
+  // fp32 results (weight gradients): whole lines, written once and next read by the optimizer: streamed
+  // past the caches, which keeps the operands of the following products resident
+  constexpr int kStoreNonTemporal = 2;  // cache-policy operand of the buffer store: the nt bit
   const rsrc_t rc = make_rsrc(p.C, p.c_bytes);
-  const rsrc_t rres = make_rsrc(p.residual ? (const void *)p.residual : p.C, p.c_bytes);
-  const rsrc_t rbias = make_rsrc(p.bias ? (const void *)p.bias : p.C, (uint32_t)p.N * 2u);
 #pragma unroll
-  for (int j = 0; j < TN; ++j) {
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int col = col_base + j * 32 + 8 * q + 4 * hh;
-      const bool col_ok = col < p.N;  // N is a multiple of 8: the four columns are in or out together
-      float bv[4] = {0.f, 0.f, 0.f, 0.f};
-      if (EPI == 0 && p.bias) {
-        const u32x2 braw = __builtin_bit_cast(
-            u32x2, __builtin_amdgcn_raw_buffer_load_b64(rbias, col_ok ? (uint32_t)col * 2u : 0xfffffff0u, 0, 0));
-        bv[0] = __builtin_bit_cast(float, braw[0] << 16);
-        bv[1] = __builtin_bit_cast(float, braw[0] & 0xffff0000u);
-        bv[2] = __builtin_bit_cast(float, braw[1] << 16);
-        bv[3] = __builtin_bit_cast(float, braw[1] & 0xffff0000u);
+    for (int j = 0; j < TN; ++j) {
+      const int col = col_base + j * 32 + l32;
+      const bool col_ok = col < p.N;
+      uint32_t off[16];
+      float old[16];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int row = row_base + i * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
+        off[v] = col_ok ? (uint32_t)(((int64_t)row * p.ldc + col) * 4) : 0xfffffff0u;
+      }
+      if (EPI == 1) {  // all sixteen reads of the tile are in flight before the first add
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          old[v] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rc, off[v], 0, kStoreNonTemporal));
       }
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int row = row_base + i * 32 + l32;
-        const uint32_t off = col_ok ? (uint32_t)(((int64_t)row * p.ldc + col) * c_elem) : 0xfffffff0u;
-        {
-          float r[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) r[e] = acc[i][j][4 * q + e] + bv[e];
-          if (p.residual) {
-            const u32x2 rr = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rres, off, 0, 0));
-            r[0] += __builtin_bit_cast(float, rr[0] << 16);
-            r[1] += __builtin_bit_cast(float, rr[0] & 0xffff0000u);
-            r[2] += __builtin_bit_cast(float, rr[1] << 16);
-            r[3] += __builtin_bit_cast(float, rr[1] & 0xffff0000u);
-          }
-          bf16x4 o;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) o[e] = (bf16)r[e];
-          __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, o), rc, off, 0, 0);
-        }
+      for (int v = 0; v < 16; ++v) {
+        const float o = EPI == 1 ? old[v] + acc[i][j][v] : acc[i][j][v];
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, o), rc, off[v], 0, kStoreNonTemporal);
       }
     }
-  }
 }
 
 // =================================================================================================
