@@ -241,7 +241,7 @@ template <int DP> __global__ __launch_bounds__(256, 1) void f32_fwd_kernel(const
     const uint32_t redo = nonfinite_rows(nonfinite_trace(o, l * 0.f), q < p.seq);  // see attn_rows.h
     if (q < p.seq && !((redo >> l32) & 1)) {
       f32_store<DP>(o, 1.f / l, p.ctx + ((int64_t)q * p.batch + n) * (p.nq * d) + g * d, d, hh);
-      if (hh == 0) p.lse[((int64_t)n * p.nq + g) * p.seq + q] = (mm + log2f(l)) * 0.6931471805599453f;
+      if (hh == 0) p.lse[((int64_t)n * p.nq + g) * p.seq + q] = row_lse(mm, l);
     }
     for (uint32_t r = redo; r; r &= r - 1) attn_row_fwd<float>(p, q0w + __builtin_ctz(r), g, n, lane);
   }

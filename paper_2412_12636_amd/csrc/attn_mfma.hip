@@ -293,7 +293,7 @@ __device__ __forceinline__ void fwd_finish(const FlashParams &p, FwdRow<DP> &r, 
   if (q < p.seq && !((redo >> (q & 31)) & 1)) {
     const int64_t trow = (int64_t)q * p.batch + n;
     store_transposed<DP, EX>(r.o, 1.f / r.l, p.ctx + trow * (p.nq * hd) + g * hd, hd, hh);
-    if (hh == 0) p.lse[((int64_t)n * p.nq + g) * p.seq + q] = (r.m + log2f(r.l)) * 0.6931471805599453f;
+    if (hh == 0) p.lse[((int64_t)n * p.nq + g) * p.seq + q] = EX ? row_lse(r.m, r.l) : (r.m + log2f(r.l)) * 0.6931471805599453f;
   }
   if constexpr (EX)
     for (uint32_t m = redo; m; m &= m - 1) attn_row_fwd<bf16>(p, q - (lane & 31) + __builtin_ctz(m), g, n, lane);

@@ -26,6 +26,12 @@ __device__ __forceinline__ uint32_t nonfinite_rows(float trace, bool valid) {
   return (uint32_t)m | (uint32_t)(m >> 32);
 }
 
+// log-sum-exp of a row from the maximum m in exponent units (base 2) and the sum l: m ln 2 + ln l with one rounding behind it
+// (ln 2 as its fp32 value and what that leaves)
+__device__ __forceinline__ float row_lse(float m, float l) {
+  return __builtin_fmaf(m, 0.693147182464599609375f, __builtin_fmaf(m, -1.904654323148236017e-09f, logf(l)));
+}
+
 template <typename T> __device__ __forceinline__ float row_dot(const T *a, const T *b, int d) {
   float s = 0.f;
   for (int e = 0; e < d; ++e) s = fmaf(to_f32(a[e]), to_f32(b[e]), s);
