@@ -177,13 +177,13 @@ WIDE_RAGGED = si.StageConfig(1, 6152, 2, 2, 128, 4104, 64, 1)
 
 @pytest.mark.parametrize("cfg", [SMALL_GPT.replace(n_layers=3), SMALL_GPT.replace(n_layers=3, seq=192),
                                  SMALL_LLAMA.replace(n_layers=2, seq=256), TINY, WIDE_RAGGED, WIDE_RAGGED.replace(seq=192)],
-                         ids=["ragged_tokens_flat_sweep", "fused_into_the_products", "fused_llama", "fp32_flat_sweep",
+                         ids=["fused_ragged_tokens", "fused_into_the_products", "fused_llama", "fp32_flat_sweep",
                               "fused_large_staggered_ragged_one_step", "fused_large_staggered_ragged_three_steps"])
 def test_backward_with_overlapped_optimizer_equals_the_two_calls(env, cfg):
     """tm_stage_bwd_adam = tm_stage_bwd then tm_adam_step, bit for bit: gradients, master weights, both moments, the
-    bf16 copy, the input gradient; two iterations, so that the second forward pass sees updated weights.  With a
-    token count that is a multiple of 64 the matrices' updates ride in the weight-gradient products' epilogues and
-    the flat sweep covers the vectors between them; otherwise (and for fp32 stages) the flat sweep does it all."""
+    bf16 copy, the input gradient; two iterations, so that the second forward pass sees updated weights.  The updates
+    of a bf16 stage's matrices ride in the weight-gradient products' epilogues, whatever the token count, and the flat
+    sweep covers the vectors between them; for fp32 stages the flat sweep does it all."""
     torch, tm = env
     flat = si.make_flat_params(cfg)
     x, dy = to_dev(torch, si.make_x(cfg), cfg.dtype), to_dev(torch, si.make_dy(cfg), cfg.dtype)
@@ -222,10 +222,54 @@ def test_backward_with_overlapped_optimizer_equals_the_two_calls(env, cfg):
     c.close()
 
 
+@pytest.mark.parametrize("cfg", [SMALL_GPT.replace(n_layers=1), SMALL_LLAMA.replace(n_layers=1, seq=256)], ids=["ragged_tokens", "whole_steps"])
+def test_update_inside_every_tile_configuration(env, monkeypatch, cfg):
+    """The update in the epilogue of each tile configuration, and as the flat sweep (TM_ADAM_UNFUSED): the same bits in
+    the gradients, master weights, moments and the bf16 copy, and weights that moved by what Adam moves them: a step of lr
+    against the gradient's sign to begin with (an element off that by a tenth of lr, or a weight left alone, fails)."""
+    torch, tm = env
+    flat = si.make_flat_params(cfg)
+    x, dy = to_dev(torch, si.make_x(cfg), cfg.dtype), to_dev(torch, si.make_dy(cfg), cfg.dtype)
+    hp = tm.make_hparams(**si.ADAM_DEFAULTS)
+
+    def step(config, fused):
+        if fused:
+            monkeypatch.delenv("TM_ADAM_UNFUSED", raising=False)
+        else:
+            monkeypatch.setenv("TM_ADAM_UNFUSED", "1")
+        st = GpuStage(torch, tm, cfg, flat)
+        tm.tm_stage_grad_mode(st.handle, True)
+        st.fwd(x)
+        tm.tm_stage_profile_enable(st.handle, True)
+        try:
+            tm.tm_gemm_force_config(config)
+            tm.tm_stage_bwd_adam(st.handle, dy, st.dx, hp, 1, stream_ptr(torch))
+        finally:
+            tm.tm_gemm_force_config(-1)
+        torch.cuda.synchronize()
+        kernels = [e["kernel"] for e in tm.tm_stage_profile_collect(st.handle)]
+        assert any("epi3" in k for k in kernels) == fused, kernels
+        out = {k: getattr(st, k).clone() for k in ("dx", "grads", "master", "m", "v", "params")}
+        st.close()
+        return out
+
+    want = step(-1, False)
+    lr, g = si.ADAM_DEFAULTS["lr"], want["grads"]
+    moved = want["master"] - torch.from_numpy(flat).cuda() * (1.0 - lr * si.ADAM_DEFAULTS["weight_decay"])
+    large = g.abs() > 1e3 * si.ADAM_DEFAULTS["eps"]
+    assert float(large.float().mean()) > 0.5
+    assert float((moved + lr * torch.sign(g))[large].abs().max()) <= 0.1 * lr
+    for config in range(-1, tm.tm_gemm_config_count()):
+        print(f"update in tile configuration {config}", flush=True)
+        got = step(config, True)
+        for name, ref in want.items():
+            assert torch.equal(got[name], ref), (config, name)
+
+
 def test_backward_with_update_rejects_bad_scalars_before_any_launch(env):
     """step < 1 or a beta outside [0, 1) is refused before the first kernel: no state is touched."""
     torch, tm = env
-    cfg = SMALL_GPT.replace(seq=192)                     # token count a multiple of 64: the fused update path
+    cfg = SMALL_GPT.replace(seq=192)
     flat = si.make_flat_params(cfg)
     x, dy = to_dev(torch, si.make_x(cfg), cfg.dtype), to_dev(torch, si.make_dy(cfg), cfg.dtype)
     st = GpuStage(torch, tm, cfg, flat)
