@@ -252,6 +252,40 @@ def test_gradient_overwrite_mode_ignores_old_contents(env):
     assert rel_err(to_host(dwf), dy.astype(np.float64).T @ x.astype(np.float64)) <= 1e-5
 
 
+@pytest.mark.parametrize("dtype", [BF16, FP32])
+def test_linear_off_the_alignment(env, dtype):
+    """Operands that start one element past a 16-byte boundary go to the plain-ALU kernel, ragged in every dimension: the three
+    products, with bias and residual and with both gradient modes, against the definition (fp32 sums of at most 200
+    terms: 1e-6; bf16 results their rounding, 2^-8)."""
+    torch, tm = env
+    T, N, K = 130, 72, 200
+    print(f"linear off the alignment dtype={dtype}", flush=True)
+    rng = np.random.default_rng(17)
+    x, w, dy = rand(rng, (T, K), 1.0, dtype), rand(rng, (N, K), 0.05, dtype), rand(rng, (T, N), 0.1, dtype)
+    bias, res, g0 = rand(rng, (N,), 0.5, dtype), rand(rng, (T, N), 1.0, dtype), rng.standard_normal((N, K)).astype(np.float32)
+
+    def off(a):
+        t = to_dev(torch, a, dtype)
+        view = torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")[1:].view(t.shape)
+        view.copy_(t)
+        return view
+
+    xd, wd, dyd, bd, rd = off(x), off(w), off(dy), off(bias), off(res)
+    y, dx = torch.empty_like(dyd), torch.empty_like(xd)
+    dw0, dw1 = torch.full((N, K), float("nan"), device="cuda"), f32_dev(torch, g0)
+    s = stream_ptr(torch)
+    tm.tm_op_linear_fwd(dtype, T, N, K, xd, wd, bd, rd, y, s)
+    tm.tm_op_linear_dgrad(dtype, T, N, K, dyd, wd, dx, s)
+    tm.tm_op_linear_wgrad(dtype, T, N, K, dyd, xd, dw0, 0, s)
+    tm.tm_op_linear_wgrad(dtype, T, N, K, dyd, xd, dw1, 1, s)
+    x64, w64, dy64 = (a.astype(np.float64) for a in (x, w, dy))
+    bound = 2.0 ** -8 if dtype == BF16 else 1e-6
+    assert rel_err(to_host(y), x64 @ w64.T + bias + res) <= bound
+    assert rel_err(to_host(dx), dy64 @ w64) <= bound
+    assert rel_err(to_host(dw0), dy64.T @ x64) <= 1e-6
+    assert rel_err(to_host(dw1), g0 + dy64.T @ x64) <= 1e-6
+
+
 @pytest.mark.parametrize("config", [-1, 3], ids=["chosen_tiles", "large_tiles"])
 def test_results_of_very_wide_rows(env, config):
     """Rows of 2^25 results: a tile's rows past the eighth and last lie 2^32 bytes further on from row 32 (fp32) or 64 (bf16)
