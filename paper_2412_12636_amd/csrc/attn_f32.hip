@@ -11,10 +11,11 @@
 // a wave, so the walk is split rather than the block made larger.)  A tile is [32 rows][DP] fp32, fetched straight into
 // LDS by one wave (DP = head size rounded up to 32; columns and rows past the tensor read as zero), double buffered.
 //
-// Bound by the MFMA rate: 64 clocks each, DP of them per tile and wave in the forward pass against about 150 vector
-// instructions, and LDS reads of one 16-byte or four 4-byte words per four MFMAs.  (The kernels these replace ran one
-// wave per row with every operand out of L2: forward and backward over 2 x 512 positions, 16 heads of 64, took 5.4 ms, this
-// form takes 0.097.)
+// Bound by the MFMA rate, 64 clocks each, DP of them per tile and wave in the forward pass against about 150 vector
+// instructions and LDS reads of one 16-byte or four 4-byte words per four MFMAs, and by how few waves a short sequence
+// gives a SIMD: over 2 x 512 positions, 16 heads of 64, the matrix cores are busy for 64 % (backward) of the cycles in which
+// a unit has waves and, with one wave a SIMD, 45 % (forward).  (One wave per row with every operand out of L2 took 5.4 ms
+// for both passes, this form takes 0.095.)  Rows with a non-finite value: attn_rows.h.
 #include <math.h>
 
 #include "attn.h"

@@ -47,11 +47,15 @@ constexpr float kLog2e = 1.4426950408889634f;
 // Head sizes.  DP: the head size rounded up to a multiple of 32, the width the products run at (32, 64, 96 or 128).
 // EX = false: head size 128, probabilities and dS go to the second product as bf16.  EX = true: every other head size
 // up to 128; columns from the head size to DP are staged as zeros, and probabilities and dS keep 16 significand bits
-// (a bf16 value plus the bf16 of what it leaves, two MFMAs), because these head sizes have always had them in fp32:
-// the error against 64 bits is the plain-ALU kernels' (1.6e-3 forward, 1.7e-3 backward, the rounding of the results).
-// What these kernels replaced ran one wave per row out of L2: 43.6 ms for a forward and backward pass over 2 sequences
-// of 1500, 16 query and 4 kv heads of 64, where this form takes 0.103 ms (33 us forward, 65 backward); bound by the
-// latency of a tile step (S product, softmax, PV product, barrier), as the short sequences of head size 128 are.
+// (a bf16 value plus the bf16 of what it leaves, two MFMAs), fewer than the 24 of the kernels with one row per wave that
+// these sizes ran on before.  The results do not show the difference: against 64 bits both are off by their rounding to bf16
+// and by ctx's rounding in the row statistics D, 1.6e-3 forward and 1.7e-3 backward, and with keys or values offset by up to 64
+// times their spread, where the gradients cancel, by the same 0.8 % to 17 % to four digits.  (A third term, all 24 bits: the
+// same errors again, forward 30 -> 36 us, backward 74 -> 85 at the size below.)  Rows with a non-finite value: attn_rows.h.
+// One wave per row out of L2 took 43.6 ms for a forward and backward pass over 2 sequences of 1500, 16 query and 4 kv heads
+// of 64, where this form takes 0.10 ms (31 us forward, 70 backward).  Of the cycles in which a unit has waves the matrix
+// cores are busy for 28 % (forward) and 46 % (backward), its three waves a SIMD issue vector instructions for 60 % and
+// 68 %: bound by the vector ALU work of a tile step and the chain through it (S product, softmax, PV product, barrier).
 //
 // A staged tile: [64][128] bf16 for DP 96 and 128, [64][64] for DP 32 and 64 (half the LDS: three blocks a unit).
 template <int DP> struct TileFmt {
