@@ -194,11 +194,11 @@ int tm_adam_step(tm_stage_t *st, const tm_adam_hparams_t *hp, int64_t step, void
  * gradients are complete.  Valid only when nothing global is
  * derived from this pass's gradients before the update: hp->grad_scale must
  * not depend on them (no norm-based clipping).  For bf16 stages in TM_GRAD_STORE
- * or TM_GRAD_TRANSIENT mode with hp->zero_grads == 0 the update of each weight
- * matrix is applied in the epilogue of its weight-gradient product, from the
+ * or TM_GRAD_TRANSIENT mode with hp->zero_grads == 0 the update of a weight
+ * matrix is applied, where that is the faster way, in the epilogue of its weight-gradient product, from the
  * accumulators (the gradient is not read back; in TM_GRAD_TRANSIENT mode with a
  * token count that is a multiple of 64 it is not stored either), and the flat
- * sweep covers the vectors between the matrices; the results are the same bits.  Everything is enqueued on
+ * sweep covers the rest; the results are the same bits.  Everything is enqueued on
  * `stream`; with TM_BWD_STREAMS=2 in the environment the weight-gradient products and the updates go to
  * internal streams that are ordered after everything enqueued on `stream` so far, and `stream` waits for
  * them before the call's work counts as done.  (Shadow iteration, section 4.2:

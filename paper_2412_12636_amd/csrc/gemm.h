@@ -53,6 +53,8 @@ int gemm_mfma_tune(const GemmArgs *variants, int n, hipStream_t s);
 // dw[N,K] = dy[T,N]^T x[T,K] (bf16 operands) with the Adam update of those N*K parameters in the product's
 // epilogue.  `supported` says whether the shapes and pointers allow it (matrix-core path).
 bool linear_wgrad_adam_supported(int64_t T, int64_t N, int64_t K, const void *dy, const void *x, const float *dw);
+// whether that is faster than the product and a flat sweep behind it
+bool linear_wgrad_adam_pays(int64_t T, int64_t N, int64_t K, const float *dw);
 int linear_wgrad_adam(int64_t T, int64_t N, int64_t K, const void *dy, const void *x, float *dw, const AdamTarget &target,
                       hipStream_t s);
 // Configurations with a form for a reduction length that is not a multiple of 64 of an operand with contiguous

@@ -211,6 +211,21 @@ static bool fused_on_large_tiles(const GemmArgs &g) {
   return on && g.K <= max_t && ceil_div(g.M, t.bm) * ceil_div(g.N, t.bn) >= 512;
 }
 
+// The update in the epilogue streams a matrix's state row by row in segments of 32 parameters: whole 128-byte lines only
+// where rows start on one.  Rows that do not make two partial lines of every segment, read and written by different blocks:
+// a backward pass with updates, fused / flat, 7480 wide 1987 / 929 us at 82 tokens and 2330 / 1687 at 2048, 4104 wide 591 / 427
+// and 1006 / 877, 1032 wide 239 / 172 and 411 / 355.
+// A token count that is no multiple of 64 stores its gradients in every gradient mode, so that the epilogue saves only their
+// reading back.  That pays on the large staggered form from some 700 tokens on (12288 wide, fused / flat: 82 tokens 1606 /
+// 1462 us, 500 1914 / 1901, 1000 2299 / 2342, 2000 3191 / 3335; 8192 wide: 500 1306 / 1245, 1000 1596 / 1609), on small tiles
+// nowhere (1024 wide: 82 tokens 236 / 216, 1000 333 / 330, 4000 762 / 747; 4096 wide: 82 tokens 469 / 443, 4000 1809 / 1683).
+bool linear_wgrad_adam_pays(int64_t T, int64_t N, int64_t K, const float *dw) {
+  if (K % 32 != 0 || (((uintptr_t)dw) & 127)) return false;
+  if (T % 64 == 0) return true;
+  GemmArgs g{N, K, T, nullptr, 1, N, nullptr, 1, K, nullptr, K, nullptr, nullptr, 3};
+  return T >= 704 && fused_on_large_tiles(g);
+}
+
 static int pick_config(const GemmArgs &g) {
   const int f = forced_config();
   if (f >= 0) return f;

@@ -628,9 +628,15 @@ static int stage_bwd(tm_stage_t *st, const void *dy_in, void *dx_out, void *stre
   const int64_t act_bytes = d.T * d.h * d.es;
   // tm_stage_bwd_adam with the gradients in overwrite mode: the update of a weight matrix rides in the epilogue of
   // its weight-gradient product (the gradient is still stored, but never read back, and the state streams while
-  // other blocks of the product still multiply); what is left for the flat sweep are the vectors between the
-  // matrices.  TM_ADAM_UNFUSED=1 keeps the whole update in the flat sweep.
-  const bool fuse = hp && acc == 0 && dt == TM_DTYPE_BF16 && !hp->zero_grads && getenv("TM_ADAM_UNFUSED") == nullptr;
+  // other blocks of the product still multiply), where that is the faster way; what is left for the flat sweep are
+  // the vectors between the matrices and the other matrices.  TM_ADAM_UNFUSED=1 keeps the whole update in the flat
+  // sweep, TM_ADAM_UNFUSED=0 fuses every matrix that the kernels take.
+  const char *unfused_env = getenv("TM_ADAM_UNFUSED");
+  const bool fuse_any = unfused_env && unfused_env[0] == '0';
+  const bool fuse = hp && acc == 0 && dt == TM_DTYPE_BF16 && !hp->zero_grads && (!unfused_env || fuse_any);
+  auto fuses = [&](int64_t N, int64_t K, const void *dyp, const void *xp, const float *dw) -> bool {
+    return fuse && linear_wgrad_adam_supported(d.T, N, K, dyp, xp, dw) && (fuse_any || linear_wgrad_adam_pays(d.T, N, K, dw));
+  };
   const AdamScalars ascal = hp ? make_adam_scalars(hp, step) : AdamScalars{};
   struct Range { int64_t first, count; };
   std::vector<Range> fused;  // this layer's matrices already updated, element ranges relative to the layer's block
@@ -641,13 +647,13 @@ static int stage_bwd(tm_stage_t *st, const void *dy_in, void *dx_out, void *stre
   const bool store_grad = st->grad_mode != TM_GRAD_TRANSIENT || d.T % 64 != 0;
   const double fused_bytes_per_param = fuse ? 26.0 + (store_grad ? 4.0 : 0.0) : 0.0;
   auto wgrad_bytes = [&](int64_t N, int64_t K, const void *dyp, const void *xp, int64_t pb, int64_t w_off) -> double {
-    return fuse && linear_wgrad_adam_supported(d.T, N, K, dyp, xp, grads + pb + w_off)
+    return fuses(N, K, dyp, xp, grads + pb + w_off)
                ? fused_bytes_per_param * (double)N * (double)K + es * (double)d.T * (double)(N + K)
                : 0.0;
   };
   auto wgrad = [&](int64_t pb, int64_t w_off, int64_t N, int64_t K, const void *dyp, const void *xp) -> int {
     float *dw = grads + pb + w_off;
-    if (fuse && linear_wgrad_adam_supported(d.T, N, K, dyp, xp, dw)) {
+    if (fuses(N, K, dyp, xp, dw)) {
       AdamTarget t;
       t.master = st->buf.master + pb + w_off;
       t.exp_avg = st->buf.exp_avg + pb + w_off;

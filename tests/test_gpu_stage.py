@@ -175,16 +175,20 @@ def test_tuning_changes_speed_only(env):
 WIDE_RAGGED = si.StageConfig(1, 6152, 2, 2, 128, 4104, 64, 1)
 
 
+@pytest.mark.parametrize("any_shape", [False, True], ids=["where_it_pays", "wherever_it_can"])
 @pytest.mark.parametrize("cfg", [SMALL_GPT.replace(n_layers=3), SMALL_GPT.replace(n_layers=3, seq=192),
                                  SMALL_LLAMA.replace(n_layers=2, seq=256), TINY, WIDE_RAGGED, WIDE_RAGGED.replace(seq=192)],
-                         ids=["fused_ragged_tokens", "fused_into_the_products", "fused_llama", "fp32_flat_sweep",
-                              "fused_large_staggered_ragged_one_step", "fused_large_staggered_ragged_three_steps"])
-def test_backward_with_overlapped_optimizer_equals_the_two_calls(env, cfg):
+                         ids=["ragged_tokens", "whole_steps", "llama", "fp32_flat_sweep",
+                              "large_staggered_ragged_one_step", "large_staggered_ragged_three_steps"])
+def test_backward_with_overlapped_optimizer_equals_the_two_calls(env, monkeypatch, cfg, any_shape):
     """tm_stage_bwd_adam = tm_stage_bwd then tm_adam_step, bit for bit: gradients, master weights, both moments, the
     bf16 copy, the input gradient; two iterations, so that the second forward pass sees updated weights.  The updates
-    of a bf16 stage's matrices ride in the weight-gradient products' epilogues, whatever the token count, and the flat
-    sweep covers the vectors between them; for fp32 stages the flat sweep does it all."""
+    of a bf16 stage's matrices ride in the weight-gradient products' epilogues where that pays or (TM_ADAM_UNFUSED=0)
+    wherever the kernels take it, ragged token counts and rows off the 128-byte lines too, and the flat sweep covers
+    the rest; for fp32 stages the flat sweep does it all."""
     torch, tm = env
+    if any_shape:
+        monkeypatch.setenv("TM_ADAM_UNFUSED", "0")
     flat = si.make_flat_params(cfg)
     x, dy = to_dev(torch, si.make_x(cfg), cfg.dtype), to_dev(torch, si.make_dy(cfg), cfg.dtype)
     a, b = GpuStage(torch, tm, cfg, flat), GpuStage(torch, tm, cfg, flat)
@@ -233,10 +237,7 @@ def test_update_inside_every_tile_configuration(env, monkeypatch, cfg):
     hp = tm.make_hparams(**si.ADAM_DEFAULTS)
 
     def step(config, fused):
-        if fused:
-            monkeypatch.delenv("TM_ADAM_UNFUSED", raising=False)
-        else:
-            monkeypatch.setenv("TM_ADAM_UNFUSED", "1")
+        monkeypatch.setenv("TM_ADAM_UNFUSED", "0" if fused else "1")
         st = GpuStage(torch, tm, cfg, flat)
         tm.tm_stage_grad_mode(st.handle, True)
         st.fwd(x)
@@ -264,6 +265,28 @@ def test_update_inside_every_tile_configuration(env, monkeypatch, cfg):
         got = step(config, True)
         for name, ref in want.items():
             assert torch.equal(got[name], ref), (config, name)
+
+
+@pytest.mark.parametrize("cfg,fused", [
+    (si.StageConfig(1, 256, 2, 2, 128, 512, 64, 1), 4),          # whole steps, rows on 128-byte lines: every matrix
+    (si.StageConfig(1, 256, 2, 2, 128, 512, 65, 1), 0),          # ragged tokens on small tiles: none
+    (si.StageConfig(1, 264, 2, 2, 128, 512, 64, 1), 0),          # rows of 264 off the lines, and what lies behind them
+    (si.StageConfig(1, 8192, 2, 2, 128, 3072, 720, 1), 2),       # ragged tokens, enough of them: the two large matrices
+    (si.StageConfig(1, 8192, 2, 2, 128, 3072, 600, 1), 0)])
+def test_where_the_update_rides_in_the_products(env, cfg, fused):
+    """How many of a layer's four weight-gradient products carry the update."""
+    torch, tm = env
+    flat = si.make_flat_params(cfg)
+    x, dy = to_dev(torch, si.make_x(cfg), cfg.dtype), to_dev(torch, si.make_dy(cfg), cfg.dtype)
+    st = GpuStage(torch, tm, cfg, flat)
+    tm.tm_stage_grad_mode(st.handle, tm.TM_GRAD_TRANSIENT)
+    st.fwd(x)
+    tm.tm_stage_profile_enable(st.handle, True)
+    tm.tm_stage_bwd_adam(st.handle, dy, st.dx, tm.make_hparams(**si.ADAM_DEFAULTS), 1, stream_ptr(torch))
+    torch.cuda.synchronize()
+    kernels = {e["kernel"]: e["launches"] for e in tm.tm_stage_profile_collect(st.handle)}
+    assert sum(n for k, n in kernels.items() if "epi3" in k) == fused, kernels
+    st.close()
 
 
 def test_backward_with_update_rejects_bad_scalars_before_any_launch(env):
