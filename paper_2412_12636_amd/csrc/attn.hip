@@ -1,5 +1,6 @@
 // Causal attention entry points: argument checks and dispatch between the MFMA flash-style
-// kernels (bf16 and fp32, head sizes up to 128) and the plain-ALU kernels (everything else).
+// kernels (bf16 and fp32, head sizes up to 128) and the plain-ALU kernels (everything else,
+// and very short sequences of many walks).
 #include "attn.h"
 #include "../../include/tm_ops.h"
 

@@ -433,7 +433,7 @@ Dims dims_of(const tm_stage_config_t &c) {
 extern "C" int tm_stage_tune(tm_stage_t *st, void *stream) {
   if (!st) return fail(TM_EINVAL, "stage_tune: NULL handle");
   const tm_stage_config_t &c = st->cfg;
-  if (c.dtype != TM_DTYPE_BF16) return TM_OK;  // the fp32 path has one kernel per product
+  if (c.dtype != TM_DTYPE_BF16) return TM_OK;  // the fp32 products choose their tiles by the size alone (gemm_f32.hip)
   const Dims d = dims_of(c);
   hipStream_t s = (hipStream_t)stream;
   char *ws = (char *)st->buf.workspace;

@@ -526,7 +526,7 @@ ATTN_SHAPES = [
     (BF16, 128, 1, 2, 2, 128),   # exactly one block
     (BF16, 1, 1, 1, 1, 128),     # a single position: ctx = v
     (BF16, 200, 1, 2, 1, 64),    # MFMA path with head size 64
-    (BF16, 70, 2, 2, 1, 32),     # plain-ALU path in bf16
+    (BF16, 70, 2, 2, 1, 32),     # MFMA path, the narrowest padded width
     (FP32, 128, 2, 4, 4, 64),    # the tiny preset's attention
     (FP32, 45, 1, 4, 2, 16),
 ]

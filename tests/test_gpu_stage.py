@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 SMALL_GPT = si.StageConfig(2, 256, 2, 2, 128, 512, 200, 2)                     # bf16, ragged sequence, batch 2
 SMALL_LLAMA = si.StageConfig(2, 256, 4, 1, 64, 328, 130, 1, norm=si.NORM_RMSNORM, act=si.ACT_SWIGLU,
                              pos=si.POS_ROTARY, has_bias=0)
-SMALL_ERF = si.StageConfig(1, 128, 2, 2, 32, 256, 40, 1, act=si.ACT_GELU_ERF)   # plain-ALU attention in bf16
+SMALL_ERF = si.StageConfig(1, 128, 2, 2, 32, 256, 40, 1, act=si.ACT_GELU_ERF)   # heads of 32
 TINY = si.PRESETS["tiny"]
 TINY_LLAMA_FP32 = si.StageConfig(1, 64, 4, 2, 16, 96, 33, 2, dtype=si.DTYPE_FP32, norm=si.NORM_RMSNORM,
                                  act=si.ACT_SWIGLU, pos=si.POS_ROTARY, has_bias=0)
