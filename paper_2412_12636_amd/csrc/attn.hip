@@ -1,6 +1,6 @@
 // Causal attention entry points: argument checks and dispatch between the MFMA flash-style
 // kernels (bf16 and fp32, head sizes up to 128) and the plain-ALU kernels (everything else,
-// and very short sequences of many walks).
+// tensors off the 16-byte alignment, and very short sequences of many walks).
 #include "attn.h"
 #include "../../include/tm_ops.h"
 
@@ -42,12 +42,19 @@ static bool rows_pay(int dtype, bool bwd, int64_t seq, int64_t walks, int64_t d)
   return !(dtype == TM_DTYPE_BF16 && d == 128) && seq <= row_kernel_positions(dtype, bwd, walks, d);
 }
 
+// The tiles move 16 bytes at a time.  Tensors off that alignment go to the kernels of one row per wave, which read element by
+// element (but for bf16 with head size 128, which has always had the tiles alone).
+static bool tiles_take(int dtype, int64_t d, const void *a, const void *b) {
+  return (dtype == TM_DTYPE_BF16 && d == 128) || !((((uintptr_t)a) | ((uintptr_t)b)) & 15);
+}
+
 extern "C" int tm_op_attn_fwd(int dtype, int64_t seq, int64_t batch, int64_t nq, int64_t nkv, int64_t d,
                               const void *qkv, void *ctx, float *lse, void *stream) {
   if (int e = check_attn("attn_fwd", dtype, seq, batch, nq, nkv, d)) return e;
   if (!qkv || !ctx || !lse) return fail(TM_EINVAL, "attn_fwd: NULL pointer");
   hipStream_t s = (hipStream_t)stream;
-  if (rows_pay(dtype, false, seq, batch * nq, d)) return attn_fwd_generic_launch(dtype, seq, batch, nq, nkv, d, qkv, ctx, lse, s);
+  if (rows_pay(dtype, false, seq, batch * nq, d) || !tiles_take(dtype, d, qkv, ctx))
+    return attn_fwd_generic_launch(dtype, seq, batch, nq, nkv, d, qkv, ctx, lse, s);
   if (attn_mfma_supported(dtype, seq, batch, nq, nkv, d)) return attn_fwd_mfma_launch(seq, batch, nq, nkv, d, qkv, ctx, lse, s);
   if (attn_f32_supported(dtype, seq, batch, nq, nkv, d)) return attn_fwd_f32_launch(seq, batch, nq, nkv, d, qkv, ctx, lse, s);
   return attn_fwd_generic_launch(dtype, seq, batch, nq, nkv, d, qkv, ctx, lse, s);
@@ -72,7 +79,7 @@ extern "C" int tm_op_attn_bwd(int dtype, int64_t seq, int64_t batch, int64_t nq,
   float *dvec = (float *)scratch;
   float *part = dvec + (batch * nq * seq + 63) / 64 * 64;
   if (int e = attn_dvec_launch(dtype, seq, batch, nq, nkv, d, ctx, dctx, dvec, s)) return e;
-  if (rows_pay(dtype, true, seq, batch * nq, d))
+  if (rows_pay(dtype, true, seq, batch * nq, d) || !tiles_take(dtype, d, qkv, dqkv) || !tiles_take(dtype, d, dctx, dctx))
     return attn_bwd_generic_launch(dtype, seq, batch, nq, nkv, d, qkv, dctx, lse, dvec, dqkv, s);
   if (attn_mfma_supported(dtype, seq, batch, nq, nkv, d))
     return attn_bwd_mfma_launch(seq, batch, nq, nkv, d, qkv, dctx, lse, dvec, part, dqkv, s);

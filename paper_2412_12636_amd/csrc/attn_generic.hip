@@ -1,5 +1,5 @@
-// Causal attention without matrix cores: head sizes above 128, tensors of 2 GiB and more, and very short sequences of many
-// heads and entries (but for bf16 with head size 128).  One wavefront per query row (forward, dQ) or per key row (dK, dV); scores of
+// Causal attention without matrix cores: head sizes above 128, tensors of 2 GiB and more or off the 16-byte alignment, and very
+// short sequences of many heads and entries (the last two but for bf16 with head size 128).  One wavefront per query row (forward, dQ) or per key row (dK, dV); scores of
 // the row live in LDS.  Summation orders are fixed, so results are bit-reproducible.
 #include <math.h>
 
@@ -53,7 +53,8 @@ __global__ __launch_bounds__(64) void attn_fwd_generic(const T *__restrict__ qkv
 // or one where blocks of four leave units idle.  (One wave per row and head left all but d / 2 bytes' worth of lanes idle
 // and launched a block for each: 16384 positions, 8 heads of 128: 34 -> 16 us.  Small calls are bound by a block's own
 // chain, to which 64-bit divisions added 2 us: 64 to 4096 rows of heads of 128, the whole backward pass 10.7 -> 8.7, 12.4 -> 10.5.)
-template <typename T, int G, int ITEMS>
+// ALIGNED false: tensors off the 16-byte alignment, element by element.
+template <typename T, int G, int ITEMS, bool ALIGNED>
 __global__ __launch_bounds__(256) void attn_dvec_kernel(const T *__restrict__ ctx, const T *__restrict__ dctx,
                                                        float *__restrict__ dvec, AttnShape a, int64_t total) {
   constexpr int VN = Vec<T>::N, PER = 256 / G;
@@ -67,8 +68,16 @@ __global__ __launch_bounds__(256) void attn_dvec_kernel(const T *__restrict__ ct
 #pragma unroll
     for (int e = 0; e < VN; ++e) c[k][e] = dc[k][e] = 0.f;
     if (live && item < total) {
-      load_vec<T>(ctx + item * a.d + l * VN, c[k]);
-      load_vec<T>(dctx + item * a.d + l * VN, dc[k]);
+      if constexpr (ALIGNED) {
+        load_vec<T>(ctx + item * a.d + l * VN, c[k]);
+        load_vec<T>(dctx + item * a.d + l * VN, dc[k]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < VN; ++e) {
+          c[k][e] = to_f32(ctx[item * a.d + l * VN + e]);
+          dc[k][e] = to_f32(dctx[item * a.d + l * VN + e]);
+        }
+      }
     }
   }
 #pragma unroll
@@ -100,10 +109,12 @@ template <typename T, int G>
 static void dvec_launch(const AttnShape &a, const void *ctx, const void *dctx, float *dvec, hipStream_t s) {
   const int64_t total = (int64_t)a.seq * a.batch * a.nq;
   const int64_t rows = 256 / G;  // of a block at a time
-  if (total >= 4 * rows * 512)
-    attn_dvec_kernel<T, G, 4><<<(unsigned)ceil_div(total, 4 * rows), 256, 0, s>>>((const T *)ctx, (const T *)dctx, dvec, a, total);
+  if ((((uintptr_t)ctx) | ((uintptr_t)dctx)) & 15)
+    attn_dvec_kernel<T, G, 1, false><<<(unsigned)ceil_div(total, rows), 256, 0, s>>>((const T *)ctx, (const T *)dctx, dvec, a, total);
+  else if (total >= 4 * rows * 512)
+    attn_dvec_kernel<T, G, 4, true><<<(unsigned)ceil_div(total, 4 * rows), 256, 0, s>>>((const T *)ctx, (const T *)dctx, dvec, a, total);
   else
-    attn_dvec_kernel<T, G, 1><<<(unsigned)ceil_div(total, rows), 256, 0, s>>>((const T *)ctx, (const T *)dctx, dvec, a, total);
+    attn_dvec_kernel<T, G, 1, true><<<(unsigned)ceil_div(total, rows), 256, 0, s>>>((const T *)ctx, (const T *)dctx, dvec, a, total);
 }
 template <typename T> static void dvec_t(const AttnShape &a, const void *ctx, const void *dctx, float *dvec, hipStream_t s) {
   const int chunks = a.d / Vec<T>::N;

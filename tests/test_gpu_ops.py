@@ -532,6 +532,44 @@ ATTN_SHAPES = [
 ]
 
 
+@pytest.mark.parametrize("which", ["qkv", "ctx", "dctx", "dqkv", "all"])
+@pytest.mark.parametrize("dtype,seq,batch,nq,nkv,d", [(BF16, 70, 2, 4, 2, 64), (BF16, 40, 1, 2, 1, 256), (FP32, 45, 1, 4, 2, 16)])
+def test_attention_off_the_alignment(env, dtype, seq, batch, nq, nkv, d, which):
+    """Tensors that start one element past a 16-byte boundary: within the stated tolerance of the definition, as the
+    aligned ones are (and no farther than twice that from each other, for the gradients)."""
+    torch, tm = env
+    print(f"attention off the alignment dtype={dtype} seq={seq} d={d} {which}", flush=True)
+    rng = np.random.default_rng(seq + d)
+    A, W = nq * d, (nq + 2 * nkv) * d
+    td, s = torch_dtype(torch, dtype), stream_ptr(torch)
+    qkv, dctx = rand(rng, (seq, batch, W), 1.0, dtype), rand(rng, (seq, batch, A), 0.1, dtype)
+    scratch = torch.empty(tm.tm_op_attn_bwd_scratch_bytes(dtype, seq, batch, nq, nkv, d) // 4, device="cuda")
+
+    def run(off):
+        def place(name, shape, value=None):
+            n = int(np.prod(shape))
+            t = torch.empty(n + 1, dtype=td, device="cuda")[int(name in off):][:n].view(shape)
+            if value is not None:
+                t.copy_(to_dev(torch, value, dtype))
+            return t
+        q, dc = place("qkv", (seq, batch, W), qkv), place("dctx", (seq, batch, A), dctx)
+        ctx, dq = place("ctx", (seq, batch, A)), place("dqkv", (seq, batch, W))
+        lse = torch.empty((batch, nq, seq), device="cuda")
+        tm.tm_op_attn_fwd(dtype, seq, batch, nq, nkv, d, q, ctx, lse, s)
+        tm.tm_op_attn_bwd(dtype, seq, batch, nq, nkv, d, q, ctx, dc, lse, scratch, dq, s)
+        return to_host(ctx), to_host(lse), to_host(dq)
+
+    off = run(("qkv", "ctx", "dctx", "dqkv") if which == "all" else (which,))
+    whole = run(())
+    q64 = qkv.astype(np.float64)
+    ref = so.attention_fwd(q64[..., :A].reshape(seq, batch, nq, d), q64[..., A:A + nkv * d].reshape(seq, batch, nkv, d),
+                           q64[..., A + nkv * d:].reshape(seq, batch, nkv, d)).reshape(seq, batch, A)
+    tol = tol_of(dtype)
+    assert rel_err(off[0], ref) <= tol
+    assert rel_err(off[1], whole[1]) <= 2 * tol
+    assert rel_err(off[2], whole[2]) <= 2 * tol
+
+
 @pytest.mark.parametrize("dtype,seq,batch,nq,nkv,d", ATTN_SHAPES)
 def test_attention_fwd_bwd(env, dtype, seq, batch, nq, nkv, d):
     torch, tm = env
