@@ -10,8 +10,11 @@
 //
 // Bound by the MFMA rate: 64 clocks for 32x32x2, a quarter of a wave's 64x64 tile per pair of reduction elements, for
 // which LDS delivers 16 bytes per clock and unit and L2 eight.  What decides the time of a small product is therefore how
-// evenly its tiles cover the SIMDs: blocks of 128x128, of 64x64, and of 32x32 whose four waves split every step's
-// reduction elements (their sums meet in LDS in wave order).
+// evenly its tiles cover the SIMDs, and how much of the barrier and the LDS latency a second wave of the SIMD covers:
+// blocks of 128x128; of 64x64 and 32x32 with two to four waves a SIMD that split every stage's reduction elements (their
+// sums meet in LDS in wave order); and of 16x16 on 16x16x4 MFMAs, where 32x32 tiles leave most units without one.
+// With one wave a SIMD on every tile before: 1024 x 1024 over 1024 23.1 -> 21.2 us, over 3072 (strided weights) 66.6 -> 56.8;
+// 256 x 256 over 1024 8.2 -> 4.5; 1500 x 768 over 768 25.0 -> 23.9 (weight gradient 31.7 -> 25.1).
 // (The twelve products of a layer of hidden 1024, SwiGLU width 4096, 1024 tokens: 4.9 ms = 21 TFLOP/s on the 64x64
 // plain-ALU tile kernel that this one replaces, 1.03 ms = 100 TFLOP/s here; its largest run at 113, the vendor BLAS reaches
 // 150 on 8192^3.  The matrix cores are busy for 80 to 84 % of the cycles in which a unit has waves on 128x128 tiles, 69 % on
@@ -25,6 +28,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
 
 constexpr int FK = 32;  // reduction elements of a step
+constexpr int64_t kUnits = 256;
 
 struct F32GemmParams {
   int M, N, K;
@@ -33,12 +37,15 @@ struct F32GemmParams {
   float *C;
   int64_t ldc;
   const float *bias, *residual;
-  int tiles_m;
+  int tiles_m, tiles_n, group;
   uint32_t a_bytes, b_bytes, c_bytes;
 };
 
+// Loaders: NW waves fetch a step's tile of R rows.  MF: rows of an MFMA (32: 32x32x2, a lane reads elements 8j + 4hh .. +3;
+// 16: 16x16x4, elements 16j + 4g .. +3, g: quarter of the wave).
+//
 // element (r, k) at base[r*ld + k]; LDS [R][32]
-template <int R, int NW> struct F32KC {
+template <int R, int NW, int MF> struct F32KC {
   static constexpr int NLOAD = R * FK * 4 / 1024 / NW, BYTES = R * FK * 4;
   static __device__ __forceinline__ int swz(int row) { return (row ^ (row >> 3)) & 7; }
   uint32_t voff[NLOAD];
@@ -59,22 +66,24 @@ template <int R, int NW> struct F32KC {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(tile + (i * NW + wave) * 1024), 16,
                                                k0 + chunk[i] < k_end ? voff[i] : 0x80000000u, (uint32_t)k0 * 4u, 0, 0);
   }
-  static __device__ __forceinline__ f32x4 frag(const char *tile, int r32, int j, int lane) {
-    const int r = r32 + (lane & 31), hh = lane >> 5;
-    return *reinterpret_cast<const f32x4 *>(tile + r * FK * 4 + (((2 * j + hh) ^ swz(r)) << 4));
+  static __device__ __forceinline__ f32x4 frag(const char *tile, int r0, int j, int lane) {
+    const int r = r0 + lane % MF;
+    return *reinterpret_cast<const f32x4 *>(tile + r * FK * 4 + (((64 / MF * j + lane / MF) ^ swz(r)) << 4));
   }
 };
 
 // element (r, k) at base[k*ld + r]; LDS [32][R].  The two halves of a wave read k-rows that are four apart: XOR of one
-// chunk bit with k bit 2 sends them to different 128-byte halves (R = 32 has only one).
-template <int R, int NW> struct F32KS {
+// chunk bit with k bit 2 sends them to different 128-byte halves (R = 32 has only one).  R = 16: the four quarters of a wave
+// read rows of 64 bytes that are four apart; row 4a + b of each 16 sits at 4b + a, so that they lie side by side.
+template <int R, int NW, int MF> struct F32KS {
   static constexpr int CPR = R / 4, NLOAD = R * FK * 4 / 1024 / NW, BYTES = R * FK * 4;
   static __device__ __forceinline__ int swz(int kk) { return CPR >= 16 ? ((kk >> 2) & 1) << 3 : 0; }
+  static __device__ __forceinline__ int slot(int kk) { return R == 16 ? (kk & 16) | ((kk & 3) << 2) | ((kk >> 2) & 3) : kk; }
   uint32_t voff[NLOAD];
   __device__ __forceinline__ void init(int64_t ld, int row0, int, int wave, int lane) {
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i) {
-      const int idx = (i * NW + wave) * 64 + lane, kk = idx / CPR, c = (idx % CPR) ^ swz(kk);
+      const int idx = (i * NW + wave) * 64 + lane, kk = slot(idx / CPR), c = (idx % CPR) ^ swz(kk);
       voff[i] = (uint32_t)(((int64_t)kk * ld + row0 + c * 4) * 4);
     }
   }
@@ -84,55 +93,88 @@ template <int R, int NW> struct F32KS {
     for (int i = 0; i < NLOAD; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(tile + (i * NW + wave) * 1024), 16, voff[i] + koff, 0, 0, 0);
   }
-  static __device__ __forceinline__ f32x4 frag(const char *tile, int r32, int j, int lane) {
-    const int r = r32 + (lane & 31), hh = lane >> 5;
+  static __device__ __forceinline__ f32x4 frag(const char *tile, int r0, int j, int lane) {
+    const int r = r0 + lane % MF, g = lane / MF;
     f32x4 x;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int kk = 8 * j + 4 * hh + i;
-      x[i] = *reinterpret_cast<const float *>(tile + kk * R * 4 + (((r >> 2) ^ swz(4 * hh)) << 4) + ((r & 3) << 2));
+      const int kk = 256 / MF * j + 4 * g + i;
+      x[i] = *reinterpret_cast<const float *>(tile + slot(kk) * R * 4 + (((r >> 2) ^ swz(4 * g)) << 4) + ((r & 3) << 2));
     }
     return x;
   }
 };
-template <int R, int NW, bool KC> struct F32Sel { typedef F32KC<R, NW> type; };
-template <int R, int NW> struct F32Sel<R, NW, false> { typedef F32KS<R, NW> type; };
+template <int R, int NW, int MF, bool KC> struct F32Sel { typedef F32KC<R, NW, MF> type; };
+template <int R, int NW, int MF> struct F32Sel<R, NW, MF, false> { typedef F32KS<R, NW, MF> type; };
+template <int MF> struct F32Mma {
+  static constexpr int NV = 16;
+  typedef f32x16 acc_t;
+  static __device__ __forceinline__ f32x16 mma(float a, float b, f32x16 c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+  static __device__ __forceinline__ int row(int v, int lane) { return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
+};
+template <> struct F32Mma<16> {
+  static constexpr int NV = 4;
+  typedef f32x4 acc_t;
+  static __device__ __forceinline__ f32x4 mma(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+  static __device__ __forceinline__ int row(int v, int lane) { return 4 * (lane >> 4) + v; }
+};
 
-// WM, WN: wave tile; KSPL: waves that split a step's reduction elements; NS: LDS stages; SUB: steps of a stage, for tiles
-// whose single step is shorter than the barrier and the LDS latency around it
+// WM, WN: wave tile (below 32: 16x16 MFMAs); KSPL: waves that split a stage's reduction elements; NS: LDS stages; SUB: steps
+// of a stage, for tiles whose single step is shorter than the barrier and the LDS latency around it
+template <int BM, int BN, int WM, int WN, int KSPL, int NS, int SUB> struct F32Cfg {
+  static constexpr int MF = WM < 32 ? 16 : 32, NT = (BM / WM) * (BN / WN), NW = NT * KSPL;
+  static constexpr int TM = WM / MF, TN = WN / MF, NV = F32Mma<MF>::NV;
+  // a step of a small tile is fewer wave-wide loads than there are waves: groups of LW waves fetch alternate steps
+  static constexpr int LW = NW * 1024 <= (BM < BN ? BM : BN) * FK * 4 ? NW : (BM < BN ? BM : BN) * FK * 4 / 1024, UG = NW / LW;
+  static constexpr int STEP = (BM + BN) * FK * 4, STAGE = SUB * STEP, J = 4 * MF / 32;  // fragments of four elements a step
+  static constexpr int SUMS = KSPL > 1 ? NW * NV * 256 : 0, LDS = NS * STAGE > SUMS ? NS * STAGE : SUMS;
+  static_assert(KSPL == 1 || (TM == 1 && TN == 1 && NV % KSPL == 0), "split waves hold one tile each");
+  static_assert(SUB % UG == 0 && SUB * J % KSPL == 0, "steps divide among the waves");
+};
 template <int BM, int BN, int WM, int WN, int KSPL, int NS, int SUB, bool A_KC, bool B_KC, int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const F32GemmParams p) {
-  constexpr int NW = (BM / WM) * (BN / WN) * KSPL, TM = WM / 32, TN = WN / 32;
-  static_assert(NW == 4, "four waves");
-  static_assert(KSPL == 1 || (KSPL == 4 && TM == 1 && TN == 1), "split waves hold one tile each");
-  typedef typename F32Sel<BM, NW, A_KC>::type LA;
-  typedef typename F32Sel<BN, NW, B_KC>::type LB;
-  constexpr int STEP = LA::BYTES + LB::BYTES, STAGE = SUB * STEP, LOADS = SUB * (LA::NLOAD + LB::NLOAD);
+__global__ __launch_bounds__((64 * F32Cfg<BM, BN, WM, WN, KSPL, NS, SUB>::NW)) void gemm_f32_kernel(const F32GemmParams p) {
+  typedef F32Cfg<BM, BN, WM, WN, KSPL, NS, SUB> C;
+  typedef F32Mma<C::MF> MM;
+  constexpr int MF = C::MF, TM = C::TM, TN = C::TN, NT = C::NT, LW = C::LW, UG = C::UG, NV = C::NV;
+  typedef typename F32Sel<BM, LW, MF, A_KC>::type LA;
+  typedef typename F32Sel<BN, LW, MF, B_KC>::type LB;
+  constexpr int LOADS = SUB / UG * (LA::NLOAD + LB::NLOAD);
   extern __shared__ __align__(1024) char lds[];
-  const int m0 = (int)(blockIdx.x % p.tiles_m) * BM, n0 = (int)(blockIdx.x / p.tiles_m) * BN;
+  int m0, n0;
+  if (p.group) {  // several blocks a unit: an XCD (ids round-robin over eight) owns a range of tiles, walked in patches
+    const int nblk = gridDim.x, xcd = blockIdx.x % 8, base = nblk / 8, rem = nblk % 8;
+    const int lid = xcd * base + (xcd < rem ? xcd : rem) + (int)(blockIdx.x / 8);
+    const int gi = lid / (p.group * p.tiles_n), first = gi * p.group, in_group = lid - first * p.tiles_n;
+    const int rows = p.tiles_m - first < p.group ? p.tiles_m - first : p.group;
+    m0 = (first + in_group % rows) * BM;
+    n0 = (in_group / rows) * BN;
+  } else {
+    m0 = (int)(blockIdx.x % p.tiles_m) * BM;
+    n0 = (int)(blockIdx.x / p.tiles_m) * BN;
+  }
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int ks = KSPL > 1 ? wave : 0, wt = KSPL > 1 ? 0 : wave;
+  const int ks = wave / NT, wt = wave % NT, lw = wave % LW, lu = wave / LW;
   const int wm = (wt / (BN / WN)) * WM, wn = (wt % (BN / WN)) * WN;
   LA la;
   LB lb;
   const rsrc_t ra = make_rsrc(p.A, p.a_bytes), rb = make_rsrc(p.B, p.b_bytes);
-  la.init(p.lda, m0, p.K, wave, lane);
-  lb.init(p.ldb, n0, p.K, wave, lane);
-  f32x16 acc[TM][TN];
+  la.init(p.lda, m0, p.K, lw, lane);
+  lb.init(p.ldb, n0, p.K, lw, lane);
+  typename MM::acc_t acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+      for (int v = 0; v < NV; ++v) acc[i][j][v] = 0.f;
   const int nk = (p.K + SUB * FK - 1) / (SUB * FK);
   auto issue = [&](int stage) {  // steps past the end of the reduction read as zero
-    char *st = lds + (stage % NS) * STAGE;
+    char *st = lds + (stage % NS) * C::STAGE;
 #pragma unroll
-    for (int u = 0; u < SUB; ++u) {
-      const int k0 = (stage * SUB + u) * FK;
-      la.issue(ra, st + u * STEP, k0, p.lda, wave);
-      lb.issue(rb, st + u * STEP + LA::BYTES, k0, p.ldb, wave);
+    for (int i = 0; i < SUB / UG; ++i) {
+      const int u = i * UG + lu, k0 = (stage * SUB + u) * FK;
+      la.issue(ra, st + u * C::STEP, k0, p.lda, lw);
+      lb.issue(rb, st + u * C::STEP + LA::BYTES, k0, p.ldb, lw);
     }
   };
 #pragma unroll
@@ -142,65 +184,63 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const F32GemmParams p) {
     __builtin_amdgcn_s_barrier();  // everyone's have; everyone has read stage kt - 1
     issue(kt + NS - 1);
 #pragma unroll
-    for (int jj = 0; jj < SUB * (4 / KSPL); ++jj) {
-      const char *As = lds + (kt % NS) * STAGE + (jj / (4 / KSPL)) * STEP, *Bs = As + LA::BYTES;
-      const int j = KSPL > 1 ? ks : jj % 4;
+    for (int i0 = 0; i0 < SUB * C::J / KSPL; ++i0) {
+      const int jj = i0 * KSPL + ks, j = jj % C::J;
+      const char *As = lds + (kt % NS) * C::STAGE + (jj / C::J) * C::STEP, *Bs = As + LA::BYTES;
       f32x4 a[TM], b[TN];
 #pragma unroll
-      for (int t = 0; t < TM; ++t) a[t] = LA::frag(As, wm + t * 32, j, lane);
+      for (int t = 0; t < TM; ++t) a[t] = LA::frag(As, wm + t * MF, j, lane);
 #pragma unroll
-      for (int t = 0; t < TN; ++t) b[t] = LB::frag(Bs, wn + t * 32, j, lane);
+      for (int t = 0; t < TN; ++t) b[t] = LB::frag(Bs, wn + t * MF, j, lane);
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-          for (int tn = 0; tn < TN; ++tn) acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[tm][i], b[tn][i], acc[tm][tn], 0, 0, 0);
+          for (int tn = 0; tn < TN; ++tn) acc[tm][tn] = MM::mma(a[tm][i], b[tn][i], acc[tm][tn]);
     }
   }
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // the look-ahead loads, before LDS is reused or the block exits
 
-  const int l32 = lane & 31, hh = lane >> 5;
-  int v_first = 0, v_count = 16;
-  if constexpr (KSPL > 1) {  // wave w finishes registers 4w .. 4w+3 of the tile, over all waves in wave order
+  constexpr int VC = NV / KSPL;
+  const int v_first = ks * VC;
+  if constexpr (KSPL > 1) {  // a wave finishes VC registers of its tile, over all split waves in order
     __syncthreads();
     float *x = reinterpret_cast<float *>(lds);
 #pragma unroll
-    for (int v = 0; v < 16; ++v) x[(wave * 16 + v) * 64 + lane] = acc[0][0][v];
+    for (int v = 0; v < NV; ++v) x[(wave * NV + v) * 64 + lane] = acc[0][0][v];
     __syncthreads();
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      float s = x[(4 * wave + e) * 64 + lane];
+    for (int e = 0; e < VC; ++e) {
+      float s = x[(wt * NV + v_first + e) * 64 + lane];
 #pragma unroll
-      for (int w = 1; w < 4; ++w) s += x[(w * 16 + 4 * wave + e) * 64 + lane];
+      for (int w = 1; w < KSPL; ++w) s += x[((w * NT + wt) * NV + v_first + e) * 64 + lane];
       acc[0][0][e] = s;
     }
-    v_first = 4 * wave;
-    v_count = 4;
   }
   const rsrc_t rc = make_rsrc(p.C, p.c_bytes);
   const rsrc_t rres = make_rsrc(p.residual ? (const void *)p.residual : p.C, p.c_bytes);
 #pragma unroll
   for (int tn = 0; tn < TN; ++tn) {
-    const int col = n0 + wn + tn * 32 + l32;
+    const int col = n0 + wn + tn * MF + lane % MF;
     const float bias = EPI == 0 && p.bias && col < p.N ? p.bias[col] : 0.f;
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
-      uint32_t off[16];
-      float old[16];
+      uint32_t off[VC];
+      float old[VC];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int v = v_first + e, row = m0 + wm + tm * 32 + 8 * (v >> 2) + 4 * hh + (v & 3);
-        off[e] = e < v_count && col < p.N && row < p.M ? (uint32_t)(((int64_t)row * p.ldc + col) * 4) : 0xfffffff0u;
+      for (int e = 0; e < VC; ++e) {
+        const int row = m0 + wm + tm * MF + MM::row(v_first + e, lane);
+        off[e] = col < p.N && row < p.M ? (uint32_t)(((int64_t)row * p.ldc + col) * 4) : 0xfffffff0u;
         old[e] = 0.f;
       }
       if (EPI == 1 || (EPI == 0 && p.residual)) {
 #pragma unroll
-        for (int e = 0; e < (KSPL > 1 ? 4 : 16); ++e)
+        for (int e = 0; e < VC; ++e)
           old[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(EPI == 1 ? rc : rres, off[e], 0, 0));
       }
 #pragma unroll
-      for (int e = 0; e < (KSPL > 1 ? 4 : 16); ++e) {
+      for (int e = 0; e < VC; ++e) {
         const float o = EPI == 0 ? (acc[tm][tn][e] + bias) + old[e] : old[e] + acc[tm][tn][e];
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, o), rc, off[e], 0, 0);
       }
@@ -208,10 +248,12 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const F32GemmParams p) {
   }
 }
 
-#define TM_F32_GEMM(AKC, BKC, EPI)                                                             \
+#define TM_F32_GEMM(AKC, BKC, EPI)                                                                         \
   template __global__ void gemm_f32_kernel<128, 128, 64, 64, 1, 2, 1, AKC, BKC, EPI>(const F32GemmParams); \
-  template __global__ void gemm_f32_kernel<64, 64, 32, 32, 1, 3, 1, AKC, BKC, EPI>(const F32GemmParams);   \
-  template __global__ void gemm_f32_kernel<32, 32, 32, 32, 4, 4, 2, AKC, BKC, EPI>(const F32GemmParams);
+  template __global__ void gemm_f32_kernel<64, 64, 32, 32, 2, 3, 1, AKC, BKC, EPI>(const F32GemmParams);   \
+  template __global__ void gemm_f32_kernel<64, 64, 32, 32, 4, 3, 2, AKC, BKC, EPI>(const F32GemmParams);   \
+  template __global__ void gemm_f32_kernel<32, 32, 32, 32, 8, 4, 2, AKC, BKC, EPI>(const F32GemmParams);   \
+  template __global__ void gemm_f32_kernel<16, 16, 16, 16, 4, 4, 4, AKC, BKC, EPI>(const F32GemmParams);
 TM_F32_GEMM(true, true, 0)
 TM_F32_GEMM(true, false, 0)
 TM_F32_GEMM(false, false, 1)
@@ -246,11 +288,12 @@ static int launch(const GemmArgs &g, hipStream_t s) {
   p.bias = (const float *)g.bias;
   p.residual = (const float *)g.residual;
   p.tiles_m = (int)ceil_div(g.M, BM);
+  p.tiles_n = (int)ceil_div(g.N, BN);
   p.a_bytes = (uint32_t)((A_KC ? g.M * g.a_rs : g.K * g.a_cs) * 4);
   p.b_bytes = (uint32_t)((B_KC ? g.N * g.b_rs : g.K * g.b_cs) * 4);
   p.c_bytes = (uint32_t)(g.M * g.ldc * 4);
-  constexpr int stages = NS * SUB * (BM + BN) * FK * 4, sums = KSPL > 1 ? 4 * 16 * 64 * 4 : 0;
-  constexpr int lds = stages > sums ? stages : sums;
+  typedef F32Cfg<BM, BN, WM, WN, KSPL, NS, SUB> C;
+  constexpr int lds = C::LDS;
   static bool attr_set = false;  // per instantiation
   if (!attr_set && hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_f32_kernel<BM, BN, WM, WN, KSPL, NS, SUB, A_KC, B_KC, EPI>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
@@ -258,19 +301,30 @@ static int launch(const GemmArgs &g, hipStream_t s) {
   attr_set = true;
   const int64_t blocks = (int64_t)p.tiles_m * ceil_div(g.N, BN);
   if (blocks > 0x7fffffff) return fail(TM_ESIZE, "gemm_f32: too many tiles");
+  // patches of 8 row-tiles: 1024 x 8192 over 1024 138 -> 131 us, its weight gradient 138 -> 128, 64 x 2048 over 2048 (16x16
+  // tiles, strided weights) 23 -> 10.  One block a unit is faster in plain order (1024 x 1024 over 4096 76 us, 80 in patches).
+  p.group = blocks > kUnits ? 8 : 0;
   g_last_kernel = "gemm_f32_kernel";
-  gemm_f32_kernel<BM, BN, WM, WN, KSPL, NS, SUB, A_KC, B_KC, EPI><<<(unsigned)blocks, 256, lds, s>>>(p);
+  gemm_f32_kernel<BM, BN, WM, WN, KSPL, NS, SUB, A_KC, B_KC, EPI><<<(unsigned)blocks, 64 * C::NW, lds, s>>>(p);
   return check_launch("gemm_f32");
 }
 
 // A block's time is its share of the MFMA rate, BM * BN per step, and a unit works through ceil(blocks / 256) of them;
-// the smaller tiles read LDS and synchronise more per MFMA (factors measured on products that fill the chip).
+// the smaller tiles read LDS and synchronise more per MFMA, and so does a unit with one block alone.  Factors from 45
+// products of 40 to 2048 rows and 136 to 8192 columns, on which the pick is the fastest tile or within 2 % of it.
 template <bool A_KC, bool B_KC, int EPI> static int pick(const GemmArgs &g, hipStream_t s) {
-  auto cost = [&](int64_t b, double factor) { return (double)ceil_div(ceil_div(g.M, b) * ceil_div(g.N, b), (int64_t)256) * b * b * factor; };
-  const double c128 = cost(128, 1.0), c64 = cost(64, 1.1), c32 = cost(32, 1.5);
-  if (c128 <= c64 && c128 <= c32) return launch<128, 128, 64, 64, 1, 2, 1, A_KC, B_KC, EPI>(g, s);
-  if (c64 <= c32) return launch<64, 64, 32, 32, 1, 3, 1, A_KC, B_KC, EPI>(g, s);
-  return launch<32, 32, 32, 32, 4, 4, 2, A_KC, B_KC, EPI>(g, s);
+  auto tiles = [&](int64_t b) { return ceil_div(g.M, b) * ceil_div(g.N, b); };
+  auto cost = [&](int64_t b, double factor) { return (double)ceil_div(tiles(b), kUnits) * b * b * factor; };
+  // the last stage of the 16x16 form reaches 4 FK rows past a strided operand's end: their offsets must not come round to its front
+  auto reaches = [&](int64_t cs) { return cs == 1 || (g.K + 4 * FK) * cs * 4 < (1LL << 32); };
+  const bool one64 = tiles(64) <= kUnits;  // four waves a SIMD make up for the other blocks (1024 x 1024 over 1024: 23.2 -> 21.2 us)
+  const double c128 = cost(128, tiles(128) <= kUnits ? 1.12 : 1.0), c64 = cost(64, one64 ? 1.33 : 1.15), c32 = cost(32, 1.4);
+  const double c16 = reaches(g.a_cs) && reaches(g.b_cs) ? cost(16, 2.0) : c32 + 1;
+  if (c128 <= c64 && c128 <= c32 && c128 <= c16) return launch<128, 128, 64, 64, 1, 2, 1, A_KC, B_KC, EPI>(g, s);
+  if (c64 <= c32 && c64 <= c16)
+    return one64 ? launch<64, 64, 32, 32, 4, 3, 2, A_KC, B_KC, EPI>(g, s) : launch<64, 64, 32, 32, 2, 3, 1, A_KC, B_KC, EPI>(g, s);
+  if (c32 <= c16) return launch<32, 32, 32, 32, 8, 4, 2, A_KC, B_KC, EPI>(g, s);
+  return launch<16, 16, 16, 16, 4, 4, 4, A_KC, B_KC, EPI>(g, s);
 }
 
 int gemm_f32(const GemmArgs &g, hipStream_t s) {

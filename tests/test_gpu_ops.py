@@ -187,6 +187,34 @@ def test_linear_fp32_tiles(env, T, N, K):
     assert np.array_equal(yb[:T].cpu().numpy()[rows], y[:T].cpu().numpy()[rows])
 
 
+@pytest.mark.parametrize("T,N,K", [(16, 16, 128), (17, 24, 136), (40, 136, 264), (250, 248, 1000), (64, 2048, 72), (577, 520, 1032), (1000, 1032, 328),
+                                   (1090, 1032, 136)],
+                         ids=["one_16", "tiles_of_16_ragged", "tiles_of_16", "tiles_of_16_long", "tiles_of_16_patches", "one_64_a_unit", "one_64_a_unit_ragged",
+                              "patches_of_64"])
+def test_linear_fp32_split_waves(env, T, N, K):
+    """The fp32 products whose waves split a stage's reduction elements (16x16, 32x32 and 64x64 tiles), at the ends of tiles
+    and stages, in plain and in patch order: an fp32 sum of n products is off by at most n 2^-24 of the sum of their
+    magnitudes and by about sqrt(n) 2^-24 for these signs, 2e-6 at 1032 terms; stored and added to."""
+    torch, tm = env
+    print(f"linear fp32 split waves T={T} N={N} K={K}", flush=True)
+    rng = np.random.default_rng(T + N + K)
+    x, w, dy = rand(rng, (T, K), 1.0, FP32), rand(rng, (N, K), 0.05, FP32), rand(rng, (T, N), 0.1, FP32)
+    bias, res, g0 = rand(rng, (N,), 0.5, FP32), rand(rng, (T, N), 1.0, FP32), rand(rng, (N, K), 1.0, FP32)
+    xd, wd, dyd, bd, rd = (to_dev(torch, a, FP32) for a in (x, w, dy, bias, res))
+    s = stream_ptr(torch)
+    y, dx, dw0 = (torch.full((r + 1, c), 7.0, device="cuda") for r, c in ((T, N), (T, K), (N, K)))  # one row more: stays as it is
+    dw1 = torch.full((N + 1, K), 7.0, device="cuda")
+    dw1[:N].copy_(to_dev(torch, g0, FP32))
+    tm.tm_op_linear_fwd(FP32, T, N, K, xd, wd, bd, rd, y, s)
+    tm.tm_op_linear_dgrad(FP32, T, N, K, dyd, wd, dx, s)
+    tm.tm_op_linear_wgrad(FP32, T, N, K, dyd, xd, dw0, 0, s)
+    tm.tm_op_linear_wgrad(FP32, T, N, K, dyd, xd, dw1, 1, s)
+    x64, w64, dy64 = (a.astype(np.float64) for a in (x, w, dy))
+    for got, ref, n in ((y, x64 @ w64.T + bias + res, T), (dx, dy64 @ w64, T), (dw0, dy64.T @ x64, N), (dw1, g0 + dy64.T @ x64, N)):
+        assert rel_err(to_host(got[:n]), ref) <= 2e-6
+        assert bool((got[n:] == 7.0).all())
+
+
 def split_gradient(env, T, N, K, seed, splits):
     """dx = dy W with scratch: whether the reduction was split shows in the scratch, which is filled before; the result meets
     the tolerance against the definition, is reproducible and independent of what the scratch held; without scratch the call
