@@ -7,9 +7,10 @@
 // IS the operand of one MFMA: register v holds rows 8(v/4) + v%4 (first half) and the row 4 further on (second half).
 //
 // A block is four waves: two groups of 32 rows that it owns, times two sides that take the even and the odd 32-row tiles
-// of its walk and meet through LDS at the end in a fixed order.  (Short sequences and few heads leave most SIMDs without
-// a wave, so the walk is split rather than the block made larger.)  A tile is [32 rows][DP] fp32, fetched straight into
-// LDS by one wave (DP = head size rounded up to 32; columns and rows past the tensor read as zero), double buffered.
+// of its walk and meet through LDS at the end in a fixed order; or one group times four sides.  (Short sequences and few
+// heads leave most SIMDs without a wave, so the walk is split rather than the block made larger.)  A tile is [32 rows][DP]
+// fp32, fetched straight into LDS by one wave (DP = head size rounded up to 32; columns and rows past the tensor read as
+// zero), double buffered (the wide head sizes on four sides: one buffer).
 //
 // Bound by the MFMA rate, 64 clocks each, DP of them per tile and wave in the forward pass against about 150 vector
 // instructions and LDS reads of one 16-byte or four 4-byte words per four MFMAs, and by how few waves a short sequence
@@ -28,7 +29,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
 
 constexpr int FT = 32;   // rows of a staged tile
-constexpr int FB = 64;   // rows a block owns
 constexpr float kLog2ef = 1.4426950408889634f;
 
 struct F32Params {
@@ -136,41 +136,59 @@ template <int DP> __device__ __forceinline__ void f32_store(const f32x16 (&acc)[
     }
 }
 __device__ __forceinline__ void f32_wait_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-// the second side's accumulators are added to the first's through LDS (x: this group's [DP / 32][16][64] floats)
-template <int DP> __device__ __forceinline__ void f32_join(f32x16 (&acc)[DP / 32], float *x, int side, int lane) {
+
+// How a block's four waves share its walk.  SIDES = 2: two groups of 32 rows, each with an even and an odd side; a wave
+// fetches one of a step's four tiles.  SIDES = 4: one group, every wave takes each fourth tile and fetches its own, so the
+// waves meet only at the end.
+template <int DP, int SIDES> struct F32Walk {
+  static constexpr int GROUPS = 4 / SIDES, FB = 32 * GROUPS;  // FB: rows a block owns
+  static constexpr int NST = SIDES == 2 || DP <= 64 ? 2 : 1;  // LDS stages
+  static constexpr int TILES = NST * SIDES * 2 * F32Tile<DP>::BYTES;
+  static constexpr int LDS = TILES + NST * SIDES * 2 * FT * (int)sizeof(float);  // and the row statistics of dK / dV
+  static_assert((SIDES - 1) * GROUPS * (DP / 2 + 2) * 256 <= TILES, "the sides' sums fit where the tiles were");
+  // the next step's loads may be issued behind this: everyone who uses a tile of that stage is done with it
+  static __device__ __forceinline__ void publish() {
+    if constexpr (SIDES == 2) __syncthreads();
+    else asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  }
+};
+// the later sides' accumulators are added to the first's through LDS in order (x: this group's [side][DP / 32][16][64] floats)
+template <int DP, int SIDES> __device__ __forceinline__ void f32_join(f32x16 (&acc)[DP / 32], float *x, int side, int lane) {
   __syncthreads();
-  if (side == 1) {
+  if (side > 0) {
 #pragma unroll
     for (int dt = 0; dt < DP / 32; ++dt)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) x[(dt * 16 + v) * 64 + lane] = acc[dt][v];
+      for (int v = 0; v < 16; ++v) x[((side - 1) * (DP / 2) + dt * 16 + v) * 64 + lane] = acc[dt][v];
   }
   __syncthreads();
   if (side == 0) {
 #pragma unroll
-    for (int dt = 0; dt < DP / 32; ++dt)
+    for (int o = 0; o < SIDES - 1; ++o)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[dt][v] += x[(dt * 16 + v) * 64 + lane];
+      for (int dt = 0; dt < DP / 32; ++dt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[dt][v] += x[(o * (DP / 2) + dt * 16 + v) * 64 + lane];
   }
 }
 
-template <int DP> constexpr int kF32Lds = 2 * 4 * F32Tile<DP>::BYTES + 2 * 2 * 2 * FT * (int)sizeof(float);
-
-// ---- forward: block = 64 query rows of one (batch entry, query head) ----------------------------------
-template <int DP> __global__ __launch_bounds__(256, 1) void f32_fwd_kernel(const F32Params p) {
+// ---- forward: block = FB query rows of one (batch entry, query head) ----------------------------------
+template <int DP, int SIDES> __global__ __launch_bounds__(256, 1) void f32_fwd_kernel(const F32Params p) {
   extern __shared__ __align__(1024) char smem[];  // [stage][side][K, V]
   using F = F32Tile<DP>;
+  using W = F32Walk<DP, SIDES>;
+  constexpr int FB = W::FB, NST = W::NST;
   const int qt = gridDim.z - 1 - blockIdx.z, g = blockIdx.x, n = blockIdx.y;  // heads fastest, longest walks first
   const int kap = g / (p.nq / p.nkv), d = p.d;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int grp = wave & 1, side = wave >> 1, l32 = lane & 31, hh = lane >> 5;
+  const int grp = wave % W::GROUPS, side = wave / W::GROUPS, l32 = lane & 31, hh = lane >> 5;
   const int q0w = qt * FB + grp * 32, q = q0w + l32;
   const int64_t ts = (int64_t)p.batch * p.row;
   const int koff = (p.nq + kap) * d, voff = (p.nq + p.nkv + kap) * d;
   const rsrc_t rs = make_rsrc(p.qkv, p.qkv_bytes);
   F32Loader<DP> ld;
   ld.init(ts, d, lane);
-  auto tile = [&](int stage, int s, int which) { return smem + ((stage * 2 + s) * 2 + which) * F::BYTES; };
+  auto tile = [&](int stage, int s, int which) { return smem + ((stage * SIDES + s) * 2 + which) * F::BYTES; };
   f32x4 qf[DP / 8];
   f32_row_frags<DP>(p.qkv + (int64_t)n * p.row + (int64_t)q * ts + g * d, q < p.seq, d, hh, qf);
   f32x16 o[DP / 32];
@@ -180,17 +198,25 @@ template <int DP> __global__ __launch_bounds__(256, 1) void f32_fwd_kernel(const
   const float sc2 = p.scale * kLog2ef;
   const uint32_t cb = f32_cols_base<DP>(lane);
   const int kv_end = qt * FB + FB < p.seq ? qt * FB + FB : p.seq;
-  const int ntile = (kv_end + FT - 1) / FT, nstep = (ntile + 1) / 2;
-  auto issue_step = [&](int step, int stage) {  // wave: one tile of side wave / 2, K or V; none past the walk's end
-    const int s = wave >> 1, which = wave & 1, jt = 2 * step + s;
-    if (jt < ntile) ld.issue(rs, tile(stage, s, which), (int64_t)jt * FT * ts, (int64_t)n * p.row + (which ? voff : koff));
+  const int ntile = (kv_end + FT - 1) / FT, nstep = (ntile + SIDES - 1) / SIDES;
+  auto issue_step = [&](int step, int stage) {  // no tile past the walk's end
+    if constexpr (SIDES == 2) {
+      const int s = wave >> 1, which = wave & 1, jt = 2 * step + s;
+      if (jt < ntile) ld.issue(rs, tile(stage, s, which), (int64_t)jt * FT * ts, (int64_t)n * p.row + (which ? voff : koff));
+    } else {
+      const int jt = SIDES * step + side;
+      if (jt < ntile) {
+        ld.issue(rs, tile(stage, side, 0), (int64_t)jt * FT * ts, (int64_t)n * p.row + koff);
+        ld.issue(rs, tile(stage, side, 1), (int64_t)jt * FT * ts, (int64_t)n * p.row + voff);
+      }
+    }
   };
   issue_step(0, 0);
   for (int step = 0; step < nstep; ++step) {
-    const int cur = step & 1, jt = 2 * step + side, j0 = jt * FT;
+    const int cur = NST == 2 ? step & 1 : 0, jt = SIDES * step + side, j0 = jt * FT;
     f32_wait_loads();
-    __syncthreads();  // this step's tiles are in LDS; everyone is done with the other stage
-    if (step + 1 < nstep) issue_step(step + 1, cur ^ 1);
+    W::publish();  // this step's tiles are in LDS; everyone is done with the other stage
+    if (NST == 2 && step + 1 < nstep) issue_step(step + 1, cur ^ 1);
     if (jt >= ntile || j0 > q0w + 31) continue;
     f32x16 s = f32_scores<DP>(tile(cur, side, 0), qf, lane);
     if (j0 + FT - 1 > q0w) {  // wave-uniform: only the tiles on the diagonal
@@ -216,28 +242,44 @@ template <int DP> __global__ __launch_bounds__(256, 1) void f32_fwd_kernel(const
       l += s[v];
     }
     f32_accumulate<DP>(tile(cur, side, 1), cb, s, o);
+    if (NST == 1 && step + 1 < nstep) {
+      W::publish();
+      issue_step(step + 1, 0);
+    }
   }
   f32_wait_loads();
   __syncthreads();
-  float *x = reinterpret_cast<float *>(smem) + (size_t)grp * (DP / 2 + 2) * 64;  // [o..., m, l][lane]
-  if (side == 1) {
+  float *x = reinterpret_cast<float *>(smem) + (size_t)grp * (SIDES - 1) * (DP / 2 + 2) * 64;  // [side][o..., m, l][lane]
+  if (side > 0) {
+    float *xs = x + (side - 1) * (DP / 2 + 2) * 64;
 #pragma unroll
     for (int dt = 0; dt < DP / 32; ++dt)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) x[(dt * 16 + v) * 64 + lane] = o[dt][v];
-    x[(DP / 2) * 64 + lane] = m;
-    x[(DP / 2 + 1) * 64 + lane] = l;
+      for (int v = 0; v < 16; ++v) xs[(dt * 16 + v) * 64 + lane] = o[dt][v];
+    xs[(DP / 2) * 64 + lane] = m;
+    xs[(DP / 2 + 1) * 64 + lane] = l;
   }
   __syncthreads();
   if (side == 0) {
-    const float m2 = x[(DP / 2) * 64 + lane], l2 = x[(DP / 2 + 1) * 64 + lane];
-    const float mm = fmaxf(m, m2);  // m is finite: the even side always has key tile 0
-    const float a1 = __builtin_amdgcn_exp2f(m - mm), a2 = __builtin_amdgcn_exp2f(m2 - mm);
-    l = l * a1 + l2 * a2;
+    float mm = m;  // finite: the first side always has key tile 0
+#pragma unroll
+    for (int t = 0; t < SIDES - 1; ++t) mm = fmaxf(mm, x[(t * (DP / 2 + 2) + DP / 2) * 64 + lane]);
+    const float a1 = __builtin_amdgcn_exp2f(m - mm);
+    l *= a1;
 #pragma unroll
     for (int dt = 0; dt < DP / 32; ++dt)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) o[dt][v] = o[dt][v] * a1 + x[(dt * 16 + v) * 64 + lane] * a2;
+      for (int v = 0; v < 16; ++v) o[dt][v] *= a1;
+#pragma unroll
+    for (int t = 0; t < SIDES - 1; ++t) {
+      const float *xs = x + t * (DP / 2 + 2) * 64;
+      const float a2 = __builtin_amdgcn_exp2f(xs[(DP / 2) * 64 + lane] - mm);
+      l += xs[(DP / 2 + 1) * 64 + lane] * a2;
+#pragma unroll
+      for (int dt = 0; dt < DP / 32; ++dt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[dt][v] += xs[(dt * 16 + v) * 64 + lane] * a2;
+    }
     l += __shfl_xor(l, 32, 64);
     const uint32_t redo = nonfinite_rows(nonfinite_trace(o, l * 0.f), q < p.seq);  // see attn_rows.h
     if (q < p.seq && !((redo >> l32) & 1)) {
@@ -249,18 +291,20 @@ template <int DP> __global__ __launch_bounds__(256, 1) void f32_fwd_kernel(const
 }
 
 // ---- dQ: the same walk; dQ^T += K^T dS^T ----------------------------------------------------------------
-template <int DP> __device__ __forceinline__ void f32_dq_block(const F32Params &p, char *smem, int qt, int g, int n) {
+template <int DP, int SIDES> __device__ __forceinline__ void f32_dq_block(const F32Params &p, char *smem, int qt, int g, int n) {
   using F = F32Tile<DP>;
+  using W = F32Walk<DP, SIDES>;
+  constexpr int FB = W::FB, NST = W::NST;
   const int kap = g / (p.nq / p.nkv), d = p.d;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int grp = wave & 1, side = wave >> 1, l32 = lane & 31, hh = lane >> 5;
+  const int grp = wave % W::GROUPS, side = wave / W::GROUPS, l32 = lane & 31, hh = lane >> 5;
   const int q0w = qt * FB + grp * 32, q = q0w + l32;
   const int64_t ts = (int64_t)p.batch * p.row, cs = (int64_t)p.batch * p.nq * d;
   const int koff = (p.nq + kap) * d, voff = (p.nq + p.nkv + kap) * d;
   const rsrc_t rs = make_rsrc(p.qkv, p.qkv_bytes);
   F32Loader<DP> ld;
   ld.init(ts, d, lane);
-  auto tile = [&](int stage, int s, int which) { return smem + ((stage * 2 + s) * 2 + which) * F::BYTES; };
+  auto tile = [&](int stage, int s, int which) { return smem + ((stage * SIDES + s) * 2 + which) * F::BYTES; };
   const bool valid = q < p.seq;
   f32x4 qf[DP / 8], dof[DP / 8];
   f32_row_frags<DP>(p.qkv + (int64_t)n * p.row + (int64_t)q * ts + g * d, valid, d, hh, qf);
@@ -272,17 +316,25 @@ template <int DP> __device__ __forceinline__ void f32_dq_block(const F32Params &
   for (int dt = 0; dt < DP / 32; ++dt) acc[dt] = f32_zero();
   const uint32_t cb = f32_cols_base<DP>(lane);
   const int kv_end = qt * FB + FB < p.seq ? qt * FB + FB : p.seq;
-  const int ntile = (kv_end + FT - 1) / FT, nstep = (ntile + 1) / 2;
+  const int ntile = (kv_end + FT - 1) / FT, nstep = (ntile + SIDES - 1) / SIDES;
   auto issue_step = [&](int step, int stage) {
-    const int s = wave >> 1, which = wave & 1, jt = 2 * step + s;
-    if (jt < ntile) ld.issue(rs, tile(stage, s, which), (int64_t)jt * FT * ts, (int64_t)n * p.row + (which ? voff : koff));
+    if constexpr (SIDES == 2) {
+      const int s = wave >> 1, which = wave & 1, jt = 2 * step + s;
+      if (jt < ntile) ld.issue(rs, tile(stage, s, which), (int64_t)jt * FT * ts, (int64_t)n * p.row + (which ? voff : koff));
+    } else {
+      const int jt = SIDES * step + side;
+      if (jt < ntile) {
+        ld.issue(rs, tile(stage, side, 0), (int64_t)jt * FT * ts, (int64_t)n * p.row + koff);
+        ld.issue(rs, tile(stage, side, 1), (int64_t)jt * FT * ts, (int64_t)n * p.row + voff);
+      }
+    }
   };
   issue_step(0, 0);
   for (int step = 0; step < nstep; ++step) {
-    const int cur = step & 1, jt = 2 * step + side, j0 = jt * FT;
+    const int cur = NST == 2 ? step & 1 : 0, jt = SIDES * step + side, j0 = jt * FT;
     f32_wait_loads();
-    __syncthreads();
-    if (step + 1 < nstep) issue_step(step + 1, cur ^ 1);
+    W::publish();
+    if (NST == 2 && step + 1 < nstep) issue_step(step + 1, cur ^ 1);
     if (jt >= ntile || j0 > q0w + 31) continue;
     f32x16 s = f32_scores<DP>(tile(cur, side, 0), qf, lane);
     const f32x16 dp = f32_scores<DP>(tile(cur, side, 1), dof, lane);
@@ -295,30 +347,40 @@ template <int DP> __device__ __forceinline__ void f32_dq_block(const F32Params &
         if (j0 + f32_acc_row(v, hh) > q) s[v] = 0.f;
     }
     f32_accumulate<DP>(tile(cur, side, 0), cb, s, acc);
+    if (NST == 1 && step + 1 < nstep) {
+      W::publish();
+      issue_step(step + 1, 0);
+    }
   }
   f32_wait_loads();
-  f32_join<DP>(acc, reinterpret_cast<float *>(smem) + (size_t)grp * (DP / 2) * 64, side, lane);
+  f32_join<DP, SIDES>(acc, reinterpret_cast<float *>(smem) + (size_t)grp * (SIDES - 1) * (DP / 2) * 64, side, lane);
   if (side > 0) return;
   const uint32_t redo = nonfinite_rows(nonfinite_trace(acc, 0.f), valid);  // see attn_rows.h
   if (valid && !((redo >> l32) & 1)) f32_store<DP>(acc, p.scale, p.dqkv + ((int64_t)q * p.batch + n) * p.row + g * d, d, hh);
   for (uint32_t r = redo; r; r &= r - 1) attn_row_dq<float>(p, q0w + __builtin_ctz(r), g, n, lane);
 }
 
-// ---- dK, dV: block = 64 key rows of one (batch entry, query head); the sides take alternate query tiles -----------
-template <int DP> __device__ __forceinline__ void f32_dkv_block(const F32Params &p, char *smem, int kt, int g, int n) {
+// ---- dK, dV: block = FB key rows of one (batch entry, query head); the sides take alternate query tiles -----------
+template <int DP, int SIDES> __device__ __forceinline__ void f32_dkv_block(const F32Params &p, char *smem, int kt, int g, int n) {
   using F = F32Tile<DP>;
+  using W = F32Walk<DP, SIDES>;
+  constexpr int FB = W::FB, NST = W::NST;
   const int kap = g / (p.nq / p.nkv), d = p.d;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int grp = wave & 1, side = wave >> 1, l32 = lane & 31, hh = lane >> 5;
+  const int grp = wave % W::GROUPS, side = wave / W::GROUPS, l32 = lane & 31, hh = lane >> 5;
   const int j0w = kt * FB + grp * 32, j = j0w + l32;
   const int64_t ts = (int64_t)p.batch * p.row, cs = (int64_t)p.batch * p.nq * d;
   const int koff = (p.nq + kap) * d, voff = (p.nq + p.nkv + kap) * d;
-  const int my_side = wave >> 1, my_which = wave & 1;  // the tile this wave fetches: Q or dO of a side
+  // SIDES = 2: the tile this wave fetches, Q or dO of a side
+  const int my_side = SIDES == 2 ? wave >> 1 : side, my_which = SIDES == 2 ? wave & 1 : 0;
   const rsrc_t rs = my_which ? make_rsrc(p.dctx, p.ctx_bytes) : make_rsrc(p.qkv, p.qkv_bytes);
   F32Loader<DP> ld;
   ld.init(my_which ? cs : ts, d, lane);
-  auto tile = [&](int stage, int s, int which) { return smem + ((stage * 2 + s) * 2 + which) * F::BYTES; };
-  float *stats = reinterpret_cast<float *>(smem + 8 * F::BYTES);  // [stage][side][lse, D][32]
+  const rsrc_t rs_do = make_rsrc(p.dctx, p.ctx_bytes);
+  F32Loader<DP> ld_do;  // SIDES = 4: a wave fetches both of its side
+  if constexpr (SIDES == 4) ld_do.init(cs, d, lane);
+  auto tile = [&](int stage, int s, int which) { return smem + ((stage * SIDES + s) * 2 + which) * F::BYTES; };
+  float *stats = reinterpret_cast<float *>(smem + W::TILES);  // [stage][side][lse, D][32]
   const bool valid = j < p.seq;
   f32x4 kf[DP / 8], vf[DP / 8];
   f32_row_frags<DP>(p.qkv + (int64_t)n * p.row + (int64_t)j * ts + koff, valid, d, hh, kf);
@@ -327,30 +389,31 @@ template <int DP> __device__ __forceinline__ void f32_dkv_block(const F32Params 
 #pragma unroll
   for (int dt = 0; dt < DP / 32; ++dt) dk[dt] = dv[dt] = f32_zero();
   const uint32_t cb = f32_cols_base<DP>(lane);
-  const int it0 = kt * FB / FT, ntile = (p.seq + FT - 1) / FT - it0, nstep = (ntile + 1) / 2;
+  const int it0 = kt * FB / FT, ntile = (p.seq + FT - 1) / FT - it0, nstep = (ntile + SIDES - 1) / SIDES;
   // the row statistics of a step are fetched one step ahead and put into LDS before the barrier that publishes its tiles:
-  // wave 2 s holds lse, wave 2 s + 1 holds D of side s, lanes 0..31
+  // SIDES = 2: wave 2 s holds lse, wave 2 s + 1 holds D of side s, lanes 0..31; SIDES = 4: the halves of a wave hold them
   float st = 0.f;
   auto issue_step = [&](int step, int stage) {
-    const int it = 2 * step + my_side, i0 = (it0 + it) * FT;
+    const int it = SIDES * step + my_side, i0 = (it0 + it) * FT;
     st = 0.f;
     if (it < ntile) {
       ld.issue(rs, tile(stage, my_side, my_which), (int64_t)i0 * (my_which ? cs : ts),
                my_which ? (int64_t)n * p.nq * d + g * d : (int64_t)n * p.row + g * d);
+      if constexpr (SIDES == 4) ld_do.issue(rs_do, tile(stage, my_side, 1), (int64_t)i0 * cs, (int64_t)n * p.nq * d + g * d);
       const int i = i0 + l32;
-      if (i < p.seq) st = (my_which ? p.dvec : p.lse_in)[((int64_t)n * p.nq + g) * p.seq + i];
+      if (i < p.seq) st = ((SIDES == 2 ? my_which : hh) ? p.dvec : p.lse_in)[((int64_t)n * p.nq + g) * p.seq + i];
     }
   };
   issue_step(0, 0);
   for (int step = 0; step < nstep; ++step) {
-    const int cur = step & 1, it = 2 * step + side, i0 = (it0 + it) * FT;
+    const int cur = NST == 2 ? step & 1 : 0, it = SIDES * step + side, i0 = (it0 + it) * FT;
     f32_wait_loads();
-    if (lane < 32) stats[((cur * 2 + my_side) * 2 + my_which) * FT + lane] = st;
-    __syncthreads();
-    if (step + 1 < nstep) issue_step(step + 1, cur ^ 1);
+    if (SIDES == 4 || lane < 32) stats[((cur * SIDES + my_side) * 2 + my_which) * FT + lane] = st;
+    W::publish();
+    if (NST == 2 && step + 1 < nstep) issue_step(step + 1, cur ^ 1);
     if (it >= ntile || i0 + 31 < j0w) continue;  // every query of the tile lies before every key of the wave
     const char *qt = tile(cur, side, 0), *dot = tile(cur, side, 1);
-    const float *lse_s = stats + (cur * 2 + side) * 2 * FT, *dv_s = lse_s + FT;
+    const float *lse_s = stats + (cur * SIDES + side) * 2 * FT, *dv_s = lse_s + FT;
     f32x16 s = f32_scores<DP>(qt, kf, lane), dp = f32_scores<DP>(dot, vf, lane);
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
@@ -370,11 +433,15 @@ template <int DP> __device__ __forceinline__ void f32_dkv_block(const F32Params 
     }
     f32_accumulate<DP>(dot, cb, s, dv);
     f32_accumulate<DP>(qt, cb, dp, dk);
+    if (NST == 1 && step + 1 < nstep) {
+      W::publish();
+      issue_step(step + 1, 0);
+    }
   }
   f32_wait_loads();
-  float *x = reinterpret_cast<float *>(smem) + (size_t)grp * (DP / 2) * 64;
-  f32_join<DP>(dk, x, side, lane);
-  f32_join<DP>(dv, x, side, lane);
+  float *x = reinterpret_cast<float *>(smem) + (size_t)grp * (SIDES - 1) * (DP / 2) * 64;
+  f32_join<DP, SIDES>(dk, x, side, lane);
+  f32_join<DP, SIDES>(dv, x, side, lane);
   if (side > 0) return;
   const uint32_t redo = nonfinite_rows(nonfinite_trace(dk, nonfinite_trace(dv, 0.f)), valid);  // see attn_rows.h
   if (valid && !((redo >> l32) & 1)) {
@@ -393,11 +460,11 @@ template <int DP> __device__ __forceinline__ void f32_dkv_block(const F32Params 
 
 // Both halves of the backward pass in one launch: the dK/dV block of key tile r and the dQ block of query tile last - r
 // alternate in dispatch order, both kinds longest walk first.
-template <int DP> __global__ __launch_bounds__(256, 1) void f32_bwd_kernel(const F32Params p) {
+template <int DP, int SIDES> __global__ __launch_bounds__(256, 1) void f32_bwd_kernel(const F32Params p) {
   extern __shared__ __align__(1024) char smem[];
   const int rank = blockIdx.z >> 1, tiles = gridDim.z >> 1, g = blockIdx.x, n = blockIdx.y;
-  if (blockIdx.z & 1) f32_dq_block<DP>(p, smem, tiles - 1 - rank, g, n);
-  else f32_dkv_block<DP>(p, smem, rank, g, n);
+  if (blockIdx.z & 1) f32_dq_block<DP, SIDES>(p, smem, tiles - 1 - rank, g, n);
+  else f32_dkv_block<DP, SIDES>(p, smem, rank, g, n);
 }
 
 // dK, dV of a kv head = sum of its query heads' partials, added in head order; thread = 4 columns
@@ -417,9 +484,11 @@ __global__ __launch_bounds__(256) void f32_dkv_reduce_kernel(const F32Params p) 
 }
 
 // instantiated by name, ahead of the host code that takes their addresses
-#define TM_F32_FAMILY(DP)                                       \
-  template __global__ void f32_fwd_kernel<DP>(const F32Params); \
-  template __global__ void f32_bwd_kernel<DP>(const F32Params);
+#define TM_F32_FAMILY(DP)                                          \
+  template __global__ void f32_fwd_kernel<DP, 2>(const F32Params); \
+  template __global__ void f32_bwd_kernel<DP, 2>(const F32Params); \
+  template __global__ void f32_fwd_kernel<DP, 4>(const F32Params); \
+  template __global__ void f32_bwd_kernel<DP, 4>(const F32Params);
 TM_F32_FAMILY(32)
 TM_F32_FAMILY(64)
 TM_F32_FAMILY(96)
@@ -444,29 +513,48 @@ static F32Params make_params(int64_t seq, int64_t batch, int64_t nq, int64_t nkv
   return p;
 }
 
-template <int DP> static int launch_fwd(const F32Params &p, hipStream_t s) {
-  static bool attr_set = false;  // per head-size family
-  if (!attr_set && hipFuncSetAttribute(reinterpret_cast<const void *>(&f32_fwd_kernel<DP>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       kF32Lds<DP>) != hipSuccess)
+// Four sides where a step's four tiles exist (a sequence of two is one step either way: 64 positions 6.9 / 6.9 us forward) and
+// the chip has room: blocks of 32 rows fill a unit's LDS one at a time, so that up to 128 blocks of 64 rows (64 of each kind
+// backward) stay one pass, and up to twice that two passes whose long and short walks even out from 256 positions.
+// Two sides -> four, forward and backward, us: 128 positions, 8 walks of 64: 9.6 -> 7.1, 18.4 -> 14.0; 1024, 8: 47.8 -> 26.8,
+// 83.7 -> 57.6; 512, 32 walks: 26.7 -> 21.6, 62.3 -> 68.7; 128, 128 walks: 10.4 -> 13.1, 26.9 -> 39.8; heads of 128, 512
+// positions, 4 walks: 42.7 -> 26.5, 77.6 -> 49.5.
+static bool f32_four_sides(const F32Params &p, bool backward) {
+  const int64_t blocks = ceil_div((int64_t)p.seq, (int64_t)64) * p.batch * p.nq * (backward ? 2 : 1);
+  return p.seq > 64 && blocks <= (p.seq >= 256 ? 256 : 128);
+}
+
+template <int DP, int SIDES> static int launch_fwd(const F32Params &p, hipStream_t s) {
+  using W = F32Walk<DP, SIDES>;
+  static bool attr_set = false;  // per instantiation
+  if (!attr_set && hipFuncSetAttribute(reinterpret_cast<const void *>(&f32_fwd_kernel<DP, SIDES>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       W::LDS) != hipSuccess)
     return fail(TM_ELAUNCH, "attn_fwd: cannot reserve LDS");
   attr_set = true;
   g_last_kernel = "f32_fwd_kernel";
-  f32_fwd_kernel<DP><<<dim3((unsigned)p.nq, (unsigned)p.batch, (unsigned)ceil_div(p.seq, FB)), 256, kF32Lds<DP>, s>>>(p);
+  f32_fwd_kernel<DP, SIDES><<<dim3((unsigned)p.nq, (unsigned)p.batch, (unsigned)ceil_div(p.seq, W::FB)), 256, W::LDS, s>>>(p);
   return check_launch("attn_fwd_f32");
 }
-template <int DP> static int launch_bwd(const F32Params &p, hipStream_t s) {
+template <int DP> static int launch_fwd(const F32Params &p, hipStream_t s) {
+  return f32_four_sides(p, false) ? launch_fwd<DP, 4>(p, s) : launch_fwd<DP, 2>(p, s);
+}
+template <int DP, int SIDES> static int launch_bwd(const F32Params &p, hipStream_t s) {
+  using W = F32Walk<DP, SIDES>;
   static bool attr_set = false;
-  if (!attr_set && hipFuncSetAttribute(reinterpret_cast<const void *>(&f32_bwd_kernel<DP>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       kF32Lds<DP>) != hipSuccess)
+  if (!attr_set && hipFuncSetAttribute(reinterpret_cast<const void *>(&f32_bwd_kernel<DP, SIDES>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       W::LDS) != hipSuccess)
     return fail(TM_ELAUNCH, "attn_bwd: cannot reserve LDS");
   attr_set = true;
   g_last_kernel = "f32_bwd_kernel";
-  f32_bwd_kernel<DP><<<dim3((unsigned)p.nq, (unsigned)p.batch, 2 * (unsigned)ceil_div(p.seq, FB)), 256, kF32Lds<DP>, s>>>(p);
+  f32_bwd_kernel<DP, SIDES><<<dim3((unsigned)p.nq, (unsigned)p.batch, 2 * (unsigned)ceil_div(p.seq, W::FB)), 256, W::LDS, s>>>(p);
   if (p.part) {
     const int64_t total = (int64_t)p.batch * p.nkv * p.seq * (2 * p.d / 4);
     f32_dkv_reduce_kernel<<<(unsigned)ceil_div(total, (int64_t)256), 256, 0, s>>>(p);
   }
   return check_launch("attn_bwd_f32");
+}
+template <int DP> static int launch_bwd(const F32Params &p, hipStream_t s) {
+  return f32_four_sides(p, true) ? launch_bwd<DP, 4>(p, s) : launch_bwd<DP, 2>(p, s);
 }
 
 int attn_fwd_f32_launch(int64_t seq, int64_t batch, int64_t nq, int64_t nkv, int64_t d, const void *qkv, void *ctx, float *lse,

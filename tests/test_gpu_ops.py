@@ -746,6 +746,14 @@ def test_attention_fp32_tiles(env, seq, batch, nq, nkv, d):
     assert bool((ctx[seq:] == 7.0).all()) and bool((dqkv[seq:] == 7.0).all())
 
 
+@pytest.mark.parametrize("seq,batch,nq,nkv,d", [(65, 2, 2, 2, 64), (96, 1, 2, 1, 24), (97, 2, 2, 2, 96), (128, 1, 4, 2, 128), (129, 2, 4, 4, 64), (160, 1, 2, 2, 32),
+                                                 (255, 1, 32, 8, 32), (256, 2, 32, 32, 32), (321, 2, 8, 2, 64), (512, 1, 16, 16, 40), (513, 1, 16, 16, 40)])
+def test_attention_fp32_walk_shares(env, seq, batch, nq, nkv, d):
+    """fp32 attention whose four waves share one walk, around the lengths and numbers of walks at which it takes over from
+    the form with two sides, with last steps of one to four tiles: bounds as for the tiles (exponents to 30: 4e-6), 1e-5."""
+    test_attention_fp32_tiles(env, seq, batch, nq, nkv, d)
+
+
 @pytest.mark.parametrize("dtype,seq,batch,nq,nkv,d", [(BF16, 8, 40000, 16, 16, 64), (BF16, 1, 25000, 16, 16, 128), (FP32, 8, 40000, 16, 1, 64)])
 def test_attention_rows_behind_a_short_sequence_read_as_zero(env, dtype, seq, batch, nq, nkv, d):
     """A few positions of a very large batch: the other rows of the staged query tiles lie behind the tensor, some of them
