@@ -179,12 +179,23 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16 &a, int v0) {
   for (int e = 0; e < 8; ++e) r[e] = (bf16)a[v0 + e];
   return r;
 }
-// what pack8 left behind: the next 8 significand bits
+// what pack8 left behind: the next 8 significand bits.  The values are taken back out of the packed words: element by
+// element the compiler converts each one a second time (235 -> 202 vector instructions for the exponentials and second
+// product of a 64-key tile).
 __device__ __forceinline__ bf16x8 pack8_rest(const f32x16 &a, const bf16x8 &hi, int v0) {
   bf16x8 r;
+  const u32x4 w = __builtin_bit_cast(u32x4, hi);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) r[e] = (bf16)(a[v0 + e] - (float)hi[e]);
+  for (int e = 0; e < 4; ++e) {
+    r[2 * e] = (bf16)(a[v0 + 2 * e] - __builtin_bit_cast(float, w[e] << 16));
+    r[2 * e + 1] = (bf16)(a[v0 + 2 * e + 1] - __builtin_bit_cast(float, w[e] & 0xffff0000u));
+  }
   return r;
+}
+// the larger of the two halves' values of a row (lanes l and l + 32), without a trip through LDS
+__device__ __forceinline__ float max_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x), false, false);
+  return fmaxf(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
 }
 // offset along the accumulator-row axis of register v in a 32x32 tile
 __device__ __forceinline__ int acc_row(int v, int hh) { return 8 * (v >> 2) + 4 * hh + (v & 3); }
@@ -224,12 +235,18 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(0)"
 // =================================================================================================
 // One wave's work on one staged K / V tile of 64 keys for its 32 query rows (lane%32 = query row): S^T = K Q^T,
 // online softmax, O^T += V^T P^T.  Only the last one or two tiles of a walk can hold a key index above a query
-// index of the wave: only those pay for the mask.  The running maximum is kept in exponent units
-// (m = max * scale * log2 e); the accumulators and the row sum are rescaled only when some row of the wave saw its
-// maximum rise (the factor is exactly 1 otherwise).
+// index of the wave: only those pay for the mask.
+// EX: exponents are taken relative to a whole number m, and m moves only when some row's maximum has risen more than kLead
+// above it (probabilities stay below 2^(kLead + 1)): with m the running maximum itself a wave rescales its accumulators
+// and row sums on nearly every tile of a walk of a few dozen (one of 32 rows sees a new maximum).  Powers of two: every
+// rescaling is exact, and the row sum's exponent joins m at the end (fwd_finish), so that the logarithm that is left is of
+// a number from 1/2 to 1.  2 x 1500 positions, 16 / 4 heads of 64: 32.2 -> 28.1 us.
+// Head size 128 keeps the maximum, and rescales when some row saw it rise (by exactly 1 where not): a row's largest
+// probability is then 1, which bf16 holds exactly; taken to a whole number ctx is 16 % further from 64 bits (2.29e-3, 1.98e-3).
+constexpr float kLead = 8.f;
 template <int DP> struct FwdRow {
   f32x16 o[DP / 32];
-  float m, l;
+  float m, l;  // reference exponent, row sum (of this half of the wave)
 };
 template <int DP, bool EX, int KT = TILE>
 __device__ __forceinline__ void fwd_tile(const char *kt, const char *vt, const bf16x8 (&qf)[DP / 16], FwdRow<DP> &r, int j0,
@@ -255,11 +272,10 @@ __device__ __forceinline__ void fwd_tile(const char *kt, const char *vt, const b
   for (int t = 0; t < KT / 32; ++t)
 #pragma unroll
     for (int v = 0; v < 16; ++v) mraw = fmaxf(mraw, s[t][v]);
-  float mx = fmaxf(r.m, mraw * sc2);
-  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-  if (__builtin_amdgcn_ballot_w64(mx > r.m) != 0) {  // wave-uniform
-    const float alpha = __builtin_amdgcn_exp2f(r.m - mx);
-    r.m = mx;
+  const float mx = max_halves(mraw) * sc2;
+  if (__builtin_amdgcn_ballot_w64(mx > (EX ? r.m + kLead : r.m)) != 0) {  // wave-uniform; the first tile: m is -inf
+    const float m = fmaxf(r.m, EX ? __builtin_ceilf(mx) : mx), alpha = __builtin_amdgcn_exp2f(r.m - m);
+    r.m = m;
     r.l *= alpha;
 #pragma unroll
     for (int dt = 0; dt < DP / 32; ++dt)
@@ -297,7 +313,9 @@ __device__ __forceinline__ void fwd_finish(const FlashParams &p, FwdRow<DP> &r, 
   if (q < p.seq && !((redo >> (q & 31)) & 1)) {
     const int64_t trow = (int64_t)q * p.batch + n;
     store_transposed<DP, EX>(r.o, 1.f / r.l, p.ctx + trow * (p.nq * hd) + g * hd, hd, hh);
-    if (hh == 0) p.lse[((int64_t)n * p.nq + g) * p.seq + q] = EX ? row_lse(r.m, r.l) : (r.m + log2f(r.l)) * 0.6931471805599453f;
+    if (hh == 0)
+      p.lse[((int64_t)n * p.nq + g) * p.seq + q] =
+          EX ? row_lse(r.m + (float)__builtin_amdgcn_frexp_expf(r.l), __builtin_amdgcn_frexp_mantf(r.l)) : (r.m + log2f(r.l)) * 0.6931471805599453f;
   }
   if constexpr (EX)
     for (uint32_t m = redo; m; m &= m - 1) attn_row_fwd<bf16>(p, q - (lane & 31) + __builtin_ctz(m), g, n, lane);
@@ -459,7 +477,9 @@ __global__ __launch_bounds__(512, DP > 64 ? 1 : NPAR == 2 ? 4 : 2) void flash_fw
 // dQ: same walk as the forward pass; dQ^T += K^T dS^T
 // =================================================================================================
 // one wave, one staged K / V tile: probabilities from the stored log-sum-exp, dS = P (dP - D), dQ^T += K^T dS^T
-template <int DP, bool EX>
+// FROM_D: dP starts from -D, which saves the subtraction behind the product; where head size 128 runs two four-wave blocks a
+// unit the registers that hold it cost more (8192 positions, 8 heads: the backward pass 507 -> 520 us).
+template <int DP, bool EX, bool FROM_D>
 __device__ __forceinline__ void dq_tile(const char *kt, const char *vt, const bf16x8 (&qf)[DP / 16],
                                         const bf16x8 (&dof)[DP / 16], f32x16 (&acc)[DP / 32], float lse2, float dq_d, int j0,
                                         int q0w, int q, int hh, float sc2, uint32_t rb, uint32_t cb) {
@@ -468,7 +488,7 @@ __device__ __forceinline__ void dq_tile(const char *kt, const char *vt, const bf
   for (int t = 0; t < 2; ++t) {
     f32x16 s, dp;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) s[v] = dp[v] = 0.f;
+    for (int v = 0; v < 16; ++v) s[v] = 0.f, dp[v] = FROM_D ? -dq_d : 0.f;
 #pragma unroll
     for (int ks = 0; ks < DP / 16; ++ks) {
       s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows_at<DP>(kt, rb, t * 32, ks), qf[ks], s, 0, 0, 0);
@@ -476,7 +496,7 @@ __device__ __forceinline__ void dq_tile(const char *kt, const char *vt, const bf
     }
 #pragma unroll
     for (int v = 0; v < 16; ++v)
-      ds[t][v] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[v], sc2, -lse2)) * (dp[v] - dq_d);
+      ds[t][v] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[v], sc2, -lse2)) * (FROM_D ? dp[v] : dp[v] - dq_d);
   }
   if (j0 + TILE - 1 > q0w) {  // wave-uniform: only the last one or two tiles can hold a key above a query
 #pragma unroll
@@ -563,7 +583,7 @@ __device__ __forceinline__ void dq_block(const FlashParams &p, char *lds_base, i
     __builtin_amdgcn_s_barrier();
     if (step + 1 < nstep) issue_step(step + 1, cur ^ 1);
     if ((NPAR > 1 && jt >= ntile) || j0 > q0w + 31) continue;
-    dq_tile<DP, EX>(tile(cur, par, 0), tile(cur, par, 1), qf, dof, acc, lse2, dq_d, j0, q0w, q, hh, sc2, rb, cb);
+    dq_tile<DP, EX, EX || NPAR == 2 || NW == 8>(tile(cur, par, 0), tile(cur, par, 1), qf, dof, acc, lse2, dq_d, j0, q0w, q, hh, sc2, rb, cb);
   }
   wait_loads();
   if constexpr (NPAR == 2) {
