@@ -1,5 +1,6 @@
 // LayerNorm / RMSNorm forward and backward, column reductions (bias and gain gradients).
 // HBM-bound kernels: 16-byte accesses, fp32 arithmetic, wavefront shuffles for row sums.
+#include "columns.h"
 #include "common.h"
 #include "../../include/tm_ops.h"
 
@@ -248,99 +249,86 @@ __global__ __launch_bounds__(kNormThreads) void norm_bwd_kernel(
   }
 }
 
-// the three column reductions of the norm's backward pass in one launch: slice s of the partial rows goes to outs[s]
-// (NULL: skipped); same summation order as reduce_partials_kernel
+// ---------------------------------------------------------------------------------------
+// Column sums.  Up to six of them share a launch: the partial rows of a norm's backward pass (gain, offset and dx sums), the
+// bias gradients of a layer, or the second halves of these.  A launch of this kind takes 3 to 5 us whatever it adds up, and
+// a layer with biases has seven or eight (6.7B shard, two layers: a step 1426 -> 1390 us with all behind the last norm together).
+// ---------------------------------------------------------------------------------------
 constexpr int kRowLanes = 16;  // row lanes of a block: 256 partial rows are four loads deep (four lanes: 7 us a launch, now 4.8)
-struct ReduceOuts {
-  float *out[3];
+constexpr int kMaxColumnTasks = 6;
+struct ColumnTask {
+  const void *src;  // [rows][ld], the first n columns of it
+  float *out;
+  int64_t ld;
+  int rows, n, first_block;
+  bool typed;       // elements of the kernel's type, otherwise fp32
 };
-__global__ __launch_bounds__(64 * kRowLanes) void reduce_partials3_kernel(const float *__restrict__ partial, int R, int h, ReduceOuts outs,
-                                                               int accumulate) {
-  __shared__ float sm[kRowLanes][64];
-  const int lane = threadIdx.x & 63, ry = threadIdx.x >> 6;
-  const int per_slice = (h + 63) / 64;
-  const int slice = blockIdx.x / per_slice, c = (blockIdx.x % per_slice) * 64 + lane;
-  float *out = outs.out[slice];
-  if (!out) return;  // uniform over the block
-  const int64_t ld = 3 * (int64_t)h;
-  const float *src = partial + (int64_t)slice * h;
-  float s = 0.f;
-  if (c < h) {
-    int r = ry;
-    for (; r + 3 * kRowLanes < R; r += 4 * kRowLanes) {
-      const float a0 = src[(int64_t)r * ld + c], a1 = src[(int64_t)(r + kRowLanes) * ld + c];
-      const float a2 = src[(int64_t)(r + 2 * kRowLanes) * ld + c], a3 = src[(int64_t)(r + 3 * kRowLanes) * ld + c];
-      s += a0;
-      s += a1;
-      s += a2;
-      s += a3;
-    }
-    for (; r < R; r += kRowLanes) s += src[(int64_t)r * ld + c];
-  }
-  sm[ry][lane] = s;
-  __syncthreads();
-  if (ry == 0 && c < h) {
-    float t = sm[0][lane];
+struct ColumnTasks {
+  ColumnTask t[kMaxColumnTasks];
+  int count;
+};
+__device__ __forceinline__ ColumnTask task_of_block(const ColumnTasks &ts) {  // uniform over the block
+  ColumnTask t = ts.t[0];
 #pragma unroll
-    for (int k = 1; k < kRowLanes; ++k) t += sm[k][lane];
-    out[c] = accumulate ? out[c] + t : t;
-  }
+  for (int k = 1; k < kMaxColumnTasks; ++k)
+    if (k < ts.count && (int)blockIdx.x >= ts.t[k].first_block) t = ts.t[k];
+  return t;
 }
-
-// out[c] (+)= sum_{r<R} partial[r*ld + c].  Block = 64 columns x 16 row lanes; lane y adds rows
+template <typename E> __device__ __forceinline__ float column_rows(const E *src, int64_t ld, int rows, int ry) {
+  float s = 0.f;
+  int r = ry;
+  for (; r + 3 * kRowLanes < rows; r += 4 * kRowLanes) {  // four independent loads in flight per trip
+    float a[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) a[k] = to_f32(src[(int64_t)(r + k * kRowLanes) * ld]);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s += a[k];
+  }
+  for (; r < rows; r += kRowLanes) s += to_f32(src[(int64_t)r * ld]);
+  return s;
+}
+// out[c] (+)= sum_{r<rows} src[r*ld + c].  Block = 64 columns x 16 row lanes; lane y adds rows
 // y, y+16, ... in ascending order, then the lane sums are added in lane order: a fixed order.
-__global__ __launch_bounds__(64 * kRowLanes) void reduce_partials_kernel(const float *__restrict__ partial, int R, int64_t ld,
-                                                              int n, float *__restrict__ out, int accumulate) {
+template <typename T>
+__global__ __launch_bounds__(64 * kRowLanes) void column_sums_kernel(const ColumnTasks ts, int accumulate) {
   __shared__ float sm[kRowLanes][64];
-  const int lane = threadIdx.x & 63, ry = threadIdx.x >> 6;
-  const int c = blockIdx.x * 64 + lane;
+  const ColumnTask t = task_of_block(ts);
+  const int lane = threadIdx.x & 63, ry = threadIdx.x >> 6, c = ((int)blockIdx.x - t.first_block) * 64 + lane;
   float s = 0.f;
-  if (c < n) {
-    int r = ry;
-    for (; r + 3 * kRowLanes < R; r += 4 * kRowLanes) {  // four independent loads in flight per trip
-      const float a0 = partial[(int64_t)r * ld + c], a1 = partial[(int64_t)(r + kRowLanes) * ld + c];
-      const float a2 = partial[(int64_t)(r + 2 * kRowLanes) * ld + c], a3 = partial[(int64_t)(r + 3 * kRowLanes) * ld + c];
-      s += a0;
-      s += a1;
-      s += a2;
-      s += a3;
-    }
-    for (; r < R; r += kRowLanes) s += partial[(int64_t)r * ld + c];
-  }
+  if (c < t.n) s = t.typed ? column_rows((const T *)t.src + c, t.ld, t.rows, ry) : column_rows((const float *)t.src + c, t.ld, t.rows, ry);
   sm[ry][lane] = s;
   __syncthreads();
-  if (ry == 0 && c < n) {
-    float t = sm[0][lane];
+  if (ry == 0 && c < t.n) {
+    float sum = sm[0][lane];
 #pragma unroll
-    for (int k = 1; k < kRowLanes; ++k) t += sm[k][lane];
-    out[c] = accumulate ? out[c] + t : t;
+    for (int k = 1; k < kRowLanes; ++k) sum += sm[k][lane];
+    t.out[c] = accumulate ? t.out[c] + sum : sum;
   }
 }
 
-// ---------------------------------------------------------------------------------------
-// column sums of dy[T,N] (bias gradients): grid (column groups, row groups) -> partial[R][N]
-// ---------------------------------------------------------------------------------------
+// First halves of column sums over many rows: block (column group, row group); task's out: partial [row groups][n]
 constexpr int kColLanes = 64, kColRowsPerBlock = 4;
-constexpr int kColsumDirectRows = 512;
+constexpr int kColsumDirectRows = 512;  // up to here in one launch, 32 rows a lane (256 rows of 256 to 1024: 3.5 us, two launches 5.0)
 
 template <typename T>
-__global__ __launch_bounds__(kColLanes *kColRowsPerBlock) void colsum_partial_kernel(
-    const T *__restrict__ dy, float *__restrict__ partial, int64_t rows, int n, int rows_per_group) {
+__global__ __launch_bounds__(kColLanes *kColRowsPerBlock) void colsum_partial_kernel(const ColumnTasks ts, int rows_per_group) {
   constexpr int VN = Vec<T>::N;
   __shared__ float sm[kColRowsPerBlock][kColLanes * VN];
+  const ColumnTask t = task_of_block(ts);
+  const T *dy = (const T *)t.src;
   const int lane = threadIdx.x % kColLanes, ry = threadIdx.x / kColLanes;
-  const int col = (blockIdx.x * kColLanes + lane) * VN;
+  const int col = (((int)blockIdx.x - t.first_block) * kColLanes + lane) * VN;
   const int64_t r0 = (int64_t)blockIdx.y * rows_per_group;
-  const int64_t r1 = (r0 + rows_per_group < rows) ? r0 + rows_per_group : rows;
+  const int64_t r1 = (r0 + rows_per_group < t.rows) ? r0 + rows_per_group : t.rows;
   float acc[VN];
 #pragma unroll
   for (int i = 0; i < VN; ++i) acc[i] = 0.f;
-  if (col < n) {
+  if (col < t.n) {
     int64_t r = r0 + ry;
     for (; r + 3 * kColRowsPerBlock < r1; r += 4 * kColRowsPerBlock) {  // four rows in flight
       float v[4][VN];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) load_vec<T>(dy + (r + k * kColRowsPerBlock) * n + col, v[k]);
+      for (int k = 0; k < 4; ++k) load_vec<T>(dy + (r + k * kColRowsPerBlock) * t.ld + col, v[k]);
 #pragma unroll
       for (int k = 0; k < 4; ++k)
 #pragma unroll
@@ -348,7 +336,7 @@ __global__ __launch_bounds__(kColLanes *kColRowsPerBlock) void colsum_partial_ke
     }
     for (; r < r1; r += kColRowsPerBlock) {
       float v[VN];
-      load_vec<T>(dy + r * n + col, v);
+      load_vec<T>(dy + r * t.ld + col, v);
 #pragma unroll
       for (int i = 0; i < VN; ++i) acc[i] += v[i];
     }
@@ -356,43 +344,14 @@ __global__ __launch_bounds__(kColLanes *kColRowsPerBlock) void colsum_partial_ke
 #pragma unroll
   for (int i = 0; i < VN; ++i) sm[ry][lane * VN + i] = acc[i];
   __syncthreads();
-  if (ry == 0 && col < n) {
+  if (ry == 0 && col < t.n) {
 #pragma unroll
     for (int i = 0; i < VN; ++i) {
       float s = 0.f;
 #pragma unroll
       for (int k = 0; k < kColRowsPerBlock; ++k) s += sm[k][lane * VN + i];
-      partial[(int64_t)blockIdx.y * n + col + i] = s;
+      t.out[(int64_t)blockIdx.y * t.n + col + i] = s;
     }
-  }
-}
-
-// The same in one launch for few rows (up to 512: 32 a lane): block = 64 columns x 16 row lanes over all rows.  Two launches
-// of which neither fills the chip took 5.0 us for 256 rows of 256 to 1024, this one 3.5.
-template <typename T>
-__global__ __launch_bounds__(64 * kRowLanes) void colsum_direct_kernel(const T *__restrict__ dy, float *__restrict__ out, int rows, int n,
-                                                                      int accumulate) {
-  __shared__ float sm[kRowLanes][64];
-  const int lane = threadIdx.x & 63, ry = threadIdx.x >> 6, c = blockIdx.x * 64 + lane;
-  float s = 0.f;
-  if (c < n) {
-    int r = ry;
-    for (; r + 3 * kRowLanes < rows; r += 4 * kRowLanes) {
-      float a[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) a[k] = to_f32(dy[(int64_t)(r + k * kRowLanes) * n + c]);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) s += a[k];
-    }
-    for (; r < rows; r += kRowLanes) s += to_f32(dy[(int64_t)r * n + c]);
-  }
-  sm[ry][lane] = s;
-  __syncthreads();
-  if (ry == 0 && c < n) {
-    float t = sm[0][lane];
-#pragma unroll
-    for (int k = 1; k < kRowLanes; ++k) t += sm[k][lane];
-    out[c] = accumulate ? out[c] + t : t;
   }
 }
 
@@ -504,6 +463,38 @@ static int norm_bwd_t(int kind, int64_t rows, int h, const void *dout, const voi
   return check_launch("norm_bwd");
 }
 
+// appends a task of 64 (column_sums_kernel) or more columns a block; returns the blocks so far
+static int add_task(ColumnTasks &ts, int blocks, int cols_per_block, const void *src, int64_t ld, int64_t rows, int64_t n, float *out, bool typed) {
+  ts.t[ts.count++] = ColumnTask{src, out, ld, (int)rows, (int)n, blocks, typed};
+  return blocks + (int)ceil_div(n, (int64_t)cols_per_block);
+}
+static int launch_column_sums(int dtype, const ColumnTasks &ts, int blocks, int accumulate, hipStream_t s, const char *what) {
+  if (dtype == TM_DTYPE_BF16) column_sums_kernel<bf16><<<(unsigned)blocks, 64 * kRowLanes, 0, s>>>(ts, accumulate);
+  else column_sums_kernel<float><<<(unsigned)blocks, 64 * kRowLanes, 0, s>>>(ts, accumulate);
+  return check_launch(what);
+}
+// The sums over T rows of `count` matrices as tasks of the column_sums_kernel launch that follows: the matrices themselves
+// where T is small, else their partial sums, which are enqueued here and go to `partial`.
+static int add_column_sums(ColumnTasks &ts, int blocks, int dtype, int64_t T, const ColumnSum *sums, int count, float *partial, hipStream_t s) {
+  if (T <= kColsumDirectRows) {
+    for (int k = 0; k < count; ++k) blocks = add_task(ts, blocks, 64, sums[k].dy, sums[k].n, T, sums[k].n, sums[k].out, true);
+    return blocks;
+  }
+  const int R = colsum_groups(T), vn = dtype == TM_DTYPE_BF16 ? 8 : 4;
+  ColumnTasks first = {};
+  int groups = 0;
+  for (int k = 0; k < count; ++k) {
+    groups = add_task(first, groups, kColLanes * vn, sums[k].dy, sums[k].n, T, sums[k].n, partial, true);
+    blocks = add_task(ts, blocks, 64, partial, sums[k].n, R, sums[k].n, sums[k].out, false);
+    partial += (int64_t)R * sums[k].n;
+  }
+  const dim3 grid((unsigned)groups, (unsigned)R);
+  const int rows_per_group = (int)ceil_div(T, (int64_t)R);
+  if (dtype == TM_DTYPE_BF16) colsum_partial_kernel<bf16><<<grid, kColLanes * kColRowsPerBlock, 0, s>>>(first, rows_per_group);
+  else colsum_partial_kernel<float><<<grid, kColLanes * kColRowsPerBlock, 0, s>>>(first, rows_per_group);
+  return blocks;
+}
+
 }  // namespace tmk
 
 using namespace tmk;
@@ -538,7 +529,8 @@ extern "C" int tm_op_norm_fwd(int dtype, int kind, int64_t T, int64_t h, double 
 
 static int norm_bwd_any(int dtype, int kind, int64_t T, int64_t h, const void *dout, const void *x, const float *mean,
                         const float *rstd, const void *gain, const void *dres, void *dx, float *dgain, float *doffset,
-                        float *dx_colsum, void *scratch, int accumulate, void *stream) {
+                        float *dx_colsum, void *scratch, int accumulate, void *stream, const ColumnSum *sums = nullptr,
+                        int count = 0, float *partial_sums = nullptr) {
   if (int e = check_width("norm_bwd", dtype, T, h)) return e;
   if (kind != TM_NORM_LAYERNORM && kind != TM_NORM_RMSNORM) return fail(TM_EINVAL, "norm_bwd: unknown kind %d", kind);
   if (!dout || !x || !rstd || !gain || !dx || !dgain || !scratch || (kind == TM_NORM_LAYERNORM && (!mean || !doffset)))
@@ -556,9 +548,25 @@ static int norm_bwd_any(int dtype, int kind, int64_t T, int64_t h, const void *d
                                : norm_bwd_t<float, false>(kind, T, (int)h, dout, x, mean, rstd, gain, dres, dx, partial, s);
   if (e) return e;
   const int G = norm_bwd_grid(T, h, dtype == TM_DTYPE_BF16 ? Vec<bf16>::N : Vec<float>::N);
-  ReduceOuts outs{{dgain, kind == TM_NORM_LAYERNORM ? doffset : nullptr, dx_colsum}};
-  reduce_partials3_kernel<<<3 * (int)ceil_div(h, 64), 64 * kRowLanes, 0, s>>>(partial, G, (int)h, outs, accumulate);
-  return check_launch("norm_bwd reduce");
+  float *outs[3] = {dgain, kind == TM_NORM_LAYERNORM ? doffset : nullptr, dx_colsum};
+  ColumnTasks ts = {};
+  int blocks = 0;
+  for (int k = 0; k < 3; ++k)
+    if (outs[k]) blocks = add_task(ts, blocks, 64, partial + k * h, 3 * h, G, h, outs[k], false);
+  if (count) blocks = add_column_sums(ts, blocks, dtype, T, sums, count, partial_sums, s);
+  return launch_column_sums(dtype, ts, blocks, accumulate, s, "norm_bwd reduce");
+}
+
+int64_t tmk::column_sums_scratch_bytes(int64_t T, int64_t width) {
+  return T <= kColsumDirectRows ? 0 : colsum_groups(T) * width * (int64_t)sizeof(float);
+}
+
+int tmk::norm_bwd_and_column_sums(int dtype, int kind, int64_t T, int64_t h, const void *dout, const void *x, const float *mean,
+                                  const float *rstd, const void *gain, const void *dres, void *dx, float *dgain, float *doffset,
+                                  float *dx_colsum, void *scratch, const ColumnSum *sums, int count, void *partial_sums,
+                                  int accumulate, hipStream_t s) {
+  return norm_bwd_any(dtype, kind, T, h, dout, x, mean, rstd, gain, dres, dx, dgain, doffset, dx_colsum, scratch, accumulate, s, sums,
+                      count, (float *)partial_sums);
 }
 
 extern "C" int tm_op_norm_bwd(int dtype, int kind, int64_t T, int64_t h, const void *dout, const void *x,
@@ -580,27 +588,9 @@ extern "C" int tm_op_bias_grad(int dtype, int64_t T, int64_t N, const void *dy, 
   if (int e = check_width("bias_grad", dtype, T, N)) return e;
   if (!dy || !db || !scratch) return fail(TM_EINVAL, "bias_grad: NULL pointer");
   hipStream_t s = (hipStream_t)stream;
-  if (T <= kColsumDirectRows) {
-    const unsigned blocks = (unsigned)ceil_div(N, (int64_t)64);
-    g_last_kernel = "colsum_direct_kernel";
-    if (dtype == TM_DTYPE_BF16)
-      colsum_direct_kernel<bf16><<<blocks, 64 * kRowLanes, 0, s>>>((const bf16 *)dy, db, (int)T, (int)N, accumulate);
-    else
-      colsum_direct_kernel<float><<<blocks, 64 * kRowLanes, 0, s>>>((const float *)dy, db, (int)T, (int)N, accumulate);
-    return check_launch("bias_grad");
-  }
-  const int R = colsum_groups(T);
-  const int rows_per_group = (int)ceil_div(T, R);
-  float *partial = (float *)scratch;
-  const int vn = dtype == TM_DTYPE_BF16 ? 8 : 4;
-  g_last_kernel = "colsum_partial_kernel";
-  dim3 grid((unsigned)ceil_div(N, (int64_t)kColLanes * vn), (unsigned)R);
-  if (dtype == TM_DTYPE_BF16)
-    colsum_partial_kernel<bf16><<<grid, kColLanes * kColRowsPerBlock, 0, s>>>((const bf16 *)dy, partial, T, (int)N,
-                                                                              rows_per_group);
-  else
-    colsum_partial_kernel<float><<<grid, kColLanes * kColRowsPerBlock, 0, s>>>((const float *)dy, partial, T, (int)N,
-                                                                               rows_per_group);
-  reduce_partials_kernel<<<(int)ceil_div(N, 64), 64 * kRowLanes, 0, s>>>(partial, R, N, (int)N, db, accumulate);
-  return check_launch("bias_grad");
+  g_last_kernel = T <= kColsumDirectRows ? "column_sums_kernel" : "colsum_partial_kernel";
+  const ColumnSum sum{dy, db, N};
+  ColumnTasks ts = {};
+  const int blocks = add_column_sums(ts, 0, dtype, T, &sum, 1, (float *)scratch, s);
+  return launch_column_sums(dtype, ts, blocks, accumulate, s, "bias_grad");
 }

@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "attn.h"
+#include "columns.h"
 #include "common.h"
 #include "gemm.h"
 #include "sandbox.h"
@@ -695,8 +696,11 @@ static int stage_bwd(tm_stage_t *st, const void *dy_in, void *dx_out, void *stre
     TM_TRY(fork());
     fused.clear();
     TM_STEP(mm(d.h, d.f), wgrad_bytes(d.h, d.f, dy, ws + k.g, pb, o.w_fc2), wgrad(pb, o.w_fc2, d.h, d.f, dy, ws + k.g));
-    // (below the top layer this bias gradient has come out of the first norm's backward pass of the layer above)
-    if (bias && l == c.n_layers - 1) TM_STEP(0, es * Th, tm_op_bias_grad(dt, d.T, d.h, dy, G(o.b_fc2), red, acc, s));
+    // the bias gradients wait for the end of the layer, where their column sums share launches with the first norm's
+    // (below the top layer FC2's has come out of the first norm's backward pass of the layer above)
+    ColumnSum sums[3];
+    int n_sums = 0;
+    if (bias && l == c.n_layers - 1) sums[n_sums++] = ColumnSum{dy, G(o.b_fc2), d.h};
     // activation
     void *du = ws + pl.dwide;
     TM_STEP(0, es * d.T * (d.f + 2 * d.f1), tm_op_act_bwd(dt, c.act, d.T, d.f, dg, ws + k.u, du, s));
@@ -706,7 +710,7 @@ static int stage_bwd(tm_stage_t *st, const void *dy_in, void *dx_out, void *stre
     if (cm) TM_TRY(tm_comm_call(cm, TM_COLL_ALL_REDUCE, TM_SCOPE_TP, TM_SITE_D_MLP_IN, dt, dc, act_bytes, s));
     TM_TRY(fork());
     TM_STEP(mm(d.f1, d.h), wgrad_bytes(d.f1, d.h, du, ws + k.c, pb, o.w_fc1), wgrad(pb, o.w_fc1, d.f1, d.h, du, ws + k.c));
-    if (bias) TM_STEP(0, es * d.T * d.f1, tm_op_bias_grad(dt, d.T, d.f1, du, G(o.b_fc1), red, acc, s));
+    if (bias) sums[n_sums++] = ColumnSum{du, G(o.b_fc1), d.f1};
     // c = Norm(x1): dx1 = dy + norm gradient
     void *dx1 = ws + pl.dx1;
     // with biases the column sums of dx1, the out-projection's bias gradient, come out of the same pass
@@ -738,19 +742,21 @@ static int stage_bwd(tm_stage_t *st, const void *dy_in, void *dx_out, void *stre
     if (cm) TM_TRY(tm_comm_call(cm, TM_COLL_ALL_REDUCE, TM_SCOPE_TP, TM_SITE_D_ATTN_IN, dt, da, act_bytes, s));
     TM_TRY(fork());
     TM_STEP(mm(d.nqkv, d.h), wgrad_bytes(d.nqkv, d.h, ws + pl.dqkv, ws + k.a, pb, o.w_qkv), wgrad(pb, o.w_qkv, d.nqkv, d.h, ws + pl.dqkv, ws + k.a));
-    if (bias) TM_STEP(0, es * d.T * d.nqkv, tm_op_bias_grad(dt, d.T, d.nqkv, ws + pl.dqkv, G(o.b_qkv), red, acc, s));
+    if (bias) sums[n_sums++] = ColumnSum{ws + pl.dqkv, G(o.b_qkv), d.nqkv};
     // a = Norm(x): dx = dx1 + norm gradient
     // dx is the output gradient of the layer below: its column sums are that layer's FC2 bias gradient
-    if (bias && l > 0)
-      TM_STEP(0, 4 * es * Th,
-              tm_op_norm_bwd_colsum(dt, c.norm, d.T, d.h, da, ws + k.x, (const float *)(ws + k.mean1),
-                                    (const float *)(ws + k.rstd1), P(o.norm1_gain), dx1, dx, G(o.norm1_gain),
-                                    G(o.norm1_offset), grads + pb - o.total + o.b_fc2, red, acc, s));
-    else
-      TM_STEP(0, 4 * es * Th,
-              tm_op_norm_bwd(dt, c.norm, d.T, d.h, da, ws + k.x, (const float *)(ws + k.mean1),
-                             (const float *)(ws + k.rstd1), P(o.norm1_gain), dx1, dx, G(o.norm1_gain),
-                             G(o.norm1_offset), red, acc, s));
+    // (their partial sums go where SwiGLU has dg, which is used up by now; a very narrow FC has no room for them)
+    int64_t sum_width = 0;
+    for (int i = 0; i < n_sums; ++i) sum_width += sums[i].n;
+    if (column_sums_scratch_bytes(d.T, sum_width) > d.T * d.f * d.es) {
+      for (int i = 0; i < n_sums; ++i)
+        TM_STEP(0, es * d.T * (double)sums[i].n, tm_op_bias_grad(dt, d.T, sums[i].n, sums[i].dy, sums[i].out, red, acc, s));
+      n_sums = 0, sum_width = 0;
+    }
+    TM_STEP(0, 4 * es * Th + es * d.T * (double)sum_width,
+            norm_bwd_and_column_sums(dt, c.norm, d.T, d.h, da, ws + k.x, (const float *)(ws + k.mean1), (const float *)(ws + k.rstd1),
+                                     P(o.norm1_gain), dx1, dx, G(o.norm1_gain), G(o.norm1_offset),
+                                     bias && l > 0 ? grads + pb - o.total + o.b_fc2 : nullptr, red, sums, n_sums, ws + pl.dmid, acc, s));
     dy = dx;
     if (hp) {
       // this layer's gradients: the products on the side stream and the norm / bias gradients on the main one

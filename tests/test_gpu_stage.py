@@ -95,6 +95,31 @@ def test_stage_iteration_matches_checker(env, cfg):
     run_and_compare(torch, tm, cfg)
 
 
+@pytest.mark.parametrize("layers,ffn,seq,norm,act,dtype", [
+    (2, 96, 512, si.NORM_LAYERNORM, si.ACT_GELU_TANH, si.DTYPE_FP32), (2, 96, 513, si.NORM_LAYERNORM, si.ACT_GELU_TANH, si.DTYPE_FP32),
+    (2, 8, 530, si.NORM_LAYERNORM, si.ACT_GELU_ERF, si.DTYPE_BF16), (1, 520, 530, si.NORM_RMSNORM, si.ACT_SWIGLU, si.DTYPE_BF16)],
+    ids=["rows_in_one_launch", "partial_rows", "no_room_for_partial_rows", "swiglu_one_layer"])
+def test_bias_gradients_behind_the_last_norm(env, layers, ffn, seq, norm, act, dtype):
+    """The bias gradients of a layer share their launches with the first norm's: with and without partial rows, where these
+    have no room (FC of 8), with two and three outputs of the norm; every tensor against the checker at the stated
+    tolerances, and a second micro-batch of the same inputs added in gives twice the gradients (a power of two: exactly
+    where the sums are the same ones, one rounding of the sum otherwise, 2^-23)."""
+    torch, tm = env
+    cfg = si.StageConfig(layers, 64, 4, 4, 16, ffn, seq, 1, dtype=dtype, norm=norm, act=act)
+    print(f"bias gradients {cfg}", flush=True)
+    run_and_compare(torch, tm, cfg)
+    st = GpuStage(torch, tm, cfg, si.make_flat_params(cfg))
+    x, dy = to_dev(torch, si.make_x(cfg), dtype), to_dev(torch, si.make_dy(cfg), dtype)
+    st.fwd(x)
+    st.bwd(dy)
+    one = st.grads.clone()
+    st.fwd(x)
+    st.bwd(dy)
+    torch.cuda.synchronize()
+    assert rel_err(to_host(st.grads), 2.0 * to_host(one)) <= 2.0 ** -23
+    st.close()
+
+
 def test_gpt6p7b_shard_full_depth(env):
     torch, tm = env
     print("stage parity gpt6p7b (4 layers, full size)", flush=True)
