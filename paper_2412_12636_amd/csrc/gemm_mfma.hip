@@ -124,6 +124,32 @@ static double config_us(const GemmArgs &g, int c, int layout) {
 static bool config_takes(const GemmArgs &g, int c, int layout) {
   return g.K % 64 == 0 || layout == 2 || c == 1 || gemm_config_takes_ragged_k(c);
 }
+// A weight gradient whose rows do not start on 128-byte lines reads and writes two partial lines for every 32 results, through
+// different blocks where a tile ends: with few tokens that, and not the main loop, is its time, and small tiles, whose
+// epilogues overlap other blocks' main loops, lose least.  Time = scale x the model's + per million results, fitted to 26
+// such matrices of 16 to 4000 tokens, for results that are added to and that are overwritten.  On those of the range below
+// (2^21 results and more; from some 1400 and 700 tokens on the model alone is as good) the pick is 0.5 % and 1.4 % slower than
+// the fastest configuration, the model's alone 20 % and 10 %: 40 tokens on 5128 x 3080 added to 57 -> 40 us, 300 on
+// 8200 x 3080 103 -> 77 (overwritten 67 -> 55), 1000 on 5128 x 3080 89 -> 75.
+struct OffLineCost {
+  int config;
+  double scale[2], per_million[2];  // added to, overwritten
+};
+static const OffLineCost kOffLine[] = {{9, {1.13, 0.99}, {2.48, 0.95}},  {13, {1.19, 0.98}, {2.34, 1.05}}, {14, {1.06, 1.01}, {2.42, 1.05}},
+                                       {16, {1.21, 1.22}, {1.02, 0.05}}, {17, {1.01, 0.96}, {1.51, 0.61}}, {18, {0.96, 0.99}, {1.98, 0.65}},
+                                       {19, {1.13, 1.07}, {1.66, 0.50}}};
+static int off_line_config(const GemmArgs &g) {  // -1: not such a product
+  if ((g.c_mode != 1 && g.c_mode != 2) || (g.ldc % 32 == 0 && (((uintptr_t)g.C) & 127) == 0) || g.M * g.N < (1LL << 21)) return -1;
+  const bool adds = g.c_mode == 1;
+  if (adds ? g.K > 1408 : g.K <= 32 || g.K > 704) return -1;
+  double best = 1e300;
+  int pick = -1;
+  for (const OffLineCost &o : kOffLine) {
+    const double us = o.scale[!adds] * config_us(g, o.config, 2) + o.per_million[!adds] * ((double)g.M * g.N / 1e6);
+    if (us < best) best = us, pick = o.config;
+  }
+  return pick;
+}
 static int heuristic_config(const GemmArgs &g) {
   double best = 1e300;
   int pick = 0;
@@ -133,6 +159,7 @@ static int heuristic_config(const GemmArgs &g) {
   // most evenly; 48 tokens, model's tiles / 64 x 128: 16384 x 4096 65 / 54 us, 8192 x 8192 59 / 49, 12288 x 6144 62 / 54, 20480 x
   // 5120 85 / 75, 8192 x 16384 119 / 99.  (Added to, the same matrices have no best tiles: each loses 5 to 15 % on some.)
   if (g.c_mode == 2 && g.K <= 64 && g.M * g.N >= (1LL << 25)) return kDeep64x128Config;
+  if (const int c = off_line_config(g); c >= 0) return c;
   for (int c = 0; c < kNumConfigs; ++c) {
     if (!config_takes(g, c, layout)) continue;
     const double us = config_us(g, c, layout);

@@ -215,6 +215,27 @@ def test_linear_fp32_split_waves(env, T, N, K):
         assert bool((got[n:] == 7.0).all())
 
 
+@pytest.mark.parametrize("T", [24, 40, 136, 704, 712, 1400, 1416])
+@pytest.mark.parametrize("N,K", [(1032, 2056), (2064, 1048)])
+def test_weight_gradients_of_rows_off_the_lines(env, T, N, K):
+    """Weight gradients of 2^21 results whose rows start inside 128-byte lines, around the token counts at which the choice
+    of tiles changes, stored and added to, against exact products' sums (fp32, at most 1416 terms: 1e-5) and, behind the last
+    row, nothing."""
+    torch, tm = env
+    print(f"weight gradient off the lines T={T} N={N} K={K}", flush=True)
+    rng = np.random.default_rng(T + N)
+    x, dy, g0 = rand(rng, (T, K), 1.0, BF16), rand(rng, (T, N), 0.1, BF16), rand(rng, (N, K), 1.0, FP32)
+    xd, dyd = to_dev(torch, x, BF16), to_dev(torch, dy, BF16)
+    dw0, dw1 = (torch.full((N + 1, K), 7.0, device="cuda") for _ in range(2))
+    dw1[:N].copy_(to_dev(torch, g0, FP32))
+    for dw, acc in ((dw0, 0), (dw1, 1)):
+        tm.tm_op_linear_wgrad(BF16, T, N, K, dyd, xd, dw, acc, stream_ptr(torch))
+    ref = (dyd.double().t().contiguous() @ xd.double()).cpu().numpy()
+    assert rel_err(to_host(dw0[:N]), ref) <= 1e-5
+    assert rel_err(to_host(dw1[:N]), g0 + ref) <= 1e-5
+    assert bool((dw0[N:] == 7.0).all()) and bool((dw1[N:] == 7.0).all())
+
+
 def split_gradient(env, T, N, K, seed, splits):
     """dx = dy W with scratch: whether the reduction was split shows in the scratch, which is filled before; the result meets
     the tolerance against the definition, is reproducible and independent of what the scratch held; without scratch the call
