@@ -1,5 +1,7 @@
 // LayerNorm / RMSNorm forward and backward, column reductions (bias and gain gradients).
 // HBM-bound kernels: 16-byte accesses, fp32 arithmetic, wavefront shuffles for row sums.
+#include <type_traits>
+
 #include "columns.h"
 #include "common.h"
 #include "../../include/tm_ops.h"
@@ -260,19 +262,21 @@ struct ColumnTask {
   const void *src;  // [rows][ld], the first n columns of it
   float *out;
   int64_t ld;
-  int rows, n, first_block;
-  bool typed;       // elements of the kernel's type, otherwise fp32
+  int rows, n, typed;  // typed: elements of the kernel's type, otherwise fp32
 };
-struct ColumnTasks {
-  ColumnTask t[kMaxColumnTasks];
-  int count;
+// MAX: tasks at most, 1, 3 or 6 (looking one up is a chain of scalar loads and the table is a kernel argument: 0.8 of 11.5 us
+// for one bias gradient of 12288 in a table of six)
+template <int MAX> struct TaskTable {
+  ColumnTask t[MAX];
+  int first_block[MAX], count;
 };
-__device__ __forceinline__ ColumnTask task_of_block(const ColumnTasks &ts) {  // uniform over the block
-  ColumnTask t = ts.t[0];
+typedef TaskTable<kMaxColumnTasks> ColumnTasks;
+template <int MAX> __device__ __forceinline__ int task_of_block(const TaskTable<MAX> &ts) {  // uniform over the block
+  int i = 0;
 #pragma unroll
-  for (int k = 1; k < kMaxColumnTasks; ++k)
-    if (k < ts.count && (int)blockIdx.x >= ts.t[k].first_block) t = ts.t[k];
-  return t;
+  for (int k = 1; k < MAX; ++k)
+    if (k < ts.count && (int)blockIdx.x >= ts.first_block[k]) i = k;
+  return i;
 }
 template <typename E> __device__ __forceinline__ float column_rows(const E *src, int64_t ld, int rows, int ry) {
   float s = 0.f;
@@ -289,11 +293,12 @@ template <typename E> __device__ __forceinline__ float column_rows(const E *src,
 }
 // out[c] (+)= sum_{r<rows} src[r*ld + c].  Block = 64 columns x 16 row lanes; lane y adds rows
 // y, y+16, ... in ascending order, then the lane sums are added in lane order: a fixed order.
-template <typename T>
-__global__ __launch_bounds__(64 * kRowLanes) void column_sums_kernel(const ColumnTasks ts, int accumulate) {
+template <typename T, int MAX>
+__global__ __launch_bounds__(64 * kRowLanes) void column_sums_kernel(const TaskTable<MAX> ts, int accumulate) {
   __shared__ float sm[kRowLanes][64];
-  const ColumnTask t = task_of_block(ts);
-  const int lane = threadIdx.x & 63, ry = threadIdx.x >> 6, c = ((int)blockIdx.x - t.first_block) * 64 + lane;
+  const int task = task_of_block<MAX>(ts);
+  const ColumnTask &t = ts.t[task];
+  const int lane = threadIdx.x & 63, ry = threadIdx.x >> 6, c = ((int)blockIdx.x - ts.first_block[task]) * 64 + lane;
   float s = 0.f;
   if (c < t.n) s = t.typed ? column_rows((const T *)t.src + c, t.ld, t.rows, ry) : column_rows((const float *)t.src + c, t.ld, t.rows, ry);
   sm[ry][lane] = s;
@@ -310,14 +315,15 @@ __global__ __launch_bounds__(64 * kRowLanes) void column_sums_kernel(const Colum
 constexpr int kColLanes = 64, kColRowsPerBlock = 4;
 constexpr int kColsumDirectRows = 512;  // up to here in one launch, 32 rows a lane (256 rows of 256 to 1024: 3.5 us, two launches 5.0)
 
-template <typename T>
-__global__ __launch_bounds__(kColLanes *kColRowsPerBlock) void colsum_partial_kernel(const ColumnTasks ts, int rows_per_group) {
+template <typename T, int MAX>
+__global__ __launch_bounds__(kColLanes *kColRowsPerBlock) void colsum_partial_kernel(const TaskTable<MAX> ts, int rows_per_group) {
   constexpr int VN = Vec<T>::N;
   __shared__ float sm[kColRowsPerBlock][kColLanes * VN];
-  const ColumnTask t = task_of_block(ts);
+  const int task = task_of_block<MAX>(ts);
+  const ColumnTask &t = ts.t[task];
   const T *dy = (const T *)t.src;
   const int lane = threadIdx.x % kColLanes, ry = threadIdx.x / kColLanes;
-  const int col = (((int)blockIdx.x - t.first_block) * kColLanes + lane) * VN;
+  const int col = (((int)blockIdx.x - ts.first_block[task]) * kColLanes + lane) * VN;
   const int64_t r0 = (int64_t)blockIdx.y * rows_per_group;
   const int64_t r1 = (r0 + rows_per_group < t.rows) ? r0 + rows_per_group : t.rows;
   float acc[VN];
@@ -465,12 +471,28 @@ static int norm_bwd_t(int kind, int64_t rows, int h, const void *dout, const voi
 
 // appends a task of 64 (column_sums_kernel) or more columns a block; returns the blocks so far
 static int add_task(ColumnTasks &ts, int blocks, int cols_per_block, const void *src, int64_t ld, int64_t rows, int64_t n, float *out, bool typed) {
-  ts.t[ts.count++] = ColumnTask{src, out, ld, (int)rows, (int)n, blocks, typed};
+  ts.first_block[ts.count] = blocks;
+  ts.t[ts.count++] = ColumnTask{src, out, ld, (int)rows, (int)n, typed};
   return blocks + (int)ceil_div(n, (int64_t)cols_per_block);
 }
+// go(table, MAX) on the smallest table that holds them
+template <typename F> static void with_table(const ColumnTasks &ts, F &&go) {
+  auto as = [&](auto max) {
+    TaskTable<max()> t;
+    for (int k = 0; k < max(); ++k) t.t[k] = ts.t[k], t.first_block[k] = ts.first_block[k];
+    t.count = ts.count;
+    go(t, max);
+  };
+  if (ts.count <= 1) as(std::integral_constant<int, 1>{});
+  else if (ts.count <= 3) as(std::integral_constant<int, 3>{});
+  else as(std::integral_constant<int, kMaxColumnTasks>{});
+}
 static int launch_column_sums(int dtype, const ColumnTasks &ts, int blocks, int accumulate, hipStream_t s, const char *what) {
-  if (dtype == TM_DTYPE_BF16) column_sums_kernel<bf16><<<(unsigned)blocks, 64 * kRowLanes, 0, s>>>(ts, accumulate);
-  else column_sums_kernel<float><<<(unsigned)blocks, 64 * kRowLanes, 0, s>>>(ts, accumulate);
+  auto go = [&](const auto &table, auto max) {
+    if (dtype == TM_DTYPE_BF16) column_sums_kernel<bf16, max()><<<(unsigned)blocks, 64 * kRowLanes, 0, s>>>(table, accumulate);
+    else column_sums_kernel<float, max()><<<(unsigned)blocks, 64 * kRowLanes, 0, s>>>(table, accumulate);
+  };
+  with_table(ts, go);
   return check_launch(what);
 }
 // The sums over T rows of `count` matrices as tasks of the column_sums_kernel launch that follows: the matrices themselves
@@ -490,8 +512,11 @@ static int add_column_sums(ColumnTasks &ts, int blocks, int dtype, int64_t T, co
   }
   const dim3 grid((unsigned)groups, (unsigned)R);
   const int rows_per_group = (int)ceil_div(T, (int64_t)R);
-  if (dtype == TM_DTYPE_BF16) colsum_partial_kernel<bf16><<<grid, kColLanes * kColRowsPerBlock, 0, s>>>(first, rows_per_group);
-  else colsum_partial_kernel<float><<<grid, kColLanes * kColRowsPerBlock, 0, s>>>(first, rows_per_group);
+  auto go = [&](const auto &table, auto max) {
+    if (dtype == TM_DTYPE_BF16) colsum_partial_kernel<bf16, max()><<<grid, kColLanes * kColRowsPerBlock, 0, s>>>(table, rows_per_group);
+    else colsum_partial_kernel<float, max()><<<grid, kColLanes * kColRowsPerBlock, 0, s>>>(table, rows_per_group);
+  };
+  with_table(first, go);
   return blocks;
 }
 
