@@ -1,8 +1,12 @@
-// Column sums that share their launches (norm.hip).
+// Norms that do more in their launches, and column sums that share theirs (norm.hip).
 #pragma once
 #include "common.h"
 
 namespace tmk {
+
+// tm_op_norm_fwd; copy (or NULL): x as it is, 16-byte aligned, no part of it x or out
+int norm_fwd_and_copy(int dtype, int kind, int64_t T, int64_t h, double eps, const void *x, const void *gain, const void *offset,
+                      void *out, float *mean, float *rstd, void *copy, hipStream_t s);
 
 struct ColumnSum {  // out[c] (+)= the sum over the rows of dy [T][n]; dy starts on 16 bytes, n is a multiple of 8
   const void *dy;

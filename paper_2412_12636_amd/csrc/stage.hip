@@ -498,19 +498,21 @@ extern "C" int tm_stage_fwd(tm_stage_t *st, const void *x_in, void *y_out, void 
     const int64_t pb = (int64_t)l * o.total;
     auto P = [&](int64_t off) -> const void * { return off < 0 ? nullptr : par + (pb + off) * d.es; };
     void *x = ws + k.x;
-    if (l == 0) {
+    // the input is kept for the backward pass: the first norm copies it, unless a hook may put another tensor in its place first
+    const bool norm_copies = l == 0 && !cm;
+    if (l == 0 && cm) {
       g_last_kernel = "copy_stage_input";
       TM_STEP(0, 2 * es * Th,
               hipMemcpyAsync(x, x_in, d.T * d.h * d.es, hipMemcpyDeviceToDevice, s) == hipSuccess
                   ? TM_OK
                   : fail(TM_ELAUNCH, "stage_fwd: copy of the stage input failed"));
-      if (cm) TM_TRY(tm_comm_call(cm, TM_COLL_RECV, TM_SCOPE_PP, TM_SITE_X, dt, x, act_bytes, s));
+      TM_TRY(tm_comm_call(cm, TM_COLL_RECV, TM_SCOPE_PP, TM_SITE_X, dt, x, act_bytes, s));
     }
     void *y = (l + 1 < c.n_layers) ? (void *)(ws + st->plan.layer[l + 1].x) : y_out;
     // a = Norm(x)
-    TM_STEP(0, 2 * es * Th,
-            tm_op_norm_fwd(dt, c.norm, d.T, d.h, c.norm_eps, x, P(o.norm1_gain), P(o.norm1_offset), ws + k.a,
-                           (float *)(ws + k.mean1), (float *)(ws + k.rstd1), s));
+    TM_STEP(0, (norm_copies ? 3 : 2) * es * Th,
+            norm_fwd_and_copy(dt, c.norm, d.T, d.h, c.norm_eps, norm_copies ? x_in : x, P(o.norm1_gain), P(o.norm1_offset), ws + k.a,
+                              (float *)(ws + k.mean1), (float *)(ws + k.rstd1), norm_copies ? x : nullptr, s));
     // qkv = a Wqkv^T + b
     TM_STEP(2.0 * d.T * d.nqkv * d.h, 0,
             tm_op_linear_fwd(dt, d.T, d.nqkv, d.h, ws + k.a, P(o.w_qkv), P(o.b_qkv), nullptr, ws + k.qkv, s));

@@ -120,6 +120,30 @@ def test_bias_gradients_behind_the_last_norm(env, layers, ffn, seq, norm, act, d
     st.close()
 
 
+@pytest.mark.parametrize("hidden,tokens,dtype", [(64, 1, si.DTYPE_BF16), (1016, 37, si.DTYPE_BF16), (2048, 300, si.DTYPE_BF16), (4104, 9, si.DTYPE_BF16),
+                                                 (264, 37, si.DTYPE_FP32), (1024, 300, si.DTYPE_FP32), (2056, 5, si.DTYPE_FP32)])
+def test_stage_keeps_its_input(env, hidden, tokens, dtype):
+    """The backward pass differentiates the input that the forward pass was given, not what the caller's buffer holds by
+    then: same bits with that buffer overwritten in between, for rows of one wave, two waves and a block."""
+    torch, tm = env
+    cfg = si.StageConfig(1, hidden, 2, 2, 16, 64, tokens, 1, dtype=dtype)
+    print(f"input kept {cfg}", flush=True)
+    st = GpuStage(torch, tm, cfg, si.make_flat_params(cfg))
+    x, dy = to_dev(torch, si.make_x(cfg), dtype), to_dev(torch, si.make_dy(cfg), dtype)
+    outs = []
+    for overwrite in (False, True):
+        st.grads.zero_()
+        mine = x.clone()
+        y = st.fwd(mine).clone()
+        if overwrite:
+            mine.fill_(float("nan"))
+        outs.append((y, st.bwd(dy).clone(), st.grads.clone()))
+    torch.cuda.synchronize()
+    for a, b in zip(*outs):
+        assert bool((a == b).all())
+    st.close()
+
+
 def test_gpt6p7b_shard_full_depth(env):
     torch, tm = env
     print("stage parity gpt6p7b (4 layers, full size)", flush=True)
