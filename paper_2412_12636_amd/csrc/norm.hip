@@ -11,9 +11,9 @@ namespace tmk {
 constexpr int kNormThreads = 512;
 constexpr int kNormMaxChunks = 4;  // 16-byte chunks per thread: hidden <= 512 * 4 * Vec::N
 
-// Threads of a row.  TPR = 512: a block per row, for rows of more than 4 KB and for few rows.  Many shorter rows leave most
+// Threads of a row.  TPR = 512: a block per row, for rows of more than 8 KB and for few rows.  Many shorter rows leave most
 // of such a block idle and one small row in flight per block (4000 rows of 2 KB: 13.3 us forward, 21 backward; a wave per
-// row: 6.4 and 11), so they take one wave (no barrier in the row sums) or two, and a block holds 512 / TPR rows.  Where the
+// row: 6.4 and 11), so they take one wave (no barrier in the row sums), two or four, and a block holds 512 / TPR rows.  Where the
 // line lies: norm_fwd_tpr, norm_bwd_tpr.
 //
 // Sum of two values over the TPR threads of this thread's row; red: 2 * 512 / 64 floats.
@@ -34,6 +34,17 @@ template <int TPR> __device__ __forceinline__ void row_sum2(float &a, float &b, 
       __syncthreads();
       a = red[w & ~1] + red[w | 1];
       b = red[NW + (w & ~1)] + red[NW + (w | 1)];
+    } else if constexpr (TPR == 256) {
+      constexpr int NW = kNormThreads / kWave;
+      const int w = threadIdx.x / kWave, w0 = w & ~3;
+      __syncthreads();
+      if (threadIdx.x % kWave == 0) {
+        red[w] = a;
+        red[NW + w] = b;
+      }
+      __syncthreads();
+      a = (red[w0] + red[w0 + 1]) + (red[w0 + 2] + red[w0 + 3]);
+      b = (red[NW + w0] + red[NW + w0 + 1]) + (red[NW + w0 + 2] + red[NW + w0 + 3]);
     }
   }
 }
@@ -385,12 +396,15 @@ static int norm_bwd_blocks(int64_t T) { return (int)(T < 256 ? T : 256); }
 // against several rows a block, bf16, backward: 1024 wide, 64 rows 5.4 / 6.9 us, 192 rows 6.5 / 7.3, 256 rows 7.2 / 7.4 (with
 // 300 rows some blocks get a second: 12 / 7.6); 512 wide (one chunk a lane, a shorter join) 32 rows 5.4 / 5.5, 96 rows 5.9 / 5.6.
 // Forward (nothing to join): two waves a row 3.1 / 3.3 at up to 256 rows 2048 wide, one wave 3.0 / 2.8.
+// Four waves a row (2048 to 4096 bf16, 1024 to 2048 fp32 wide) have two chunks of a lane in flight instead of one.  Forward, one
+// row a block / two: 2048 rows of 4096 bf16 8.7 / 7.5 us, 8192 rows 25.4 / 21.8, 2048 of 1536 fp32 7.8 / 6.2; backward from 1024
+// rows on, 2048 of 4096 17.6 / 17.2, 8192 42.2 / 37.8, 2048 of 1536 fp32 14.1 / 12.3, but 1000 of 3000 12.8 / 13.2, 500 of 4096 11.8 / 13.1.
 static int norm_fwd_tpr(int64_t T, int64_t h, int vn) {
-  return h <= 2 * 64 * vn ? 64 : h <= 2 * 128 * vn && T > 256 ? 128 : kNormThreads;
+  return h <= 2 * 64 * vn ? 64 : h <= 2 * 128 * vn && T > 256 ? 128 : h <= 2 * 256 * vn && T > 256 ? 256 : kNormThreads;
 }
 static int norm_bwd_tpr(int64_t T, int64_t h, int vn) {
   if (T <= (h <= 64 * vn ? 64 : 192)) return kNormThreads;
-  return h <= 2 * 64 * vn ? 64 : h <= 2 * 128 * vn ? 128 : kNormThreads;
+  return h <= 2 * 64 * vn ? 64 : h <= 2 * 128 * vn ? 128 : h <= 2 * 256 * vn && T > 1024 ? 256 : kNormThreads;
 }
 // blocks of the backward pass = partial rows: never more than norm_bwd_blocks, which sizes the scratch
 static int norm_bwd_grid(int64_t T, int64_t h, int vn) {
@@ -443,6 +457,7 @@ static int norm_fwd_t(int kind, int64_t rows, int h, float eps, const void *x, c
   if (tpr == 64 && h <= 64 * Vec<T>::N) TM_NORM_FWD_NARROW(1, 64);
   if (tpr == 64) TM_NORM_FWD_NARROW(2, 64);
   if (tpr == 128) TM_NORM_FWD_NARROW(2, 128);
+  if (tpr == 256) TM_NORM_FWD_NARROW(2, 256);
 #undef TM_NORM_FWD_NARROW
   if (kind == TM_NORM_LAYERNORM) {
     TM_NCH_SWITCH(nch, (norm_fwd_kernel<T, TM_NORM_LAYERNORM, NCH, COPY><<<dim3((unsigned)rows), kNormThreads, 0, s>>>(
@@ -474,6 +489,7 @@ static int norm_bwd_t(int kind, int64_t rows, int h, const void *dout, const voi
   if (tpr == 64 && h <= 64 * Vec<T>::N) TM_NORM_BWD_NARROW(1, 64);
   if (tpr == 64) TM_NORM_BWD_NARROW(2, 64);
   if (tpr == 128) TM_NORM_BWD_NARROW(2, 128);
+  if (tpr == 256) TM_NORM_BWD_NARROW(2, 256);
 #undef TM_NORM_BWD_NARROW
   if (kind == TM_NORM_LAYERNORM) {
     TM_NCH_SWITCH(nch, (norm_bwd_kernel<T, TM_NORM_LAYERNORM, NCH, XSUM><<<G, kNormThreads, 0, s>>>(

@@ -495,6 +495,15 @@ def test_norm_rows_of_a_wave_or_two(env, dtype, kind, T, h):
     test_norm_fwd_bwd(env, dtype, kind, T, h)
 
 
+@pytest.mark.parametrize("dtype,kind,T,h", [
+    (BF16, so.NORM_LAYERNORM, 256, 2056), (BF16, so.NORM_LAYERNORM, 257, 2056), (BF16, so.NORM_RMSNORM, 1024, 4096), (BF16, so.NORM_RMSNORM, 1025, 4096),
+    (BF16, so.NORM_LAYERNORM, 1027, 4088), (BF16, so.NORM_LAYERNORM, 1026, 4104), (FP32, so.NORM_LAYERNORM, 1025, 1032), (FP32, so.NORM_RMSNORM, 1031, 2048)])
+def test_norm_rows_of_four_waves(env, dtype, kind, T, h):
+    """The widths and row counts at which a row goes to four waves, with a row too few for the last block: as
+    test_norm_fwd_bwd."""
+    test_norm_fwd_bwd(env, dtype, kind, T, h)
+
+
 @pytest.mark.parametrize("dtype,T,N", [(BF16, 1, 8), (BF16, 513, 520), (FP32, 2049, 264), (BF16, 17000, 24)])
 def test_bias_grad_row_groups(env, dtype, T, N):
     """One group of one row, and the row counts at which the number of row groups changes, as test_bias_grad."""
