@@ -156,10 +156,11 @@ template <int DP, int SIDES> struct F32Walk {
 template <int DP, int SIDES> __device__ __forceinline__ void f32_join(f32x16 (&acc)[DP / 32], float *x, int side, int lane) {
   __syncthreads();
   if (side > 0) {
+    const int at = SIDES == 2 ? 0 : (side - 1) * (DP / 2);
 #pragma unroll
     for (int dt = 0; dt < DP / 32; ++dt)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) x[((side - 1) * (DP / 2) + dt * 16 + v) * 64 + lane] = acc[dt][v];
+      for (int v = 0; v < 16; ++v) x[(at + dt * 16 + v) * 64 + lane] = acc[dt][v];
   }
   __syncthreads();
   if (side == 0) {
@@ -251,7 +252,7 @@ template <int DP, int SIDES> __global__ __launch_bounds__(256, 1) void f32_fwd_k
   __syncthreads();
   float *x = reinterpret_cast<float *>(smem) + (size_t)grp * (SIDES - 1) * (DP / 2 + 2) * 64;  // [side][o..., m, l][lane]
   if (side > 0) {
-    float *xs = x + (side - 1) * (DP / 2 + 2) * 64;
+    float *xs = SIDES == 2 ? x : x + (side - 1) * (DP / 2 + 2) * 64;
 #pragma unroll
     for (int dt = 0; dt < DP / 32; ++dt)
 #pragma unroll

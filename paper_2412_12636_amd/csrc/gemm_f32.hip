@@ -153,7 +153,9 @@ __global__ __launch_bounds__((64 * F32Cfg<BM, BN, WM, WN, KSPL, NS, SUB>::NW)) v
     n0 = (int)(blockIdx.x / p.tiles_m) * BN;
   }
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int ks = wave / NT, wt = wave % NT, lw = wave % LW, lu = wave / LW;
+  // (zeros that the compiler can see: 5 % of the short products)
+  const int ks = KSPL > 1 ? wave / NT : 0, wt = KSPL > 1 ? wave % NT : wave;
+  const int lw = UG > 1 ? wave % LW : wave, lu = UG > 1 ? wave / LW : 0;
   const int wm = (wt / (BN / WN)) * WM, wn = (wt % (BN / WN)) * WN;
   LA la;
   LB lb;
@@ -250,10 +252,12 @@ __global__ __launch_bounds__((64 * F32Cfg<BM, BN, WM, WN, KSPL, NS, SUB>::NW)) v
 
 #define TM_F32_GEMM(AKC, BKC, EPI)                                                                         \
   template __global__ void gemm_f32_kernel<128, 128, 64, 64, 1, 2, 1, AKC, BKC, EPI>(const F32GemmParams); \
+  template __global__ void gemm_f32_kernel<64, 64, 32, 32, 1, 3, 1, AKC, BKC, EPI>(const F32GemmParams);   \
   template __global__ void gemm_f32_kernel<64, 64, 32, 32, 2, 3, 1, AKC, BKC, EPI>(const F32GemmParams);   \
   template __global__ void gemm_f32_kernel<64, 64, 32, 32, 4, 3, 2, AKC, BKC, EPI>(const F32GemmParams);   \
   template __global__ void gemm_f32_kernel<32, 32, 32, 32, 8, 4, 2, AKC, BKC, EPI>(const F32GemmParams);   \
   template __global__ void gemm_f32_kernel<16, 16, 16, 16, 4, 4, 4, AKC, BKC, EPI>(const F32GemmParams);
+template __global__ void gemm_f32_kernel<32, 32, 32, 32, 4, 4, 2, true, false, 0>(const F32GemmParams);
 TM_F32_GEMM(true, true, 0)
 TM_F32_GEMM(true, false, 0)
 TM_F32_GEMM(false, false, 1)
@@ -303,7 +307,10 @@ static int launch(const GemmArgs &g, hipStream_t s) {
   if (blocks > 0x7fffffff) return fail(TM_ESIZE, "gemm_f32: too many tiles");
   // patches of 8 row-tiles: 1024 x 8192 over 1024 138 -> 131 us, its weight gradient 138 -> 128, 64 x 2048 over 2048 (16x16
   // tiles, strided weights) 23 -> 10.  One block a unit is faster in plain order (1024 x 1024 over 4096 76 us, 80 in patches).
-  p.group = blocks > kUnits ? 8 : 0;
+  // So are short reductions, whose time is the results' (weight gradient of 2048 x 1536 over 700 36.6, 38.5 in patches;
+  // 1000 x 512 over 512 8.3, 8.7; 2000 x 1536 over 600 37.0, 35.6).
+  // (32x32 tiles from four blocks a unit on: 512 x 1000 over 1024, two, 12.4 / 12.8 in patches)
+  p.group = blocks > (BM == 32 ? 4 : 1) * kUnits && g.K >= (g.c_mode ? 1024 : 576) ? 8 : 0;
   g_last_kernel = "gemm_f32_kernel";
   gemm_f32_kernel<BM, BN, WM, WN, KSPL, NS, SUB, A_KC, B_KC, EPI><<<(unsigned)blocks, 64 * C::NW, lds, s>>>(p);
   return check_launch("gemm_f32");
@@ -317,12 +324,23 @@ template <bool A_KC, bool B_KC, int EPI> static int pick(const GemmArgs &g, hipS
   auto cost = [&](int64_t b, double factor) { return (double)ceil_div(tiles(b), kUnits) * b * b * factor; };
   // the last stage of the 16x16 form reaches 4 FK rows past a strided operand's end: their offsets must not come round to its front
   auto reaches = [&](int64_t cs) { return cs == 1 || (g.K + 4 * FK) * cs * 4 < (1LL << 32); };
-  const bool one64 = tiles(64) <= kUnits;  // four waves a SIMD make up for the other blocks (1024 x 1024 over 1024: 23.2 -> 21.2 us)
-  const double c128 = cost(128, tiles(128) <= kUnits ? 1.12 : 1.0), c64 = cost(64, one64 ? 1.33 : 1.15), c32 = cost(32, 1.4);
+  const bool one64 = tiles(64) <= kUnits;  // four waves a SIMD make up for the other blocks
+  const bool brief = g.K < 512;  // reductions so short that the split's end shows: 3000 x 768 over 300 19.2 us on 64x64, 20.3 on 32x32
+  const double c128 = cost(128, !brief && tiles(128) <= kUnits ? 1.12 : 1.0), c64 = cost(64, brief ? 1.1 : one64 ? 1.33 : 1.15);
+  const double c32 = cost(32, brief ? 1.5 : 1.4);
   const double c16 = reaches(g.a_cs) && reaches(g.b_cs) ? cost(16, 2.0) : c32 + 1;
   if (c128 <= c64 && c128 <= c32 && c128 <= c16) return launch<128, 128, 64, 64, 1, 2, 1, A_KC, B_KC, EPI>(g, s);
-  if (c64 <= c32 && c64 <= c16)
-    return one64 ? launch<64, 64, 32, 32, 4, 3, 2, A_KC, B_KC, EPI>(g, s) : launch<64, 64, 32, 32, 2, 3, 1, A_KC, B_KC, EPI>(g, s);
+  if (c64 <= c32 && c64 <= c16) {
+    // waves that share a stage have to meet at the end, which short reductions do not pay for: one block a unit from 512
+    // elements on (1024 x 1024 over 1024 23.2 -> 21.2 us, over 64 4.0 -> 4.5), several from 1024 on (weight gradient of
+    // 3072 x 1024 over 1024 57.8 -> 55.5, of 5104 x 896 over 167 20.2 -> 21.9)
+    if (one64 && g.K >= 512) return launch<64, 64, 32, 32, 4, 3, 2, A_KC, B_KC, EPI>(g, s);
+    if (!one64 && g.K >= 1024) return launch<64, 64, 32, 32, 2, 3, 1, A_KC, B_KC, EPI>(g, s);
+    return launch<64, 64, 32, 32, 1, 3, 1, A_KC, B_KC, EPI>(g, s);
+  }
+  // (strided weights, one block a unit: 896 columns over 5104 30.4 us on four waves, 30.9 on eight)
+  if constexpr (A_KC && !B_KC)
+    if (c32 <= c16 && tiles(32) <= kUnits) return launch<32, 32, 32, 32, 4, 4, 2, A_KC, B_KC, EPI>(g, s);
   if (c32 <= c16) return launch<32, 32, 32, 32, 8, 4, 2, A_KC, B_KC, EPI>(g, s);
   return launch<16, 16, 16, 16, 4, 4, 4, A_KC, B_KC, EPI>(g, s);
 }
