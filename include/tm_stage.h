@@ -159,7 +159,8 @@ int tm_stage_fwd(tm_stage_t *st, const void *x_in, void *y_out, void *stream);
 /*
  * Backward pass for the most recent tm_stage_fwd (the pipeline receive of the
  * output gradient is served by dy_in; sends are skipped).  Writes the input
- * gradient to dx_out and ADDS parameter gradients into buffers.grads.
+ * gradient to dx_out and ADDS parameter gradients into buffers.grads.  dx_out may be
+ * dy_in or overlap it; neither may alias the workspace.
  * TM_ESTATE if no forward pass precedes it.  Must be enqueued on the same
  * stream as that forward pass or after it has completed.
  */

@@ -565,6 +565,11 @@ static int adam_slice(tm_stage *st, int64_t first, int64_t count, const tm_adam_
                      lowp ? (char *)st->buf.params + first * 2 : nullptr, hp, step, s);
 }
 
+static bool overlap(const void *a, const void *b, int64_t bytes) {
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+  return (x > y ? x - y : y - x) < (uintptr_t)bytes;
+}
+
 // hp != NULL: every layer's parameters are updated as soon as its gradients are complete
 static int stage_bwd(tm_stage_t *st, const void *dy_in, void *dx_out, void *stream, const tm_adam_hparams_t *hp,
                      int64_t step) {
@@ -699,10 +704,14 @@ static int stage_bwd(tm_stage_t *st, const void *dy_in, void *dx_out, void *stre
     fused.clear();
     TM_STEP(mm(d.h, d.f), wgrad_bytes(d.h, d.f, dy, ws + k.g, pb, o.w_fc2), wgrad(pb, o.w_fc2, d.h, d.f, dy, ws + k.g));
     // the bias gradients wait for the end of the layer, where their column sums share launches with the first norm's
-    // (below the top layer FC2's has come out of the first norm's backward pass of the layer above)
+    // (below the top layer FC2's has come out of the first norm's backward pass of the layer above).  That norm writes dx
+    // before they are formed: a caller's dx over its dy leaves FC2's no time to wait.
     ColumnSum sums[3];
     int n_sums = 0;
-    if (bias && l == c.n_layers - 1) sums[n_sums++] = ColumnSum{dy, G(o.b_fc2), d.h};
+    if (bias && l == c.n_layers - 1) {
+      if (overlap(dy, dx, act_bytes)) TM_STEP(0, es * Th, tm_op_bias_grad(dt, d.T, d.h, dy, G(o.b_fc2), red, acc, s));
+      else sums[n_sums++] = ColumnSum{dy, G(o.b_fc2), d.h};
+    }
     // activation
     void *du = ws + pl.dwide;
     TM_STEP(0, es * d.T * (d.f + 2 * d.f1), tm_op_act_bwd(dt, c.act, d.T, d.f, dg, ws + k.u, du, s));

@@ -120,6 +120,35 @@ def test_bias_gradients_behind_the_last_norm(env, layers, ffn, seq, norm, act, d
     st.close()
 
 
+@pytest.mark.parametrize("update", [False, True], ids=["bwd", "bwd_adam"])
+@pytest.mark.parametrize("layers,seq,shift", [(1, 512, 0), (1, 513, 0), (1, 513, 128), (2, 512, 0), (2, 513, 128)])
+def test_input_gradient_over_the_output_gradient(env, layers, seq, shift, update):
+    """dx_out may be dy_in, or overlap it (shift: elements between the two): the same bits as with separate buffers, for one
+    layer, whose last launches write dx, and for two; column sums in one launch (512 tokens) and with partial rows (513)."""
+    torch, tm = env
+    cfg = si.StageConfig(layers, 64, 4, 4, 16, 96, seq, 1)
+    print(f"in place {cfg} shift={shift} update={update}", flush=True)
+    flat = si.make_flat_params(cfg)
+    x, dy = to_dev(torch, si.make_x(cfg), cfg.dtype), to_dev(torch, si.make_dy(cfg), cfg.dtype)
+    outs = []
+    for in_place in (False, True):
+        st = GpuStage(torch, tm, cfg, flat)
+        st.fwd(x)
+        room = torch.empty(dy.numel() + shift, dtype=dy.dtype, device="cuda")
+        mine = room[:dy.numel()].view(dy.shape)
+        mine.copy_(dy)
+        dx = room[shift:].view(dy.shape) if in_place else torch.empty_like(dy)
+        if update:
+            tm.tm_stage_bwd_adam(st.handle, mine, dx, tm.make_hparams(**si.ADAM_DEFAULTS), 1, stream_ptr(torch))
+        else:
+            tm.tm_stage_bwd(st.handle, mine, dx, stream_ptr(torch))
+        torch.cuda.synchronize()
+        outs.append({"dx": dx.clone(), **{k: getattr(st, k).clone() for k in ("grads", "params", "master", "m", "v")}})
+        st.close()
+    for name, ref in outs[0].items():
+        assert torch.equal(outs[1][name], ref), name
+
+
 @pytest.mark.parametrize("hidden,tokens,dtype", [(64, 1, si.DTYPE_BF16), (1016, 37, si.DTYPE_BF16), (2048, 300, si.DTYPE_BF16), (4104, 9, si.DTYPE_BF16),
                                                  (264, 37, si.DTYPE_FP32), (1024, 300, si.DTYPE_FP32), (2056, 5, si.DTYPE_FP32)])
 def test_stage_keeps_its_input(env, hidden, tokens, dtype):
