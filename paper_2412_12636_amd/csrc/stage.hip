@@ -604,7 +604,8 @@ static int stage_bwd(tm_stage_t *st, const void *dy_in, void *dx_out, void *stre
   // chain has already produced, onto a side stream; the main stream waits for the side stream before it reuses
   // the scratch buffers (start of the next layer) and before the call returns in stream order.
   const char *streams_env = getenv("TM_BWD_STREAMS");
-  bool two = !st->prof.on && streams_env && atoi(streams_env) >= 2;
+  // (one layer that writes dx over its dy has no later join that would keep dx behind FC2's weight gradient)
+  bool two = !st->prof.on && streams_env && atoi(streams_env) >= 2 && !(c.n_layers == 1 && overlap(dy_in, dx_out, d.T * d.h * d.es));
   if (two && !st->side) {
     bool ok = hipStreamCreateWithFlags(&st->side, hipStreamNonBlocking) == hipSuccess;
     for (hipEvent_t &e : st->ev_fork) ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;

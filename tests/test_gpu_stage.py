@@ -122,12 +122,15 @@ def test_bias_gradients_behind_the_last_norm(env, layers, ffn, seq, norm, act, d
 
 @pytest.mark.parametrize("update", [False, True], ids=["bwd", "bwd_adam"])
 @pytest.mark.parametrize("layers,seq,shift", [(1, 512, 0), (1, 513, 0), (1, 513, 128), (2, 512, 0), (2, 513, 128)])
-def test_input_gradient_over_the_output_gradient(env, layers, seq, shift, update):
+@pytest.mark.parametrize("streams", ["1", "2"])
+def test_input_gradient_over_the_output_gradient(env, monkeypatch, layers, seq, shift, update, streams):
     """dx_out may be dy_in, or overlap it (shift: elements between the two): the same bits as with separate buffers, for one
-    layer, whose last launches write dx, and for two; column sums in one launch (512 tokens) and with partial rows (513)."""
+    layer, whose last launches write dx, and for two; column sums in one launch (512 tokens) and with partial rows (513); the
+    weight gradients on the one stream or on their own."""
     torch, tm = env
+    monkeypatch.setenv("TM_BWD_STREAMS", streams)
     cfg = si.StageConfig(layers, 64, 4, 4, 16, 96, seq, 1)
-    print(f"in place {cfg} shift={shift} update={update}", flush=True)
+    print(f"in place {cfg} shift={shift} update={update} streams={streams}", flush=True)
     flat = si.make_flat_params(cfg)
     x, dy = to_dev(torch, si.make_x(cfg), cfg.dtype), to_dev(torch, si.make_dy(cfg), cfg.dtype)
     outs = []
