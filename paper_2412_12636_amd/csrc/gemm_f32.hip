@@ -11,15 +11,17 @@
 // Bound by the MFMA rate: 64 clocks for 32x32x2, a quarter of a wave's 64x64 tile per pair of reduction elements, for
 // which LDS delivers 16 bytes per clock and unit and L2 eight.  What decides the time of a small product is therefore how
 // evenly its tiles cover the SIMDs, and how much of the barrier and the LDS latency a second wave of the SIMD covers:
-// blocks of 128x128; of 64x64 and 32x32 with two to four waves a SIMD that split every stage's reduction elements (their
-// sums meet in LDS in wave order); and of 16x16 on 16x16x4 MFMAs, where 32x32 tiles leave most units without one.
-// With one wave a SIMD on every tile before: 1024 x 1024 over 1024 23.1 -> 21.2 us, over 3072 (strided weights) 66.6 -> 56.8;
-// 256 x 256 over 1024 8.2 -> 4.5; 1500 x 768 over 768 25.0 -> 23.9 (weight gradient 31.7 -> 25.1).
+// blocks of 128x128 and 64x64, one wave a SIMD; of 64x64 with four waves a SIMD, and of 32x32 with one or two, that split
+// every stage's reduction elements (their sums meet in LDS in wave order); and of 16x16, split four ways, on 16x16x4 MFMAs,
+// where 32x32 tiles leave most units without one.  Which one: gemm_f32_form.h.
+// With one wave a SIMD on every tile and none of 16x16 before: 1024 x 1024 over 1024 23.7 -> 21.9 us, over 3072 (strided
+// weights) 64 -> 58; 256 x 256 over 1024 8.2 -> 4.5; 1500 x 768 over 768 25.1 -> 24.2 (weight gradient 29.9 -> 25.4).
 // (The twelve products of a layer of hidden 1024, SwiGLU width 4096, 1024 tokens: 4.9 ms = 21 TFLOP/s on the 64x64
 // plain-ALU tile kernel that this one replaces, 1.03 ms = 100 TFLOP/s here; its largest run at 113, the vendor BLAS reaches
 // 150 on 8192^3.  The matrix cores are busy for 80 to 84 % of the cycles in which a unit has waves on 128x128 tiles, 69 % on
 // 64x64.)
 #include "gemm.h"
+#include "gemm_f32_form.h"
 
 namespace tmk {
 
@@ -27,8 +29,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
 
-constexpr int FK = 32;  // reduction elements of a step
-constexpr int64_t kUnits = 256;
+constexpr int FK = 32;     // reduction elements of a step
+constexpr int kPatch = 8;  // row-tiles of a patch
 
 struct F32GemmParams {
   int M, N, K;
@@ -37,7 +39,7 @@ struct F32GemmParams {
   float *C;
   int64_t ldc;
   const float *bias, *residual;
-  int tiles_m, tiles_n, group;
+  int tiles_m, tiles_n;
   uint32_t a_bytes, b_bytes, c_bytes;
 };
 
@@ -120,18 +122,21 @@ template <> struct F32Mma<16> {
 };
 
 // WM, WN: wave tile (below 32: 16x16 MFMAs); KSPL: waves that split a stage's reduction elements; NS: LDS stages; SUB: steps
-// of a stage, for tiles whose single step is shorter than the barrier and the LDS latency around it
+// of a stage, for tiles whose single step is shorter than the barrier and the LDS latency around it.  PATCH: the order of the
+// walk, a form of its own (its arithmetic ahead of the first load cost the others 1 to 3 %, and weight gradients of four
+// 64x64 tiles a unit 8 %: 4784 x 776 over 1324 94 -> 102 us)
 template <int BM, int BN, int WM, int WN, int KSPL, int NS, int SUB> struct F32Cfg {
   static constexpr int MF = WM < 32 ? 16 : 32, NT = (BM / WM) * (BN / WN), NW = NT * KSPL;
   static constexpr int TM = WM / MF, TN = WN / MF, NV = F32Mma<MF>::NV;
   // a step of a small tile is fewer wave-wide loads than there are waves: groups of LW waves fetch alternate steps
   static constexpr int LW = NW * 1024 <= (BM < BN ? BM : BN) * FK * 4 ? NW : (BM < BN ? BM : BN) * FK * 4 / 1024, UG = NW / LW;
   static constexpr int STEP = (BM + BN) * FK * 4, STAGE = SUB * STEP, J = 4 * MF / 32;  // fragments of four elements a step
+  static constexpr int WJ = KSPL < J ? KSPL : J, JW = J / WJ;  // split waves on the fragments of one step, and how many each takes
   static constexpr int SUMS = KSPL > 1 ? NW * NV * 256 : 0, LDS = NS * STAGE > SUMS ? NS * STAGE : SUMS;
   static_assert(KSPL == 1 || (TM == 1 && TN == 1 && NV % KSPL == 0), "split waves hold one tile each");
-  static_assert(SUB % UG == 0 && SUB * J % KSPL == 0, "steps divide among the waves");
+  static_assert(SUB % UG == 0 && SUB * J % KSPL == 0 && J % WJ == 0 && KSPL % WJ == 0, "steps divide among the waves");
 };
-template <int BM, int BN, int WM, int WN, int KSPL, int NS, int SUB, bool A_KC, bool B_KC, int EPI>
+template <int BM, int BN, int WM, int WN, int KSPL, int NS, int SUB, bool PATCH, bool A_KC, bool B_KC, int EPI>
 __global__ __launch_bounds__((64 * F32Cfg<BM, BN, WM, WN, KSPL, NS, SUB>::NW)) void gemm_f32_kernel(const F32GemmParams p) {
   typedef F32Cfg<BM, BN, WM, WN, KSPL, NS, SUB> C;
   typedef F32Mma<C::MF> MM;
@@ -141,11 +146,12 @@ __global__ __launch_bounds__((64 * F32Cfg<BM, BN, WM, WN, KSPL, NS, SUB>::NW)) v
   constexpr int LOADS = SUB / UG * (LA::NLOAD + LB::NLOAD);
   extern __shared__ __align__(1024) char lds[];
   int m0, n0;
-  if (p.group) {  // several blocks a unit: an XCD (ids round-robin over eight) owns a range of tiles, walked in patches
-    const int nblk = gridDim.x, xcd = blockIdx.x % 8, base = nblk / 8, rem = nblk % 8;
+  if constexpr (PATCH) {  // an XCD (ids round-robin over eight) owns a range of tiles, walked in patches
+    asm volatile("" ::"s"(p.A), "s"(p.B), "s"(p.lda), "s"(p.ldb), "s"(p.K), "s"(p.a_bytes));  // fetched now, not behind the divisions
+    const int nblk = p.tiles_m * p.tiles_n, xcd = blockIdx.x % 8, base = nblk / 8, rem = nblk % 8;
     const int lid = xcd * base + (xcd < rem ? xcd : rem) + (int)(blockIdx.x / 8);
-    const int gi = lid / (p.group * p.tiles_n), first = gi * p.group, in_group = lid - first * p.tiles_n;
-    const int rows = p.tiles_m - first < p.group ? p.tiles_m - first : p.group;
+    const int gi = lid / (kPatch * p.tiles_n), first = gi * kPatch, in_group = lid - first * p.tiles_n;
+    const int rows = p.tiles_m - first < kPatch ? p.tiles_m - first : kPatch;
     m0 = (first + in_group % rows) * BM;
     n0 = (in_group / rows) * BN;
   } else {
@@ -187,8 +193,8 @@ __global__ __launch_bounds__((64 * F32Cfg<BM, BN, WM, WN, KSPL, NS, SUB>::NW)) v
     issue(kt + NS - 1);
 #pragma unroll
     for (int i0 = 0; i0 < SUB * C::J / KSPL; ++i0) {
-      const int jj = i0 * KSPL + ks, j = jj % C::J;
-      const char *As = lds + (kt % NS) * C::STAGE + (jj / C::J) * C::STEP, *Bs = As + LA::BYTES;
+      const int j = i0 % C::JW * C::WJ + ks % C::WJ, u = i0 / C::JW * (KSPL / C::WJ) + ks / C::WJ;
+      const char *As = lds + (kt % NS) * C::STAGE + u * C::STEP, *Bs = As + LA::BYTES;
       f32x4 a[TM], b[TN];
 #pragma unroll
       for (int t = 0; t < TM; ++t) a[t] = LA::frag(As, wm + t * MF, j, lane);
@@ -250,18 +256,21 @@ __global__ __launch_bounds__((64 * F32Cfg<BM, BN, WM, WN, KSPL, NS, SUB>::NW)) v
   }
 }
 
-#define TM_F32_GEMM(AKC, BKC, EPI)                                                                         \
-  template __global__ void gemm_f32_kernel<128, 128, 64, 64, 1, 2, 1, AKC, BKC, EPI>(const F32GemmParams); \
-  template __global__ void gemm_f32_kernel<64, 64, 32, 32, 1, 3, 1, AKC, BKC, EPI>(const F32GemmParams);   \
-  template __global__ void gemm_f32_kernel<64, 64, 32, 32, 2, 3, 1, AKC, BKC, EPI>(const F32GemmParams);   \
-  template __global__ void gemm_f32_kernel<64, 64, 32, 32, 4, 3, 2, AKC, BKC, EPI>(const F32GemmParams);   \
-  template __global__ void gemm_f32_kernel<32, 32, 32, 32, 8, 4, 2, AKC, BKC, EPI>(const F32GemmParams);   \
-  template __global__ void gemm_f32_kernel<16, 16, 16, 16, 4, 4, 4, AKC, BKC, EPI>(const F32GemmParams);
-template __global__ void gemm_f32_kernel<32, 32, 32, 32, 4, 4, 2, true, false, 0>(const F32GemmParams);
-TM_F32_GEMM(true, true, 0)
-TM_F32_GEMM(true, false, 0)
-TM_F32_GEMM(false, false, 1)
-TM_F32_GEMM(false, false, 2)
+#define TM_F32_GEMM(W32, AKC, BKC, EPI)                                                                            \
+  template __global__ void gemm_f32_kernel<128, 128, 64, 64, 1, 2, 1, false, AKC, BKC, EPI>(const F32GemmParams); \
+  template __global__ void gemm_f32_kernel<64, 64, 32, 32, 1, 3, 1, false, AKC, BKC, EPI>(const F32GemmParams);   \
+  template __global__ void gemm_f32_kernel<64, 64, 32, 32, 4, 3, 2, false, AKC, BKC, EPI>(const F32GemmParams);   \
+  template __global__ void gemm_f32_kernel<32, 32, 32, 32, 4, 4, 2, false, AKC, BKC, EPI>(const F32GemmParams);   \
+  template __global__ void gemm_f32_kernel<32, 32, 32, 32, W32, 4, 2, true, AKC, BKC, EPI>(const F32GemmParams);  \
+  template __global__ void gemm_f32_kernel<16, 16, 16, 16, 4, 4, 4, false, AKC, BKC, EPI>(const F32GemmParams);
+TM_F32_GEMM(4, true, true, 0)
+TM_F32_GEMM(4, true, false, 0)
+TM_F32_GEMM(8, false, false, 1)
+TM_F32_GEMM(8, false, false, 2)
+template __global__ void gemm_f32_kernel<16, 16, 16, 16, 4, 4, 4, true, true, true, 0>(const F32GemmParams);
+template __global__ void gemm_f32_kernel<16, 16, 16, 16, 4, 4, 4, true, true, false, 0>(const F32GemmParams);
+template __global__ void gemm_f32_kernel<32, 32, 32, 32, 8, 4, 2, false, false, false, 1>(const F32GemmParams);
+template __global__ void gemm_f32_kernel<32, 32, 32, 32, 8, 4, 2, false, false, false, 2>(const F32GemmParams);
 
 // One of each operand's strides is 1, 16-byte chunks along it are aligned and whole, 32-bit offsets reach everything.
 bool gemm_f32_supported(const GemmArgs &g) {
@@ -277,7 +286,7 @@ bool gemm_f32_supported(const GemmArgs &g) {
   return g.c_mode ? (g.a_cs != 1 && g.b_cs != 1) : g.a_cs == 1;
 }
 
-template <int BM, int BN, int WM, int WN, int KSPL, int NS, int SUB, bool A_KC, bool B_KC, int EPI>
+template <int BM, int BN, int WM, int WN, int KSPL, int NS, int SUB, bool PATCH, bool A_KC, bool B_KC, int EPI>
 static int launch(const GemmArgs &g, hipStream_t s) {
   F32GemmParams p;
   p.M = (int)g.M;
@@ -299,50 +308,32 @@ static int launch(const GemmArgs &g, hipStream_t s) {
   typedef F32Cfg<BM, BN, WM, WN, KSPL, NS, SUB> C;
   constexpr int lds = C::LDS;
   static bool attr_set = false;  // per instantiation
-  if (!attr_set && hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_f32_kernel<BM, BN, WM, WN, KSPL, NS, SUB, A_KC, B_KC, EPI>),
+  if (!attr_set && hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_f32_kernel<BM, BN, WM, WN, KSPL, NS, SUB, PATCH, A_KC, B_KC, EPI>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
     return fail(TM_ELAUNCH, "gemm_f32: cannot reserve %d bytes of LDS", lds);
   attr_set = true;
   const int64_t blocks = (int64_t)p.tiles_m * ceil_div(g.N, BN);
   if (blocks > 0x7fffffff) return fail(TM_ESIZE, "gemm_f32: too many tiles");
-  // patches of 8 row-tiles: 1024 x 8192 over 1024 138 -> 131 us, its weight gradient 138 -> 128, 64 x 2048 over 2048 (16x16
-  // tiles, strided weights) 23 -> 10.  One block a unit is faster in plain order (1024 x 1024 over 4096 76 us, 80 in patches).
-  // So are short reductions, whose time is the results' (weight gradient of 2048 x 1536 over 700 36.6, 38.5 in patches;
-  // 1000 x 512 over 512 8.3, 8.7; 2000 x 1536 over 600 37.0, 35.6).
-  // (32x32 tiles from four blocks a unit on: 512 x 1000 over 1024, two, 12.4 / 12.8 in patches)
-  p.group = blocks > (BM == 32 ? 4 : 1) * kUnits && g.K >= (g.c_mode ? 1024 : 576) ? 8 : 0;
   g_last_kernel = "gemm_f32_kernel";
-  gemm_f32_kernel<BM, BN, WM, WN, KSPL, NS, SUB, A_KC, B_KC, EPI><<<(unsigned)blocks, 64 * C::NW, lds, s>>>(p);
+  gemm_f32_kernel<BM, BN, WM, WN, KSPL, NS, SUB, PATCH, A_KC, B_KC, EPI><<<(unsigned)blocks, 64 * C::NW, lds, s>>>(p);
   return check_launch("gemm_f32");
 }
 
-// A block's time is its share of the MFMA rate, BM * BN per step, and a unit works through ceil(blocks / 256) of them;
-// the smaller tiles read LDS and synchronise more per MFMA, and so does a unit with one block alone.  Factors from 45
-// products of 40 to 2048 rows and 136 to 8192 columns, on which the pick is the fastest tile or within 2 % of it.
 template <bool A_KC, bool B_KC, int EPI> static int pick(const GemmArgs &g, hipStream_t s) {
-  auto tiles = [&](int64_t b) { return ceil_div(g.M, b) * ceil_div(g.N, b); };
-  auto cost = [&](int64_t b, double factor) { return (double)ceil_div(tiles(b), kUnits) * b * b * factor; };
   // the last stage of the 16x16 form reaches 4 FK rows past a strided operand's end: their offsets must not come round to its front
   auto reaches = [&](int64_t cs) { return cs == 1 || (g.K + 4 * FK) * cs * 4 < (1LL << 32); };
-  const bool one64 = tiles(64) <= kUnits;  // four waves a SIMD make up for the other blocks
-  const bool brief = g.K < 512;  // reductions so short that the split's end shows: 3000 x 768 over 300 19.2 us on 64x64, 20.3 on 32x32
-  const double c128 = cost(128, !brief && tiles(128) <= kUnits ? 1.12 : 1.0), c64 = cost(64, brief ? 1.1 : one64 ? 1.33 : 1.15);
-  const double c32 = cost(32, brief ? 1.5 : 1.4);
-  const double c16 = reaches(g.a_cs) && reaches(g.b_cs) ? cost(16, 2.0) : c32 + 1;
-  if (c128 <= c64 && c128 <= c32 && c128 <= c16) return launch<128, 128, 64, 64, 1, 2, 1, A_KC, B_KC, EPI>(g, s);
-  if (c64 <= c32 && c64 <= c16) {
-    // waves that share a stage have to meet at the end, which short reductions do not pay for: one block a unit from 512
-    // elements on (1024 x 1024 over 1024 23.2 -> 21.2 us, over 64 4.0 -> 4.5), several from 1024 on (weight gradient of
-    // 3072 x 1024 over 1024 57.8 -> 55.5, of 5104 x 896 over 167 20.2 -> 21.9)
-    if (one64 && g.K >= 512) return launch<64, 64, 32, 32, 4, 3, 2, A_KC, B_KC, EPI>(g, s);
-    if (!one64 && g.K >= 1024) return launch<64, 64, 32, 32, 2, 3, 1, A_KC, B_KC, EPI>(g, s);
-    return launch<64, 64, 32, 32, 1, 3, 1, A_KC, B_KC, EPI>(g, s);
+  const F32Form f = f32_form(g.M, g.N, g.K, EPI != 0, reaches(g.a_cs) && reaches(g.b_cs));
+  if (f.tile == 128) return launch<128, 128, 64, 64, 1, 2, 1, false, A_KC, B_KC, EPI>(g, s);
+  if (f.tile == 64 && f.split == 4) return launch<64, 64, 32, 32, 4, 3, 2, false, A_KC, B_KC, EPI>(g, s);
+  if (f.tile == 64) return launch<64, 64, 32, 32, 1, 3, 1, false, A_KC, B_KC, EPI>(g, s);
+  if (f.tile == 32 && f.patches) return launch<32, 32, 32, 32, EPI ? 8 : 4, 4, 2, true, A_KC, B_KC, EPI>(g, s);
+  if constexpr (EPI != 0) {
+    if (f.tile == 32 && f.split == 8) return launch<32, 32, 32, 32, 8, 4, 2, false, A_KC, B_KC, EPI>(g, s);
+  } else {
+    if (f.tile == 16 && f.patches) return launch<16, 16, 16, 16, 4, 4, 4, true, A_KC, B_KC, EPI>(g, s);
   }
-  // (strided weights, one block a unit: 896 columns over 5104 30.4 us on four waves, 30.9 on eight)
-  if constexpr (A_KC && !B_KC)
-    if (c32 <= c16 && tiles(32) <= kUnits) return launch<32, 32, 32, 32, 4, 4, 2, A_KC, B_KC, EPI>(g, s);
-  if (c32 <= c16) return launch<32, 32, 32, 32, 8, 4, 2, A_KC, B_KC, EPI>(g, s);
-  return launch<16, 16, 16, 16, 4, 4, 4, A_KC, B_KC, EPI>(g, s);
+  if (f.tile == 32) return launch<32, 32, 32, 32, 4, 4, 2, false, A_KC, B_KC, EPI>(g, s);
+  return launch<16, 16, 16, 16, 4, 4, 4, false, A_KC, B_KC, EPI>(g, s);
 }
 
 int gemm_f32(const GemmArgs &g, hipStream_t s) {

@@ -8,6 +8,7 @@ import pytest
 
 import synth_inputs as si
 from oracle import stage_oracle as so
+from tests.f32_form import forms
 from tests.gpu_util import (TOL_ADAM, TOL_BF16, TOL_FP32, f32_dev, rand, rel_err, require_gpu, stream_ptr, to_dev,
                             to_host, torch_dtype)
 
@@ -155,8 +156,10 @@ def test_reduction_lengths_off_the_step_in_every_configuration(env, T, N, K):
         tm.tm_gemm_force_config(-1)
 
 
-@pytest.mark.parametrize("T,N,K", [(1, 8, 8), (33, 40, 72), (257, 136, 200), (300, 1096, 520), (2050, 2056, 40), (2048, 2040, 72)],
-                         ids=["one_row", "split_waves", "split_waves_ragged", "tiles_of_64", "tiles_of_64_ragged", "tiles_of_128"])
+@pytest.mark.parametrize("T,N,K", [(1, 8, 8), (33, 40, 72), (257, 136, 200), (300, 1096, 520), (2050, 2056, 40), (2048, 2040, 72), (2040, 136, 2040),
+                                   (136, 2040, 2040)],
+                         ids=["one_row", "tiles_of_16", "tiles_of_16_ragged", "tiles_of_32_and_64", "tiles_of_64_ragged", "tiles_of_128", "tiles_of_128_dgrad",
+                              "tiles_of_128_wgrad"])
 def test_linear_fp32_tiles(env, T, N, K):
     """The fp32 products in each of their tile forms, ragged in every dimension, against the definition (fp32 sums of
     at most 2056 terms: 1e-5), with one infinite row of x: its neighbours stay as they are."""
@@ -187,14 +190,18 @@ def test_linear_fp32_tiles(env, T, N, K):
     assert np.array_equal(yb[:T].cpu().numpy()[rows], y[:T].cpu().numpy()[rows])
 
 
-@pytest.mark.parametrize("T,N,K", [(16, 16, 128), (17, 24, 136), (40, 136, 264), (250, 248, 1000), (64, 2048, 72), (577, 520, 1032), (1000, 1032, 328),
-                                   (1090, 1032, 136)],
-                         ids=["one_16", "tiles_of_16_ragged", "tiles_of_16", "tiles_of_16_long", "tiles_of_16_patches", "one_64_a_unit", "one_64_a_unit_ragged",
-                              "patches_of_64"])
-def test_linear_fp32_split_waves(env, T, N, K):
+@pytest.mark.parametrize("T,N,K,which", [
+    (16, 16, 128, "16/4 16/4 16/4"), (17, 24, 136, "16/4 16/4 16/4"), (40, 136, 264, "16/4 16/4 16/4"), (64, 2048, 72, "16/4 16/4 32/4"),
+    (250, 248, 1000, "16/4 32/4 32/4"), (330, 296, 1032, "16/4 32/4 32/8"), (90, 1048, 1080, "16/4p 16/4p 32/4"), (1090, 1032, 136, "32/4 32/4 32/8"),
+    (577, 520, 1032, "32/4 32/4 32/8"), (1000, 1032, 328, "32/4 32/4 32/8"), (777, 776, 1032, "32/4p 64/4 64/4"), (1001, 776, 904, "64/4 64/4 32/8p"),
+    (1001, 1000, 776, "64/4 64/4 64/4"), (1028, 840, 1032, "64/4 32/4p 64/4"),
+    (520, 328, 1032, "32/4 64/1 32/8"), (1100, 1504, 1032, "64/1 32/4p 64/1")], ids=str)
+def test_linear_fp32_split_waves(env, T, N, K, which):
     """The fp32 products whose waves split a stage's reduction elements (16x16, 32x32 and 64x64 tiles), at the ends of tiles
-    and stages, in plain and in patch order: an fp32 sum of n products is off by at most n 2^-24 of the sum of their
-    magnitudes and by about sqrt(n) 2^-24 for these signs, 2e-6 at 1032 terms; stored and added to."""
+    and stages, in plain order and in patches; which: the forms of the three products (tile / split, p: patches), so that
+    a change of the rule shows here.  An fp32 sum of n products is off by at most n 2^-24 of the sum of their
+    magnitudes and by about sqrt(n) 2^-24 for these signs, 2e-6 at 1100 terms; stored and added to."""
+    assert forms(T, N, K) == which
     torch, tm = env
     print(f"linear fp32 split waves T={T} N={N} K={K}", flush=True)
     rng = np.random.default_rng(T + N + K)
