@@ -396,15 +396,17 @@ static int norm_bwd_blocks(int64_t T) { return (int)(T < 256 ? T : 256); }
 // against several rows a block, bf16, backward: 1024 wide, 64 rows 5.4 / 6.9 us, 192 rows 6.5 / 7.3, 256 rows 7.2 / 7.4 (with
 // 300 rows some blocks get a second: 12 / 7.6); 512 wide (one chunk a lane, a shorter join) 32 rows 5.4 / 5.5, 96 rows 5.9 / 5.6.
 // Forward (nothing to join): two waves a row 3.1 / 3.3 at up to 256 rows 2048 wide, one wave 3.0 / 2.8.
-// Four waves a row (2048 to 4096 bf16, 1024 to 2048 fp32 wide) have two chunks of a lane in flight instead of one.  Forward, one
-// row a block / two: 2048 rows of 4096 bf16 8.7 / 7.5 us, 8192 rows 25.4 / 21.8, 2048 of 1536 fp32 7.8 / 6.2; backward from 1024
-// rows on, 2048 of 4096 17.6 / 17.2, 8192 42.2 / 37.8, 2048 of 1536 fp32 14.1 / 12.3, but 1000 of 3000 12.8 / 13.2, 500 of 4096 11.8 / 13.1.
+// Four waves a row (4 to 8 KB of it) have two chunks of a lane in flight instead of one, and two rows a block.  Forward, one
+// row a block / two: 2048 rows of 4096 bf16 8.7 / 7.5 us, 8192 rows 25.4 / 21.8, 2048 of 1536 fp32 7.8 / 6.2.  Backward their
+// join and registers cost, so only for rows of up to 5.5 KB, which leave more of a block idle, and from 1280 rows on, bf16
+// 2304: 2391 of 1144 fp32 16.8 / 14.5, 7181 of 2480 bf16 44 / 39, but 1179 of 2176 12.8 / 13.7, 500 of 4096 11.8 / 13.1, 1641
+// of 3968 17.3 / 17.8, 11941 of 3664 69.5 / 75.1 (1 to 10 % slower in most such sizes).
 static int norm_fwd_tpr(int64_t T, int64_t h, int vn) {
   return h <= 2 * 64 * vn ? 64 : h <= 2 * 128 * vn && T > 256 ? 128 : h <= 2 * 256 * vn && T > 256 ? 256 : kNormThreads;
 }
 static int norm_bwd_tpr(int64_t T, int64_t h, int vn) {
   if (T <= (h <= 64 * vn ? 64 : 192)) return kNormThreads;
-  return h <= 2 * 64 * vn ? 64 : h <= 2 * 128 * vn ? 128 : h <= 2 * 256 * vn && T > 1024 ? 256 : kNormThreads;
+  return h <= 2 * 64 * vn ? 64 : h <= 2 * 128 * vn ? 128 : h <= 352 * vn && T > (vn == 8 ? 2304 : 1280) ? 256 : kNormThreads;
 }
 // blocks of the backward pass = partial rows: never more than norm_bwd_blocks, which sizes the scratch
 static int norm_bwd_grid(int64_t T, int64_t h, int vn) {

@@ -504,10 +504,12 @@ def test_norm_rows_of_a_wave_or_two(env, dtype, kind, T, h):
 
 @pytest.mark.parametrize("dtype,kind,T,h", [
     (BF16, so.NORM_LAYERNORM, 256, 2056), (BF16, so.NORM_LAYERNORM, 257, 2056), (BF16, so.NORM_RMSNORM, 1024, 4096), (BF16, so.NORM_RMSNORM, 1025, 4096),
-    (BF16, so.NORM_LAYERNORM, 1027, 4088), (BF16, so.NORM_LAYERNORM, 1026, 4104), (FP32, so.NORM_LAYERNORM, 1025, 1032), (FP32, so.NORM_RMSNORM, 1031, 2048)])
+    (BF16, so.NORM_LAYERNORM, 1027, 4088), (BF16, so.NORM_LAYERNORM, 1026, 4104), (FP32, so.NORM_LAYERNORM, 1025, 1032), (FP32, so.NORM_RMSNORM, 1031, 2048),
+    (FP32, so.NORM_LAYERNORM, 1280, 1032), (FP32, so.NORM_LAYERNORM, 1281, 1032), (FP32, so.NORM_RMSNORM, 1283, 1408), (BF16, so.NORM_LAYERNORM, 2304, 2056),
+    (BF16, so.NORM_LAYERNORM, 2305, 2056), (BF16, so.NORM_RMSNORM, 2307, 2816), (BF16, so.NORM_LAYERNORM, 2307, 2824)])
 def test_norm_rows_of_four_waves(env, dtype, kind, T, h):
-    """The widths and row counts at which a row goes to four waves, with a row too few for the last block: as
-    test_norm_fwd_bwd."""
+    """The widths and row counts at which a row goes to four waves, forward (more than 256 rows of 4 to 8 KB) and backward (more
+    than 1280 in fp32, 2304 in bf16, up to 5.5 KB), with a row too few for the last block: as test_norm_fwd_bwd."""
     test_norm_fwd_bwd(env, dtype, kind, T, h)
 
 
