@@ -290,8 +290,7 @@ constexpr int kMaxColumnTasks = 6;
 struct ColumnTask {
   const void *src;  // [rows][ld], the first n columns of it
   float *out;
-  int64_t ld;
-  int rows, n, typed;  // typed: elements of the kernel's type, otherwise fp32
+  int ld, rows, n, typed;  // typed: elements of the kernel's type, otherwise fp32
 };
 // MAX: tasks at most, 1, 3 or 6 (looking one up is a chain of scalar loads and the table is a kernel argument: 0.8 of 11.5 us
 // for one bias gradient of 12288 in a table of six)
@@ -307,7 +306,8 @@ template <int MAX> __device__ __forceinline__ int task_of_block(const TaskTable<
     if (k < ts.count && (int)blockIdx.x >= ts.first_block[k]) i = k;
   return i;
 }
-template <typename E> __device__ __forceinline__ float column_rows(const E *src, int64_t ld, int rows, int ry) {
+template <int MAX> __device__ __forceinline__ int first_block_of(const TaskTable<MAX> &ts, int task) { return MAX == 1 ? 0 : ts.first_block[task]; }
+template <typename E> __device__ __forceinline__ float column_rows(const E *src, int ld, int rows, int ry) {
   float s = 0.f;
   int r = ry;
   for (; r + 3 * kRowLanes < rows; r += 4 * kRowLanes) {  // four independent loads in flight per trip
@@ -322,14 +322,15 @@ template <typename E> __device__ __forceinline__ float column_rows(const E *src,
 }
 // out[c] (+)= sum_{r<rows} src[r*ld + c].  Block = 64 columns x 16 row lanes; lane y adds rows
 // y, y+16, ... in ascending order, then the lane sums are added in lane order: a fixed order.
-template <typename T, int MAX>
+// BOTH: some tasks' rows are typed and some fp32; otherwise all are T (asking each costs a few percent of the short launches).
+template <typename T, int MAX, bool BOTH>
 __global__ __launch_bounds__(64 * kRowLanes) void column_sums_kernel(const TaskTable<MAX> ts, int accumulate) {
   __shared__ float sm[kRowLanes][64];
   const int task = task_of_block<MAX>(ts);
   const ColumnTask &t = ts.t[task];
-  const int lane = threadIdx.x & 63, ry = threadIdx.x >> 6, c = ((int)blockIdx.x - ts.first_block[task]) * 64 + lane;
+  const int lane = threadIdx.x & 63, ry = threadIdx.x >> 6, c = ((int)blockIdx.x - first_block_of<MAX>(ts, task)) * 64 + lane;
   float s = 0.f;
-  if (c < t.n) s = t.typed ? column_rows((const T *)t.src + c, t.ld, t.rows, ry) : column_rows((const float *)t.src + c, t.ld, t.rows, ry);
+  if (c < t.n) s = BOTH && !t.typed ? column_rows((const float *)t.src + c, t.ld, t.rows, ry) : column_rows((const T *)t.src + c, t.ld, t.rows, ry);
   sm[ry][lane] = s;
   __syncthreads();
   if (ry == 0 && c < t.n) {
@@ -352,7 +353,7 @@ __global__ __launch_bounds__(kColLanes *kColRowsPerBlock) void colsum_partial_ke
   const ColumnTask &t = ts.t[task];
   const T *dy = (const T *)t.src;
   const int lane = threadIdx.x % kColLanes, ry = threadIdx.x / kColLanes;
-  const int col = (((int)blockIdx.x - ts.first_block[task]) * kColLanes + lane) * VN;
+  const int col = (((int)blockIdx.x - first_block_of<MAX>(ts, task)) * kColLanes + lane) * VN;
   const int64_t r0 = (int64_t)blockIdx.y * rows_per_group;
   const int64_t r1 = (r0 + rows_per_group < t.rows) ? r0 + rows_per_group : t.rows;
   float acc[VN];
@@ -508,7 +509,7 @@ static int norm_bwd_t(int kind, int64_t rows, int h, const void *dout, const voi
 // appends a task of 64 (column_sums_kernel) or more columns a block; returns the blocks so far
 static int add_task(ColumnTasks &ts, int blocks, int cols_per_block, const void *src, int64_t ld, int64_t rows, int64_t n, float *out, bool typed) {
   ts.first_block[ts.count] = blocks;
-  ts.t[ts.count++] = ColumnTask{src, out, ld, (int)rows, (int)n, typed};
+  ts.t[ts.count++] = ColumnTask{src, out, (int)ld, (int)rows, (int)n, typed};
   return blocks + (int)ceil_div(n, (int64_t)cols_per_block);
 }
 // go(table, MAX) on the smallest table that holds them
@@ -524,9 +525,12 @@ template <typename F> static void with_table(const ColumnTasks &ts, F &&go) {
   else as(std::integral_constant<int, kMaxColumnTasks>{});
 }
 static int launch_column_sums(int dtype, const ColumnTasks &ts, int blocks, int accumulate, hipStream_t s, const char *what) {
+  bool typed = false, plain = false;  // (fp32: the same)
+  for (int k = 0; k < ts.count; ++k) (ts.t[k].typed && dtype == TM_DTYPE_BF16 ? typed : plain) = true;
   auto go = [&](const auto &table, auto max) {
-    if (dtype == TM_DTYPE_BF16) column_sums_kernel<bf16, max()><<<(unsigned)blocks, 64 * kRowLanes, 0, s>>>(table, accumulate);
-    else column_sums_kernel<float, max()><<<(unsigned)blocks, 64 * kRowLanes, 0, s>>>(table, accumulate);
+    if (typed && plain) column_sums_kernel<bf16, max(), true><<<(unsigned)blocks, 64 * kRowLanes, 0, s>>>(table, accumulate);
+    else if (typed) column_sums_kernel<bf16, max(), false><<<(unsigned)blocks, 64 * kRowLanes, 0, s>>>(table, accumulate);
+    else column_sums_kernel<float, max(), false><<<(unsigned)blocks, 64 * kRowLanes, 0, s>>>(table, accumulate);
   };
   with_table(ts, go);
   return check_launch(what);
