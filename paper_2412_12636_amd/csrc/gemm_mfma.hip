@@ -126,22 +126,22 @@ static bool config_takes(const GemmArgs &g, int c, int layout) {
 }
 // A weight gradient whose rows do not start on 128-byte lines reads and writes two partial lines for every 32 results, through
 // different blocks where a tile ends: with few tokens that, and not the main loop, is its time, and small tiles, whose
-// epilogues overlap other blocks' main loops, lose least.  Time = scale x the model's + per million results, fitted to 26
-// such matrices of 16 to 4000 tokens, for results that are added to and that are overwritten.  On those of the range below
-// (2^21 results and more; from some 1400 and 700 tokens on the model alone is as good) the pick is 0.5 % and 1.4 % slower than
-// the fastest configuration, the model's alone 20 % and 10 %: 40 tokens on 5128 x 3080 added to 57 -> 40 us, 300 on
-// 8200 x 3080 103 -> 77 (overwritten 67 -> 55), 1000 on 5128 x 3080 89 -> 75.
+// epilogues overlap other blocks' main loops, lose least.  Time = scale x the model's + per million results, for results that
+// are added to and that are overwritten, fitted to 393 and 199 such matrices.  On matrices left out of the fit the pick is
+// 18 % and 9 % faster than the model's alone (the fastest configuration: 19 % and 14 %) and slower by more than 3 % on 10 and 8
+// of them.  The range: below 2^23 results one matrix in six lost 3 to 28 %, and from some 1000 and 480 tokens on the model alone
+// is as good.  40 tokens on 5128 x 3080 added to 50 -> 38 us, 300 on 8200 x 3080 104 -> 76 (overwritten 60 -> 50), 1000 on
+// 5128 x 3080 91 -> 77.
 struct OffLineCost {
   int config;
   double scale[2], per_million[2];  // added to, overwritten
 };
-static const OffLineCost kOffLine[] = {{9, {1.13, 0.99}, {2.48, 0.95}},  {13, {1.19, 0.98}, {2.34, 1.05}}, {14, {1.06, 1.01}, {2.42, 1.05}},
-                                       {16, {1.21, 1.22}, {1.02, 0.05}}, {17, {1.01, 0.96}, {1.51, 0.61}}, {18, {0.96, 0.99}, {1.98, 0.65}},
-                                       {19, {1.13, 1.07}, {1.66, 0.50}}};
+static const OffLineCost kOffLine[] = {{13, {1.03, 0.83}, {2.40, 1.05}}, {14, {0.86, 0.81}, {2.39, 1.05}}, {17, {0.82, 0.72}, {1.72, 0.79}},
+                                       {18, {0.77, 0.76}, {2.09, 0.80}}, {19, {0.87, 0.94}, {1.95, 0.54}}};
 static int off_line_config(const GemmArgs &g) {  // -1: not such a product
-  if ((g.c_mode != 1 && g.c_mode != 2) || (g.ldc % 32 == 0 && (((uintptr_t)g.C) & 127) == 0) || g.M * g.N < (1LL << 21)) return -1;
+  if ((g.c_mode != 1 && g.c_mode != 2) || (g.ldc % 32 == 0 && (((uintptr_t)g.C) & 127) == 0) || g.M * g.N < (1LL << 23)) return -1;
   const bool adds = g.c_mode == 1;
-  if (adds ? g.K > 1408 : g.K <= 32 || g.K > 704) return -1;
+  if (adds ? g.K > 1024 : g.K <= 32 || g.K > 480) return -1;
   double best = 1e300;
   int pick = -1;
   for (const OffLineCost &o : kOffLine) {

@@ -222,11 +222,11 @@ def test_linear_fp32_split_waves(env, T, N, K, which):
         assert bool((got[n:] == 7.0).all())
 
 
-@pytest.mark.parametrize("T", [24, 40, 136, 704, 712, 1400, 1416])
-@pytest.mark.parametrize("N,K", [(1032, 2056), (2064, 1048)])
+@pytest.mark.parametrize("T", [24, 32, 33, 136, 480, 488, 704, 712, 1024, 1032, 1400, 1416])
+@pytest.mark.parametrize("N,K", [(1032, 2056), (2064, 1048), (2056, 4104), (4128, 2056), (2040, 4104)])
 def test_weight_gradients_of_rows_off_the_lines(env, T, N, K):
-    """Weight gradients of 2^21 results whose rows start inside 128-byte lines, around the token counts at which the choice
-    of tiles changes, stored and added to, against exact products' sums (fp32, at most 1416 terms: 1e-5) and, behind the last
+    """Weight gradients whose rows start inside 128-byte lines, below and above the 2^23 results and around the token counts
+    at which the choice of tiles changes, stored and added to, against exact products' sums (fp32, at most 1416 terms: 1e-5) and, behind the last
     row, nothing."""
     torch, tm = env
     print(f"weight gradient off the lines T={T} N={N} K={K}", flush=True)
