@@ -756,6 +756,55 @@ def test_attention_head_sizes_below_128(env, monkeypatch, form, seq, batch, nq, 
     assert bool((ctx[seq:] == 7.0).all()) and bool((dqkv[seq:] == 7.0).all())
 
 
+@pytest.mark.parametrize("form", ["0", "1", "2"], ids=["separate_blocks", "split_and_single_launch", "shared_walks"])
+@pytest.mark.parametrize("d", [32, 64, 96, 120, 128])
+def test_attention_maxima_that_rise_along_the_keys(env, monkeypatch, form, d):
+    """Row maxima that rise by 3, 7.9, 8.1 and 30 powers of two from one tile of 64 keys to the next, in two thirds of the rows
+    of a wave, half of these the other way round (falling): what a walk has summed up is rescaled, or kept beside probabilities
+    of up to 2^8, in every block form.  Bounds as for random scores; an exponent of magnitude up to 72 is off by a few
+    72 * 2^-24, which leaves 5e-5 for the log-sum-exp."""
+    torch, tm = env
+    for name in ("TM_ATTN_SPLIT", "TM_ATTN_BWD_BOTH"):
+        monkeypatch.setenv(name, form)
+    print(f"attention rising maxima form={form} d={d}", flush=True)
+    seq, batch, nq, nkv = 596, 1, 2, 1
+    rng = np.random.default_rng(d)
+    A, B, W = nq * d, nkv * d, (nq + 2 * nkv) * d
+    qkv, dctx = rand(rng, (seq, batch, W), 1.0, BF16), rand(rng, (seq, batch, A), 0.1, BF16)
+    tile = np.arange(seq) // 64
+    height = np.cumsum([0, 3, 7.9, 8.1, 30, 3, 7.9, 8.1, 3, 0])[tile] * math.log(2.0) * math.sqrt(d)
+    coarse = si.snap_to_bf16_grid(height.astype(np.float32))
+    k = qkv[:, 0, A:A + B]
+    k[:] = si.snap_to_bf16_grid(0.25 * k)
+    k[:, 0], k[:, 1] = coarse, si.snap_to_bf16_grid((height - coarse).astype(np.float32))
+    for g in range(nq):                                       # rows that follow the rise, that fall with it, that ignore it
+        qkv[:, 0, g * d:g * d + 2] = np.array([1.0, -1.0, 0.0], np.float32)[(np.arange(seq) + g) % 3][:, None]
+    s = stream_ptr(torch)
+    qd = to_dev(torch, qkv, BF16)
+    ctx = torch.empty((seq, batch, A), dtype=torch.bfloat16, device="cuda")
+    dqkv = torch.empty((seq, batch, W), dtype=torch.bfloat16, device="cuda")
+    lse = torch.zeros((batch, nq, seq), dtype=torch.float32, device="cuda")
+    scratch = torch.empty(tm.tm_op_attn_bwd_scratch_bytes(BF16, seq, batch, nq, nkv, d), dtype=torch.uint8, device="cuda")
+    tm.tm_op_attn_fwd(BF16, seq, batch, nq, nkv, d, qd, ctx, lse, s)
+    tm.tm_op_attn_bwd(BF16, seq, batch, nq, nkv, d, qd, ctx, to_dev(torch, dctx, BF16), lse, scratch, dqkv, s)
+    q64 = qkv.astype(np.float64)
+    q, k, v = (a.reshape(seq, batch, -1, d) for a in (q64[..., :A], q64[..., A:A + B], q64[..., A + B:]))
+    bounds = (tol_of(BF16), tol_of(BF16)) if d == 128 else (2.0 ** -8, 2.0 ** -7)
+    assert rel_err(to_host(ctx), so.attention_fwd(q, k, v).reshape(seq, batch, A)) <= bounds[0]
+    for g in range(nq):
+        sc = np.where(np.tril(np.ones((seq, seq), bool)), q[:, 0, g] @ k[:, 0, 0].T / math.sqrt(d), -np.inf)
+        mx = sc.max(axis=1)
+        assert np.abs(to_host(lse[0, g]) - (mx + np.log(np.exp(sc - mx[:, None]).sum(axis=1)))).max() <= 5e-5
+        rises = np.diff([sc[-20:, 64 * t:64 * t + 64].max(axis=1) for t in range(9)], axis=0) / math.log(2.0)
+        assert rises.max() > 25 and ((rises > 2) & (rises < 7.9)).any() and ((rises > 8.1) & (rises < 12)).any()
+    refs = so.attention_bwd(dctx.astype(np.float64).reshape(seq, batch, nq, d), q, k, v)
+    got = to_host(dqkv)
+    # (the two columns of dQ that the heights are in: their hundreds times ctx's rounding in the row statistics)
+    assert rel_err(got[..., :A].reshape(seq, batch, nq, d)[..., 2:], refs[0][..., 2:]) <= bounds[1]
+    for part, ref in zip((got[..., A:A + B], got[..., A + B:]), refs[1:]):
+        assert rel_err(part, ref.reshape(seq, batch, -1)) <= bounds[1]
+
+
 @pytest.mark.parametrize("seq,batch,nq,nkv,d", [(1, 2, 2, 1, 24), (5, 2, 2, 1, 8), (32, 1, 2, 2, 32), (33, 2, 4, 2, 40), (64, 1, 1, 1, 64), (65, 1, 4, 1, 64),
                                                  (200, 2, 2, 2, 80), (130, 1, 2, 1, 96), (127, 1, 2, 2, 104), (257, 1, 2, 1, 128)])
 def test_attention_fp32_tiles(env, seq, batch, nq, nkv, d):
