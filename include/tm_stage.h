@@ -267,7 +267,9 @@ void tm_stage_destroy(tm_stage_t *st);
  * (at most max_entries; `kernel` points at static storage), clears the record list and returns
  * the number of entries filled.  flops counts 2*M*N*K per matrix product and 2*b*nq*s^2*d per
  * causal attention forward (twice that backward); bytes counts the operands and results of the
- * streaming kernels once.  Disabling frees the events.  Events are host objects: no device
+ * streaming kernels once.  A step is booked under its first kernel: a layer's bias gradients, whose column
+ * sums share launches with its first norm's backward pass, under norm_bwd_kernel with the bytes they read,
+ * and the copy of the stage's input, which its first norm makes, under norm_fwd_kernel.  Disabling frees the events.  Events are host objects: no device
  * memory is allocated.
  */
 typedef struct {

@@ -519,7 +519,9 @@ static F32Params make_params(int64_t seq, int64_t batch, int64_t nq, int64_t nkv
 // backward) stay one pass, and up to twice that two passes whose long and short walks even out from 256 positions.
 // Two sides -> four, forward and backward, us: 128 positions, 8 walks of 64: 9.6 -> 7.1, 18.4 -> 14.0; 1024, 8: 47.8 -> 26.8,
 // 83.7 -> 57.6; 512, 32 walks: 26.7 -> 21.6, 62.3 -> 68.7; 128, 128 walks: 10.4 -> 13.1, 26.9 -> 39.8; heads of 128, 512
-// positions, 4 walks: 42.7 -> 26.5, 77.6 -> 49.5.
+// positions, 4 walks: 42.7 -> 26.5, 77.6 -> 49.5.  Four / two sides on 300 random calls (geometric mean): up to 128 blocks 0.76
+// below 256 positions and 0.66 above, backward 0.81 and 0.70; 129 to 256 blocks of 256 positions and more 0.69 for heads of up to
+// 64 and 0.74 above, with their one buffer (backward 0.75, 0.80), of fewer positions 1.0 (0.8 to 1.3).
 static bool f32_four_sides(const F32Params &p, bool backward) {
   const int64_t blocks = ceil_div((int64_t)p.seq, (int64_t)64) * p.batch * p.nq * (backward ? 2 : 1);
   return p.seq > 64 && blocks <= (p.seq >= 256 ? 256 : 128);

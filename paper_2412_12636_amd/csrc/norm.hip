@@ -52,8 +52,9 @@ template <int TPR> __device__ __forceinline__ void row_sum2(float &a, float &b, 
 // ---------------------------------------------------------------------------------------
 // forward: one block per token row; the row stays in registers between the passes.
 // Every access goes through a per-row buffer descriptor (chunks past the row read as zero).
-// COPY: x goes to `copy` as well, byte for byte (a form of its own: as a branch it cost the others up to 7 %).  A stage keeps its input so; a copy ahead of the norm was one more pass
-// and launch (a step of the tiny preset 203.3 -> 200.5 us, the small bf16 layer's 0.979 -> 0.971 of the former time).
+// COPY: x goes to `copy` as well, byte for byte (a form of its own: as a branch it cost the others up to 7 %).  A stage keeps
+// its input so; a copy ahead of the norm was one more pass and launch (a step of the tiny preset 203.3 -> 200.5 us, the small
+// bf16 layer's 0.8 % shorter).
 // ---------------------------------------------------------------------------------------
 template <typename T, int KIND, int NCH, bool COPY, int TPR = kNormThreads>
 __global__ __launch_bounds__(kNormThreads) void norm_fwd_kernel(
@@ -283,7 +284,8 @@ __global__ __launch_bounds__(kNormThreads) void norm_bwd_kernel(
 // ---------------------------------------------------------------------------------------
 // Column sums.  Up to six of them share a launch: the partial rows of a norm's backward pass (gain, offset and dx sums), the
 // bias gradients of a layer, or the second halves of these.  A launch of this kind takes 3 to 5 us whatever it adds up, and
-// a layer with biases has seven or eight (together behind the last norm: 1.7 % of a step of the 6.7B shard, tiny preset 216 -> 203 us).
+// a layer with biases has seven or eight (together behind the last norm: 1.7 % of a step of the 6.7B shard, tiny preset 216 ->
+// 203 us).
 // ---------------------------------------------------------------------------------------
 constexpr int kRowLanes = 16;  // row lanes of a block: 256 partial rows are four loads deep (four lanes: 7 us a launch, now 4.8)
 constexpr int kMaxColumnTasks = 6;
@@ -445,16 +447,16 @@ static int norm_fwd_t(int kind, int64_t rows, int h, float eps, const void *x, c
                       void *out, float *mean, float *rstd, void *copy, hipStream_t s) {
   const int nch = pick_nch(h, Vec<T>::N);
   g_last_kernel = "norm_fwd_kernel";
-#define TM_NORM_FWD_NARROW(NCH, TPR)                                                                              \
-  do {                                                                                                            \
-    const unsigned grid = (unsigned)ceil_div(rows, (int64_t)(kNormThreads / TPR));                                \
-    if (kind == TM_NORM_LAYERNORM)                                                                                \
-      norm_fwd_kernel<T, TM_NORM_LAYERNORM, NCH, COPY, TPR><<<grid, kNormThreads, 0, s>>>(                              \
-          (const T *)x, (const T *)gain, (const T *)offset, (T *)out, mean, rstd, (T *)copy, rows, h, eps);                  \
-    else                                                                                                          \
-      norm_fwd_kernel<T, TM_NORM_RMSNORM, NCH, COPY, TPR><<<grid, kNormThreads, 0, s>>>(                                \
-          (const T *)x, (const T *)gain, nullptr, (T *)out, mean, rstd, (T *)copy, rows, h, eps);                            \
-    return check_launch("norm_fwd");                                                                              \
+#define TM_NORM_FWD_NARROW(NCH, TPR)                                                                        \
+  do {                                                                                                      \
+    const unsigned grid = (unsigned)ceil_div(rows, (int64_t)(kNormThreads / TPR));                          \
+    if (kind == TM_NORM_LAYERNORM)                                                                          \
+      norm_fwd_kernel<T, TM_NORM_LAYERNORM, NCH, COPY, TPR><<<grid, kNormThreads, 0, s>>>(                  \
+          (const T *)x, (const T *)gain, (const T *)offset, (T *)out, mean, rstd, (T *)copy, rows, h, eps); \
+    else                                                                                                    \
+      norm_fwd_kernel<T, TM_NORM_RMSNORM, NCH, COPY, TPR><<<grid, kNormThreads, 0, s>>>(                    \
+          (const T *)x, (const T *)gain, nullptr, (T *)out, mean, rstd, (T *)copy, rows, h, eps);           \
+    return check_launch("norm_fwd");                                                                        \
   } while (0)
   const int tpr = norm_fwd_tpr(rows, h, Vec<T>::N);
   if (tpr == 64 && h <= 64 * Vec<T>::N) TM_NORM_FWD_NARROW(1, 64);

@@ -140,8 +140,9 @@ struct LayerStash {  // byte offsets into the workspace
 struct Plan {
   std::vector<LayerStash> layer;
   int64_t dstream[2];  // ping-pong buffers for the gradient of the residual stream, [T,h]
-  int64_t dwide;       // [T, max(f1, h)] : dg -> du, later da
-  int64_t dmid;        // [T, f]  : dg under SwiGLU (du needs its own buffer)
+  int64_t dwide;       // [T, max(f1, h)] : dg -> du, which the column sums read at the end of the layer
+  int64_t dmid;        // [T, f]  : dg under SwiGLU (du needs its own buffer); behind the activation the partial rows of the
+                       // bias gradients' column sums, where they fit (else these take launches of their own, through reduce)
   int64_t dx1;         // [T, h]
   int64_t dnorm;       // [T, h]  : gradient w.r.t. a norm's output (dc, da)
   int64_t dctx;        // [T, A]
