@@ -194,7 +194,7 @@ int tm_adam_step(tm_stage_t *st, const tm_adam_hparams_t *hp, int64_t step, void
  * tm_adam_step, but every layer's update is enqueued as soon as that layer's
  * gradients are complete.  Valid only when nothing global is
  * derived from this pass's gradients before the update: hp->grad_scale must
- * not depend on them (no norm-based clipping).  For bf16 stages in TM_GRAD_STORE
+ * not depend on them (no norm-based clipping).  dx may overlap dy, as in tm_stage_bwd.  For bf16 stages in TM_GRAD_STORE
  * or TM_GRAD_TRANSIENT mode with hp->zero_grads == 0 the update of a weight
  * matrix is applied, where that is the faster way, in the epilogue of its weight-gradient product, from the
  * accumulators (the gradient is not read back; in TM_GRAD_TRANSIENT mode with a
@@ -267,9 +267,10 @@ void tm_stage_destroy(tm_stage_t *st);
  * (at most max_entries; `kernel` points at static storage), clears the record list and returns
  * the number of entries filled.  flops counts 2*M*N*K per matrix product and 2*b*nq*s^2*d per
  * causal attention forward (twice that backward); bytes counts the operands and results of the
- * streaming kernels once.  A step is booked under its first kernel: a layer's bias gradients, whose column
- * sums share launches with its first norm's backward pass, under norm_bwd_kernel with the bytes they read,
- * and the copy of the stage's input, which its first norm makes, under norm_fwd_kernel.  Disabling frees the events.  Events are host objects: no device
+ * streaming kernels once.  A step is booked under its first kernel: a layer's bias gradients, whose
+ * column sums share launches with its first norm's backward pass, under norm_bwd_kernel with the
+ * bytes they read, and the copy of the stage's input, which its first norm makes, under
+ * norm_fwd_kernel.  Disabling frees the events.  Events are host objects: no device
  * memory is allocated.
  */
 typedef struct {

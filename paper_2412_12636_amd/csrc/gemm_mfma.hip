@@ -131,7 +131,7 @@ static bool config_takes(const GemmArgs &g, int c, int layout) {
 // 18 % and 9 % faster than the model's alone (the fastest configuration: 19 % and 14 %) and slower by more than 3 % on 10 and 8
 // of them.  The range: below 2^23 results one matrix in six lost 3 to 28 %, and from some 1000 and 480 tokens on the model alone
 // is as good.  40 tokens on 5128 x 3080 added to 50 -> 38 us, 300 on 8200 x 3080 104 -> 76 (overwritten 60 -> 50), 1000 on
-// 5128 x 3080 91 -> 77.
+// 5128 x 3080 91 -> 73.
 struct OffLineCost {
   int config;
   double scale[2], per_million[2];  // added to, overwritten
