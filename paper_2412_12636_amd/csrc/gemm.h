@@ -37,6 +37,10 @@ int gemm_generic(int dtype, const GemmArgs &g, hipStream_t s);
 // fp32 operands through the matrix cores.
 bool gemm_f32_supported(const GemmArgs &g);
 int gemm_f32(const GemmArgs &g, hipStream_t s);
+// The same on the bf16 matrix instructions, operands as three bf16 terms (gemm_f32_split.hip); tile 128 or 64.  Besides what
+// gemm_f32_supported() asks for, the results' rows, the bias and the residual are whole 16-byte chunks.
+bool gemm_f32_split_supported(const GemmArgs &g);
+int gemm_f32_split(const GemmArgs &g, int tile, hipStream_t s);
 
 // bf16 operands through the matrix cores.  Needs: one of each operand's strides equal to 1, the
 // other a multiple of 8; the extent along each operand's contiguous axis a multiple of 8;

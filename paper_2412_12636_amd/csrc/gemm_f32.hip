@@ -13,7 +13,8 @@
 // evenly its tiles cover the SIMDs, and how much of the barrier and the LDS latency a second wave of the SIMD covers:
 // blocks of 128x128 and 64x64, one wave a SIMD; of 64x64 with four waves a SIMD, and of 32x32 with one or two, that split
 // every stage's reduction elements (their sums meet in LDS in wave order); and of 16x16, split four ways, on 16x16x4 MFMAs,
-// where 32x32 tiles leave most units without one.  Which one: gemm_f32_form.h.
+// where 32x32 tiles leave most units without one.  Which one: gemm_f32_form.h.  Larger products go to the bf16 instructions in
+// three terms an element (gemm_f32_split.hip).
 // With one wave a SIMD on every tile and none of 16x16 before: 1024 x 1024 over 1024 23.7 -> 21.9 us, over 3072 (strided
 // weights) 64 -> 58; 256 x 256 over 1024 8.2 -> 4.5; 1500 x 768 over 768 25.1 -> 24.2 (weight gradient 29.9 -> 25.4).
 // (The twelve products of a layer of hidden 1024, SwiGLU width 4096, 1024 tokens: 4.9 ms = 21 TFLOP/s on the 64x64
@@ -322,7 +323,10 @@ static int launch(const GemmArgs &g, hipStream_t s) {
 template <bool A_KC, bool B_KC, int EPI> static int pick(const GemmArgs &g, hipStream_t s) {
   // the last stage of the 16x16 form reaches 4 FK rows past a strided operand's end: their offsets must not come round to its front
   auto reaches = [&](int64_t cs) { return cs == 1 || (g.K + 4 * FK) * cs * 4 < (1LL << 32); };
-  const F32Form f = f32_form(g.M, g.N, g.K, EPI != 0, reaches(g.a_cs) && reaches(g.b_cs));
+  const bool reach16 = reaches(g.a_cs) && reaches(g.b_cs);
+  const int split_tile = gemm_f32_split_supported(g) ? f32_split_tile(g.M, g.N, g.K, EPI != 0, reach16) : 0;
+  if (split_tile) return gemm_f32_split(g, split_tile, s);
+  const F32Form f = f32_form(g.M, g.N, g.K, EPI != 0, reach16);
   if (f.tile == 128) return launch<128, 128, 64, 64, 1, 2, 1, false, A_KC, B_KC, EPI>(g, s);
   if (f.tile == 64 && f.split == 4) return launch<64, 64, 32, 32, 4, 3, 2, false, A_KC, B_KC, EPI>(g, s);
   if (f.tile == 64) return launch<64, 64, 32, 32, 1, 3, 1, false, A_KC, B_KC, EPI>(g, s);
