@@ -1,9 +1,8 @@
 // Activation (GeLU / SwiGLU) forward and backward, rotary positions, fused Adam.
 // All HBM-bound: 16-byte accesses, fp32 arithmetic.
-#include <math.h>
-
 #include <mutex>
 
+#include "act.h"
 #include "adam.h"
 #include "common.h"
 #include "../../include/tm_ops.h"
@@ -12,20 +11,6 @@ namespace tmk {
 
 constexpr int kEwThreads = 256;
 
-__device__ __forceinline__ float gelu_tanh_f(float u) {
-  const float k = 0.7978845608028654f;  // sqrt(2/pi)
-  return 0.5f * u * (1.f + tanhf(k * (u + 0.044715f * u * u * u)));
-}
-__device__ __forceinline__ float gelu_tanh_grad_f(float u) {
-  const float k = 0.7978845608028654f;
-  const float th = tanhf(k * (u + 0.044715f * u * u * u));
-  return 0.5f * (1.f + th) + 0.5f * u * (1.f - th * th) * k * (1.f + 0.134145f * u * u);
-}
-__device__ __forceinline__ float gelu_erf_f(float u) { return 0.5f * u * (1.f + erff(u * 0.7071067811865476f)); }
-__device__ __forceinline__ float gelu_erf_grad_f(float u) {
-  const float pdf = 0.3989422804014327f * expf(-0.5f * u * u);
-  return 0.5f * (1.f + erff(u * 0.7071067811865476f)) + u * pdf;
-}
 __device__ __forceinline__ float sigmoid_f(float z) { return 1.f / (1.f + expf(-z)); }
 
 // g = gelu(u), chunked over the flat array

@@ -30,6 +30,10 @@ struct GemmArgs {
   // y-th of k_splits results [M, ldc] behind C (c_mode 2).
   int k_splits = 1;
   const AdamTarget *adam = nullptr;  // c_mode 3
+  // GeLU in the epilogue (gemm_f32_act, gemm_f32_pair): its second result, or where the derivative is taken; rows of ldc
+  int act = 0;
+  void *act_g = nullptr;
+  const void *act_u = nullptr;
 };
 
 int gemm_generic(int dtype, const GemmArgs &g, hipStream_t s);
@@ -41,6 +45,11 @@ int gemm_f32(const GemmArgs &g, hipStream_t s);
 // gemm_f32_supported() asks for, the results' rows, the bias and the residual are whole 16-byte chunks.
 bool gemm_f32_split_supported(const GemmArgs &g);
 int gemm_f32_split(const GemmArgs &g, int tile, hipStream_t s);
+
+// Small products only; false: not launched (status NULL: only asked).  Input gradient (act_u: times the derivative of GeLU there)
+// and weight gradient in one launch; and a product that also writes its GeLU.
+bool gemm_f32_pair(const GemmArgs &dgrad, const GemmArgs &wgrad, hipStream_t s, int *status);
+bool gemm_f32_act(const GemmArgs &g, hipStream_t s, int *status);
 
 // bf16 operands through the matrix cores.  Needs: one of each operand's strides equal to 1, the
 // other a multiple of 8; the extent along each operand's contiguous axis a multiple of 8;
@@ -56,6 +65,12 @@ int gemm_mfma_tune(const GemmArgs *variants, int n, hipStream_t s);
 // Number of tile configurations, and a process-wide override (index, or -1 for the automatic choice).
 // dw[N,K] = dy[T,N]^T x[T,K] (bf16 operands) with the Adam update of those N*K parameters in the product's
 // epilogue.  `supported` says whether the shapes and pointers allow it (matrix-core path).
+// The two gradient products of a linear map in one launch, and a linear map with its GeLU, where they are small fp32 ones: as
+// gemm_f32_pair and gemm_f32_act.  u: NULL, or dx is multiplied by the derivative of GeLU at u (rows of K).
+bool linear_bwd_pair(int dtype, int64_t T, int64_t N, int64_t K, const void *dy, const void *w, void *dx, const void *x, float *dw,
+                     int accumulate, int act, const void *u, hipStream_t s, int *status);
+bool linear_fwd_gelu(int dtype, int64_t T, int64_t N, int64_t K, const void *x, const void *w, const void *bias, void *u, int act, void *out,
+                     hipStream_t s, int *status);
 bool linear_wgrad_adam_supported(int64_t T, int64_t N, int64_t K, const void *dy, const void *x, const float *dw);
 // whether that is faster than the product and a flat sweep behind it
 bool linear_wgrad_adam_pays(int64_t T, int64_t N, int64_t K, const float *dw);

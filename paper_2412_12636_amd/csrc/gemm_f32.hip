@@ -21,6 +21,7 @@
 // plain-ALU tile kernel that this one replaces, 1.03 ms = 100 TFLOP/s here; its largest run at 113, the vendor BLAS reaches
 // 150 on 8192^3.  The matrix cores are busy for 80 to 84 % of the cycles in which a unit has waves on 128x128 tiles, 69 % on
 // 64x64.)
+#include "act.h"
 #include "gemm.h"
 #include "gemm_f32_form.h"
 
@@ -32,6 +33,7 @@ typedef __attribute__((address_space(3))) void *lds_ptr_t;
 
 constexpr int FK = 32;     // reduction elements of a step
 constexpr int kPatch = 8;  // row-tiles of a patch
+constexpr int kPairBlocks = 512;  // tiles of either gradient up to which the two share a launch: two a unit, what fits at once
 
 struct F32GemmParams {
   int M, N, K;
@@ -40,6 +42,9 @@ struct F32GemmParams {
   float *C;
   int64_t ldc;
   const float *bias, *residual;
+  const float *u;  // EPI 4
+  float *g;        // EPI 3
+  int act;
   int tiles_m, tiles_n;
   uint32_t a_bytes, b_bytes, c_bytes;
 };
@@ -137,29 +142,30 @@ template <int BM, int BN, int WM, int WN, int KSPL, int NS, int SUB> struct F32C
   static_assert(KSPL == 1 || (TM == 1 && TN == 1 && NV % KSPL == 0), "split waves hold one tile each");
   static_assert(SUB % UG == 0 && SUB * J % KSPL == 0 && J % WJ == 0 && KSPL % WJ == 0, "steps divide among the waves");
 };
+// EPI 0: results with bias and residual.  1: added to C.  2: stored.  3: results with bias, and their GeLU to g.  4: results
+// times the derivative of GeLU at u.
 template <int BM, int BN, int WM, int WN, int KSPL, int NS, int SUB, bool PATCH, bool A_KC, bool B_KC, int EPI>
-__global__ __launch_bounds__((64 * F32Cfg<BM, BN, WM, WN, KSPL, NS, SUB>::NW)) void gemm_f32_kernel(const F32GemmParams p) {
+__device__ __forceinline__ void f32_block(const F32GemmParams &p, char *lds, const int block, const int tid) {
   typedef F32Cfg<BM, BN, WM, WN, KSPL, NS, SUB> C;
   typedef F32Mma<C::MF> MM;
   constexpr int MF = C::MF, TM = C::TM, TN = C::TN, NT = C::NT, LW = C::LW, UG = C::UG, NV = C::NV;
   typedef typename F32Sel<BM, LW, MF, A_KC>::type LA;
   typedef typename F32Sel<BN, LW, MF, B_KC>::type LB;
   constexpr int LOADS = SUB / UG * (LA::NLOAD + LB::NLOAD);
-  extern __shared__ __align__(1024) char lds[];
   int m0, n0;
   if constexpr (PATCH) {  // an XCD (ids round-robin over eight) owns a range of tiles, walked in patches
     asm volatile("" ::"s"(p.A), "s"(p.B), "s"(p.lda), "s"(p.ldb), "s"(p.K), "s"(p.a_bytes));  // fetched now, not behind the divisions
-    const int nblk = p.tiles_m * p.tiles_n, xcd = blockIdx.x % 8, base = nblk / 8, rem = nblk % 8;
-    const int lid = xcd * base + (xcd < rem ? xcd : rem) + (int)(blockIdx.x / 8);
+    const int nblk = p.tiles_m * p.tiles_n, xcd = block % 8, base = nblk / 8, rem = nblk % 8;
+    const int lid = xcd * base + (xcd < rem ? xcd : rem) + block / 8;
     const int gi = lid / (kPatch * p.tiles_n), first = gi * kPatch, in_group = lid - first * p.tiles_n;
     const int rows = p.tiles_m - first < kPatch ? p.tiles_m - first : kPatch;
     m0 = (first + in_group % rows) * BM;
     n0 = (in_group / rows) * BN;
   } else {
-    m0 = (int)(blockIdx.x % p.tiles_m) * BM;
-    n0 = (int)(blockIdx.x / p.tiles_m) * BN;
+    m0 = (block % p.tiles_m) * BM;
+    n0 = (block / p.tiles_m) * BN;
   }
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // (zeros that the compiler can see: 5 % of the short products)
   const int ks = KSPL > 1 ? wave / NT : 0, wt = KSPL > 1 ? wave % NT : wave;
   const int lw = UG > 1 ? wave % LW : wave, lu = UG > 1 ? wave / LW : 0;
@@ -228,11 +234,11 @@ __global__ __launch_bounds__((64 * F32Cfg<BM, BN, WM, WN, KSPL, NS, SUB>::NW)) v
     }
   }
   const rsrc_t rc = make_rsrc(p.C, p.c_bytes);
-  const rsrc_t rres = make_rsrc(p.residual ? (const void *)p.residual : p.C, p.c_bytes);
+  const rsrc_t raux = make_rsrc(EPI == 3 ? p.g : EPI == 4 ? p.u : p.residual ? p.residual : p.C, p.c_bytes);
 #pragma unroll
   for (int tn = 0; tn < TN; ++tn) {
     const int col = n0 + wn + tn * MF + lane % MF;
-    const float bias = EPI == 0 && p.bias && col < p.N ? p.bias[col] : 0.f;
+    const float bias = (EPI == 0 || EPI == 3) && p.bias && col < p.N ? p.bias[col] : 0.f;
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm) {
       uint32_t off[VC];
@@ -243,17 +249,54 @@ __global__ __launch_bounds__((64 * F32Cfg<BM, BN, WM, WN, KSPL, NS, SUB>::NW)) v
         off[e] = col < p.N && row < p.M ? (uint32_t)(((int64_t)row * p.ldc + col) * 4) : 0xfffffff0u;
         old[e] = 0.f;
       }
-      if (EPI == 1 || (EPI == 0 && p.residual)) {
+      if (EPI == 1 || EPI == 4 || (EPI == 0 && p.residual)) {
 #pragma unroll
         for (int e = 0; e < VC; ++e)
-          old[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(EPI == 1 ? rc : rres, off[e], 0, 0));
+          old[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(EPI == 1 ? rc : raux, off[e], 0, 0));
       }
 #pragma unroll
       for (int e = 0; e < VC; ++e) {
-        const float o = EPI == 0 ? (acc[tm][tn][e] + bias) + old[e] : old[e] + acc[tm][tn][e];
+        const float o = EPI == 4   ? acc[tm][tn][e] * gelu_grad_f(p.act, old[e])
+                        : EPI == 0 ? (acc[tm][tn][e] + bias) + old[e]
+                        : EPI == 3 ? acc[tm][tn][e] + bias
+                                   : old[e] + acc[tm][tn][e];
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, o), rc, off[e], 0, 0);
+        if (EPI == 3) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, gelu_f(p.act, o)), raux, off[e], 0, 0);
       }
     }
+  }
+}
+
+template <int BM, int BN, int WM, int WN, int KSPL, int NS, int SUB, bool PATCH, bool A_KC, bool B_KC, int EPI>
+__global__ __launch_bounds__((64 * F32Cfg<BM, BN, WM, WN, KSPL, NS, SUB>::NW)) void gemm_f32_kernel(const F32GemmParams p) {
+  extern __shared__ __align__(1024) char lds[];
+  f32_block<BM, BN, WM, WN, KSPL, NS, SUB, PATCH, A_KC, B_KC, EPI>(p, lds, (int)blockIdx.x, (int)threadIdx.x);
+}
+
+// Input gradient and weight gradient of one linear map in one launch: blocks of DT x DT results of the first, then blocks of
+// WT x WT of the second.  Both read the same output gradient and neither waits for the other; small ones, each a few
+// microseconds of launch, first loads and epilogue around a few hundred cycles of MFMAs, cover each other: 16x16 tiles of both 6.7
+// -> 3.7 us, 32x32 ones 9.3 -> 8.0.  Blocks of eight waves with 32x32 weight-gradient tiles split eight ways, whose 16x16 tiles of
+// the input gradient come in pairs.  With GeLU and its derivative in the epilogues too, a step of one layer of hidden 256, FC of
+// 1024: 33 tokens 88 -> 75 us, 512 127 -> 114, 1024 164 -> 155; the tiny preset's step 198 -> 178.
+template <int DT, int WT, int WSPL> struct F32Pair {
+  static constexpr int NW = WSPL, TWO = DT == 16 && WSPL == 8 ? 2 : 1, DSPL = DT == 16 ? 4 : WSPL, DSUB = TWO == 2 ? 2 : DT == 16 ? 4 : 2;
+  typedef F32Cfg<DT, DT, DT, DT, DSPL, 4, DSUB> D;
+  typedef F32Cfg<WT, WT, WT, WT, WSPL, 4, WT == 16 ? 4 : 2> W;
+  static constexpr int LDS = TWO * D::LDS > W::LDS ? TWO * D::LDS : W::LDS;
+  static_assert(D::NW * TWO == NW && W::NW == NW && 2 * LDS <= 160 * 1024, "blocks of one size, two to a unit");
+};
+template <int DT, int WT, int WSPL, int DEPI, int WEPI>
+__global__ __launch_bounds__((64 * F32Pair<DT, WT, WSPL>::NW)) void gemm_f32_pair_kernel(const F32GemmParams d, const F32GemmParams w,
+                                                                                         const int d_blocks) {
+  extern __shared__ __align__(1024) char lds[];
+  typedef F32Pair<DT, WT, WSPL> P;
+  if ((int)blockIdx.x < d_blocks) {
+    const int sub = P::TWO == 2 ? (int)(threadIdx.x / 256) : 0;  // (a tile behind the last: every load and store is out of range)
+    f32_block<DT, DT, DT, DT, P::DSPL, 4, P::DSUB, false, true, false, DEPI>(d, lds + sub * P::D::LDS, (int)blockIdx.x * P::TWO + sub,
+                                                                             (int)threadIdx.x - sub * 256);
+  } else {
+    f32_block<WT, WT, WT, WT, WSPL, 4, WT == 16 ? 4 : 2, false, false, false, WEPI>(w, lds, (int)blockIdx.x - d_blocks, (int)threadIdx.x);
   }
 }
 
@@ -268,6 +311,19 @@ TM_F32_GEMM(4, true, true, 0)
 TM_F32_GEMM(4, true, false, 0)
 TM_F32_GEMM(8, false, false, 1)
 TM_F32_GEMM(8, false, false, 2)
+template __global__ void gemm_f32_kernel<32, 32, 32, 32, 4, 4, 2, false, true, true, 3>(const F32GemmParams);
+template __global__ void gemm_f32_kernel<16, 16, 16, 16, 4, 4, 4, false, true, true, 3>(const F32GemmParams);
+#define TM_F32_PAIR(DT, WT, WSPL)                                                                                  \
+  template __global__ void gemm_f32_pair_kernel<DT, WT, WSPL, 0, 1>(const F32GemmParams, const F32GemmParams, int); \
+  template __global__ void gemm_f32_pair_kernel<DT, WT, WSPL, 0, 2>(const F32GemmParams, const F32GemmParams, int); \
+  template __global__ void gemm_f32_pair_kernel<DT, WT, WSPL, 4, 1>(const F32GemmParams, const F32GemmParams, int); \
+  template __global__ void gemm_f32_pair_kernel<DT, WT, WSPL, 4, 2>(const F32GemmParams, const F32GemmParams, int);
+TM_F32_PAIR(16, 16, 4)
+TM_F32_PAIR(32, 16, 4)
+TM_F32_PAIR(16, 32, 4)
+TM_F32_PAIR(32, 32, 4)
+TM_F32_PAIR(16, 32, 8)
+TM_F32_PAIR(32, 32, 8)
 template __global__ void gemm_f32_kernel<16, 16, 16, 16, 4, 4, 4, true, true, true, 0>(const F32GemmParams);
 template __global__ void gemm_f32_kernel<16, 16, 16, 16, 4, 4, 4, true, true, false, 0>(const F32GemmParams);
 template __global__ void gemm_f32_kernel<32, 32, 32, 32, 8, 4, 2, false, false, false, 1>(const F32GemmParams);
@@ -287,25 +343,34 @@ bool gemm_f32_supported(const GemmArgs &g) {
   return g.c_mode ? (g.a_cs != 1 && g.b_cs != 1) : g.a_cs == 1;
 }
 
-template <int BM, int BN, int WM, int WN, int KSPL, int NS, int SUB, bool PATCH, bool A_KC, bool B_KC, int EPI>
-static int launch(const GemmArgs &g, hipStream_t s) {
+static F32GemmParams make_params(const GemmArgs &g, int tile) {
+  const bool a_kc = g.a_cs == 1, b_kc = g.b_cs == 1;
   F32GemmParams p;
   p.M = (int)g.M;
   p.N = (int)g.N;
   p.K = (int)g.K;
   p.A = (const float *)g.A;
-  p.lda = A_KC ? g.a_rs : g.a_cs;
+  p.lda = a_kc ? g.a_rs : g.a_cs;
   p.B = (const float *)g.B;
-  p.ldb = B_KC ? g.b_rs : g.b_cs;
+  p.ldb = b_kc ? g.b_rs : g.b_cs;
   p.C = (float *)g.C;
   p.ldc = g.ldc;
   p.bias = (const float *)g.bias;
   p.residual = (const float *)g.residual;
-  p.tiles_m = (int)ceil_div(g.M, BM);
-  p.tiles_n = (int)ceil_div(g.N, BN);
-  p.a_bytes = (uint32_t)((A_KC ? g.M * g.a_rs : g.K * g.a_cs) * 4);
-  p.b_bytes = (uint32_t)((B_KC ? g.N * g.b_rs : g.K * g.b_cs) * 4);
+  p.u = (const float *)g.act_u;
+  p.g = (float *)g.act_g;
+  p.act = g.act;
+  p.tiles_m = (int)ceil_div(g.M, tile);
+  p.tiles_n = (int)ceil_div(g.N, tile);
+  p.a_bytes = (uint32_t)((a_kc ? g.M * g.a_rs : g.K * g.a_cs) * 4);
+  p.b_bytes = (uint32_t)((b_kc ? g.N * g.b_rs : g.K * g.b_cs) * 4);
   p.c_bytes = (uint32_t)(g.M * g.ldc * 4);
+  return p;
+}
+
+template <int BM, int BN, int WM, int WN, int KSPL, int NS, int SUB, bool PATCH, bool A_KC, bool B_KC, int EPI>
+static int launch(const GemmArgs &g, hipStream_t s) {
+  const F32GemmParams p = make_params(g, BM);
   typedef F32Cfg<BM, BN, WM, WN, KSPL, NS, SUB> C;
   constexpr int lds = C::LDS;
   static bool attr_set = false;  // per instantiation
@@ -320,13 +385,16 @@ static int launch(const GemmArgs &g, hipStream_t s) {
   return check_launch("gemm_f32");
 }
 
-template <bool A_KC, bool B_KC, int EPI> static int pick(const GemmArgs &g, hipStream_t s) {
-  // the last stage of the 16x16 form reaches 4 FK rows past a strided operand's end: their offsets must not come round to its front
+// the last stage of the 16x16 form reaches 4 FK rows past a strided operand's end: their offsets must not come round to its front
+static bool reach16(const GemmArgs &g) {
   auto reaches = [&](int64_t cs) { return cs == 1 || (g.K + 4 * FK) * cs * 4 < (1LL << 32); };
-  const bool reach16 = reaches(g.a_cs) && reaches(g.b_cs);
-  const int split_tile = gemm_f32_split_supported(g) ? f32_split_tile(g.M, g.N, g.K, EPI != 0, reach16) : 0;
+  return reaches(g.a_cs) && reaches(g.b_cs);
+}
+
+template <bool A_KC, bool B_KC, int EPI> static int pick(const GemmArgs &g, hipStream_t s) {
+  const int split_tile = gemm_f32_split_supported(g) ? f32_split_tile(g.M, g.N, g.K, EPI != 0, reach16(g)) : 0;
   if (split_tile) return gemm_f32_split(g, split_tile, s);
-  const F32Form f = f32_form(g.M, g.N, g.K, EPI != 0, reach16);
+  const F32Form f = f32_form(g.M, g.N, g.K, EPI != 0, reach16(g));
   if (f.tile == 128) return launch<128, 128, 64, 64, 1, 2, 1, false, A_KC, B_KC, EPI>(g, s);
   if (f.tile == 64 && f.split == 4) return launch<64, 64, 32, 32, 4, 3, 2, false, A_KC, B_KC, EPI>(g, s);
   if (f.tile == 64) return launch<64, 64, 32, 32, 1, 3, 1, false, A_KC, B_KC, EPI>(g, s);
@@ -338,6 +406,48 @@ template <bool A_KC, bool B_KC, int EPI> static int pick(const GemmArgs &g, hipS
   }
   if (f.tile == 32) return launch<32, 32, 32, 32, 4, 4, 2, false, A_KC, B_KC, EPI>(g, s);
   return launch<16, 16, 16, 16, 4, 4, 4, false, A_KC, B_KC, EPI>(g, s);
+}
+
+// f32_form's choice where it is a small tile walked in plain order and no other kernel has the product
+static bool small_form(const GemmArgs &g, bool wgrad, F32Form *f) {
+  if (!gemm_f32_supported(g)) return false;
+  *f = f32_form(g.M, g.N, g.K, wgrad, reach16(g));
+  return f->tile <= 32 && !f->patches && !(gemm_f32_split_supported(g) && f32_split_tile(g.M, g.N, g.K, wgrad, reach16(g)));
+}
+
+template <int DT, int WT, int WSPL, int DEPI, int WEPI> static int launch_pair(const GemmArgs &d, const GemmArgs &w, hipStream_t s) {
+  typedef F32Pair<DT, WT, WSPL> P;
+  const F32GemmParams pd = make_params(d, DT), pw = make_params(w, WT);
+  static bool attr_set = false;  // per instantiation
+  if (!attr_set && hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_f32_pair_kernel<DT, WT, WSPL, DEPI, WEPI>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, P::LDS) != hipSuccess)
+    return fail(TM_ELAUNCH, "gemm_f32_pair: cannot reserve %d bytes of LDS", P::LDS);
+  attr_set = true;
+  const int d_blocks = (int)ceil_div((int64_t)pd.tiles_m * pd.tiles_n, P::TWO);
+  g_last_kernel = "gemm_f32_pair_kernel";
+  gemm_f32_pair_kernel<DT, WT, WSPL, DEPI, WEPI><<<(unsigned)(d_blocks + pw.tiles_m * pw.tiles_n), 64 * P::NW, P::LDS, s>>>(pd, pw, d_blocks);
+  return check_launch("gemm_f32_pair");
+}
+template <int DT, int WT, int WSPL> static int pick_pair(const GemmArgs &d, const GemmArgs &w, hipStream_t s) {
+  if (d.act_u) return w.c_mode == 1 ? launch_pair<DT, WT, WSPL, 4, 1>(d, w, s) : launch_pair<DT, WT, WSPL, 4, 2>(d, w, s);
+  return w.c_mode == 1 ? launch_pair<DT, WT, WSPL, 0, 1>(d, w, s) : launch_pair<DT, WT, WSPL, 0, 2>(d, w, s);
+}
+bool gemm_f32_pair(const GemmArgs &d, const GemmArgs &w, hipStream_t s, int *status) {
+  F32Form fd, fw;
+  if (d.c_mode != 0 || d.b_cs == 1 || (w.c_mode != 1 && w.c_mode != 2) || !small_form(d, false, &fd) || !small_form(w, true, &fw)) return false;
+  if (ceil_div(d.M, fd.tile) * ceil_div(d.N, fd.tile) > kPairBlocks || ceil_div(w.M, fw.tile) * ceil_div(w.N, fw.tile) > kPairBlocks) return false;
+  if (!status) return true;
+  if (fw.tile == 16) *status = fd.tile == 16 ? pick_pair<16, 16, 4>(d, w, s) : pick_pair<32, 16, 4>(d, w, s);
+  else if (fw.split == 4) *status = fd.tile == 16 ? pick_pair<16, 32, 4>(d, w, s) : pick_pair<32, 32, 4>(d, w, s);
+  else *status = fd.tile == 16 ? pick_pair<16, 32, 8>(d, w, s) : pick_pair<32, 32, 8>(d, w, s);
+  return true;
+}
+bool gemm_f32_act(const GemmArgs &g, hipStream_t s, int *status) {
+  F32Form f;
+  if (g.c_mode != 0 || g.b_cs != 1 || g.residual || !small_form(g, false, &f)) return false;
+  if (!status) return true;
+  *status = f.tile == 16 ? launch<16, 16, 16, 16, 4, 4, 4, false, true, true, 3>(g, s) : launch<32, 32, 32, 32, 4, 4, 2, false, true, true, 3>(g, s);
+  return true;
 }
 
 int gemm_f32(const GemmArgs &g, hipStream_t s) {

@@ -64,6 +64,22 @@ extern "C" int tm_op_linear_wgrad(int dtype, int64_t T, int64_t N, int64_t K, co
 }
 
 namespace tmk {
+bool linear_bwd_pair(int dtype, int64_t T, int64_t N, int64_t K, const void *dy, const void *w, void *dx, const void *x, float *dw,
+                     int accumulate, int act, const void *u, hipStream_t s, int *status) {
+  if (dtype != TM_DTYPE_FP32) return false;
+  GemmArgs d{T, K, N, dy, N, 1, w, 1, K, dx, K, nullptr, nullptr, 0}, g{N, K, T, dy, 1, N, x, 1, K, dw, K, nullptr, nullptr, accumulate ? 1 : 2};
+  d.act = act;
+  d.act_u = u;
+  return gemm_f32_pair(d, g, s, status);
+}
+bool linear_fwd_gelu(int dtype, int64_t T, int64_t N, int64_t K, const void *x, const void *w, const void *bias, void *u, int act, void *out,
+                     hipStream_t s, int *status) {
+  if (dtype != TM_DTYPE_FP32) return false;
+  GemmArgs g{T, N, K, x, K, 1, w, K, 1, u, N, bias, nullptr, 0};
+  g.act = act;
+  g.act_g = out;
+  return gemm_f32_act(g, s, status);
+}
 bool linear_wgrad_adam_supported(int64_t T, int64_t N, int64_t K, const void *dy, const void *x, const float *dw) {
   if (T <= 0 || N <= 0 || K <= 0) return false;
   GemmArgs g{N, K, T, dy, 1, N, x, 1, K, const_cast<float *>(dw), K, nullptr, nullptr, 3};

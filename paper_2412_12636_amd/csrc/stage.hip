@@ -539,9 +539,14 @@ extern "C" int tm_stage_fwd(tm_stage_t *st, const void *x_in, void *y_out, void 
             tm_op_norm_fwd(dt, c.norm, d.T, d.h, c.norm_eps, ws + k.x1, P(o.norm2_gain), P(o.norm2_offset), ws + k.c,
                            (float *)(ws + k.mean2), (float *)(ws + k.rstd2), s));
     // u = c W1^T + b ; g = act(u)
+    auto with_gelu = [&](int *status) {  // small fp32 products: both in one launch
+      return c.act != TM_ACT_SWIGLU && linear_fwd_gelu(dt, d.T, d.f1, d.h, ws + k.c, P(o.w_fc1), P(o.b_fc1), ws + k.u, c.act, ws + k.g, s, status);
+    };
+    const bool gelu_done = with_gelu(nullptr);
+    int status = TM_OK;
     TM_STEP(2.0 * d.T * d.f1 * d.h, 0,
-            tm_op_linear_fwd(dt, d.T, d.f1, d.h, ws + k.c, P(o.w_fc1), P(o.b_fc1), nullptr, ws + k.u, s));
-    TM_STEP(0, es * d.T * (d.f1 + d.f), tm_op_act_fwd(dt, c.act, d.T, d.f, ws + k.u, ws + k.g, s));
+            gelu_done ? (with_gelu(&status), status) : tm_op_linear_fwd(dt, d.T, d.f1, d.h, ws + k.c, P(o.w_fc1), P(o.b_fc1), nullptr, ws + k.u, s));
+    if (!gelu_done) TM_STEP(0, es * d.T * (d.f1 + d.f), tm_op_act_fwd(dt, c.act, d.T, d.f, ws + k.u, ws + k.g, s));
     // y = x1 + g W2^T + b
     if (!tp_cut) {
       TM_STEP(2.0 * d.T * d.h * d.f, 0,
@@ -699,12 +704,24 @@ static int stage_bwd(tm_stage_t *st, const void *dy_in, void *dx_out, void *stre
     auto G = [&](int64_t off) -> float * { return off < 0 ? nullptr : grads + pb + off; };
     void *dx = (l == 0) ? dx_out : (void *)(ws + pl.dstream[l & 1]);
 
+    // small fp32 products: the two gradients of a linear map in one launch (u: and the derivative of GeLU there); false: not done
+    auto pair = [&](int64_t N, int64_t K, const void *dyp, int64_t w_off, void *dxp, const void *xp, const void *u, int *status) {
+      return !two && linear_bwd_pair(dt, d.T, N, K, dyp, P(w_off), dxp, xp, G(w_off), acc, c.act, u, s, status);
+    };
+    int status = TM_OK;
+
     // y = x1 + g W2^T + b2
     void *dg = (c.act == TM_ACT_SWIGLU) ? (void *)(ws + pl.dmid) : (void *)(ws + pl.dwide);
-    TM_STEP(mm(d.h, d.f), 0, tm_op_linear_dgrad_ws(dt, d.T, d.h, d.f, dy, P(o.w_fc2), dg, ws + pl.splitk, pl.splitk_bytes, s));
-    TM_TRY(fork());
+    const void *gelu_u = c.act == TM_ACT_SWIGLU ? nullptr : ws + k.u;
     fused.clear();
-    TM_STEP(mm(d.h, d.f), wgrad_bytes(d.h, d.f, dy, ws + k.g, pb, o.w_fc2), wgrad(pb, o.w_fc2, d.h, d.f, dy, ws + k.g));
+    const bool pair2 = pair(d.h, d.f, dy, o.w_fc2, dg, ws + k.g, gelu_u, nullptr);
+    if (pair2) {
+      TM_STEP(2 * mm(d.h, d.f), 0, (pair(d.h, d.f, dy, o.w_fc2, dg, ws + k.g, gelu_u, &status), status));
+    } else {
+      TM_STEP(mm(d.h, d.f), 0, tm_op_linear_dgrad_ws(dt, d.T, d.h, d.f, dy, P(o.w_fc2), dg, ws + pl.splitk, pl.splitk_bytes, s));
+      TM_TRY(fork());
+      TM_STEP(mm(d.h, d.f), wgrad_bytes(d.h, d.f, dy, ws + k.g, pb, o.w_fc2), wgrad(pb, o.w_fc2, d.h, d.f, dy, ws + k.g));
+    }
     // the bias gradients wait for the end of the layer, where their column sums share launches with the first norm's
     // (below the top layer FC2's has come out of the first norm's backward pass of the layer above).  That norm writes dx
     // before they are formed: a caller's dx over its dy leaves FC2's no time to wait.
@@ -716,13 +733,15 @@ static int stage_bwd(tm_stage_t *st, const void *dy_in, void *dx_out, void *stre
     }
     // activation
     void *du = ws + pl.dwide;
-    TM_STEP(0, es * d.T * (d.f + 2 * d.f1), tm_op_act_bwd(dt, c.act, d.T, d.f, dg, ws + k.u, du, s));
+    if (!pair2 || !gelu_u) TM_STEP(0, es * d.T * (d.f + 2 * d.f1), tm_op_act_bwd(dt, c.act, d.T, d.f, dg, ws + k.u, du, s));
     // u = c W1^T + b1
     void *dc = ws + pl.dnorm;
-    TM_STEP(mm(d.f1, d.h), 0, tm_op_linear_dgrad_ws(dt, d.T, d.f1, d.h, du, P(o.w_fc1), dc, ws + pl.splitk, pl.splitk_bytes, s));
+    const bool pair1 = pair(d.f1, d.h, du, o.w_fc1, dc, ws + k.c, nullptr, nullptr);
+    if (pair1) TM_STEP(2 * mm(d.f1, d.h), 0, (pair(d.f1, d.h, du, o.w_fc1, dc, ws + k.c, nullptr, &status), status));
+    else TM_STEP(mm(d.f1, d.h), 0, tm_op_linear_dgrad_ws(dt, d.T, d.f1, d.h, du, P(o.w_fc1), dc, ws + pl.splitk, pl.splitk_bytes, s));
     if (cm) TM_TRY(tm_comm_call(cm, TM_COLL_ALL_REDUCE, TM_SCOPE_TP, TM_SITE_D_MLP_IN, dt, dc, act_bytes, s));
     TM_TRY(fork());
-    TM_STEP(mm(d.f1, d.h), wgrad_bytes(d.f1, d.h, du, ws + k.c, pb, o.w_fc1), wgrad(pb, o.w_fc1, d.f1, d.h, du, ws + k.c));
+    if (!pair1) TM_STEP(mm(d.f1, d.h), wgrad_bytes(d.f1, d.h, du, ws + k.c, pb, o.w_fc1), wgrad(pb, o.w_fc1, d.f1, d.h, du, ws + k.c));
     if (bias) sums[n_sums++] = ColumnSum{du, G(o.b_fc1), d.f1};
     // c = Norm(x1): dx1 = dy + norm gradient
     void *dx1 = ws + pl.dx1;
@@ -738,9 +757,13 @@ static int stage_bwd(tm_stage_t *st, const void *dy_in, void *dx_out, void *stre
                              (const float *)(ws + k.rstd2), P(o.norm2_gain), dy, dx1, G(o.norm2_gain),
                              G(o.norm2_offset), red, acc, s));
     // x1 = x + ctx Wout^T + bout
-    TM_STEP(mm(d.h, d.A), 0, tm_op_linear_dgrad_ws(dt, d.T, d.h, d.A, dx1, P(o.w_out), ws + pl.dctx, ws + pl.splitk, pl.splitk_bytes, s));
-    TM_TRY(fork());
-    TM_STEP(mm(d.h, d.A), wgrad_bytes(d.h, d.A, dx1, ws + k.ctx, pb, o.w_out), wgrad(pb, o.w_out, d.h, d.A, dx1, ws + k.ctx));
+    if (pair(d.h, d.A, dx1, o.w_out, ws + pl.dctx, ws + k.ctx, nullptr, nullptr)) {
+      TM_STEP(2 * mm(d.h, d.A), 0, (pair(d.h, d.A, dx1, o.w_out, ws + pl.dctx, ws + k.ctx, nullptr, &status), status));
+    } else {
+      TM_STEP(mm(d.h, d.A), 0, tm_op_linear_dgrad_ws(dt, d.T, d.h, d.A, dx1, P(o.w_out), ws + pl.dctx, ws + pl.splitk, pl.splitk_bytes, s));
+      TM_TRY(fork());
+      TM_STEP(mm(d.h, d.A), wgrad_bytes(d.h, d.A, dx1, ws + k.ctx, pb, o.w_out), wgrad(pb, o.w_out, d.h, d.A, dx1, ws + k.ctx));
+    }
     // attention, rotary
     TM_STEP(2 * attn_flops, 0,
             tm_op_attn_bwd(dt, c.seq, c.micro_batch, c.n_q_heads, c.n_kv_heads, c.head_dim, ws + k.qkv, ws + k.ctx,
@@ -751,10 +774,12 @@ static int stage_bwd(tm_stage_t *st, const void *dy_in, void *dx_out, void *stre
                            ws + pl.dqkv, s));
     // qkv = a Wqkv^T + b
     void *da = ws + pl.dnorm;
-    TM_STEP(mm(d.nqkv, d.h), 0, tm_op_linear_dgrad_ws(dt, d.T, d.nqkv, d.h, ws + pl.dqkv, P(o.w_qkv), da, ws + pl.splitk, pl.splitk_bytes, s));
+    const bool pair_qkv = pair(d.nqkv, d.h, ws + pl.dqkv, o.w_qkv, da, ws + k.a, nullptr, nullptr);
+    if (pair_qkv) TM_STEP(2 * mm(d.nqkv, d.h), 0, (pair(d.nqkv, d.h, ws + pl.dqkv, o.w_qkv, da, ws + k.a, nullptr, &status), status));
+    else TM_STEP(mm(d.nqkv, d.h), 0, tm_op_linear_dgrad_ws(dt, d.T, d.nqkv, d.h, ws + pl.dqkv, P(o.w_qkv), da, ws + pl.splitk, pl.splitk_bytes, s));
     if (cm) TM_TRY(tm_comm_call(cm, TM_COLL_ALL_REDUCE, TM_SCOPE_TP, TM_SITE_D_ATTN_IN, dt, da, act_bytes, s));
     TM_TRY(fork());
-    TM_STEP(mm(d.nqkv, d.h), wgrad_bytes(d.nqkv, d.h, ws + pl.dqkv, ws + k.a, pb, o.w_qkv), wgrad(pb, o.w_qkv, d.nqkv, d.h, ws + pl.dqkv, ws + k.a));
+    if (!pair_qkv) TM_STEP(mm(d.nqkv, d.h), wgrad_bytes(d.nqkv, d.h, ws + pl.dqkv, ws + k.a, pb, o.w_qkv), wgrad(pb, o.w_qkv, d.nqkv, d.h, ws + pl.dqkv, ws + k.a));
     if (bias) sums[n_sums++] = ColumnSum{ws + pl.dqkv, G(o.b_qkv), d.nqkv};
     // a = Norm(x): dx = dx1 + norm gradient
     // dx is the output gradient of the layer below: its column sums are that layer's FC2 bias gradient
