@@ -71,6 +71,15 @@ template <typename T> __device__ __forceinline__ void buf_store_vec(rsrc_t r, ui
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u32, u.raw), r, byte_off, 0, 0);
 }
 
+// 16 bytes a lane from a buffer straight into LDS (lane l's at lds + 16 l), out of the compiler's sight: it knows the builtin's
+// loads, but not which LDS bytes they write, and waits for all of them before the next transposing LDS read, also for those
+// that were just issued for a later step.  The kernels wait themselves (s_waitcnt vmcnt ahead of the barrier that publishes
+// a step).  Writes M0 behind the compiler's back: a kernel has all of its LDS loads through this.
+__device__ __forceinline__ void load_to_lds(rsrc_t r, const char *lds, uint32_t voff, uint32_t soff) {
+  const uint32_t at = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)lds;
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(at), "v"(voff), "s"(r), "s"(soff) : "memory");
+}
+
 // ---- reductions ---------------------------------------------------------------
 constexpr int kWave = 64;
 

@@ -16,6 +16,9 @@ int gemm_mfma_nt(const GemmArgs &g, int config, hipStream_t s);  // y = x W^T   
 int gemm_mfma_nn(const GemmArgs &g, int config, hipStream_t s);  // dx = dy W       (W read along its strided axis)
 int gemm_mfma_tn(const GemmArgs &g, int config, hipStream_t s);  // dW (+)= dy^T x  (both strided, fp32 result)
 int gemm_mfma_nn_partial(const GemmArgs &g, bool large, hipStream_t s);  // dx = dy W in k_splits fp32 parts
+// bf16 results of few tiles, the reduction split among a block's waves (gemm_mfma_small.hip)
+bool gemm_mfma_small_pays(const GemmArgs &g);
+int gemm_mfma_small(const GemmArgs &g, hipStream_t s);
 
 bool gemm_mfma_supported(const GemmArgs &g) {
   auto operand_ok = [&](const void *ptr, int64_t rs, int64_t cs, int64_t rows) {
@@ -359,6 +362,7 @@ int gemm_mfma(const GemmArgs &g, hipStream_t s) {
                                                                               (bf16 *)g.C, g.ldc);
     return check_launch("splitk_reduce");
   }
+  if (forced_config() < 0 && gemm_mfma_small_pays(g)) return gemm_mfma_small(g, s);
   return launch_config(g, pick_config(g), s);
 }
 
