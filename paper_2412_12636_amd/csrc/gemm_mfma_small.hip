@@ -169,16 +169,17 @@ template <bool B_KC> static int launch_small(const GemmArgs &g, hipStream_t s) {
   return check_launch("gemm_small");
 }
 
-// bf16 results over 1024 elements and more, with a tile on every unit at most, or on half of the units a second one where both
-// operands lie along the reduction.  Against the tiles chosen before, 1400 random products of each kind (8 to 4096 rows, 64 to 8192
-// columns, 64 to 12288 elements), forward / input gradient, geometric means over up to 256 tiles: 0.55 / 0.62 of the time to 4096
-// elements, 0.45 / 0.57 beyond; 257 to 384 tiles 0.84 / 1.03, 385 to 560 tiles 1.00 / 1.19.  256 x 512 over 2048 10.6 -> 4.9 us.  With
-// eight waves, or three or four chunks in flight, 2 to 10 % slower.  Shorter reductions (0.92 to 0.72) keep the tiles whose sums
+// bf16 results over 1024 elements and more, with a tile on every unit at most, or two where both operands lie along the
+// reduction.  Against the tiles chosen before, 1900 random products of each kind (8 to 4096 rows, 64 to 8192 columns, 64 to 12288
+// elements), forward / input gradient, geometric means over up to 256 tiles: 0.60 / 0.67 of the time to 2048 elements, 0.51 / 0.61 to
+// 4096, 0.46 / 0.60 beyond; 257 to 384 tiles 0.85 / 1.03, to 512 0.90 / 1.09 (one in sixty forward ones 4 to 7 % slower), to 560 1.20 /
+// 1.45.  256 x 512 over 2048 10.6 -> 4.9 us.  With eight waves, or three or four chunks in flight, 2 to 10 % slower; 64x64 tiles
+// split the same way as fast as the unsplit ones at best.  Shorter reductions (0.92 to 0.72) keep the tiles whose sums
 // all configurations share bit for bit, and so do weight gradients, which have them with the update in the epilogue.
 bool gemm_mfma_small_pays(const GemmArgs &g) {
   if (g.c_mode != 0 || g.N % 8 != 0 || g.K < 1024) return false;
   const int64_t tiles = ceil_div(g.M, 32) * ceil_div(g.N, 32);
-  return tiles <= (g.b_cs == 1 ? 384 : 256);
+  return tiles <= (g.b_cs == 1 ? 512 : 256);
 }
 int gemm_mfma_small(const GemmArgs &g, hipStream_t s) { return g.b_cs == 1 ? launch_small<true>(g, s) : launch_small<false>(g, s); }
 

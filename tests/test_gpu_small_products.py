@@ -20,8 +20,8 @@ def env():
     (32, 64, 1088),          # whole tiles; the first wave has one chunk more than the others
     (500, 504, 2056),        # 256 tiles
     (500, 520, 2048),        # 272: forward still, the input gradient on the larger tiles
-    (384, 1024, 1024),       # 384
-    (385, 1024, 1024),       # 416: neither
+    (512, 1024, 1024),       # 512
+    (513, 1024, 1024),       # 544: neither
     (7, 8200, 4104)])        # 257 columns of tiles
 def test_products_of_few_tiles(env, M, N, K):
     """C[M,N] over K as a forward product, with and without bias and residual, and as an input gradient, between infinities and
