@@ -288,7 +288,7 @@ __global__ __launch_bounds__(kNormThreads) void norm_bwd_kernel(
 // 203 us).
 // ---------------------------------------------------------------------------------------
 constexpr int kRowLanes = 16;  // row lanes of a block: 256 partial rows are four loads deep (four lanes: 7 us a launch, now 4.8)
-constexpr int kMaxColumnTasks = 6;
+constexpr int kMaxColumnTasks = 9;
 struct ColumnTask {
   const void *src;  // [rows][ld], the first n columns of it
   float *out;
@@ -524,6 +524,7 @@ template <typename F> static void with_table(const ColumnTasks &ts, F &&go) {
   };
   if (ts.count <= 1) as(std::integral_constant<int, 1>{});
   else if (ts.count <= 3) as(std::integral_constant<int, 3>{});
+  else if (ts.count <= 6) as(std::integral_constant<int, 6>{});
   else as(std::integral_constant<int, kMaxColumnTasks>{});
 }
 static int launch_column_sums(int dtype, const ColumnTasks &ts, int blocks, int accumulate, hipStream_t s, const char *what) {
@@ -604,7 +605,7 @@ extern "C" int tm_op_norm_fwd(int dtype, int kind, int64_t T, int64_t h, double 
 static int norm_bwd_any(int dtype, int kind, int64_t T, int64_t h, const void *dout, const void *x, const float *mean,
                         const float *rstd, const void *gain, const void *dres, void *dx, float *dgain, float *doffset,
                         float *dx_colsum, void *scratch, int accumulate, void *stream, const ColumnSum *sums = nullptr,
-                        int count = 0, float *partial_sums = nullptr) {
+                        int count = 0, float *partial_sums = nullptr, const NormSums *earlier = nullptr, NormSums *later = nullptr) {
   if (int e = check_width("norm_bwd", dtype, T, h)) return e;
   if (kind != TM_NORM_LAYERNORM && kind != TM_NORM_RMSNORM) return fail(TM_EINVAL, "norm_bwd: unknown kind %d", kind);
   if (!dout || !x || !rstd || !gain || !dx || !dgain || !scratch || (kind == TM_NORM_LAYERNORM && (!mean || !doffset)))
@@ -622,11 +623,16 @@ static int norm_bwd_any(int dtype, int kind, int64_t T, int64_t h, const void *d
                                : norm_bwd_t<float, false>(kind, T, (int)h, dout, x, mean, rstd, gain, dres, dx, partial, s);
   if (e) return e;
   const int G = norm_bwd_grid(T, h, dtype == TM_DTYPE_BF16 ? Vec<bf16>::N : Vec<float>::N);
-  float *outs[3] = {dgain, kind == TM_NORM_LAYERNORM ? doffset : nullptr, dx_colsum};
+  const NormSums own{partial, G, h, {dgain, kind == TM_NORM_LAYERNORM ? doffset : nullptr, dx_colsum}};
+  if (later) {
+    *later = own;
+    return TM_OK;
+  }
   ColumnTasks ts = {};
   int blocks = 0;
-  for (int k = 0; k < 3; ++k)
-    if (outs[k]) blocks = add_task(ts, blocks, 64, partial + k * h, 3 * h, G, h, outs[k], false);
+  for (const NormSums *n : {&own, earlier})
+    for (int k = 0; n && n->partial && k < 3; ++k)
+      if (n->out[k]) blocks = add_task(ts, blocks, 64, n->partial + k * n->h, 3 * n->h, n->rows, n->h, n->out[k], false);
   if (count) blocks = add_column_sums(ts, blocks, dtype, T, sums, count, partial_sums, s);
   return launch_column_sums(dtype, ts, blocks, accumulate, s, "norm_bwd reduce");
 }
@@ -638,9 +644,19 @@ int64_t tmk::column_sums_scratch_bytes(int64_t T, int64_t width) {
 int tmk::norm_bwd_and_column_sums(int dtype, int kind, int64_t T, int64_t h, const void *dout, const void *x, const float *mean,
                                   const float *rstd, const void *gain, const void *dres, void *dx, float *dgain, float *doffset,
                                   float *dx_colsum, void *scratch, const ColumnSum *sums, int count, void *partial_sums,
-                                  int accumulate, hipStream_t s) {
+                                  const NormSums &earlier, int accumulate, hipStream_t s) {
   return norm_bwd_any(dtype, kind, T, h, dout, x, mean, rstd, gain, dres, dx, dgain, doffset, dx_colsum, scratch, accumulate, s, sums,
-                      count, (float *)partial_sums);
+                      count, (float *)partial_sums, &earlier);
+}
+
+int64_t tmk::norm_bwd_partial_bytes(int dtype, int64_t T, int64_t h) {
+  return (int64_t)norm_bwd_grid(T, h, dtype == TM_DTYPE_BF16 ? Vec<bf16>::N : Vec<float>::N) * 3 * h * (int64_t)sizeof(float);
+}
+int tmk::norm_bwd_rows(int dtype, int kind, int64_t T, int64_t h, const void *dout, const void *x, const float *mean, const float *rstd,
+                       const void *gain, const void *dres, void *dx, float *dgain, float *doffset, float *dx_colsum, void *scratch,
+                       NormSums *later, hipStream_t s) {
+  return norm_bwd_any(dtype, kind, T, h, dout, x, mean, rstd, gain, dres, dx, dgain, doffset, dx_colsum, scratch, 0, s, nullptr, 0, nullptr,
+                      nullptr, later);
 }
 
 extern "C" int tm_op_norm_bwd(int dtype, int kind, int64_t T, int64_t h, const void *dout, const void *x,
