@@ -681,6 +681,11 @@ static int stage_bwd(tm_stage_t *st, const void *dy_in, void *dx_out, void *stre
     }
     return tm_op_linear_wgrad(dt, d.T, N, K, dyp, xp, dw, acc, sw);
   };
+  // stretches of parameters that the flat sweep has yet to update.  A layer's sweep is a launch of some 5 us where the layer is
+  // small: up to 8 M parameters (their gradients 32 MiB, still in the memory-side cache) they wait for the layers below.
+  std::vector<int64_t> seg_first, seg_count;
+  int64_t left = 0;
+  constexpr int64_t kSweepWaits = 1LL << 23;
   auto run = [&]() -> int {
   const void *dy = dy_in;
   if (cm) {
@@ -825,23 +830,31 @@ static int stage_bwd(tm_stage_t *st, const void *dy_in, void *dx_out, void *stre
       // the flat sweep over what the products have not updated: the stretches between the fused matrices
       std::sort(fused.begin(), fused.end(), [](const Range &a, const Range &b) { return a.first < b.first; });
       // (one launch for all of them: the vectors of a layer are a few thousand elements each)
-      std::vector<int64_t> seg_first, seg_count;
-      int64_t at = 0, left = 0;
+      int64_t at = 0;
       for (size_t i = 0; i <= fused.size(); ++i) {
         const int64_t end = i < fused.size() ? fused[i].first : o.total;
-        if (end > at) {
+        if (end > at && i == fused.size() && !seg_first.empty() && pb + end == seg_first[0]) {  // goes on in the layer above
+          seg_first[0] = pb + at;
+          seg_count[0] += end - at;
+          left += end - at;
+        } else if (end > at) {
           seg_first.push_back(pb + at);
           seg_count.push_back(end - at);
           left += end - at;
         }
         if (i < fused.size()) at = fused[i].first + fused[i].count;
       }
-      if (left > 0) {
+      // small layers that are updated whole wait for the ones below: their one stretch grows
+      const bool wait = !two && l > 0 && fused.empty() && seg_first.size() == 1 && left < kSweepWaits;
+      if (left > 0 && !wait) {
         const bool lowp = c.dtype == TM_DTYPE_BF16;
         float *master = lowp ? st->buf.master : (float *)st->buf.params;
         TM_STEP(0, per_param * (double)left,
                 adam_launch_segments((int)seg_first.size(), seg_first.data(), seg_count.data(), master, st->buf.grads,
                                      st->buf.exp_avg, st->buf.exp_avg_sq, lowp ? st->buf.params : nullptr, hp, step, so));
+        seg_first.clear();
+        seg_count.clear();
+        left = 0;
       }
       s = s_keep;
     }
