@@ -17,7 +17,7 @@ namespace tmk {
 
 constexpr int kMoeMaxExperts = 64, kMoeMaxTopK = 8, kMoeThreads = 256;
 static_assert(kMoeMaxExperts <= kWave, "one lane per expert count");
-constexpr int kWgradSegTokens = 128;  // tokens per block of the router weight gradient
+constexpr int kWgradSegTokens = 512;  // tokens per block of the router weight gradient
 __device__ __forceinline__ int ceil_div_dev(int a, int b) { return (a + b - 1) / b; }
 
 struct MoeDims {
@@ -109,80 +109,98 @@ static MoePlan moe_plan(const tm_moe_config_t *c) {
   return p;
 }
 
-// ---- router: one block per 8 tokens; a thread keeps 8 x 16 partial logits over its share of the hidden axis, so a
-// chunk of a router row is fetched once for 8 tokens (one block per token fetched the whole router matrix per token:
-// 1.3 GB through L2 at 2048 tokens and 16 experts).  More than 16 experts: in groups of 16.
-constexpr int kRouterTokens = 8, kRouterGroup = 16;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+// Element i of 16 bytes.
+template <typename T> __device__ __forceinline__ float elem(const u32x4 &x, int i) {
+  if constexpr (sizeof(T) == 2) {
+    return __builtin_bit_cast(float, i % 2 ? x[i / 2] & 0xffff0000u : x[i / 2] << 16);
+  } else {
+    const uint32_t w = x[i];  // (bit_cast of the element itself takes the vector's first)
+    return __builtin_bit_cast(float, w);
+  }
+}
+
+// ---- router: a block forms the logits of 16 tokens and, 16 experts at a time, chooses each token's.  Its sixteen waves take
+// every sixteenth 128 bytes of the rows and multiply them as a 16x16 result.  Every product starts from zero and sums meet in
+// trees but for the chain over a wave's turns, 128 bytes times 32: accumulated in the matrix instructions, 20480 elements were
+// 1.16e-7 from 64 bits, here 9.6e-8 (sums a thread, before: 9.7e-8).  Bound by the way of the rows from HBM: four row pieces and four weight pieces of a wave are in flight.
+// 8 tokens a block with 8x16 sums a thread, all 128 of them to be added up over 64 lanes: 2048 tokens of 20480, 16 experts
+// 76 us, 600 of 1024, 4 experts 32; here 50 and 8.
+constexpr int kRouterTokens = 16, kRouterGroup = 16, kRouterWaves = 16;
+// One product, and the tree of four or sixteen sums that start at zero.
+template <typename T> struct RouterSums {
+  static constexpr int N = sizeof(T) == 2 ? 4 : 16;
+  f32x4 v[N];
+  __device__ __forceinline__ void product(const u32x4 &a, const u32x4 &b, int set) {
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (sizeof(T) == 2) {
+      v[set] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), zero, 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[4 * set + i] = __builtin_amdgcn_mfma_f32_16x16x4f32(elem<T>(a, i), elem<T>(b, i), zero, 0, 0, 0);
+    }
+  }
+  __device__ __forceinline__ f32x4 sum() {
+#pragma unroll
+    for (int half = N / 2; half; half /= 2)
+#pragma unroll
+      for (int i = 0; i < half; ++i) v[i] += v[i + half];
+    return v[0];
+  }
+};
 template <typename T>
-__global__ __launch_bounds__(kMoeThreads) void moe_router_kernel(const T *__restrict__ c, const T *__restrict__ wr,
-                                                                 float *__restrict__ logits, int *__restrict__ top_idx,
-                                                                 float *__restrict__ gates, int n_tokens, int h, int E, int k) {
-  constexpr int VN = Vec<T>::N;
-  constexpr int NWAVE = kMoeThreads / kWave;
-  __shared__ float part[NWAVE][kRouterTokens][kRouterGroup];
+__global__ __launch_bounds__(kRouterWaves * kWave) void moe_router_kernel(const T *__restrict__ c, const T *__restrict__ wr,
+                                                                          float *__restrict__ logits, int *__restrict__ top_idx,
+                                                                          float *__restrict__ gates, int n_tokens, int h, int E, int k) {
+  constexpr int VN = Vec<T>::N, STEP = kRouterWaves * 8;
+  __shared__ float part[kRouterWaves][kRouterTokens][kRouterGroup + 1];
   __shared__ float lg[kRouterTokens][kMoeMaxExperts];
   const int t0 = blockIdx.x * kRouterTokens, tid = threadIdx.x, nch = h / VN;
-  const int wave = tid / kWave, lane = tid % kWave;
+  const int lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave), r = lane % 16, q = lane / 16;
+  // (tokens past the end repeat the last one, experts past the end the last expert; those results are never stored)
+  const T *row = c + (int64_t)(t0 + r < n_tokens ? t0 + r : n_tokens - 1) * h;
   for (int e0 = 0; e0 < E; e0 += kRouterGroup) {
-    float acc[kRouterTokens][kRouterGroup];
+    const T *w = wr + (int64_t)(e0 + r < E ? e0 + r : E - 1) * h;
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    for (int s = wave * 8; s < nch; s += 2 * STEP) {
+      u32x4 a[4], b[4];
+      int ch[4];
 #pragma unroll
-    for (int j = 0; j < kRouterTokens; ++j)
-#pragma unroll
-      for (int e = 0; e < kRouterGroup; ++e) acc[j][e] = 0.f;
-    for (int ch = tid; ch < nch; ch += kMoeThreads) {
-      // All 24 loads of a chunk are issued before the first use, raw, with no branches around them (tokens past the
-      // end repeat the last token, experts past the end the last expert; those results are never stored).
-      typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-      u32x4 ra[kRouterTokens], rw[kRouterGroup];
-#pragma unroll
-      for (int j = 0; j < kRouterTokens; ++j) {
-        const int tj = t0 + j < n_tokens ? t0 + j : n_tokens - 1;
-        ra[j] = *reinterpret_cast<const u32x4 *>(c + (int64_t)tj * h + ch * VN);
+      for (int i = 0; i < 4; ++i) {
+        ch[i] = s + i / 2 * STEP + i % 2 * 4 + q;
+        const int at = ch[i] < nch ? ch[i] : 0;
+        a[i] = *reinterpret_cast<const u32x4 *>(row + (int64_t)at * VN);
+        b[i] = *reinterpret_cast<const u32x4 *>(w + (int64_t)at * VN);
       }
+      __builtin_amdgcn_sched_barrier(0);  // all eight loads ahead of the first product
+      RouterSums<T> sums;
 #pragma unroll
-      for (int e = 0; e < kRouterGroup; ++e) {
-        const int ee = e0 + e < E ? e0 + e : E - 1;
-        rw[e] = *reinterpret_cast<const u32x4 *>(wr + (int64_t)ee * h + ch * VN);
+      for (int i = 0; i < 4; ++i) {
+        if (ch[i] >= nch) a[i] = b[i] = u32x4{0u, 0u, 0u, 0u};
+        sums.product(a[i], b[i], i);
       }
-      float a[kRouterTokens][VN];
-#pragma unroll
-      for (int j = 0; j < kRouterTokens; ++j) {
-        union { u32x4 raw; Vec<T> v; } u;
-        u.raw = ra[j];
-#pragma unroll
-        for (int i = 0; i < VN; ++i) a[j][i] = to_f32(u.v.v[i]);
-      }
-#pragma unroll
-      for (int e = 0; e < kRouterGroup; ++e) {
-        union { u32x4 raw; Vec<T> v; } u;
-        u.raw = rw[e];
-#pragma unroll
-        for (int i = 0; i < VN; ++i) {
-          const float w = to_f32(u.v.v[i]);
-#pragma unroll
-          for (int j = 0; j < kRouterTokens; ++j) acc[j][e] = fmaf(a[j][i], w, acc[j][e]);
-        }
-      }
+      sum += sums.sum();
     }
-    // lanes, then waves in wave order
 #pragma unroll
-    for (int j = 0; j < kRouterTokens; ++j)
-#pragma unroll
-      for (int e = 0; e < kRouterGroup; ++e) {
-        const float v = wave_sum(acc[j][e]);
-        if (lane == 0) part[wave][j][e] = v;
-      }
+    for (int v = 0; v < 4; ++v) part[wave][4 * q + v][r] = sum[v];
     __syncthreads();
     if (tid < kRouterTokens * kRouterGroup) {
       const int j = tid / kRouterGroup, e = tid % kRouterGroup;
-      float v = part[0][j][e];
+      float v[kRouterWaves];
 #pragma unroll
-      for (int w = 1; w < NWAVE; ++w) v += part[w][j][e];
-      if (e0 + e < E) lg[j][e0 + e] = v;
+      for (int i = 0; i < kRouterWaves; ++i) v[i] = part[i][j][e];
+#pragma unroll
+      for (int half = kRouterWaves / 2; half; half /= 2)
+#pragma unroll
+        for (int i = 0; i < half; ++i) v[i] += v[i + half];
+      if (e0 + e < E) lg[j][e0 + e] = v[0];
     }
     __syncthreads();
   }
-  for (int i = tid; i < kRouterTokens * E; i += kMoeThreads) {
+  for (int i = tid; i < kRouterTokens * E; i += kRouterWaves * kWave) {
     const int j = i / E, e = i % E;
     if (t0 + j < n_tokens) logits[(int64_t)(t0 + j) * E + e] = lg[j][e];
   }
@@ -399,56 +417,109 @@ __global__ __launch_bounds__(kMoeThreads) void moe_dispatch_bwd_kernel(const T *
   }
 }
 
-// ---- router weights: dWr[e, col] (+)= sum over tokens, in token order, of dlogit[t, e] c[t, col] ------
-// A block owns 256 columns and one segment of the tokens and keeps one fp32 accumulator per (expert, column)
-// in LDS; a token touches the accumulators of its k chosen experts only.  The segments' partial sums are
-// added in segment order by a second kernel.
+// ---- router weights: dWr[e, col] (+)= sum over tokens of dlogit[t, e] c[t, col] ----------------------
+// A block owns 128 (fp32: 64) columns, 16 experts and a segment of the tokens: a 16x16 product over tokens for every column
+// of a lane's 16 bytes, on the fp32 matrix instructions for both types, so that dlogit keeps its 24 bits.  dlogit is nearly
+// empty and lies in LDS as a table.  Eight waves take four tokens each in turn and meet in a tree; the sums of several
+// segments are added in segment order by a second kernel, one segment goes to its place at once.  Bound by the rows' way from
+// HBM: a wave has eight pieces of four rows in flight.  Accumulators in LDS before, k dependent updates for every token and
+// column: 2048 tokens of 20480, 16 experts 97 + 7 us, 600 of 1024, 4 experts 57 + 5; here 29 + 5 and 11 + 4.
+constexpr int kWgradWaves = 8, kWgradExperts = 16, kWgradDepth = 8;
 template <typename T>
-__global__ __launch_bounds__(kMoeThreads) void moe_router_wgrad_kernel(const T *__restrict__ c, const int *__restrict__ top_idx,
-                                                                       const float *__restrict__ dlog, float *__restrict__ part,
-                                                                       int n_tok, int h, int E, int k) {
-  extern __shared__ __align__(16) char smem[];
-  float *acc = reinterpret_cast<float *>(smem);                         // [E][256]
-  int *s_idx = reinterpret_cast<int *>(acc + (size_t)E * kMoeThreads);  // [segment tokens][k]
-  float *s_dl = reinterpret_cast<float *>(s_idx + kWgradSegTokens * kMoeMaxTopK);
-  const int tid = threadIdx.x, col = blockIdx.x * kMoeThreads + tid, seg = blockIdx.y;
-  const bool valid = col < h;
-  const int t0 = seg * kWgradSegTokens;
-  const int n = n_tok - t0 < kWgradSegTokens ? n_tok - t0 : kWgradSegTokens;
-  for (int e = 0; e < E; ++e) acc[e * kMoeThreads + tid] = 0.f;
-  for (int i = tid; i < n * k; i += kMoeThreads) {
-    s_idx[i] = top_idx[(int64_t)t0 * k + i];
-    s_dl[i] = dlog[(int64_t)t0 * k + i];
+__global__ __launch_bounds__(kWgradWaves * kWave) void moe_router_wgrad_kernel(const T *__restrict__ c, const int *__restrict__ top_idx,
+                                                                               const float *__restrict__ dlog, float *__restrict__ out,
+                                                                               int n_tok, int h, int E, int k, int accumulate) {
+  constexpr int VN = Vec<T>::N, TURN = kWgradWaves * 4;
+  __shared__ __align__(16) float lds[kWgradSegTokens * kWgradExperts];
+  static_assert(kWgradSegTokens % (kWgradDepth * TURN) == 0, "whole rounds of a segment fit the table");
+  static_assert(kWgradWaves / 2 * VN * kWave * 4 <= kWgradSegTokens * kWgradExperts, "the sums meet where the table was");
+  const int tid = threadIdx.x, lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave), r = lane % 16, q = lane / 16;
+  const int seg = blockIdx.y, e0 = blockIdx.z * kWgradExperts;
+  const int64_t t0 = (int64_t)seg * kWgradSegTokens;
+  const int n = n_tok - t0 < kWgradSegTokens ? (int)(n_tok - t0) : kWgradSegTokens, turns = ceil_div_dev(n, kWgradDepth * TURN) * kWgradDepth;
+  // (whole rounds of eight turns: tokens past the end are rows of zeros)
+  for (int i = tid; i < turns * TURN * kWgradExperts; i += kWgradWaves * kWave) lds[i] = 0.f;
+  __syncthreads();
+  for (int i = tid; i < n * k; i += kWgradWaves * kWave) {
+    const int e = top_idx[t0 * k + i] - e0;
+    if (e >= 0 && e < kWgradExperts) lds[i / k * kWgradExperts + e] = dlog[t0 * k + i];
   }
   __syncthreads();
-#pragma unroll 8
-  for (int tt = 0; tt < n; ++tt) {
-    const float cv = valid ? to_f32(c[(int64_t)(t0 + tt) * h + col]) : 0.f;
-    for (int i = 0; i < k; ++i) {
-      float *a = acc + s_idx[tt * k + i] * kMoeThreads + tid;
-      *a = fmaf(s_dl[tt * k + i], cv, *a);
+  const int col = (blockIdx.x * 16 + r) * VN;
+  const T *from = c + t0 * h + (col < h ? col : h - VN);  // (columns and tokens past the end: others, not stored or times zero)
+  f32x4 acc[VN];
+#pragma unroll
+  for (int i = 0; i < VN; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int j0 = 0; j0 < turns; j0 += kWgradDepth) {
+    u32x4 x[kWgradDepth];
+#pragma unroll
+    for (int j = 0; j < kWgradDepth; ++j) {
+      const int t = (j0 + j) * TURN + wave * 4 + q;
+      x[j] = *reinterpret_cast<const u32x4 *>(from + (int64_t)(t < n ? t : n - 1) * h);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < kWgradDepth; ++j) {
+      const float d = lds[((j0 + j) * TURN + wave * 4) * kWgradExperts + lane];
+#pragma unroll
+      for (int i = 0; i < VN; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(d, elem<T>(x[j], i), acc[i], 0, 0, 0);
     }
   }
-  if (valid)
-    for (int e = 0; e < E; ++e) part[((int64_t)seg * E + e) * h + col] = acc[e * kMoeThreads + tid];
+#pragma unroll
+  for (int half = kWgradWaves / 2; half; half /= 2) {
+    __syncthreads();  // the table, or the sums before, have been read
+    f32x4 *at = reinterpret_cast<f32x4 *>(lds) + lane;
+    if (wave >= half && wave < 2 * half)
+#pragma unroll
+      for (int i = 0; i < VN; ++i) at[((wave - half) * VN + i) * kWave] = acc[i];
+    __syncthreads();
+    if (wave < half)
+#pragma unroll
+      for (int i = 0; i < VN; ++i) acc[i] += at[(wave * VN + i) * kWave];
+  }
+  if (wave || col >= h) return;
+  // An infinity or NaN times the table's zeros is NaN for experts that the token did not choose: sums that are not finite are
+  // formed again over the chosen ones only.
+  float finite = 0.f;
+#pragma unroll
+  for (int i = 0; i < VN; ++i)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) finite = fmaf(acc[i][v], 0.f, finite);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int e = e0 + 4 * q + v;
+    if (e >= E) break;
+    float sum[VN];
+#pragma unroll
+    for (int i = 0; i < VN; ++i) sum[i] = acc[i][v];
+    if (finite != 0.f) {
+      for (int i = 0; i < VN; ++i) sum[i] = 0.f;
+      for (int a = 0; a < n * k; ++a) {
+        if (top_idx[t0 * k + a] != e) continue;
+        const u32x4 x = *reinterpret_cast<const u32x4 *>(from + (int64_t)(a / k) * h);
+#pragma unroll
+        for (int i = 0; i < VN; ++i) sum[i] = fmaf(dlog[t0 * k + a], elem<T>(x, i), sum[i]);
+      }
+    }
+    f32x4 *dst = reinterpret_cast<f32x4 *>(out + ((int64_t)seg * E + e) * h + col);
+#pragma unroll
+    for (int i = 0; i < VN / 4; ++i) {
+      f32x4 s = {sum[4 * i], sum[4 * i + 1], sum[4 * i + 2], sum[4 * i + 3]};
+      if (accumulate) s += dst[i];
+      dst[i] = s;
+    }
+  }
 }
 
 __global__ __launch_bounds__(kMoeThreads) void moe_router_wgrad_reduce_kernel(const float *__restrict__ part, float *__restrict__ dwr,
                                                                               int64_t n, int segs, int accumulate) {
-  const int64_t i = (int64_t)blockIdx.x * kMoeThreads + threadIdx.x;
+  const int64_t i = ((int64_t)blockIdx.x * kMoeThreads + threadIdx.x) * 4;  // n is a multiple of 8
   if (i >= n) return;
-  float sum = accumulate ? dwr[i] : 0.f;
-  for (int sg = 0; sg < segs; ++sg) sum += part[(int64_t)sg * n + i];
-  dwr[i] = sum;
-}
-
-template <typename K> static int set_lds(K kernel, int bytes, const char *what) {
-  if (bytes > 160 * 1024) return fail(TM_ESIZE, "%s: needs %d bytes of LDS", what, bytes);
-  if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(TM_ELAUNCH, "%s: cannot reserve %d bytes of LDS", what, bytes);
-  }
-  return TM_OK;
+  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+  if (accumulate) sum = *reinterpret_cast<const f32x4 *>(dwr + i);
+#pragma unroll 4
+  for (int sg = 0; sg < segs; ++sg) sum += *reinterpret_cast<const f32x4 *>(part + (int64_t)sg * n + i);
+  *reinterpret_cast<f32x4 *>(dwr + i) = sum;
 }
 
 }  // namespace tmk
@@ -539,10 +610,10 @@ extern "C" int tm_moe_fwd(const tm_moe_config_t *cfg, const void *params, const 
   g_last_kernel = "moe_router_kernel";
   const unsigned router_blocks = (unsigned)ceil_div(d.T, (int64_t)kRouterTokens);
   if (dt == TM_DTYPE_BF16)
-    moe_router_kernel<bf16><<<router_blocks, kMoeThreads, 0, s>>>((const bf16 *)c, (const bf16 *)par, logits, top_idx, gates, (int)d.T,
+    moe_router_kernel<bf16><<<router_blocks, kRouterWaves * kWave, 0, s>>>((const bf16 *)c, (const bf16 *)par, logits, top_idx, gates, (int)d.T,
                                                                   (int)d.h, (int)d.E, (int)d.k);
   else
-    moe_router_kernel<float><<<router_blocks, kMoeThreads, 0, s>>>((const float *)c, (const float *)par, logits, top_idx, gates,
+    moe_router_kernel<float><<<router_blocks, kRouterWaves * kWave, 0, s>>>((const float *)c, (const float *)par, logits, top_idx, gates,
                                                                    (int)d.T, (int)d.h, (int)d.E, (int)d.k);
   moe_plan_kernel<<<1, kPlanWaves * kWave, 0, s>>>(top_idx, slot_row, row_src, (int)(d.T * d.k), (int)d.E, (int)d.El, (int)d.ep, (int)d.C);
   if (dt == TM_DTYPE_BF16)
@@ -612,24 +683,24 @@ extern "C" int tm_moe_bwd(const tm_moe_config_t *cfg, const void *params, const 
     TM_TRY(tm_op_linear_wgrad(dt, grows, d.f, d.h, dg, buf, grads + w1.offset, acc, stream));
     if (cfg->has_bias) TM_TRY(tm_op_bias_grad(dt, grows, d.f, dg, grads + tn[1 + j * per + 1].offset, red, acc, stream));
   }
-  const int wg_lds = (int)(d.E * kMoeThreads * 4) + kWgradSegTokens * kMoeMaxTopK * 8;
-  const dim3 wg_grid((unsigned)ceil_div(d.h, kMoeThreads), (unsigned)p.wr_segs);
-  float *wr_part = (float *)(ws + p.wr_part);
+  const dim3 wg_grid((unsigned)ceil_div(d.h * d.es, 256), (unsigned)p.wr_segs, (unsigned)ceil_div(d.E, kWgradExperts));
+  const bool one_seg = p.wr_segs == 1;
+  float *wr_out = one_seg ? grads : (float *)(ws + p.wr_part);
+  const int wr_acc = one_seg ? acc : 0;
   g_last_kernel = "moe_dispatch_bwd_kernel";
   if (dt == TM_DTYPE_BF16) {
     moe_dispatch_bwd_kernel<bf16><<<(unsigned)d.T, kMoeThreads, 0, s>>>((const bf16 *)(ws + p.dbuf), (const bf16 *)par, slot_row, top_idx,
                                                                         gates, dgate, dlog, (bf16 *)dc, (int)d.h, (int)d.k);
-    TM_TRY(set_lds(moe_router_wgrad_kernel<bf16>, wg_lds, "moe_bwd"));
-    moe_router_wgrad_kernel<bf16><<<wg_grid, kMoeThreads, wg_lds, s>>>((const bf16 *)c, top_idx, dlog, wr_part, (int)d.T, (int)d.h,
-                                                                       (int)d.E, (int)d.k);
+    moe_router_wgrad_kernel<bf16><<<wg_grid, kWgradWaves * kWave, 0, s>>>((const bf16 *)c, top_idx, dlog, wr_out, (int)d.T, (int)d.h,
+                                                                          (int)d.E, (int)d.k, wr_acc);
   } else {
     moe_dispatch_bwd_kernel<float><<<(unsigned)d.T, kMoeThreads, 0, s>>>((const float *)(ws + p.dbuf), (const float *)par, slot_row,
                                                                          top_idx, gates, dgate, dlog, (float *)dc, (int)d.h, (int)d.k);
-    TM_TRY(set_lds(moe_router_wgrad_kernel<float>, wg_lds, "moe_bwd"));
-    moe_router_wgrad_kernel<float><<<wg_grid, kMoeThreads, wg_lds, s>>>((const float *)c, top_idx, dlog, wr_part, (int)d.T, (int)d.h,
-                                                                        (int)d.E, (int)d.k);
+    moe_router_wgrad_kernel<float><<<wg_grid, kWgradWaves * kWave, 0, s>>>((const float *)c, top_idx, dlog, wr_out, (int)d.T, (int)d.h,
+                                                                           (int)d.E, (int)d.k, wr_acc);
   }
-  moe_router_wgrad_reduce_kernel<<<(unsigned)ceil_div(d.E * d.h, kMoeThreads), kMoeThreads, 0, s>>>(wr_part, grads, d.E * d.h,
-                                                                                                    (int)p.wr_segs, acc);
+  if (!one_seg)
+    moe_router_wgrad_reduce_kernel<<<(unsigned)ceil_div(d.E * d.h, 4 * kMoeThreads), kMoeThreads, 0, s>>>(
+        (const float *)(ws + p.wr_part), grads, d.E * d.h, (int)p.wr_segs, acc);
   return check_launch("moe_bwd router");
 }

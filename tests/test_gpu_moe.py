@@ -228,3 +228,45 @@ def test_moe_at_the_5t_shard_shape_on_sampled_outputs(env):
     assert rel_err(to_host(grads[offb:offb + h]), d_o.sum(axis=0)) <= TOL_BF16
     print(f"  weight-gradient samples done at {time.time() - t0:.1f} s", flush=True)
     assert bool(torch.isfinite(grads).all()) and bool(torch.isfinite(out.float()).all())
+
+
+# tokens around a block of 16 and a segment of 512, experts around a group of 16, hidden around a wave's columns (128, fp32 64)
+@pytest.mark.parametrize("T,h,E,k,dtype", [(1, 8, 2, 1, BF16), (16, 136, 16, 2, BF16), (17, 72, 17, 8, FP32), (511, 128, 15, 2, BF16),
+                                           (513, 1032, 33, 3, BF16), (1025, 264, 64, 8, FP32), (33, 4104, 3, 2, BF16), (530, 2056, 4, 2, FP32)])
+def test_router_products(env, T, h, E, k, dtype):
+    torch, tm = env
+    cfg = si.MoeConfig(T, h, 64, E, 1, k, T, dtype=dtype, has_bias=0)
+    print(f"router products {cfg}", flush=True)
+    p = si.make_moe_params(cfg, router_std=0.05)
+    c, dout = si.make_moe_io(cfg)
+    flat, layout = flat_of(cfg, tm, p)
+    pd, cd, dd = to_dev(torch, flat, dtype), to_dev(torch, c, dtype), to_dev(torch, dout, dtype)
+    ws = torch.empty(tm.tm_moe_workspace_bytes(cfg), dtype=torch.uint8, device="cuda")
+    out, dc = torch.empty_like(cd), torch.empty_like(cd)
+    s = stream_ptr(torch)
+
+    def step(accumulate, grads):
+        tm.tm_moe_fwd(cfg, pd, cd, out, ws, s)
+        tm.tm_moe_bwd(cfg, pd, cd, dd, dc, grads, accumulate, ws, s)
+        torch.cuda.synchronize()
+        return grads[:E * h].cpu().numpy().astype(np.float64).reshape(E, h)
+
+    dwr = step(0, torch.full((flat.size,), 7.0, device="cuda"))
+    idx = read_ws(torch, tm, cfg, ws, tm.TM_MOE_WS_TOP_IDX, torch.int32).reshape(T, k)
+    _, st = mo.moe_fwd(c, p, E, 1, k, T, cfg.act)
+    assert rel_err(read_ws(torch, tm, cfg, ws, tm.TM_MOE_WS_LOGITS, torch.float32), st["logits"].reshape(-1)) <= 1e-5
+    if (idx == st["idx"]).all():  # (no tie within rounding: the checker's gradients are of the same routing)
+        _, rgr = mo.moe_bwd(dout, p, st, E, 1, k, T, cfg.act)
+        assert rel_err(dwr, rgr["w_router"]) <= (TOL_BF16 if dtype == BF16 else TOL_FP32)
+    # added to: one more rounding of the sum (2^-24 of 1 + |dWr|)
+    added = step(1, torch.full((flat.size,), 1.0, device="cuda"))
+    assert np.abs(added - 1.0 - dwr).max() <= 2.0 ** -22 * (1.0 + np.abs(dwr).max())
+    # a token that is not finite reaches the experts that it chose and no other
+    if T > 1 and k < E:
+        t = T // 2
+        cd[t, h - 1] = float("inf")
+        got = step(0, torch.zeros(flat.size, device="cuda"))
+        touched = np.zeros(E, bool)
+        touched[idx[t]] = touched[read_ws(torch, tm, cfg, ws, tm.TM_MOE_WS_TOP_IDX, torch.int32).reshape(T, k)[t]] = True
+        # (the same terms, here in token order: 24 bits over at most T of them)
+        assert np.isfinite(got[~touched]).all() and np.abs(got - dwr)[~touched].max(initial=0.0) <= T * 2.0 ** -24 * np.abs(dwr).max() * 8
