@@ -287,14 +287,6 @@ __global__ __launch_bounds__(kPlanWaves * kWave) void moe_plan_kernel(const int 
   }
 }
 
-// Threads for a row of `bytes` (gather, combine, input gradient: a block a row).  Rows of fewer than 256 pieces of 16 bytes leave a
-// block of 256 with waves that have nothing to do but take up places: 4000 rows of 1 KB 10.4 -> 6.5 us (input
-// gradient), the whole shard of 2 experts and FC 512 141 -> 135; 600 rows of 2 KB 112 -> 110.
-static unsigned moe_row_threads(int64_t bytes) {
-  const int64_t waves = ceil_div(bytes, (int64_t)16 * kWave);
-  return (unsigned)(waves * kWave < kMoeThreads ? waves * kWave : kMoeThreads);
-}
-
 // ---- buffers: row = the token's input row, or zero ---------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(kMoeThreads) void moe_gather_kernel(const T *__restrict__ c, const int *__restrict__ row_src,
@@ -305,7 +297,7 @@ __global__ __launch_bounds__(kMoeThreads) void moe_gather_kernel(const T *__rest
   const int src = row_src[row];
   u32x4 *dst = reinterpret_cast<u32x4 *>(buf + row * h);
   const u32x4 *from = reinterpret_cast<const u32x4 *>(c + (int64_t)(src < 0 ? 0 : src / k) * h);
-  for (int ch = threadIdx.x; ch < h / VN; ch += blockDim.x) dst[ch] = src < 0 ? u32x4{0u, 0u, 0u, 0u} : from[ch];
+  for (int ch = threadIdx.x; ch < h / VN; ch += kMoeThreads) dst[ch] = src < 0 ? u32x4{0u, 0u, 0u, 0u} : from[ch];
 }
 
 // ---- combine: out[t] = sum over kept assignments of gate * o[row] ----------------------------------
@@ -322,7 +314,7 @@ __global__ __launch_bounds__(kMoeThreads) void moe_combine_kernel(const T *__res
     rows[i] = i < k ? slot_row[t * k + i] : -1;
     gt[i] = i < k ? gates[t * k + i] : 0.f;
   }
-  for (int ch = threadIdx.x; ch < h / VN; ch += blockDim.x) {
+  for (int ch = threadIdx.x; ch < h / VN; ch += kMoeThreads) {
     float acc[VN];
 #pragma unroll
     for (int j = 0; j < VN; ++j) acc[j] = 0.f;
@@ -401,7 +393,7 @@ __global__ __launch_bounds__(kMoeThreads) void moe_dispatch_bwd_kernel(const T *
     dch[i] = gt * (dch[i] - s);  // softmax over the chosen logits
     if (threadIdx.x == 0 && i < k) dlog[t * k + i] = dch[i];
   }
-  for (int ch = threadIdx.x; ch < h / VN; ch += blockDim.x) {
+  for (int ch = threadIdx.x; ch < h / VN; ch += kMoeThreads) {
     float acc[VN];
 #pragma unroll
     for (int j = 0; j < VN; ++j) acc[j] = 0.f;
@@ -615,7 +607,6 @@ extern "C" int tm_moe_fwd(const tm_moe_config_t *cfg, const void *params, const 
   const int dt = cfg->dtype;
   float *logits = (float *)(ws + p.logits), *gates = (float *)(ws + p.gates);
   int *top_idx = (int *)(ws + p.top_idx), *slot_row = (int *)(ws + p.slot_row), *row_src = (int *)(ws + p.row_src);
-  const unsigned row_threads = moe_row_threads(d.h * d.es);
   g_last_kernel = "moe_router_kernel";
   const unsigned router_blocks = (unsigned)ceil_div(d.T, (int64_t)kRouterTokens);
   if (dt == TM_DTYPE_BF16)
@@ -626,9 +617,9 @@ extern "C" int tm_moe_fwd(const tm_moe_config_t *cfg, const void *params, const 
                                                                    (int)d.T, (int)d.h, (int)d.E, (int)d.k);
   moe_plan_kernel<<<1, kPlanWaves * kWave, 0, s>>>(top_idx, slot_row, row_src, (int)(d.T * d.k), (int)d.E, (int)d.El, (int)d.ep, (int)d.C);
   if (dt == TM_DTYPE_BF16)
-    moe_gather_kernel<bf16><<<(unsigned)d.rows, row_threads, 0, s>>>((const bf16 *)c, row_src, (bf16 *)(ws + p.buf), (int)d.h, (int)d.k);
+    moe_gather_kernel<bf16><<<(unsigned)d.rows, kMoeThreads, 0, s>>>((const bf16 *)c, row_src, (bf16 *)(ws + p.buf), (int)d.h, (int)d.k);
   else
-    moe_gather_kernel<float><<<(unsigned)d.rows, row_threads, 0, s>>>((const float *)c, row_src, (float *)(ws + p.buf), (int)d.h, (int)d.k);
+    moe_gather_kernel<float><<<(unsigned)d.rows, kMoeThreads, 0, s>>>((const float *)c, row_src, (float *)(ws + p.buf), (int)d.h, (int)d.k);
   TM_TRY(check_launch("moe_fwd routing"));
   // the experts: local expert j works on the ep buffers that the identity exchange leaves with it
   const int64_t grows = d.ep * d.C;
@@ -645,9 +636,9 @@ extern "C" int tm_moe_fwd(const tm_moe_config_t *cfg, const void *params, const 
   }
   g_last_kernel = "moe_combine_kernel";
   if (dt == TM_DTYPE_BF16)
-    moe_combine_kernel<bf16><<<(unsigned)d.T, row_threads, 0, s>>>((const bf16 *)(ws + p.o), slot_row, gates, (bf16 *)out, (int)d.h, (int)d.k);
+    moe_combine_kernel<bf16><<<(unsigned)d.T, kMoeThreads, 0, s>>>((const bf16 *)(ws + p.o), slot_row, gates, (bf16 *)out, (int)d.h, (int)d.k);
   else
-    moe_combine_kernel<float><<<(unsigned)d.T, row_threads, 0, s>>>((const float *)(ws + p.o), slot_row, gates, (float *)out, (int)d.h, (int)d.k);
+    moe_combine_kernel<float><<<(unsigned)d.T, kMoeThreads, 0, s>>>((const float *)(ws + p.o), slot_row, gates, (float *)out, (int)d.h, (int)d.k);
   return check_launch("moe_fwd combine");
 }
 
@@ -693,18 +684,17 @@ extern "C" int tm_moe_bwd(const tm_moe_config_t *cfg, const void *params, const 
     if (cfg->has_bias) TM_TRY(tm_op_bias_grad(dt, grows, d.f, dg, grads + tn[1 + j * per + 1].offset, red, acc, stream));
   }
   const dim3 wg_grid((unsigned)ceil_div(d.h * d.es, 256), (unsigned)p.wr_segs, (unsigned)ceil_div(d.E, kWgradExperts));
-  const unsigned row_threads = moe_row_threads(d.h * d.es);
   const bool one_seg = p.wr_segs == 1;
   float *wr_out = one_seg ? grads : (float *)(ws + p.wr_part);
   const int wr_acc = one_seg ? acc : 0;
   g_last_kernel = "moe_dispatch_bwd_kernel";
   if (dt == TM_DTYPE_BF16) {
-    moe_dispatch_bwd_kernel<bf16><<<(unsigned)d.T, row_threads, 0, s>>>((const bf16 *)(ws + p.dbuf), (const bf16 *)par, slot_row, top_idx,
+    moe_dispatch_bwd_kernel<bf16><<<(unsigned)d.T, kMoeThreads, 0, s>>>((const bf16 *)(ws + p.dbuf), (const bf16 *)par, slot_row, top_idx,
                                                                         gates, dgate, dlog, (bf16 *)dc, (int)d.h, (int)d.k);
     moe_router_wgrad_kernel<bf16><<<wg_grid, kWgradWaves * kWave, 0, s>>>((const bf16 *)c, top_idx, dlog, wr_out, (int)d.T, (int)d.h,
                                                                           (int)d.E, (int)d.k, wr_acc);
   } else {
-    moe_dispatch_bwd_kernel<float><<<(unsigned)d.T, row_threads, 0, s>>>((const float *)(ws + p.dbuf), (const float *)par, slot_row,
+    moe_dispatch_bwd_kernel<float><<<(unsigned)d.T, kMoeThreads, 0, s>>>((const float *)(ws + p.dbuf), (const float *)par, slot_row,
                                                                          top_idx, gates, dgate, dlog, (float *)dc, (int)d.h, (int)d.k);
     moe_router_wgrad_kernel<float><<<wg_grid, kWgradWaves * kWave, 0, s>>>((const float *)c, top_idx, dlog, wr_out, (int)d.T, (int)d.h,
                                                                            (int)d.E, (int)d.k, wr_acc);
