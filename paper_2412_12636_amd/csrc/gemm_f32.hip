@@ -392,8 +392,7 @@ static bool reach16(const GemmArgs &g) {
 }
 
 template <bool A_KC, bool B_KC, int EPI> static int pick(const GemmArgs &g, hipStream_t s) {
-  const int split_tile = gemm_f32_split_supported(g) ? f32_split_tile(g.M, g.N, g.K, EPI != 0, reach16(g)) : 0;
-  if (split_tile) return gemm_f32_split(g, split_tile, s);
+  if (gemm_f32_split_supported(g) && f32_split(g.M, g.N, g.K, EPI != 0, reach16(g))) return gemm_f32_split(g, s);
   const F32Form f = f32_form(g.M, g.N, g.K, EPI != 0, reach16(g));
   if (f.tile == 128) return launch<128, 128, 64, 64, 1, 2, 1, false, A_KC, B_KC, EPI>(g, s);
   if (f.tile == 64 && f.split == 4) return launch<64, 64, 32, 32, 4, 3, 2, false, A_KC, B_KC, EPI>(g, s);
@@ -412,7 +411,7 @@ template <bool A_KC, bool B_KC, int EPI> static int pick(const GemmArgs &g, hipS
 static bool small_form(const GemmArgs &g, bool wgrad, F32Form *f) {
   if (!gemm_f32_supported(g)) return false;
   *f = f32_form(g.M, g.N, g.K, wgrad, reach16(g));
-  return f->tile <= 32 && !f->patches && !(gemm_f32_split_supported(g) && f32_split_tile(g.M, g.N, g.K, wgrad, reach16(g)));
+  return f->tile <= 32 && !f->patches && !(gemm_f32_split_supported(g) && f32_split(g.M, g.N, g.K, wgrad, reach16(g)));
 }
 
 template <int DT, int WT, int WSPL, int DEPI, int WEPI> static int launch_pair(const GemmArgs &d, const GemmArgs &w, hipStream_t s) {

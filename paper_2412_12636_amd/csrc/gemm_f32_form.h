@@ -42,21 +42,19 @@ inline F32Form f32_form(int64_t M, int64_t N, int64_t K, bool wgrad, bool reach1
   return {32, wgrad ? 8 : 4, patches(32, 6)};
 }
 
-// The tile, 128 or 64, of the kernel on bf16 terms (gemm_f32_split.hip) where that is the faster one, 0 where f32_form's is.
+// Whether the kernel on bf16 terms (gemm_f32_split.hip, 128x128 tiles) is the faster one.
 //
-// Both times in us from the passes over the chip (r; one block a unit on bf16 terms), the tiles a unit has on average (u) and
-// the reduction length, fitted by non-negative least squares to every form's time on 600 products of each kind with 96 to 8192
-// rows, columns and 32 to 8192 reduction elements; they meet them to 4 to 8 %.  The faster one has to win by 5 %.  On those
-// products the choice takes 0.95 of the time (geometric mean; 0.80 where f32_form has 128x128 tiles or the split 64x64
-// ones) and is never more than 3 % slower; products of fewer than 256 elements, where it was up to 7 %, stay.
+// Times in us from the passes over the chip (r; one block a unit on bf16 terms), the tiles a unit has on average (u) and the
+// reduction length, fitted by non-negative least squares to every form's time on 300 to 600 products of each kind with 96 to 8192
+// rows and columns over 256 to 8192 elements; they meet them to 3 to 6 %.  It has to win by 5 %: on 900 products (forward, input
+// gradient, weight gradient) it was taken for 247, which took 0.84 of their time and at most 1.00; 128x128 tiles 0.79, 64x64 ones
+// that a unit has several of 0.9, 32x32 ones rarely.  Never for the 64x64 tiles that split the reduction (1.9 of their time).
 //
-// Never at the price of precision: an fp32 accumulator's roundings are what both are off the exact sums by.  64x64 tiles here
-// split the reduction over four waves (2.4e-7 of the result at 1024 elements of N(0,1) data; f32_form's four-way forms 2.9e-7,
-// its eight-way one 2.0e-7), 128x128 ones do not (4.9e-7; f32_form's whole walks 5.7e-7).
-inline int f32_split_tile(int64_t M, int64_t N, int64_t K, bool wgrad, bool reach16) {
-  if (K < 256) return 0;
+// Never at the price of precision: its error on N(0,1) data, 1.9e-7 of the result over 1024 elements, is below that of the whole
+// walks (5.7e-7) and the four-way ones (2.9e-7) that it replaces; weight gradients that eight waves split (2.0e-7) stay.
+inline bool f32_split(int64_t M, int64_t N, int64_t K, bool wgrad, bool reach16) {
   const F32Form f = f32_form(M, N, K, wgrad, reach16);
-  if (f.tile == 16 || f.split == 8) return 0;
+  if (K < 256 || f.tile == 16 || f.split != (f.tile == 32 ? 4 : 1)) return false;
   struct Grid {
     double r, u;
   };
@@ -65,16 +63,11 @@ inline int f32_split_tile(int64_t M, int64_t N, int64_t K, bool wgrad, bool reac
     return Grid{(double)((n + 255) / 256), (double)n / 256};
   };
   const double k = (double)K / 1024;
-  const Grid g = grid(f.tile), g64 = grid(64), g128 = grid(128);
-  if (g64.u > 1 << 14) return 0;  // a launch has at most 2^32 threads
-  const double now = f.tile == 128    ? 4.0 + g.r * (3.0 + 61 * k)
-                     : f.tile == 32   ? 2.7 + g.r * (0.3 + 5.1 * k) + g.u * 0.4
-                     : f.split == 4   ? g.r * (4.7 + 16.2 * k) + g.u * 2 * k
-                                      : 2.9 + g.r * (0.4 + 16.8 * k) + g.u * 0.5;
-  const double c64 = 1.6 + g64.r * (3.1 + 10.6 * k) + g64.u * (0.4 + 2.5 * k);
-  const double c128 = 2.3 + g128.r * (3.4 + 28.8 * k) + g128.u * (2.4 + 7.1 * k);
-  const bool whole = f.split == 1 && c128 < c64;
-  return (whole ? c128 : c64) * 1.05 > now ? 0 : whole ? 128 : 64;
+  const Grid g = grid(f.tile), t = grid(128);
+  const double now = f.tile == 128  ? 4.0 + g.r * (3.0 + 61 * k)
+                     : f.tile == 64 ? 2.9 + g.r * (0.4 + 16.8 * k) + g.u * 0.5
+                                    : 2.7 + g.r * (0.3 + 5.1 * k) + g.u * 0.4;
+  return 1.05 * (1.0 + t.r * (6.0 + 33.9 * k) + t.u * (1.2 + 11.9 * k)) < now;
 }
 
 }  // namespace tmk

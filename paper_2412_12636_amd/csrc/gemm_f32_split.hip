@@ -1,25 +1,26 @@
 // fp32 GEMM on the bf16 matrix instructions: every operand element as three bf16 terms.
 //
 // x = h + m + l with h = bf16(x), m = bf16(x - h), l = x - h - m: 24 significand bits in three times eight, exact as long as
-// nothing underflows.  Of the nine products of two such sums the six down to 2^-16 of the largest are formed (hh, hm, mh, mm,
-// hl, lh), the smallest first, into one fp32 accumulator; the three left out are below 2^-24 of |a b|, under the rounding
-// of a fp32 product.  Six 32x32x16 MFMAs take 192 clocks where eight 32x32x2 fp32 ones take 512.
+// nothing underflows.  Of the nine products of two such sums all but ll are formed, which is below 2^-34 of |a b|.  hh is exact in
+// fp32 and has an accumulator of its own; the seven others, 2^-8 of it and less, share a second one, and the two meet once at
+// the end.  What rounds is one sum of hh for every eight elements, where a chain of fused multiply-adds rounds each.  Errors against
+// 64 bits, of the result, fp32 instructions / here: 256 N(0,1) elements 2.9e-7 / 0.9e-7, 2048 8.1e-7 / 2.7e-7; rows of 16 elements
+// that are not zero 7.4e-8 / 3.4e-8, of four 4.0e-8 / 2.6e-8, of one 2.53e-8 / 2.53e-8 (0.500 / 0.506 ulp at most).  With all terms in
+// one accumulator these were 1.4e-7, 7.3e-8 and 3.5e-8 (1.4 ulp); with ml and lm left out 3.4e-8, 2.7e-8 and 2.6e-8 (0.95 ulp).
+// Eight 32x32x16 MFMAs take 256 clocks where eight 32x32x2 fp32 ones take 512.
 //
-// A block has four waves that multiply and eight that fetch, four for each operand.  The fetching waves read fp32 rows from
+// A block has four waves that multiply and four that fetch, two for each operand.  The fetching waves read fp32 rows from
 // global memory two stages ahead into registers, split them (5.5 vector instructions an element) and write the three planes to
-// LDS, [row][BK] bf16 each, for both kinds of layout: a lane that reads along a strided reduction axis holds a 4x4 block and
-// packs its columns, which transposes it for free.  The multiplying waves own 64x64 results and read 16-byte fragments one
-// batch of 24 MFMAs ahead.  Three LDS stages: one read, one complete (its first fragments are fetched ahead of the barrier), one
-// written.  The results leave through LDS as whole rows, all twelve waves storing.
+// LDS, [row][32] bf16 each, for both kinds of layout: a lane that reads along a strided reduction axis holds 4x4 blocks and
+// packs their columns, which transposes them for free.  The multiplying waves own 64x64 results and read 16-byte fragments one
+// batch of 32 MFMAs ahead; two sets of fragments and two of accumulators are 224 of the 256 registers that two waves a SIMD
+// leave.  Three LDS stages: one read, one complete (its first fragments are fetched ahead of the barrier), one written.  The
+// results leave through LDS as whole rows, all eight waves storing.
 //
-// 128x128 tiles: bound by the MFMA rate that random data sustains (1.13 us a stage of 32 elements with every unit busy and
-// nothing to fetch or split, 0.9 with a quarter of them, 0.64 at the nominal clock); 1.24 to 1.3 measured, 1.2 PFLOP/s of bf16
-// products = 200 TFLOP/s of fp32 ones.  64x64 tiles: a stage of 64 elements takes 0.9 us where its MFMAs take 0.35 to 0.6;
-// splitting operands that serve only 64 results of the other side costs as much as multiplying them.  With four fetching waves
-// instead of eight 1.0; with chunks placed for 32 LDS banks instead of 64 1.1; with results stored by the waves that hold them
-// 2 us more a block.
-// Against the fp32 instructions: 1024 x 8192 over 1024 131 -> 88 us, 1024 x 4096 over 1024 70 -> 47, 2048 x 2048 over 2048 142 -> 85,
-// 1024 x 1024 over 1024 23.6 -> 17.5, over 4096 72 -> 57.
+// Bound by the MFMA rate: a stage of 32 elements takes 1.43 us with every unit busy, 0.85 at the nominal clock and 1.5 at the
+// rate that random data sustains; 188 TFLOP/s of fp32 products.  64x64 tiles, whose operands are split for only 64 results of the
+// other side, were 6 % slower than the fp32 instructions (1024 x 1024 over 1024 21.6 us against 20.4).
+// Against the fp32 instructions: 1024 x 8192 over 1024 137 -> 114 us, 1024 x 4096 over 1024 77 -> 58, 2048 x 2048 over 2048 135 -> 108.
 #include "gemm.h"
 #include "gemm_f32_form.h"
 
@@ -47,12 +48,17 @@ struct F32SplitParams {
   uint32_t a_bytes, b_bytes, c_bytes;
 };
 
-// Byte of 16-byte chunk c of a row in a plane [R][BK].  Sixteen lanes that read one chunk of sixteen consecutive rows, and 32
-// that write eight bytes each, of whole rows or of two chunks of eight rows four apart, meet each of the 64 banks once.
-template <int BK> __device__ __forceinline__ int plane_pos(int row, int c) {
-  if (BK == 32)
-    return (row >> 2) * 256 + ((row ^ (row >> 2)) & 3) * 64 + ((c ^ ((row >> 2) & 3) ^ ((row >> 3) & 2)) << 4);
-  return (row >> 1) * 256 + ((row ^ (row >> 2)) & 1) * 128 + ((c ^ ((row >> 2) & 3) ^ (((row >> 2) ^ (row << 1)) & 4)) << 4);
+constexpr int kTile = 128, kStep = 32;            // a block's results; reduction elements of a stage
+constexpr int kPlane = kTile * kStep * 2;         // a term of an operand's stage, [row][kStep] bf16
+constexpr int kStage = 6 * kPlane, kStages = 3;   // A's terms, B's terms
+constexpr int kOutPitch = kTile + 8;              // floats; 4 of these are 32 banks off a whole round of 64
+constexpr int kSplitLds = kStages * kStage;
+static_assert(kTile * kOutPitch * 4 <= kSplitLds, "the results leave through the stages' place");
+
+// Byte of 16-byte chunk c of a row in a plane.  Sixteen lanes that read one chunk of sixteen consecutive rows, and 32 that write
+// eight bytes each, of whole rows or of two chunks of eight rows four apart, meet each of the 64 banks once.
+__device__ __forceinline__ int plane_pos(int row, int c) {
+  return (row >> 2) * 256 + ((row ^ (row >> 2)) & 3) * 64 + ((c ^ ((row >> 2) & 3) ^ ((row >> 3) & 2)) << 4);
 }
 
 // The leading bf16 of both, and what it leaves.  (x - h as one bf16 dot product with -1, seven instructions for three terms of
@@ -63,38 +69,33 @@ __device__ __forceinline__ uint32_t split_term(f32x2 &x) {
   x[1] -= __builtin_bit_cast(float, h & 0xffff0000u);
   return h;
 }
-template <int PLANE> __device__ __forceinline__ void write_terms(char *at, f32x2 x, f32x2 y) {
+__device__ __forceinline__ void write_terms(char *at, f32x2 x, f32x2 y) {
 #pragma unroll
   for (int p = 0; p < 3; ++p) {
     const uint32_t a = split_term(x), b = split_term(y);
-    *reinterpret_cast<u32x2 *>(at + p * PLANE) = u32x2{a, b};
+    *reinterpret_cast<u32x2 *>(at + p * kPlane) = u32x2{a, b};
   }
 }
 
-// Fetching four waves' share of R rows by BK reduction elements.
-template <int R, int BK, bool KC> struct SplitLoad {
-  static constexpr int PLANE = R * BK * 2, NL = R * BK / 1024;  // 16-byte loads of a lane
+// Fetching two waves' share of a stage of one operand.
+template <bool KC> struct SplitLoad {
+  static constexpr int NL = kTile * kStep / 512;  // 16-byte loads of a lane
   uint32_t voff[NL];
   int k_first[NL], lds_at[NL];
   f32x4 x[2][NL];
   __device__ __forceinline__ void init(int64_t ld, int row0, int t) {
-    if constexpr (KC) {
 #pragma unroll
-      for (int i = 0; i < NL; ++i) {
-        const int idx = i * 256 + t, row = idx / (BK / 4), kc = idx % (BK / 4);
+    for (int i = 0; i < NL; ++i) {
+      if constexpr (KC) {
+        const int idx = i * 128 + t, row = idx / (kStep / 4), kc = idx % (kStep / 4);
         voff[i] = (uint32_t)(((int64_t)(row0 + row) * ld + kc * 4) * 4);
         k_first[i] = kc * 4;
-        lds_at[i] = plane_pos<BK>(row, kc >> 1) + (kc & 1) * 8;
-      }
-    } else {  // a wave: eight row groups by eight groups of four reduction elements; element i of the block is a load
-      static_assert(NL == 4, "one block of 4x4 a lane");
-      const int wave = t / 64, lane = t % 64;
-      const int kg = wave % (BK / 32) * 8 + lane / 8, rg = wave / (BK / 32) * 8 + lane % 8;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        k_first[i] = kg * 4 + i;
+        lds_at[i] = plane_pos(row, kc >> 1) + (kc & 1) * 8;
+      } else {  // a wave, twice: eight row groups by eight groups of four reduction elements; element i % 4 of a block is a load
+        const int kg = t % 64 / 8, rg = (t / 64 + i / 4 * 2) * 8 + t % 8;
+        k_first[i] = kg * 4 + i % 4;
         voff[i] = (uint32_t)(((int64_t)k_first[i] * ld + row0 + rg * 4) * 4);
-        lds_at[i] = plane_pos<BK>(rg * 4 + i, kg >> 1) + (kg & 1) * 8;
+        lds_at[i] = plane_pos(rg * 4 + i % 4, kg >> 1) + (kg & 1) * 8;
       }
     }
   }
@@ -109,10 +110,11 @@ template <int R, int BK, bool KC> struct SplitLoad {
   template <int SET> __device__ __forceinline__ void store(char *tile) const {
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
+      const f32x4 *b = x[SET] + i / 4 * 4;
       if constexpr (KC)
-        write_terms<PLANE>(tile + lds_at[i], f32x2{x[SET][i][0], x[SET][i][1]}, f32x2{x[SET][i][2], x[SET][i][3]});
+        write_terms(tile + lds_at[i], f32x2{x[SET][i][0], x[SET][i][1]}, f32x2{x[SET][i][2], x[SET][i][3]});
       else
-        write_terms<PLANE>(tile + lds_at[i], f32x2{x[SET][0][i], x[SET][1][i]}, f32x2{x[SET][2][i], x[SET][3][i]});
+        write_terms(tile + lds_at[i], f32x2{b[0][i % 4], b[1][i % 4]}, f32x2{b[2][i % 4], b[3][i % 4]});
     }
   }
 };
@@ -154,42 +156,32 @@ __device__ __forceinline__ f32x16 fp32_tile(const F32SplitParams &p, int m0, int
   return acc;
 }
 
-template <int BM, int BN, int BK> struct F32SplitCfg {
-  static constexpr int NT = (BM / 64) * (BN / 64), KSPL = 4 / NT, SUBS = BK / 16 / KSPL;
-  static constexpr int PA = BM * BK * 2, PB = BN * BK * 2, STAGE = 3 * (PA + PB);
-  // the results of a wave's share of the reduction on their way out; 4 PITCH is 32 banks off a whole round of 64
-  static constexpr int PITCH = BN + 8, OUT = BM * PITCH * 4, LDS = 3 * STAGE > KSPL * OUT ? 3 * STAGE : KSPL * OUT;
-  static_assert(NT * KSPL == 4 && SUBS >= 1 && 4 * PITCH % 64 == 32, "four multiplying waves of 64x64");
-};
-
-template <int BM, int BN, int BK, bool A_KC, bool B_KC, int EPI>
-__global__ __launch_bounds__(768) void gemm_f32_split_kernel(const F32SplitParams p) {
-  typedef F32SplitCfg<BM, BN, BK> C;
-  constexpr int KSPL = C::KSPL, SUBS = C::SUBS, NT = C::NT;
+template <bool A_KC, bool B_KC, int EPI>
+__global__ __launch_bounds__(512) void gemm_f32_split_kernel(const F32SplitParams p) {
   extern __shared__ __align__(1024) char lds[];
   // an XCD (ids round-robin over eight) owns a range of tiles, walked in patches
   const int nblk = p.tiles_m * p.tiles_n, xcd = blockIdx.x % 8, base = nblk / 8, rem = nblk % 8;
   const int lid = xcd * base + (xcd < rem ? xcd : rem) + (int)(blockIdx.x / 8);
   const int gi = lid / (kSplitPatch * p.tiles_n), first = gi * kSplitPatch, in_group = lid - first * p.tiles_n;
   const int rows = p.tiles_m - first < kSplitPatch ? p.tiles_m - first : kSplitPatch;
-  const int m0 = (first + in_group % rows) * BM, n0 = (in_group / rows) * BN;
+  const int m0 = (first + in_group % rows) * kTile, n0 = (in_group / rows) * kTile;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nk = (p.K + BK - 1) / BK;
+  const int nk = (p.K + kStep - 1) / kStep;
   float *const out = reinterpret_cast<float *>(lds);
   bool redo = false;
 
   if (wave >= 4) {
     auto feed = [&](auto load, const float *src, uint32_t bytes, int64_t ld, int row0, char *slot) {
       const rsrc_t rs = make_rsrc(src, bytes);
-      char *const last = slot + 2 * C::STAGE;
-      load.init(ld, row0, (int)threadIdx.x & 255);
+      char *const last = slot + (kStages - 1) * kStage;
+      load.init(ld, row0, (int)threadIdx.x & 127);
       load.template fetch<0>(rs, 0, p.K, ld);
-      if (nk > 1) load.template fetch<1>(rs, BK, p.K, ld);
+      if (nk > 1) load.template fetch<1>(rs, kStep, p.K, ld);
       auto stage = [&](auto set, int s) {
         constexpr int SET = decltype(set)::value;
         load.template store<SET>(slot);
-        if (s + 2 < nk) load.template fetch<SET>(rs, (s + 2) * BK, p.K, ld);
-        slot = slot == last ? slot - 2 * C::STAGE : slot + C::STAGE;
+        if (s + 2 < nk) load.template fetch<SET>(rs, (s + 2) * kStep, p.K, ld);
+        slot = slot == last ? slot - (kStages - 1) * kStage : slot + kStage;
         split_barrier();  // stage s is whole; stage s - 2 has been read
       };
       for (int s = 0; s < nk; s += 2) {
@@ -197,35 +189,31 @@ __global__ __launch_bounds__(768) void gemm_f32_split_kernel(const F32SplitParam
         if (s + 1 < nk) stage(std::integral_constant<int, 1>{}, s + 1);
       }
     };
-    if (wave < 8)
-      feed(SplitLoad<BM, BK, A_KC>{}, p.A, p.a_bytes, p.lda, m0, lds);
+    if (wave < 6)
+      feed(SplitLoad<A_KC>{}, p.A, p.a_bytes, p.lda, m0, lds);
     else
-      feed(SplitLoad<BN, BK, B_KC>{}, p.B, p.b_bytes, p.ldb, n0, lds + 3 * C::PA);
+      feed(SplitLoad<B_KC>{}, p.B, p.b_bytes, p.ldb, n0, lds + 3 * kPlane);
     split_barrier();
     split_barrier();
   } else {
-    const int ks = wave / NT, wt = wave % NT;
-    const int wm = wt / (BN / 64) * 64, wn = wt % (BN / 64) * 64;
-    f32x16 acc[2][2];
+    const int wm = wave / 2 * 64, wn = wave % 2 * 64;
+    f32x16 lead[2][2], rest[2][2];  // the leading terms' products; all others
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+      for (int v = 0; v < 16; ++v) lead[i >> 1][i & 1][v] = rest[i >> 1][i & 1][v] = 0.f;
     struct Frags {
       bf16x8 a[2][3], b[2][3];
     } f[2];
-    static_assert(SUBS <= 2, "the second 16 reduction elements of a wave: 32 bytes across in the lane address");
-    const int at = plane_pos<BK>(lane % 32, 2 * ks * SUBS + lane / 32);
+    const int at = plane_pos(lane % 32, lane / 32);  // (the second 16 reduction elements: 32 bytes across)
     auto fetch = [&](Frags &x, const char *slot, int s) {
-      const char *A = slot + wm * BK * 2 + (at ^ (s * 32)), *B = slot + 3 * C::PA + wn * BK * 2 + (at ^ (s * 32));
+      const char *A = slot + wm * kStep * 2 + (at ^ (s * 32)), *B = slot + 3 * kPlane + wn * kStep * 2 + (at ^ (s * 32));
 #pragma unroll
       for (int q = 2; q >= 0; --q)
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-          x.a[t][q] = *reinterpret_cast<const bf16x8 *>(A + q * C::PA + t * 32 * BK * 2);
-          x.b[t][q] = *reinterpret_cast<const bf16x8 *>(B + q * C::PB + t * 32 * BK * 2);
+          x.a[t][q] = *reinterpret_cast<const bf16x8 *>(A + q * kPlane + t * 32 * kStep * 2);
+          x.b[t][q] = *reinterpret_cast<const bf16x8 *>(B + q * kPlane + t * 32 * kStep * 2);
         }
     };
     uint32_t bits[4] = {0, 0, 0, 0};  // of the leading terms of the lane's rows: of A in both tiles, of B in both
@@ -236,62 +224,42 @@ __global__ __launch_bounds__(768) void gemm_f32_split_kernel(const F32SplitParam
         bits[t] |= a[0] | a[1], bits[t] |= a[2] | a[3];
         bits[2 + t] |= b[0] | b[1], bits[2 + t] |= b[2] | b[3];
       }
-      constexpr int qa[6] = {2, 0, 1, 1, 0, 0}, qb[6] = {0, 2, 1, 0, 1, 0};
+      constexpr int qa[8] = {0, 2, 1, 2, 0, 1, 1, 0}, qb[8] = {0, 1, 2, 0, 2, 1, 0, 1};
 #pragma unroll
-      for (int q = 0; q < 6; ++q)
+      for (int q = 0; q < 8; ++q)
 #pragma unroll
-        for (int tm = 0; tm < 2; ++tm)
-#pragma unroll
-          for (int tn = 0; tn < 2; ++tn)
-            acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.a[tm][qa[q]], x.b[tn][qb[q]], acc[tm][tn], 0, 0, 0);
+        for (int i = 0; i < 4; ++i) {
+          f32x16 &to = q ? rest[i >> 1][i & 1] : lead[i >> 1][i & 1];
+          to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.a[i >> 1][qa[q]], x.b[i & 1][qb[q]], to, 0, 0, 0);
+        }
     };
-    const char *cur = lds, *next = lds + C::STAGE;
-    auto advance = [&] {
-      cur = next;
-      next = next == lds + 2 * C::STAGE ? lds : next + C::STAGE;
-    };
+    const char *cur = lds, *next = lds + kStage;
     split_barrier();
     fetch(f[0], cur, 0);
-    if constexpr (SUBS == 1) {
-      for (int t = 0; t < nk; t += 2) {  // (the fragments fetched behind the last stage are not used)
-        split_barrier();
-        fetch(f[1], next, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(f[0]);
-        advance();
-        if (t + 1 < nk) {
-          split_barrier();
-          fetch(f[0], next, 0);
-          __builtin_amdgcn_sched_barrier(0);
-          multiply(f[1]);
-          advance();
-        }
-      }
-    } else {
-      static_assert(SUBS == 1 || SUBS % 2 == 0, "fragment sets alternate");
-      for (int t = 0; t < nk; ++t) {
-        split_barrier();
-#pragma unroll
-        for (int s = 0; s < SUBS; ++s) {
-          fetch(f[(s + 1) & 1], s + 1 < SUBS ? cur : next, (s + 1) % SUBS);
-          __builtin_amdgcn_sched_barrier(0);
-          multiply(f[s & 1]);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-        advance();
-      }
+    for (int t = 0; t < nk; ++t) {
+      split_barrier();
+      fetch(f[1], cur, 1);
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(f[0]);
+      __builtin_amdgcn_sched_barrier(0);
+      fetch(f[0], next, 0);  // (behind the last stage: not used)
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(f[1]);
+      __builtin_amdgcn_sched_barrier(0);
+      cur = next;
+      next = next == lds + (kStages - 1) * kStage ? lds : next + kStage;
     }
 
     const int out_lane = lane_again();
     split_barrier();  // everyone has read its last fragments
-    float *x = out + ks * (C::OUT / 4) + (wm + 4 * (out_lane >> 5)) * C::PITCH + wn + out_lane % 32;
+    float *x = out + (wm + 4 * (out_lane >> 5)) * kOutPitch + wn + out_lane % 32;
     float finite = 0.f;  // stays zero unless a product with an infinity or NaN gets in
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const float r = acc[i >> 1][i & 1][v];
-        x[((i >> 1) * 32 + 8 * (v >> 2) + (v & 3)) * C::PITCH + (i & 1) * 32] = r;
+        const float r = lead[i >> 1][i & 1][v] + rest[i >> 1][i & 1][v];
+        x[((i >> 1) * 32 + 8 * (v >> 2) + (v & 3)) * kOutPitch + (i & 1) * 32] = r;
         finite = __builtin_fmaf(r, 0.f, finite);
       }
     redo = finite != 0.f;
@@ -303,28 +271,21 @@ __global__ __launch_bounds__(768) void gemm_f32_split_kernel(const F32SplitParam
   }
   const int out_lane = lane_again(), tid = wave * 64 + out_lane;
   if (__syncthreads_or(redo)) {
-    for (int i = wave; i < (BM / 32) * (BN / 32); i += 12) {
-      const int tm = i / (BN / 32) * 32, tn = i % (BN / 32) * 32;
+    for (int i = wave; i < 16; i += 8) {
+      const int tm = i / 4 * 32, tn = i % 4 * 32;
       const f32x16 r = fp32_tile<A_KC, B_KC>(p, m0 + tm, n0 + tn, out_lane);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        float *x = out + (tm + 8 * (v >> 2) + 4 * (out_lane >> 5) + (v & 3)) * C::PITCH + tn + out_lane % 32;
-        x[0] = r[v];
-        for (int w = 1; w < KSPL; ++w) x[w * (C::OUT / 4)] = 0.f;
-      }
+      for (int v = 0; v < 16; ++v) out[(tm + 8 * (v >> 2) + 4 * (out_lane >> 5) + (v & 3)) * kOutPitch + tn + out_lane % 32] = r[v];
     }
     __syncthreads();
   }
   const rsrc_t rc = make_rsrc(p.C, p.c_bytes), rres = make_rsrc(p.residual, p.c_bytes);
-  const int col = tid % (BN / 4) * 4;
+  const int col = tid % (kTile / 4) * 4;
   f32x4 bias = {0.f, 0.f, 0.f, 0.f};
   if (EPI == 0 && p.bias && n0 + col < p.N) bias = *reinterpret_cast<const f32x4 *>(p.bias + n0 + col);
 #pragma unroll 2
-  for (int row = tid / (BN / 4); row < BM; row += 768 / (BN / 4)) {
-    const float *x = out + row * C::PITCH + col;
-    f32x4 r = *reinterpret_cast<const f32x4 *>(x);
-#pragma unroll
-    for (int w = 1; w < KSPL; ++w) r += *reinterpret_cast<const f32x4 *>(x + w * (C::OUT / 4));
+  for (int row = tid / (kTile / 4); row < kTile; row += 512 / (kTile / 4)) {
+    f32x4 r = *reinterpret_cast<const f32x4 *>(out + row * kOutPitch + col);
     const uint32_t off = m0 + row < p.M && n0 + col < p.N ? (uint32_t)(((int64_t)(m0 + row) * p.ldc + n0 + col) * 4) : 0x80000000u;
     if (EPI == 0) {
       r += bias;
@@ -336,7 +297,7 @@ __global__ __launch_bounds__(768) void gemm_f32_split_kernel(const F32SplitParam
   }
 }
 
-template <int BM, int BN, int BK, bool A_KC, bool B_KC, int EPI> static int launch(const GemmArgs &g, hipStream_t s) {
+template <bool A_KC, bool B_KC, int EPI> static int launch(const GemmArgs &g, hipStream_t s) {
   F32SplitParams p;
   p.M = (int)g.M;
   p.N = (int)g.N;
@@ -349,37 +310,31 @@ template <int BM, int BN, int BK, bool A_KC, bool B_KC, int EPI> static int laun
   p.ldc = g.ldc;
   p.bias = (const float *)g.bias;
   p.residual = (const float *)g.residual;
-  p.tiles_m = (int)ceil_div(g.M, BM);
-  p.tiles_n = (int)ceil_div(g.N, BN);
+  p.tiles_m = (int)ceil_div(g.M, kTile);
+  p.tiles_n = (int)ceil_div(g.N, kTile);
   p.a_bytes = (uint32_t)((A_KC ? g.M * g.a_rs : g.K * g.a_cs) * 4);
   p.b_bytes = (uint32_t)((B_KC ? g.N * g.b_rs : g.K * g.b_cs) * 4);
   p.c_bytes = (uint32_t)(g.M * g.ldc * 4);
-  constexpr int lds = F32SplitCfg<BM, BN, BK>::LDS;
   static bool attr_set = false;  // per instantiation
-  if (!attr_set && hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_f32_split_kernel<BM, BN, BK, A_KC, B_KC, EPI>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess)
-    return fail(TM_ELAUNCH, "gemm_f32_split: cannot reserve %d bytes of LDS", lds);
+  if (!attr_set && hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_f32_split_kernel<A_KC, B_KC, EPI>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, kSplitLds) != hipSuccess)
+    return fail(TM_ELAUNCH, "gemm_f32_split: cannot reserve %d bytes of LDS", kSplitLds);
   attr_set = true;
   const int64_t blocks = (int64_t)p.tiles_m * p.tiles_n;
   if (blocks > 0x7fffffff) return fail(TM_ESIZE, "gemm_f32_split: too many tiles");
   g_last_kernel = "gemm_f32_split_kernel";
-  gemm_f32_split_kernel<BM, BN, BK, A_KC, B_KC, EPI><<<(unsigned)blocks, 768, lds, s>>>(p);
+  gemm_f32_split_kernel<A_KC, B_KC, EPI><<<(unsigned)blocks, 512, kSplitLds, s>>>(p);
   return check_launch("gemm_f32_split");
-}
-
-template <bool A_KC, bool B_KC, int EPI> static int pick(const GemmArgs &g, int tile, hipStream_t s) {
-  if (tile == 128) return launch<128, 128, 32, A_KC, B_KC, EPI>(g, s);
-  return launch<64, 64, 64, A_KC, B_KC, EPI>(g, s);
 }
 
 bool gemm_f32_split_supported(const GemmArgs &g) {
   return gemm_f32_supported(g) && g.N % 4 == 0 && g.ldc % 4 == 0 && (((uintptr_t)g.C | (uintptr_t)g.bias | (uintptr_t)g.residual) & 15) == 0;
 }
 
-int gemm_f32_split(const GemmArgs &g, int tile, hipStream_t s) {
-  if (g.c_mode == 1) return pick<false, false, 1>(g, tile, s);
-  if (g.c_mode == 2) return pick<false, false, 2>(g, tile, s);
-  return g.b_cs == 1 ? pick<true, true, 0>(g, tile, s) : pick<true, false, 0>(g, tile, s);
+int gemm_f32_split(const GemmArgs &g, hipStream_t s) {
+  if (g.c_mode == 1) return launch<false, false, 1>(g, s);
+  if (g.c_mode == 2) return launch<false, false, 2>(g, s);
+  return g.b_cs == 1 ? launch<true, true, 0>(g, s) : launch<true, false, 0>(g, s);
 }
 
 }  // namespace tmk

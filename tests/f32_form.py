@@ -11,9 +11,7 @@ extern "C" void f32_form(int64_t M, int64_t N, int64_t K, int wgrad, int reach16
   const tmk::F32Form f = tmk::f32_form(M, N, K, wgrad, reach16);
   out[0] = f.tile, out[1] = f.split, out[2] = f.patches;
 }
-extern "C" int f32_split(int64_t M, int64_t N, int64_t K, int wgrad, int reach16) {
-  return tmk::f32_split_tile(M, N, K, wgrad, reach16);
-}
+extern "C" int f32_split(int64_t M, int64_t N, int64_t K, int wgrad, int reach16) { return tmk::f32_split(M, N, K, wgrad, reach16); }
 """
 
 
@@ -40,11 +38,11 @@ def forms(T, N, K):
                     for t, s, p in (form(T, N, K, False), form(T, K, N, False), form(N, K, T, True)))
 
 
-def split_tile(M, N, K, wgrad, reach16=True):
-    """Tile of C[M,N] over K on bf16 terms (128 or 64), 0 where form() holds."""
-    return _lib().f32_split(*(ctypes.c_int64(v) for v in (M, N, K)), int(wgrad), int(reach16))
+def split(M, N, K, wgrad, reach16=True):
+    """Whether C[M,N] over K goes to the kernel on bf16 terms; form() holds where not."""
+    return bool(_lib().f32_split(*(ctypes.c_int64(v) for v in (M, N, K)), int(wgrad), int(reach16)))
 
 
-def split_tiles(T, N, K):
+def splits(T, N, K):
     """Of the three products of a linear map: forward, input gradient, weight gradient."""
-    return split_tile(T, N, K, False), split_tile(T, K, N, False), split_tile(N, K, T, True)
+    return split(T, N, K, False), split(T, K, N, False), split(N, K, T, True)

@@ -1,19 +1,26 @@
 """fp32 products on the bf16 matrix instructions (csrc/gemm_f32_split.hip): three bf16 terms an operand element."""
 import pytest
 
-from tests.f32_form import split_tile, split_tiles
+from tests.f32_form import form, split, splits
 
 FP32 = 0
 
 
-def test_split_tiles_keep_out_where_they_would_lose():
-    """Short reductions, results small enough for 16x16 tiles, weight gradients whose eight-way sums are the more exact ones, and
-    more tiles than a launch has threads for."""
+def test_where_the_terms_keep_out():
+    """Short reductions, results of few tiles, a row of tiles that are nearly empty, and every form whose sums are split finer than
+    these: the 16x16 tiles, the four-way 64x64 and the eight-way 32x32 ones."""
     for wgrad in (False, True):
-        assert split_tile(4096, 4096, 255, wgrad) == 0 and split_tile(4096, 4096, 256, wgrad) == 128
-        assert split_tile(256, 256, 8192, wgrad) == 0
-        assert split_tile(8, 1 << 26, 256, wgrad) == 0
-    assert split_tile(1032, 520, 2000, True) == 0 and split_tile(1032, 520, 2000, False) == 64
+        assert not split(2048, 2048, 255, wgrad) and split(2048, 2048, 256, wgrad)
+        assert not split(256, 256, 8192, wgrad)
+        assert not split(8, 1 << 26, 256, wgrad)
+        kept = set()
+        for M in range(96, 2400, 136):
+            for N in range(96, 2400, 136):
+                for K in (328, 1024, 4096):
+                    if form(M, N, K, wgrad)[:2] in ((16, 4), (64, 4), (32, 8)):
+                        kept.add(form(M, N, K, wgrad)[:2])
+                        assert not split(M, N, K, wgrad)
+        assert len(kept) == 2 + wgrad
 
 
 @pytest.fixture(scope="module")
@@ -27,26 +34,30 @@ def env():
 
 
 def close(got, ref, size, n):
-    """|got - ref| against the sums' roundings: six terms for every 16 of n products and the meeting of four waves, each half an
-    ulp of at most the sum of the magnitudes `size`; the products left out are 2^-24 of each."""
-    return bool(((got.double() - ref).abs() <= (0.375 * n + 8) * 2.0 ** -24 * size + 1e-44).all())
+    """|got - ref| against the sums' roundings: one of half an ulp for every eight of n products, taken twice, and a few for the
+    meeting of the accumulators and the epilogue, of at most the sum of the magnitudes `size`."""
+    return bool(((got.double() - ref).abs() <= (0.125 * n + 8) * 2.0 ** -24 * size + 1e-44).all())
+
+
+def off(got, ref):
+    return ((got.double() - ref).norm() / ref.norm()).item()
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("T,N,K,tiles", [
-    (1000, 1000, 1000, (64, 64, 64)),          # a reduction that ends inside a stage, edges inside a tile
-    (3077, 776, 2056, (128, 128, 64)),         # odd token counts; 2056 = 64 stages of 32 and 8 elements
-    (1100, 1928, 1992, (64, 64, 128)),
-    (1601, 1640, 328, (128, 64, 0)),           # one row and one column of tiles nearly empty
-    (1023, 1544, 520, (0, 64, 64)),            # weight gradient over 1023 tokens
-    (2048, 2048, 256, (128, 0, 0)),            # the shortest reduction
+@pytest.mark.parametrize("T,N,K,taken", [
+    (3077, 776, 2056, (True, True, False)),    # odd token counts; 2056 = 64 stages of 32 and 8 elements
+    (1100, 1928, 1992, (True, True, True)),    # edges inside a tile, a reduction that ends inside a stage
+    (1536, 1544, 1544, (True, True, True)),    # one column of tiles nearly empty
+    (1021, 3096, 1032, (True, False, True)),   # weight gradient over 1021 tokens
+    (1601, 2312, 328, (True, False, False)),
+    (2048, 2048, 256, (True, False, False)),   # the shortest reduction
 ])
-def test_products_of_split_operands(env, T, N, K, tiles):
+def test_products_of_split_operands(env, T, N, K, taken):
     """Forward with and without bias and residual, input gradient, weight gradient stored and added, against 64 bits and the bound
     of the sums; then with an infinite and a tiny row in x and a NaN in dy: only what reads those is not finite, and the
     tiny row's results keep their precision."""
     torch, tm, s = env
-    assert split_tiles(T, N, K) == tiles
+    assert splits(T, N, K) == taken
     print(f"split fp32 products T={T} N={N} K={K}", flush=True)
     g = torch.Generator(device="cuda")
     g.manual_seed(T + N)
@@ -86,11 +97,11 @@ def test_elements_of_extreme_size(env):
     """Magnitudes whose leading bf16 is infinite or whose lower terms underflow, and results next to the largest number, beside
     their exact values."""
     torch, tm, s = env
-    T, N, K = 1024, 1024, 1024
-    assert split_tiles(T, N, K) == (64, 64, 64)
+    T, N, K = 2048, 2048, 2048
+    assert splits(T, N, K)[0]
     g = torch.Generator(device="cuda")
     g.manual_seed(3)
-    x, w = (torch.randn(1024, 1024, device="cuda", generator=g) for _ in range(2))
+    x, w = (torch.randn(2048, 2048, device="cuda", generator=g) for _ in range(2))
     y = torch.empty(T, N, device="cuda")
     for sx, sw in ((1e-37, 1e30), (1e30, 1e-37), (1e-39, 1e30), (1e36, 1e-3)):
         a, b = x * sx, w * sw
@@ -102,3 +113,40 @@ def test_elements_of_extreme_size(env):
     b[:, 31] = 1e-3
     tm.tm_op_linear_fwd(FP32, T, N, K, a, b, None, None, y, s)
     assert y.isfinite().all() and close(y, a.double() @ b.double().t(), a.double().abs() @ b.double().abs().t(), K)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("T,N,K", [(2048, 2048, 256), (1100, 1928, 1992)])
+def test_no_less_precise_than_fused_multiply_adds(env, T, N, K):
+    """Rows with one element that is not zero: the product rounded once, 0.51 ulp (the second accumulator's roundings are 2^-8 of
+    an ulp, the omitted product 2^-10); with a few: no further from 64 bits, in the root mean square, than a chain
+    of fused multiply-adds, each of which rounds; full ones: an eighth of the products round, partial sums of n N(0,1) products
+    grow like their root, an ulp's rounding is 2.4e-8 of a value, so 2.4e-8 sqrt(n / 16 + 1), here with a quarter to spare (one
+    of the omitted 2^-16 products would be 1e-6)."""
+    torch, tm, s = env
+    assert split(T, N, K, False)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K)
+    rnd = lambda *shape: torch.randn(shape, device="cuda", generator=g)
+    w, y = rnd(N, K), torch.empty(T, N, device="cuda")
+    for count in (1, 2, 4, 16, 64):
+        at = torch.rand(T, K, device="cuda", generator=g).topk(count, 1).indices.sort(1).values
+        values = rnd(T, count)
+        x = torch.zeros(T, K, device="cuda").scatter_(1, at, values)
+        tm.tm_op_linear_fwd(FP32, T, N, K, x, w, None, None, y, s)
+        ref = x.double() @ w.double().t()
+        if count == 1:
+            ulp = torch.exp2(torch.floor(torch.log2(ref.abs())) - 23)
+            assert bool(((y.double() - ref).abs() <= 0.51 * ulp).all())
+            continue
+        rows = slice(0, T, 16)
+        chain = torch.zeros(len(range(0, T, 16)), N, device="cuda")
+        for i in range(count):
+            chain = (chain.double() + values[rows, i, None].double() * w[:, at[rows, i]].t().double()).float()
+        print(f"{count} of {K}: {off(y, ref):.3e}, chain {off(chain, ref[rows]):.3e}", flush=True)
+        assert off(y, ref) <= off(chain, ref[rows])
+    x = rnd(T, K)
+    tm.tm_op_linear_fwd(FP32, T, N, K, x, w, None, None, y, s)
+    e = off(y, x.double() @ w.double().t())
+    print(f"all of {K}: {e:.3e}", flush=True)
+    assert e <= 3e-8 * (K / 16 + 1) ** 0.5
