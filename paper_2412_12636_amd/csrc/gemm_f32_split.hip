@@ -1,7 +1,9 @@
 // fp32 GEMM on the bf16 matrix instructions: every operand element as three bf16 terms.
 //
-// x = h + m + l with h = bf16(x), m = bf16(x - h), l = x - h - m: 24 significand bits in three times eight, exact as long as
-// nothing underflows.  Of the nine products of two such sums all but ll are formed, which is below 2^-34 of |a b|.  hh is exact in
+// 2^24 x = h + m + l with h = bf16(2^24 x), m = bf16 of what h leaves, l the rest: 24 significand bits in three times eight.  The
+// instructions take subnormal terms for zero; at this scale the last bit of any x is 2^-125 or more, so that no term is
+// subnormal and the sum is exact, small elements beside large ones included.  Elements of 2^104 and more and results of 2^80 and
+// more come out as infinities and NaN, and are formed on the fp32 instructions as those are.  Of the nine products of two such sums all but ll are formed, which is below 2^-34 of |a b|.  hh is exact in
 // fp32 and has an accumulator of its own; the seven others, 2^-8 of it and less, share a second one, and the two meet once at
 // the end.  What rounds is one sum of hh for every eight elements, where a chain of fused multiply-adds rounds each.  Errors against
 // 64 bits, of the result, fp32 instructions / here: 256 N(0,1) elements 2.9e-7 / 0.9e-7, 2048 8.1e-7 / 2.7e-7; rows of 16 elements
@@ -10,7 +12,7 @@
 // Eight 32x32x16 MFMAs take 256 clocks where eight 32x32x2 fp32 ones take 512.
 //
 // A block has four waves that multiply and four that fetch, two for each operand.  The fetching waves read fp32 rows from
-// global memory two stages ahead into registers, split them (5.5 vector instructions an element) and write the three planes to
+// global memory two stages ahead into registers, split them (6.5 vector instructions an element) and write the three planes to
 // LDS, [row][32] bf16 each, for both kinds of layout: a lane that reads along a strided reduction axis holds 4x4 blocks and
 // packs their columns, which transposes them for free.  The multiplying waves own 64x64 results and read 16-byte fragments one
 // batch of 32 MFMAs ahead; two sets of fragments and two of accumulators are 224 of the 256 registers that two waves a SIMD
@@ -33,9 +35,9 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int v4u32 __attribute__((__vector_size__(16)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kSplitPatch = 8;  // row-tiles of a patch
+constexpr float kUp = 0x1p24f, kDown = 0x1p-48f;  // the operands' scale, and back from their products'
 
 struct F32SplitParams {
   int M, N, K;
@@ -70,6 +72,7 @@ __device__ __forceinline__ uint32_t split_term(f32x2 &x) {
   return h;
 }
 __device__ __forceinline__ void write_terms(char *at, f32x2 x, f32x2 y) {
+  x[0] *= kUp, x[1] *= kUp, y[0] *= kUp, y[1] *= kUp;
 #pragma unroll
   for (int p = 0; p < 3; ++p) {
     const uint32_t a = split_term(x), b = split_term(y);
@@ -131,8 +134,8 @@ __device__ __forceinline__ void split_barrier() {
 __device__ __forceinline__ int lane_again() { return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
 
 // The 32x32 results at (m0, n0) again on the fp32 matrix instructions, operands straight from global memory: for tiles with a
-// value that is not finite (an infinite element has no remainder, one above the largest bf16 has an infinite leading term) or
-// with an operand row of nothing but elements below 2^-95, whose lower terms the bf16 instructions take for zero.
+// value that is not finite (an infinite element has no remainder, one that the scale takes past the largest bf16 has an infinite
+// leading term).
 template <bool A_KC, bool B_KC>
 __device__ __forceinline__ f32x16 fp32_tile(const F32SplitParams &p, int m0, int n0, int lane) {
   const rsrc_t ra = make_rsrc(p.A, p.a_bytes), rb = make_rsrc(p.B, p.b_bytes);
@@ -216,14 +219,7 @@ __global__ __launch_bounds__(512) void gemm_f32_split_kernel(const F32SplitParam
           x.b[t][q] = *reinterpret_cast<const bf16x8 *>(B + q * kPlane + t * 32 * kStep * 2);
         }
     };
-    uint32_t bits[4] = {0, 0, 0, 0};  // of the leading terms of the lane's rows: of A in both tiles, of B in both
     auto multiply = [&](const Frags &x) {
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const u32x4 a = __builtin_bit_cast(u32x4, x.a[t][0]), b = __builtin_bit_cast(u32x4, x.b[t][0]);
-        bits[t] |= a[0] | a[1], bits[t] |= a[2] | a[3];
-        bits[2 + t] |= b[0] | b[1], bits[2 + t] |= b[2] | b[3];
-      }
       constexpr int qa[8] = {0, 2, 1, 2, 0, 1, 1, 0}, qb[8] = {0, 1, 2, 0, 2, 1, 0, 1};
 #pragma unroll
       for (int q = 0; q < 8; ++q)
@@ -258,16 +254,11 @@ __global__ __launch_bounds__(512) void gemm_f32_split_kernel(const F32SplitParam
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const float r = lead[i >> 1][i & 1][v] + rest[i >> 1][i & 1][v];
+        const float r = (lead[i >> 1][i & 1][v] + rest[i >> 1][i & 1][v]) * kDown;
         x[((i >> 1) * 32 + 8 * (v >> 2) + (v & 3)) * kOutPitch + (i & 1) * 32] = r;
         finite = __builtin_fmaf(r, 0.f, finite);
       }
     redo = finite != 0.f;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {  // all of a row's elements below 2^-95 (an exponent field under 32), and not all zero
-      const uint32_t b = bits[t] | (uint32_t)__shfl_xor((int)bits[t], 32), e = b | b >> 16;
-      redo |= (e & 0x7fff) != 0 && (e & 0x7000) == 0;
-    }
   }
   const int out_lane = lane_again(), tid = wave * 64 + out_lane;
   if (__syncthreads_or(redo)) {

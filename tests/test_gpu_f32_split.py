@@ -94,8 +94,8 @@ def test_products_of_split_operands(env, T, N, K, taken):
 
 @pytest.mark.gpu
 def test_elements_of_extreme_size(env):
-    """Magnitudes whose leading bf16 is infinite or whose lower terms underflow, and results next to the largest number, beside
-    their exact values."""
+    """Magnitudes whose leading bf16 is infinite at the terms' scale or would underflow without it, and results beyond the scaled
+    sums or next to the largest number, beside their exact values."""
     torch, tm, s = env
     T, N, K = 2048, 2048, 2048
     assert splits(T, N, K)[0]
@@ -103,7 +103,7 @@ def test_elements_of_extreme_size(env):
     g.manual_seed(3)
     x, w = (torch.randn(2048, 2048, device="cuda", generator=g) for _ in range(2))
     y = torch.empty(T, N, device="cuda")
-    for sx, sw in ((1e-37, 1e30), (1e30, 1e-37), (1e-39, 1e30), (1e36, 1e-3)):
+    for sx, sw in ((1e-37, 1e30), (1e30, 1e-37), (1e-39, 1e30), (1e36, 1e-3), (1e13, 1e13)):
         a, b = x * sx, w * sw
         tm.tm_op_linear_fwd(FP32, T, N, K, a, b, None, None, y, s)
         assert close(y, a.double() @ b.double().t(), a.double().abs() @ b.double().abs().t(), K), (sx, sw)
@@ -113,6 +113,35 @@ def test_elements_of_extreme_size(env):
     b[:, 31] = 1e-3
     tm.tm_op_linear_fwd(FP32, T, N, K, a, b, None, None, y, s)
     assert y.isfinite().all() and close(y, a.double() @ b.double().t(), a.double().abs() @ b.double().abs().t(), K)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("small", [1e-30, 1e-36, 1e-39])
+def test_small_elements_beside_ordinary_ones(env, small):
+    """Rows of one operand with an ordinary element that meets zeros: what the small ones, normal and subnormal numbers, sum up to
+    has the precision that it has alone, in either operand and in the weight gradient."""
+    torch, tm, s = env
+    T, N, K = 2048, 2048, 2048
+    assert splits(T, N, K) == (True, True, True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(9)
+    rnd = lambda *shape: torch.randn(shape, device="cuda", generator=g)
+    mixed, plain, out = rnd(2048, 2048) * small, rnd(2048, 2048), torch.empty(2048, 2048, device="cuda")
+    mixed[:, 77], plain[:, 77] = rnd(2048), 0.0
+
+    def right(a, b):  # (normal numbers: in the root mean square too, as test_no_less_precise_than_fused_multiply_adds)
+        ref = a.double() @ b.double().t()
+        return close(out, ref, a.double().abs() @ b.double().abs().t(), 2048) and (small < 1e-38 or off(out, ref) <= 3e-8 * 129 ** 0.5)
+
+    for a, b in ((mixed, plain), (plain, mixed)):
+        print(f"small elements of {small}, first operand {'mixed' if a is mixed else 'plain'}", flush=True)
+        tm.tm_op_linear_fwd(FP32, T, N, K, a, b, None, None, out, s)
+        assert right(a, b)
+        a_t, b_t = a.t().contiguous(), b.t().contiguous()
+        tm.tm_op_linear_dgrad(FP32, T, N, K, a, b_t, out, s)
+        assert right(a, b)
+        tm.tm_op_linear_wgrad(FP32, T, N, K, a_t, b_t, out, 0, s)
+        assert right(a, b)
 
 
 @pytest.mark.gpu
