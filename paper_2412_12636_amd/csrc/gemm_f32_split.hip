@@ -262,11 +262,20 @@ __global__ __launch_bounds__(512) void gemm_f32_split_kernel(const F32SplitParam
   }
   const int out_lane = lane_again(), tid = wave * 64 + out_lane;
   if (__syncthreads_or(redo)) {
+    // only results that are not finite are replaced, so that no row's bits depend on what the others hold
     for (int i = wave; i < 16; i += 8) {
       const int tm = i / 4 * 32, tn = i % 4 * 32;
+      float *x = out + (tm + 4 * (out_lane >> 5)) * kOutPitch + tn + out_lane % 32;
+      bool bad = false;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) bad |= !__builtin_isfinite(x[(8 * (v >> 2) + (v & 3)) * kOutPitch]);
+      if (!__any(bad)) continue;
       const f32x16 r = fp32_tile<A_KC, B_KC>(p, m0 + tm, n0 + tn, out_lane);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) out[(tm + 8 * (v >> 2) + 4 * (out_lane >> 5) + (v & 3)) * kOutPitch + tn + out_lane % 32] = r[v];
+      for (int v = 0; v < 16; ++v) {
+        float &at = x[(8 * (v >> 2) + (v & 3)) * kOutPitch];
+        if (!__builtin_isfinite(at)) at = r[v];
+      }
     }
     __syncthreads();
   }

@@ -116,6 +116,58 @@ def test_elements_of_extreme_size(env):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("T,N,K,taken", [(1100, 1928, 1992, (True, True, True)), (1601, 2312, 328, (True, False, False))])
+def test_rows_keep_their_bits_beside_others(env, T, N, K, taken):
+    """An infinity, a NaN and an element past the terms' scale in one row each, of either operand: every result that reads none of
+    them has the bits that it had without; those that read the large element are the finite ones of the definition."""
+    torch, tm, s = env
+    assert splits(T, N, K) == taken
+    print(f"rows beside others T={T} N={N} K={K}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T)
+    rnd = lambda *shape: torch.randn(shape, device="cuda", generator=g)
+
+    def check(run, a, b):  # of a [M, K], b [N, K]
+        for mine, other in ((a, b), (b, a)):
+            first = run(a, b)
+            rows = [1, mine.shape[0] // 2, mine.shape[0] - 1]
+            was = mine[rows].clone()
+            mine[rows[0], 5], mine[rows[1], 6], mine[rows[2], 7] = float("inf"), float("nan"), 1e33
+            got = run(a, b)
+            ref = a[rows[2]].double() @ b.double().t() if mine is a else a.double() @ b[rows[2]].double()
+            size = other.double().abs() @ mine[rows[2]].double().abs()
+            mine[rows] = was
+            keep = torch.ones(mine.shape[0], dtype=torch.bool, device="cuda")
+            keep[rows] = False
+            if mine is b:
+                first, got = first.t(), got.t()
+            assert torch.equal(first[keep], got[keep])
+            assert got[rows[1]].isnan().all() and not got[rows[0]].isfinite().any()
+            assert close(got[rows[2]], ref, size, a.shape[1])
+
+    def fwd(a, b):
+        y = torch.empty(T, N, device="cuda")
+        tm.tm_op_linear_fwd(FP32, T, N, K, a, b, None, None, y, s)
+        return y
+
+    def wgrad(a, b):
+        dw = torch.empty(N, K, device="cuda")
+        tm.tm_op_linear_wgrad(FP32, T, N, K, a.t().contiguous(), b.t().contiguous(), dw, 0, s)
+        return dw
+
+    def dgrad(a, b):
+        dx = torch.empty(T, K, device="cuda")
+        tm.tm_op_linear_dgrad(FP32, T, N, K, a, b.t().contiguous(), dx, s)
+        return dx
+
+    check(fwd, rnd(T, K), rnd(N, K))
+    if taken[1]:
+        check(dgrad, rnd(T, N), rnd(K, N))
+    if taken[2]:
+        check(wgrad, rnd(N, T), rnd(K, T))
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("small", [1e-30, 1e-36, 1e-39])
 def test_small_elements_beside_ordinary_ones(env, small):
     """Rows of one operand with an ordinary element that meets zeros: what the small ones, normal and subnormal numbers, sum up to
