@@ -135,26 +135,42 @@ __device__ __forceinline__ int lane_again() { return (int)__builtin_amdgcn_mbcnt
 
 // The 32x32 results at (m0, n0) again on the fp32 matrix instructions, operands straight from global memory: for tiles with a
 // value that is not finite (an infinite element has no remainder, one that the scale takes past the largest bf16 has an infinite
-// leading term).
+// leading term).  Bound by the loads' latency, hence 16 of them under way: 2048 x 2048 over 2048 110 us, with an infinite row 160
+// (weight gradient 310), all of it formed again 280 to 315, 130 to 157 on the fp32 instructions alone; with one load of four
+// under way at a time all of it took 420 to 970.
 template <bool A_KC, bool B_KC>
 __device__ __forceinline__ f32x16 fp32_tile(const F32SplitParams &p, int m0, int n0, int lane) {
   const rsrc_t ra = make_rsrc(p.A, p.a_bytes), rb = make_rsrc(p.B, p.b_bytes);
-  auto frag = [&](rsrc_t rs, bool kc, int64_t ld, int row, int rows, int k) {
+  auto frag = [&](auto kc, rsrc_t rs, int64_t ld, int row, int rows, int k) {  // four reduction elements (K: a multiple of 4 if kc)
     f32x4 x;
+    if constexpr (decltype(kc)::value) {
+      x = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+              rs, row < rows && k < p.K ? (uint32_t)((row * ld + k) * 4) : 0x80000000u, 0, 0));
+    } else {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      x[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                 rs, row < rows && k + i < p.K ? (uint32_t)((kc ? row * ld + k + i : (k + i) * ld + row) * 4) : 0x80000000u, 0, 0));
+      for (int i = 0; i < 4; ++i)
+        x[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                   rs, row < rows && k + i < p.K ? (uint32_t)(((k + i) * ld + row) * 4) : 0x80000000u, 0, 0));
+    }
     return x;
   };
   f32x16 acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-  for (int k0 = 0; k0 < p.K; k0 += 8) {
-    const f32x4 a = frag(ra, A_KC, p.lda, m0 + lane % 32, p.M, k0 + 4 * (lane / 32));
-    const f32x4 b = frag(rb, B_KC, p.ldb, n0 + lane % 32, p.N, k0 + 4 * (lane / 32));
+  constexpr int kAhead = 8;  // loads of both operands under way, eight elements each
+  for (int k0 = 0; k0 < p.K; k0 += 8 * kAhead) {
+    f32x4 a[kAhead], b[kAhead];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], acc, 0, 0, 0);
+    for (int j = 0; j < kAhead; ++j) {
+      const int k = k0 + 8 * j + 4 * (lane / 32);
+      a[j] = frag(std::bool_constant<A_KC>{}, ra, p.lda, m0 + lane % 32, p.M, k);
+      b[j] = frag(std::bool_constant<B_KC>{}, rb, p.ldb, n0 + lane % 32, p.N, k);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j][i], b[j][i], acc, 0, 0, 0);
   }
   return acc;
 }
