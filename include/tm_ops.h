@@ -24,9 +24,12 @@ extern "C" {
 #endif
 
 /* The bf16 products choose among tm_gemm_config_count() tile configurations (by a cost model, or by measurement after
- * tm_stage_tune); every configuration adds the terms of an output element in the same order, so the choice changes
- * speed only.  tm_gemm_force_config(i) makes every later product of the process use configuration i; -1 restores the
- * automatic choice.  A testing and tuning aid; not thread-safe. */
+ * tm_stage_tune); every configuration adds the terms of an output element in the same order, so the choice among them
+ * changes speed only.  Two kinds of product take none of them and add in another order, which depends on the shape only:
+ * bf16 results of few 32x32 tiles (at most 512, input gradients 256) over 1024 elements and more, in four interleaved sums,
+ * and the split input gradients of tm_op_linear_dgrad_ws.  tm_gemm_force_config(i) makes every later product of
+ * the process, these two kinds included, use configuration i, so that their results differ from the automatic choice's
+ * by fp32 summation order; -1 restores the automatic choice.  A testing and tuning aid; not thread-safe. */
 int tm_gemm_config_count(void);
 int tm_gemm_force_config(int index);
 

@@ -143,7 +143,9 @@ int tm_stage_init(const tm_stage_config_t *cfg, const tm_stage_buffers_t *buffer
  * results: call it before the first forward pass (a stash from an earlier
  * forward pass is invalidated: the next call must be tm_stage_fwd).  Without
  * it a cost model picks the configurations.  The choice changes speed only:
- * every configuration accumulates each output in the same order.
+ * every configuration accumulates each output in the same order.  Products
+ * whose kernel follows from the shape alone (few tiles over a long reduction,
+ * tm_gemm_config_count in tm_ops.h) are not measured and stay as they are.
  */
 int tm_stage_tune(tm_stage_t *st, void *stream);
 

@@ -382,6 +382,7 @@ int gemm_mfma_tune(const GemmArgs *variants, int n, hipStream_t s) {
     g.residual = nullptr;
     if (g.c_mode == 1) g.c_mode = 2;
   }
+  if (gemm_mfma_small_pays(v[0])) return TM_OK;  // takes none of the configurations
   const TuneKey key(layout_of(v[0]), v[0].M, v[0].N, v[0].K);
   {
     std::lock_guard<std::mutex> lock(g_tuned_mutex);

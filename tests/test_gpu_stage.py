@@ -231,6 +231,31 @@ def test_overwrite_mode_equals_accumulation_into_zeros(env):
     b.close()
 
 
+def test_tuning_leaves_products_of_few_tiles(env, monkeypatch, capfd):
+    """bf16 results of few 32x32 tiles over 1024 elements and more have one kernel, which no measurement replaces: the tuning
+    neither times them nor changes a bit."""
+    torch, tm = env
+    cfg = si.StageConfig(1, 1032, 2, 2, 128, 2056, 33, 1)     # no other test tunes these shapes
+    flat = si.make_flat_params(cfg)
+    x, dy = to_dev(torch, si.make_x(cfg), cfg.dtype), to_dev(torch, si.make_dy(cfg), cfg.dtype)
+    st = GpuStage(torch, tm, cfg, flat)
+    outs = []
+    monkeypatch.setenv("TM_GEMM_TUNE_LOG", "1")
+    for tune in (False, True):
+        if tune:
+            tm.tm_stage_tune(st.handle, stream_ptr(torch))
+        st.grads.zero_()
+        st.fwd(x)
+        st.bwd(dy)
+        torch.cuda.synchronize()
+        outs.append((st.y.clone(), st.dx.clone(), st.grads.clone()))
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
+    timed = {l.split(":")[0] for l in capfd.readouterr().err.splitlines() if l.startswith(("tune layout 0", "tune layout 1"))}
+    # shorter reductions: the out-projection's over 256, the input gradient of QKV over 768
+    assert timed == {"tune layout 0 M=33 N=1032 K=256", "tune layout 1 M=33 N=1032 K=768"}
+    st.close()
+
+
 def test_tuning_changes_speed_only(env):
     """Timing the tile configurations keeps every result bit for bit (each configuration accumulates an
     output element in the same order), overwrites the workspace, and asks for a new forward pass."""
