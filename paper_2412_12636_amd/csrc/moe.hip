@@ -478,28 +478,25 @@ __global__ __launch_bounds__(kWgradWaves * kWave) void moe_router_wgrad_kernel(c
       for (int i = 0; i < VN; ++i) acc[i] += at[(wave * VN + i) * kWave];
   }
   if (wave || col >= h) return;
-  // An infinity or NaN times the table's zeros is NaN for experts that the token did not choose: sums that are not finite are
-  // formed again over the chosen ones only.
-  float finite = 0.f;
-#pragma unroll
-  for (int i = 0; i < VN; ++i)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) finite = fmaf(acc[i][v], 0.f, finite);
+  // An infinity or NaN times the table's zeros is NaN for experts that the token did not choose: sums that are not finite, and
+  // only those, are formed again over the chosen ones.
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     const int e = e0 + 4 * q + v;
     if (e >= E) break;
-    float sum[VN];
+    float sum[VN], finite = 0.f;
 #pragma unroll
-    for (int i = 0; i < VN; ++i) sum[i] = acc[i][v];
+    for (int i = 0; i < VN; ++i) sum[i] = acc[i][v], finite = fmaf(sum[i], 0.f, finite);
     if (finite != 0.f) {
-      for (int i = 0; i < VN; ++i) sum[i] = 0.f;
+      float again[VN] = {};
       for (int a = 0; a < n * k; ++a) {
         if (top_idx[t0 * k + a] != e) continue;
         const u32x4 x = *reinterpret_cast<const u32x4 *>(from + (int64_t)(a / k) * h);
 #pragma unroll
-        for (int i = 0; i < VN; ++i) sum[i] = fmaf(dlog[t0 * k + a], elem<T>(x, i), sum[i]);
+        for (int i = 0; i < VN; ++i) again[i] = fmaf(dlog[t0 * k + a], elem<T>(x, i), again[i]);
       }
+#pragma unroll
+      for (int i = 0; i < VN; ++i) sum[i] = __builtin_isfinite(sum[i]) ? sum[i] : again[i];
     }
     f32x4 *dst = reinterpret_cast<f32x4 *>(out + ((int64_t)seg * E + e) * h + col);
 #pragma unroll
