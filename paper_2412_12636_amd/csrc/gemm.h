@@ -60,17 +60,17 @@ int gemm_mfma(const GemmArgs &g, hipStream_t s);
 int64_t gemm_mfma_splitk_bytes(const GemmArgs &g);
 // Measures the tile configurations for one layout and shape, on n instances of the product that live
 // in different memory (the launches cycle through them), and makes later gemm_mfma() calls of that layout
-// and shape use the fastest.  Overwrites every C; waits for the stream.  Without it a cost model picks.
+// and shape use the fastest.  Overwrites every C; waits for the stream.  Without it a cost model picks.  Shapes that the
+// kernel for few tiles takes (gemm_mfma_small.hip) are left alone.
 int gemm_mfma_tune(const GemmArgs *variants, int n, hipStream_t s);
-// Number of tile configurations, and a process-wide override (index, or -1 for the automatic choice).
-// dw[N,K] = dy[T,N]^T x[T,K] (bf16 operands) with the Adam update of those N*K parameters in the product's
-// epilogue.  `supported` says whether the shapes and pointers allow it (matrix-core path).
 // The two gradient products of a linear map in one launch, and a linear map with its GeLU, where they are small fp32 ones: as
 // gemm_f32_pair and gemm_f32_act.  u: NULL, or dx is multiplied by the derivative of GeLU at u (rows of K).
 bool linear_bwd_pair(int dtype, int64_t T, int64_t N, int64_t K, const void *dy, const void *w, void *dx, const void *x, float *dw,
                      int accumulate, int act, const void *u, hipStream_t s, int *status);
 bool linear_fwd_gelu(int dtype, int64_t T, int64_t N, int64_t K, const void *x, const void *w, const void *bias, void *u, int act, void *out,
                      hipStream_t s, int *status);
+// dw[N,K] = dy[T,N]^T x[T,K] (bf16 operands) with the Adam update of those N*K parameters in the product's
+// epilogue.  `supported` says whether the shapes and pointers allow it (matrix-core path).
 bool linear_wgrad_adam_supported(int64_t T, int64_t N, int64_t K, const void *dy, const void *x, const float *dw);
 // whether that is faster than the product and a flat sweep behind it
 bool linear_wgrad_adam_pays(int64_t T, int64_t N, int64_t K, const float *dw);
@@ -79,6 +79,7 @@ int linear_wgrad_adam(int64_t T, int64_t N, int64_t K, const void *dy, const voi
 // Configurations with a form for a reduction length that is not a multiple of 64 of an operand with contiguous
 // reduction axis; the others run such products as 128x128 (configuration 1).
 inline bool gemm_config_takes_ragged_k(int config) { return config >= 13 && config != 15; }
+// Number of tile configurations, and a process-wide override (index, or -1 for the automatic choice).
 int gemm_mfma_config_count();
 int gemm_mfma_force_config(int index);
 

@@ -292,7 +292,9 @@ __global__ __launch_bounds__((64 * F32Pair<DT, WT, WSPL>::NW)) void gemm_f32_pai
   extern __shared__ __align__(1024) char lds[];
   typedef F32Pair<DT, WT, WSPL> P;
   if ((int)blockIdx.x < d_blocks) {
-    const int sub = P::TWO == 2 ? (int)(threadIdx.x / 256) : 0;  // (a tile behind the last: every load and store is out of range)
+    // (a tile behind the last one, of an odd number, starts past the last column: it reads rows of the operands that are there,
+    // the next reduction row's elements or zeros past the end, and stores nothing)
+    const int sub = P::TWO == 2 ? (int)(threadIdx.x / 256) : 0;
     f32_block<DT, DT, DT, DT, P::DSPL, 4, P::DSUB, false, true, false, DEPI>(d, lds + sub * P::D::LDS, (int)blockIdx.x * P::TWO + sub,
                                                                              (int)threadIdx.x - sub * 256);
   } else {

@@ -1,14 +1,15 @@
 // fp32 GEMM on the bf16 matrix instructions: every operand element as three bf16 terms.
 //
-// 2^24 x = h + m + l with h = bf16(2^24 x), m = bf16 of what h leaves, l the rest: 24 significand bits in three times eight.  The
-// instructions take subnormal terms for zero; at this scale the last bit of any x is 2^-125 or more, so that no term is
-// subnormal and the sum is exact, small elements beside large ones included.  Elements of 2^104 and more and results of 2^80 and
-// more come out as infinities and NaN, and are formed on the fp32 instructions as those are.  Of the nine products of two such sums all but ll are formed, which is below 2^-34 of |a b|.  hh is exact in
-// fp32 and has an accumulator of its own; the seven others, 2^-8 of it and less, share a second one, and the two meet once at
-// the end.  What rounds is one sum of hh for every eight elements, where a chain of fused multiply-adds rounds each.  Errors against
-// 64 bits, of the result, fp32 instructions / here: 256 N(0,1) elements 2.9e-7 / 0.9e-7, 2048 8.1e-7 / 2.7e-7; rows of 16 elements
-// that are not zero 7.4e-8 / 3.4e-8, of four 4.0e-8 / 2.6e-8, of one 2.53e-8 / 2.53e-8 (0.500 / 0.506 ulp at most).  With all terms in
-// one accumulator these were 1.4e-7, 7.3e-8 and 3.5e-8 (1.4 ulp); with ml and lm left out 3.4e-8, 2.7e-8 and 2.6e-8 (0.95 ulp).
+// 2^24 x = h + m + l with h = bf16(2^24 x), m = bf16 of what h leaves, l the rest: 24 significand bits in three times eight.
+// The instructions take subnormal terms for zero; at this scale the last bit of any x is 2^-125 or more, so that no term is
+// subnormal and the sum is exact, small elements beside large ones included.  Elements of 2^104 and more and results of 2^80
+// and more come out as infinities and NaN, and are formed on the fp32 instructions as those are.  Of the nine products of two
+// such sums all but ll are formed, which is below 2^-34 of |a b|.  hh is exact in fp32 and has an accumulator of its own; the
+// seven others, 2^-8 of it and less, share a second one, and the two meet once at the end.  What rounds is one sum of hh for
+// every eight elements, where a chain of fused multiply-adds rounds each.  Errors against 64 bits, of the result, fp32
+// instructions / here: 256 N(0,1) elements 2.9e-7 / 0.9e-7, 2048 8.1e-7 / 2.7e-7; rows of 16 elements that are not zero 7.4e-8
+// / 3.4e-8, of four 4.0e-8 / 2.6e-8, of one 2.53e-8 / 2.53e-8 (0.500 / 0.506 ulp at most).  With all terms in one accumulator
+// these were 1.4e-7, 7.3e-8 and 3.5e-8 (1.4 ulp); with ml and lm left out 3.4e-8, 2.7e-8 and 2.6e-8 (0.95 ulp).
 // Eight 32x32x16 MFMAs take 256 clocks where eight 32x32x2 fp32 ones take 512.
 //
 // A block has four waves that multiply and four that fetch, two for each operand.  The fetching waves read fp32 rows from
@@ -19,9 +20,11 @@
 // leave.  Three LDS stages: one read, one complete (its first fragments are fetched ahead of the barrier), one written.  The
 // results leave through LDS as whole rows, all eight waves storing.
 //
-// Bound by the MFMA rate: a stage of 32 elements takes 1.43 us with every unit busy, 0.85 at the nominal clock and 1.5 at the
-// rate that random data sustains; 188 TFLOP/s of fp32 products.  64x64 tiles, whose operands are split for only 64 results of the
-// other side, were 6 % slower than the fp32 instructions (1024 x 1024 over 1024 21.6 us against 20.4).
+// Bound by the MFMA rate that random data sustains: a stage of 32 elements takes 1.43 us with every unit busy (188 TFLOP/s of fp32
+// products), 1.5 at that rate and 0.85 at the nominal clock; the matrix cores are busy for 65 to 68 % of the cycles, first loads and
+// epilogue included.  Neither a higher priority of the fetching or the multiplying waves nor fewer scheduling barriers change it by
+// more than 2 %.  64x64 tiles, whose operands are split for only 64 results of the other side, were 6 % slower than the fp32
+// instructions (1024 x 1024 over 1024 21.6 us against 20.4).
 // Against the fp32 instructions: 1024 x 8192 over 1024 137 -> 114 us, 1024 x 4096 over 1024 77 -> 58, 2048 x 2048 over 2048 135 -> 108.
 #include "gemm.h"
 #include "gemm_f32_form.h"

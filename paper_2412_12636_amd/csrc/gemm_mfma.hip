@@ -334,7 +334,9 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
 // The constants are fitted to 69 products of 1 to 4096 rows over 4096 to 20480: the choice is 1.2 % slower than the better of
 // the two on them (geometric mean), where always splitting is 3 % slower and never splitting 14 %.  (2048 x 2048 over 4096: 58 us
 // split, 30 unsplit on 128x128 tiles; 2048 x 512 over 4096: 29 against 17; 2048 x 1536 over 12288, the 175B shard's: 84 against 106;
-// 3 x 64 over 8832: 24 against 27.)
+// 3 x 64 over 8832: 24 against 27.)  The unsplit time is that of the tile configurations, also where the kernel for few tiles would
+// have the product: that one, which the same call without scratch takes, is the faster of the two up to 256 rows (16 x 1024 over
+// 8192 19.5 us, split 24.4; 64 x 1024 over 12288 28 and 32; 200 x 512 over 6144 13 and 21; 256 x 1024 over 8192 19 and 26).
 static bool split_pays(const GemmArgs &g, int parts, bool large) {
   GemmArgs p = g;
   p.K = g.K / parts;

@@ -170,7 +170,8 @@ template <bool B_KC> static int launch_small(const GemmArgs &g, hipStream_t s) {
 }
 
 // bf16 results over 1024 elements and more, with a tile on every unit at most, or two where both operands lie along the
-// reduction.  Against the tiles chosen before, 1900 random products of each kind (8 to 4096 rows, 64 to 8192 columns, 64 to 12288
+// reduction.  Input gradients with scratch are asked about only where gemm_mfma() does not split their reduction (split_pays in
+// gemm_mfma.hip).  Against the unsplit tiles chosen before, 1900 random products of each kind (8 to 4096 rows, 64 to 8192 columns, 64 to 12288
 // elements), forward / input gradient, geometric means over up to 256 tiles: 0.60 / 0.67 of the time to 2048 elements, 0.51 / 0.61 to
 // 4096, 0.46 / 0.60 beyond; 257 to 384 tiles 0.85 / 1.03, to 512 0.90 / 1.09 (one in sixty forward ones 4 to 7 % slower), to 560 1.20 /
 // 1.45.  256 x 512 over 2048 10.6 -> 4.9 us.  With eight waves, or three or four chunks in flight, 2 to 10 % slower; 64x64 tiles

@@ -282,8 +282,8 @@ __global__ __launch_bounds__(kNormThreads) void norm_bwd_kernel(
 }
 
 // ---------------------------------------------------------------------------------------
-// Column sums.  Up to six of them share a launch: the partial rows of a norm's backward pass (gain, offset and dx sums), the
-// bias gradients of a layer, or the second halves of these.  A launch of this kind takes 3 to 5 us whatever it adds up, and
+// Column sums.  Up to nine of them share a launch: the partial rows of a layer's norms in the backward pass (gain, offset and dx
+// sums of each), its bias gradients, or the second halves of these.  A launch of this kind takes 3 to 5 us whatever it adds up, and
 // a layer with biases has seven or eight (together behind the last norm: 1.7 % of a step of the 6.7B shard, tiny preset 216 ->
 // 203 us).
 // ---------------------------------------------------------------------------------------
@@ -294,7 +294,7 @@ struct ColumnTask {
   float *out;
   int ld, rows, n, typed;  // typed: elements of the kernel's type, otherwise fp32
 };
-// MAX: tasks at most, 1, 3 or 6 (looking one up is a chain of scalar loads and the table is a kernel argument: 0.8 of 11.5 us
+// MAX: tasks at most, 1, 3, 6 or 9 (looking one up is a chain of scalar loads and the table is a kernel argument: 0.8 of 11.5 us
 // for one bias gradient of 12288 in a table of six)
 template <int MAX> struct TaskTable {
   ColumnTask t[MAX];
