@@ -1,7 +1,7 @@
 """fp32 products on the bf16 matrix instructions (csrc/gemm_f32_split.hip): three bf16 terms an operand element."""
 import pytest
 
-from tests.f32_form import form, split, splits
+from tests.f32_form import form, forms, split, splits
 
 FP32 = 0
 
@@ -231,3 +231,29 @@ def test_no_less_precise_than_fused_multiply_adds(env, T, N, K):
     e = off(y, x.double() @ w.double().t())
     print(f"all of {K}: {e:.3e}", flush=True)
     assert e <= 3e-8 * (K / 16 + 1) ** 0.5
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("T,N,K,which", [(2048, 2048, 256, "128/1"), (3077, 776, 2056, "64/1"), (870, 2376, 1000, "32/4p")])
+def test_results_off_the_16_byte_grid(env, T, N, K, which):
+    """Products that the terms would have, results, bias and residual one element off 16 bytes: the fp32 instructions form them, to
+    n 2^-24 of the sum of the magnitudes, between guards that stay."""
+    torch, tm, s = env
+    assert split(T, N, K, False) and forms(T, N, K).split()[0] == which
+    print(f"results off the grid T={T} N={N} K={K}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T)
+    rnd = lambda *shape: torch.randn(shape, device="cuda", generator=g)
+    x, w = rnd(T, K), rnd(N, K)
+    bias, res = rnd(N + 1)[1:], rnd(T * N + 1)[1:].view(T, N)
+    buf = torch.full((T * N + 8,), 7.0, device="cuda")
+    aligned = torch.empty(T, N, device="cuda")
+    X, W = x.double(), w.double()
+    for b, r, y in ((None, None, buf[1:1 + T * N].view(T, N)), (bias, None, aligned), (None, res, aligned)):
+        tm.tm_op_linear_fwd(FP32, T, N, K, x, w, b, r, y, s)
+        ref, size = X @ W.t(), X.abs() @ W.abs().t()
+        for extra in (b, r):
+            if extra is not None:
+                ref, size = ref + extra.double(), size + extra.double().abs()
+        assert bool(((y.double() - ref).abs() <= (K + 8) * 2.0 ** -24 * size).all())
+    assert bool((buf[:1] == 7.0).all()) and bool((buf[1 + T * N:] == 7.0).all())
