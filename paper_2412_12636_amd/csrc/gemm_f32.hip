@@ -42,11 +42,11 @@ struct F32GemmParams {
   float *C;
   int64_t ldc;
   const float *bias, *residual;
+  int tiles_m, tiles_n;
+  uint32_t a_bytes, b_bytes, c_bytes;
   const float *u;  // EPI 4
   float *g;        // EPI 3
   int act;
-  int tiles_m, tiles_n;
-  uint32_t a_bytes, b_bytes, c_bytes;
 };
 
 // Loaders: NW waves fetch a step's tile of R rows.  MF: rows of an MFMA (32: 32x32x2, a lane reads elements 8j + 4hh .. +3;
@@ -145,7 +145,7 @@ template <int BM, int BN, int WM, int WN, int KSPL, int NS, int SUB> struct F32C
 // EPI 0: results with bias and residual.  1: added to C.  2: stored.  3: results with bias, and their GeLU to g.  4: results
 // times the derivative of GeLU at u.
 template <int BM, int BN, int WM, int WN, int KSPL, int NS, int SUB, bool PATCH, bool A_KC, bool B_KC, int EPI>
-__device__ __forceinline__ void f32_block(const F32GemmParams &p, char *lds, const int block, const int tid) {
+__device__ __forceinline__ void f32_block(const F32GemmParams &p, char *lds, const unsigned block, const unsigned tid) {
   typedef F32Cfg<BM, BN, WM, WN, KSPL, NS, SUB> C;
   typedef F32Mma<C::MF> MM;
   constexpr int MF = C::MF, TM = C::TM, TN = C::TN, NT = C::NT, LW = C::LW, UG = C::UG, NV = C::NV;
@@ -155,15 +155,15 @@ __device__ __forceinline__ void f32_block(const F32GemmParams &p, char *lds, con
   int m0, n0;
   if constexpr (PATCH) {  // an XCD (ids round-robin over eight) owns a range of tiles, walked in patches
     asm volatile("" ::"s"(p.A), "s"(p.B), "s"(p.lda), "s"(p.ldb), "s"(p.K), "s"(p.a_bytes));  // fetched now, not behind the divisions
-    const int nblk = p.tiles_m * p.tiles_n, xcd = block % 8, base = nblk / 8, rem = nblk % 8;
-    const int lid = xcd * base + (xcd < rem ? xcd : rem) + block / 8;
+    const int nblk = p.tiles_m * p.tiles_n, xcd = (int)(block % 8), base = nblk / 8, rem = nblk % 8;
+    const int lid = xcd * base + (xcd < rem ? xcd : rem) + (int)(block / 8);
     const int gi = lid / (kPatch * p.tiles_n), first = gi * kPatch, in_group = lid - first * p.tiles_n;
     const int rows = p.tiles_m - first < kPatch ? p.tiles_m - first : kPatch;
     m0 = (first + in_group % rows) * BM;
     n0 = (in_group / rows) * BN;
   } else {
-    m0 = (block % p.tiles_m) * BM;
-    n0 = (block / p.tiles_m) * BN;
+    m0 = (int)(block % p.tiles_m) * BM;
+    n0 = (int)(block / p.tiles_m) * BN;
   }
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // (zeros that the compiler can see: 5 % of the short products)
@@ -270,7 +270,7 @@ __device__ __forceinline__ void f32_block(const F32GemmParams &p, char *lds, con
 template <int BM, int BN, int WM, int WN, int KSPL, int NS, int SUB, bool PATCH, bool A_KC, bool B_KC, int EPI>
 __global__ __launch_bounds__((64 * F32Cfg<BM, BN, WM, WN, KSPL, NS, SUB>::NW)) void gemm_f32_kernel(const F32GemmParams p) {
   extern __shared__ __align__(1024) char lds[];
-  f32_block<BM, BN, WM, WN, KSPL, NS, SUB, PATCH, A_KC, B_KC, EPI>(p, lds, (int)blockIdx.x, (int)threadIdx.x);
+  f32_block<BM, BN, WM, WN, KSPL, NS, SUB, PATCH, A_KC, B_KC, EPI>(p, lds, blockIdx.x, threadIdx.x);
 }
 
 // Input gradient and weight gradient of one linear map in one launch: blocks of DT x DT results of the first, then blocks of
@@ -295,10 +295,10 @@ __global__ __launch_bounds__((64 * F32Pair<DT, WT, WSPL>::NW)) void gemm_f32_pai
     // (a tile behind the last one, of an odd number, starts past the last column: it reads rows of the operands that are there,
     // the next reduction row's elements or zeros past the end, and stores nothing)
     const int sub = P::TWO == 2 ? (int)(threadIdx.x / 256) : 0;
-    f32_block<DT, DT, DT, DT, P::DSPL, 4, P::DSUB, false, true, false, DEPI>(d, lds + sub * P::D::LDS, (int)blockIdx.x * P::TWO + sub,
-                                                                             (int)threadIdx.x - sub * 256);
+    f32_block<DT, DT, DT, DT, P::DSPL, 4, P::DSUB, false, true, false, DEPI>(d, lds + sub * P::D::LDS, blockIdx.x * P::TWO + sub,
+                                                                             threadIdx.x - sub * 256);
   } else {
-    f32_block<WT, WT, WT, WT, WSPL, 4, WT == 16 ? 4 : 2, false, false, false, WEPI>(w, lds, (int)blockIdx.x - d_blocks, (int)threadIdx.x);
+    f32_block<WT, WT, WT, WT, WSPL, 4, WT == 16 ? 4 : 2, false, false, false, WEPI>(w, lds, blockIdx.x - d_blocks, threadIdx.x);
   }
 }
 
