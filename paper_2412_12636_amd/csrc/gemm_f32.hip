@@ -16,7 +16,7 @@
 // where 32x32 tiles leave most units without one.  Which one: gemm_f32_form.h.
 //
 // Not on the bf16 instructions, whose rate is sixteen times the fp32 ones': three bf16 terms an element and six of their nine
-// products in one accumulator (1024 x 4096 over 1024 77 -> 47 us, a layer of hidden 1024 1060 -> 880) are less precise on rows of
+// products in one accumulator (1024 x 4096 over 1024 77 -> 47 us, a layer of hidden 1024 1062 -> 890) are less precise on rows of
 // few elements that are not zero (16 of 256: 1.4e-7 of the result from 64 bits, here 7.4e-8; one: 1.4 ulp, here 0.5), and take the
 // lower terms of elements under 2^-95 for zero.  As precise as this kernel they are with eight products in two accumulators on
 // elements scaled by 2^24; then 58 us, a layer of hidden 1024 1007 to 1069 on three machines, and 60 other layers between 6 %
