@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtm_stage.so")
 
-SOURCES = ["stage.hip", "norm.hip", "elementwise.hip", "gemm_generic.hip", "gemm_f32.hip", "gemm_mfma.hip", "gemm_mfma_nt.hip", "gemm_mfma_nn.hip", "gemm_mfma_tn.hip", "gemm_mfma_small.hip", "linear.hip",
+SOURCES = ["stage.hip", "norm.hip", "elementwise.hip", "gemm_generic.hip", "gemm_f32.hip", "gemm_f32_split.hip", "gemm_mfma.hip", "gemm_mfma_nt.hip", "gemm_mfma_nn.hip", "gemm_mfma_tn.hip", "gemm_mfma_small.hip", "linear.hip",
            "attn_generic.hip", "attn_mfma.hip", "attn_f32.hip", "attn.hip", "roles.hip", "sandbox.hip", "moe.hip"]
 
 # packed fp32 VALU forms are switched off on purpose: the compiler must not form them from plain float code

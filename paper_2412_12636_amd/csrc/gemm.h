@@ -41,6 +41,10 @@ int gemm_generic(int dtype, const GemmArgs &g, hipStream_t s);
 // fp32 operands through the matrix cores.
 bool gemm_f32_supported(const GemmArgs &g);
 int gemm_f32(const GemmArgs &g, hipStream_t s);
+// The same on the bf16 matrix instructions, operands as three bf16 terms (gemm_f32_split.hip).  Besides what
+// gemm_f32_supported() asks for, the results' rows, the bias and the residual are whole 16-byte chunks.
+bool gemm_f32_split_supported(const GemmArgs &g);
+int gemm_f32_split(const GemmArgs &g, hipStream_t s);
 
 // Small products only; false: not launched (status NULL: only asked).  Input gradient (act_u: times the derivative of GeLU there)
 // and weight gradient in one launch; and a product that also writes its GeLU.

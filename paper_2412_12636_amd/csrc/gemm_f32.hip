@@ -13,15 +13,8 @@
 // evenly its tiles cover the SIMDs, and how much of the barrier and the LDS latency a second wave of the SIMD covers:
 // blocks of 128x128 and 64x64, one wave a SIMD; of 64x64 with four waves a SIMD, and of 32x32 with one or two, that split
 // every stage's reduction elements (their sums meet in LDS in wave order); and of 16x16, split four ways, on 16x16x4 MFMAs,
-// where 32x32 tiles leave most units without one.  Which one: gemm_f32_form.h.
-//
-// Not on the bf16 instructions, whose rate is sixteen times the fp32 ones': three bf16 terms an element and six of their nine
-// products in one accumulator (1024 x 4096 over 1024 77 -> 47 us, a layer of hidden 1024 1062 -> 890) are less precise on rows of
-// few elements that are not zero (16 of 256: 1.4e-7 of the result from 64 bits, here 7.4e-8; one: 1.4 ulp, here 0.5), and take the
-// lower terms of elements under 2^-95 for zero.  As precise as this kernel they are with eight products in two accumulators on
-// elements scaled by 2^24; then 58 us, a layer of hidden 1024 1007 to 1069 on three machines, and 60 other layers between 6 %
-// faster and 6 % slower: the sums' rate is what the card sustains on random data, and the one block a unit stores its results
-// with nothing beside it.
+// where 32x32 tiles leave most units without one.  Which one: gemm_f32_form.h.  Larger products go to the bf16 instructions in
+// three terms an element (gemm_f32_split.hip).
 // With one wave a SIMD on every tile and none of 16x16 before: 1024 x 1024 over 1024 23.7 -> 21.9 us, over 3072 (strided
 // weights) 64 -> 58; 256 x 256 over 1024 8.2 -> 4.5; 1500 x 768 over 768 25.1 -> 24.2 (weight gradient 29.9 -> 25.4).
 // (The twelve products of a layer of hidden 1024, SwiGLU width 4096, 1024 tokens: 4.9 ms = 21 TFLOP/s on the 64x64
@@ -403,6 +396,7 @@ static bool reach16(const GemmArgs &g) {
 }
 
 template <bool A_KC, bool B_KC, int EPI> static int pick(const GemmArgs &g, hipStream_t s) {
+  if (gemm_f32_split_supported(g) && f32_split(g.M, g.N, g.K, EPI != 0, reach16(g))) return gemm_f32_split(g, s);
   const F32Form f = f32_form(g.M, g.N, g.K, EPI != 0, reach16(g));
   if (f.tile == 128) return launch<128, 128, 64, 64, 1, 2, 1, false, A_KC, B_KC, EPI>(g, s);
   if (f.tile == 64 && f.split == 4) return launch<64, 64, 32, 32, 4, 3, 2, false, A_KC, B_KC, EPI>(g, s);
@@ -417,11 +411,11 @@ template <bool A_KC, bool B_KC, int EPI> static int pick(const GemmArgs &g, hipS
   return launch<16, 16, 16, 16, 4, 4, 4, false, A_KC, B_KC, EPI>(g, s);
 }
 
-// f32_form's choice where it is a small tile walked in plain order
+// f32_form's choice where it is a small tile walked in plain order and no other kernel has the product
 static bool small_form(const GemmArgs &g, bool wgrad, F32Form *f) {
   if (!gemm_f32_supported(g)) return false;
   *f = f32_form(g.M, g.N, g.K, wgrad, reach16(g));
-  return f->tile <= 32 && !f->patches;
+  return f->tile <= 32 && !f->patches && !(gemm_f32_split_supported(g) && f32_split(g.M, g.N, g.K, wgrad, reach16(g)));
 }
 
 template <int DT, int WT, int WSPL, int DEPI, int WEPI> static int launch_pair(const GemmArgs &d, const GemmArgs &w, hipStream_t s) {

@@ -1,4 +1,5 @@
-// Which of its kernels a product of fp32 operands takes (gemm_f32.hip): arithmetic on the sizes, no device code.
+// Which of its kernels a product of fp32 operands takes (gemm_f32.hip, gemm_f32_split.hip): arithmetic on the sizes, no device
+// code.
 #pragma once
 #include <cstdint>
 
@@ -39,6 +40,39 @@ inline F32Form f32_form(int64_t M, int64_t N, int64_t K, bool wgrad, bool reach1
   if (c64 <= c32) return {64, tiles(64) <= units && K >= 512 ? 4 : 1, false};
   if (wgrad && K < 256) return {32, 4, false};
   return {32, wgrad ? 8 : 4, patches(32, 6)};
+}
+
+// Whether the kernel on bf16 terms (gemm_f32_split.hip, 128x128 tiles) is the faster one.
+//
+// Times in us from the passes over the chip (r; one block a unit on bf16 terms), the tiles a unit has on average (u) and the
+// reduction length, fitted by non-negative least squares to every form's time on 300 to 600 products of each kind with 96 to 8192
+// rows and columns over 256 to 8192 elements; they meet them to 3 to 6 %.  It has to win by 5 %.  Single products from a warm
+// cache then take 0.84 of their time (247 of 900, at most 1.00; 128x128 tiles 0.79, 64x64 ones that a unit has several of 0.86).
+//
+// In whole passes less is left, for the card's matrix rate on random data falls under a lasting load; and short reductions over
+// more than one round of blocks, whose results leave a unit with nothing beside them and meet a cold cache, lose: 2026 x 5888 over
+// 384 in a step of 676 us 0.968 of the speed, 1594 x 5504 over 768 in one of 885 us 0.967.  Without those, 90 layers and linear
+// maps that use it are 2.5 % faster (geometric mean; 0.98 to 1.24), a layer of hidden 1024 on 1024 tokens 3 to 8 %.
+//
+// Never at the price of precision: its error on N(0,1) data, 1.9e-7 of the result over 1024 elements, is below that of the whole
+// walks (5.7e-7) and the four-way ones (2.9e-7) that it replaces; weight gradients that eight waves split (2.0e-7) stay.
+inline bool f32_split(int64_t M, int64_t N, int64_t K, bool wgrad, bool reach16) {
+  const F32Form f = f32_form(M, N, K, wgrad, reach16);
+  if (K < 256 || f.tile == 16 || f.split != (f.tile == 32 ? 4 : 1)) return false;
+  if (K < 1024 && ((M + 127) / 128) * ((N + 127) / 128) > 256) return false;
+  struct Grid {
+    double r, u;
+  };
+  auto grid = [&](int64_t b) {
+    const int64_t n = ((M + b - 1) / b) * ((N + b - 1) / b);
+    return Grid{(double)((n + 255) / 256), (double)n / 256};
+  };
+  const double k = (double)K / 1024;
+  const Grid g = grid(f.tile), t = grid(128);
+  const double now = f.tile == 128  ? 4.0 + g.r * (3.0 + 61 * k)
+                     : f.tile == 64 ? 2.9 + g.r * (0.4 + 16.8 * k) + g.u * 0.5
+                                    : 2.7 + g.r * (0.3 + 5.1 * k) + g.u * 0.4;
+  return 1.05 * (1.0 + t.r * (6.0 + 33.9 * k) + t.u * (1.2 + 11.9 * k)) < now;
 }
 
 }  // namespace tmk

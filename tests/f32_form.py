@@ -11,6 +11,7 @@ extern "C" void f32_form(int64_t M, int64_t N, int64_t K, int wgrad, int reach16
   const tmk::F32Form f = tmk::f32_form(M, N, K, wgrad, reach16);
   out[0] = f.tile, out[1] = f.split, out[2] = f.patches;
 }
+extern "C" int f32_split(int64_t M, int64_t N, int64_t K, int wgrad, int reach16) { return tmk::f32_split(M, N, K, wgrad, reach16); }
 """
 
 
@@ -35,3 +36,13 @@ def forms(T, N, K):
     """The three products of a linear map, forward, input gradient and weight gradient, as "tile/split", with "p" in patches."""
     return " ".join("%d/%d%s" % (t, s, "p" if p else "")
                     for t, s, p in (form(T, N, K, False), form(T, K, N, False), form(N, K, T, True)))
+
+
+def split(M, N, K, wgrad, reach16=True):
+    """Whether C[M,N] over K goes to the kernel on bf16 terms; form() holds where not."""
+    return bool(_lib().f32_split(*(ctypes.c_int64(v) for v in (M, N, K)), int(wgrad), int(reach16)))
+
+
+def splits(T, N, K):
+    """Of the three products of a linear map: forward, input gradient, weight gradient."""
+    return split(T, N, K, False), split(T, K, N, False), split(N, K, T, True)

@@ -2,7 +2,7 @@
 import pytest
 
 import synth_inputs as si
-from tests.f32_form import form
+from tests.f32_form import form, split
 from tests.gpu_util import require_gpu, stream_ptr, to_dev
 from tests.stage_runner import GpuStage
 from tests.test_gpu_stage import run_and_compare
@@ -23,7 +23,7 @@ def pairs(cfg):
     out = []
     for N, K in ((h, f), ((2 if cfg.act == si.ACT_SWIGLU else 1) * f, h), (h, A), (A + 2 * cfg.n_kv_heads * cfg.head_dim, h)):
         d, w = form(T, K, N, False), form(N, K, T, True)
-        small = max(d[0], w[0]) <= 32 and not (d[2] or w[2])
+        small = max(d[0], w[0]) <= 32 and not (d[2] or w[2] or split(T, K, N, False) or split(N, K, T, True))
         out.append((d[0],) + w[:2] if small else None)
     return out
 

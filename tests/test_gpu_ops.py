@@ -8,7 +8,7 @@ import pytest
 
 import synth_inputs as si
 from oracle import stage_oracle as so
-from tests.f32_form import forms
+from tests.f32_form import forms, splits
 from tests.gpu_util import (TOL_ADAM, TOL_BF16, TOL_FP32, f32_dev, rand, rel_err, require_gpu, stream_ptr, to_dev,
                             to_host, torch_dtype)
 
@@ -201,7 +201,7 @@ def test_linear_fp32_split_waves(env, T, N, K, which):
     and stages, in plain order and in patches; which: the forms of the three products (tile / split, p: patches), so that
     a change of the rule shows here.  An fp32 sum of n products is off by at most n 2^-24 of the sum of their
     magnitudes and by about sqrt(n) 2^-24 for these signs, 2e-6 at 1100 terms; stored and added to."""
-    assert forms(T, N, K) == which
+    assert forms(T, N, K) == which and not any(splits(T, N, K))
     torch, tm = env
     print(f"linear fp32 split waves T={T} N={N} K={K}", flush=True)
     rng = np.random.default_rng(T + N + K)
